@@ -78,7 +78,7 @@ int check_shape(const moe_shape_t* s) {
 
 // Tile shapes and split-K factor of the two expert GEMMs (bf16 MFMA path).
 struct FfnPlan {
-    bool mfma;          // false: plain fp32-ALU GEMM (fp32 layers)
+    bool mfma;          // false: the fp32 kernels (fp32 layers)
     int MT, NW1, NW2;   // row tile; waves per work-group of GEMM-1 / GEMM-2
     int ksplit2;        // split-K factor of GEMM-2 (1 = none)
     bool tiled;         // more than 64 rows per expert: the tiled (matrix-core-bound) kernel
@@ -111,7 +111,7 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
 
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
-    size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, xe, h, ye, hd, dense, partial, total;
+    size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, h, ye, hd, dense, partial, total;
 };
 
 WsLayout ws_layout(const moe_shape_t* s) {
@@ -131,11 +131,10 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.rows = take(E * 4);
     L.order = take(2 * (E + 1) * 4);  // two launch orders of the experts, each followed by the tile-dealing flag
     L.slot_token = take(E * C * 4);
-    L.xe = take(plan.mfma ? 0 : E * C * d * es);       // the MFMA path gathers rows inside GEMM-1
     L.h = take(E * C * f * es);
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
-    L.dense = take(s->residual ? T * d * es : 0);      // the dense branch's output where it is not combined in place
+    L.dense = take(s->residual && plan.mfma ? T * d * es : 0);   // the dense branch's output where it is not combined in place
     L.partial = take(plan.ksplit2 > 1 ? (size_t)plan.ksplit2 * E * C * d * 4 : 0);
     L.total = off;
     return L;
@@ -227,17 +226,44 @@ int run_gate(const moe_shape_t* s, const void* x, const float* Wg, const float* 
     return rc;
 }
 
-// the two GEMMs of an FFN on the plain fp32-ALU kernel (fp32 layers)
-int run_ffn_simple(int dtype, int G, int max_rows, const int32_t* rows, int fixed_rows, int d, int f, const void* xin,
-                   const void* W1, const void* b1, const void* W2, const void* b2, void* h, void* yout, hipStream_t st) {
+// The two GEMMs of the expert FFNs in fp32.  row_map == nullptr: rows are xin[e*C + r], else xin[row_map[e*C + r]]
+// (dispatch fused in).  scatter_map == nullptr: rows of `out` are e*C + r, else the tokens' (top-1 combine fused in).
+int run_expert_ffn_f32(const moe_shape_t* s, const void* xin, const int32_t* row_map, const int32_t* rows, const void* W1,
+                       const void* b1, const void* W2, const void* b2, void* h, const int32_t* scatter_map,
+                       const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
     GemmArgs a{};
-    a.A = xin; a.B = W1; a.bias = b1; a.out = h; a.rows = rows; a.row_map = nullptr;
-    a.fixed_rows = fixed_rows; a.max_rows = max_rows; a.G = G; a.K = d; a.N = f;
-    a.a_group_stride = max_rows; a.o_group_stride = max_rows; a.gelu = 1; a.dtype = dtype;
-    int rc = launch_gemm_simple(a, st);
+    a.A = xin; a.B = W1; a.bias = b1; a.out = h; a.rows = rows; a.row_map = row_map;
+    a.max_rows = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
+    a.a_group_stride = s->capacity; a.o_group_stride = s->capacity;
+    prof_pre(ST_GEMM1, st);
+    int rc = launch_gemm_f32(a, EPI_GELU, st);
+    prof_mark(ST_GEMM1, st);
     if (rc != MOE_OK) return rc;
-    a.A = h; a.B = W2; a.bias = b2; a.out = yout; a.K = f; a.N = d; a.gelu = 0;
-    return launch_gemm_simple(a, st);
+    a.A = h; a.B = W2; a.bias = b2; a.out = out; a.row_map = nullptr; a.K = s->d_ffn; a.N = s->d_model;
+    a.scatter_map = scatter_map; a.T = s->T; a.gate_w = gate_w; a.slot_idx = slot_idx; a.top_k = s->top_k;
+    prof_pre(ST_GEMM2, st);
+    rc = launch_gemm_f32(a, scatter_map ? EPI_SCATTER : EPI_STORE, st);
+    prof_mark(ST_GEMM2, st);
+    return rc;
+}
+
+// Dense branch of an fp32 Residual-MoE layer, the combine fused into its second GEMM.
+int run_dense_f32(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, const void* Wd2, const void* bd2,
+                  void* hd, const void* ye, const int32_t* expert_idx, const int32_t* slot_idx, const float* gate_w, void* out,
+                  hipStream_t st) {
+    GemmArgs a{};
+    a.A = x; a.B = Wd1; a.bias = bd1; a.out = hd; a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1;
+    a.K = s->d_model; a.N = s->d_ffn;
+    prof_pre(ST_DENSE1, st);
+    int rc = launch_gemm_f32(a, EPI_GELU, st);
+    prof_mark(ST_DENSE1, st);
+    if (rc != MOE_OK) return rc;
+    a.A = hd; a.B = Wd2; a.bias = bd2; a.out = out; a.K = s->d_ffn; a.N = s->d_model;
+    a.ye = ye; a.expert_idx = expert_idx; a.slot_idx = slot_idx; a.gate_w = gate_w; a.top_k = s->top_k; a.C = s->capacity;
+    prof_pre(ST_DENSE2, st);
+    rc = launch_gemm_f32(a, EPI_COMBINE, st);
+    prof_mark(ST_DENSE2, st);
+    return rc;
 }
 
 inline const uint16_t* u16(const void* p) { return static_cast<const uint16_t*>(p); }
@@ -497,8 +523,8 @@ int moe_expert_ffn(const moe_shape_t* shape, const void* xe, const int32_t* expe
     hipStream_t st = static_cast<hipStream_t>(stream);
     const FfnPlan plan = plan_ffn(shape);
     if (!plan.mfma)
-        return run_ffn_simple(shape->dtype, shape->E, shape->capacity, expert_rows, 0, shape->d_model, shape->d_ffn, xe,
-                              W1, b1, W2, b2, at<void>(ws, L.h), ye, st);
+        return run_expert_ffn_f32(shape, xe, nullptr, expert_rows, W1, b1, W2, b2, at<void>(ws, L.h), nullptr, nullptr, nullptr,
+                                  ye, st);
     int32_t* order = at<int32_t>(ws, L.order);
     rc = launch_expert_order(expert_rows, shape->E, shape->capacity, order, st);
     if (rc != MOE_OK) return rc;
@@ -599,27 +625,17 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
     if (rc != MOE_OK) return rc;
     const FfnPlan plan = plan_ffn(shape);
     if (!plan.mfma) {
-        // fp32 layer: the unfused sequence dispatch -> FFN -> [dense branch] -> combine
-        prof_pre(ST_DISPATCH, st);
-        rc = launch_dispatch(x, dt, slot_token, rows, at<void>(ws, L.xe), E, C, d, st);
-        prof_mark(ST_DISPATCH, st);
-        if (rc != MOE_OK) return rc;
-        prof_pre(ST_GEMM2, st);
-        rc = run_ffn_simple(dt, E, C, rows, 0, d, f, at<void>(ws, L.xe), W1, b1, W2, b2, at<void>(ws, L.h),
-                            at<void>(ws, L.ye), st);
-        prof_mark(ST_GEMM2, st);
-        if (rc != MOE_OK) return rc;
-        const void* addend = nullptr;
-        if (shape->residual) {
-            prof_pre(ST_DENSE2, st);
-            rc = run_ffn_simple(dt, 1, T, nullptr, T, d, f, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd),
-                                at<void>(ws, L.dense), st);
-            prof_mark(ST_DENSE2, st);
-            if (rc != MOE_OK) return rc;
-            addend = at<void>(ws, L.dense);
-        }
+        // fp32 layer: rows gathered inside GEMM-1; combine inside GEMM-2 (top-1), the dense branch's second GEMM
+        // (residual) or, for top-2, a kernel of its own
+        const bool scatter = k == 1 && !shape->residual;
+        void* ye = at<void>(ws, L.ye);
+        rc = run_expert_ffn_f32(shape, x, slot_token, rows, W1, b1, W2, b2, at<void>(ws, L.h), scatter ? slot_token : nullptr,
+                                slot_idx, gate_w, scatter ? out : ye, st);
+        if (rc != MOE_OK || scatter) return rc;
+        if (shape->residual)
+            return run_dense_f32(shape, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd), ye, expert_idx, slot_idx, gate_w, out, st);
         prof_pre(ST_COMBINE, st);
-        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, addend, out, T, k, C, d, st);
+        rc = launch_combine(ye, dt, expert_idx, slot_idx, gate_w, nullptr, out, T, k, C, d, st);
         prof_mark(ST_COMBINE, st);
         return rc;
     }

@@ -1,0 +1,280 @@
+// Grouped GEMM of the fp32 layer on the fp32 matrix cores (paper Sec. 3.1: each expert is an FFN; this is one of its
+// two products), with the layout transforms of Sec. 5.4 fused in as in the bf16 kernels:
+//   out[g, r, n] = epi( sum_k A[row(g, r), k] B[g, k, n] + bias[g, n] ),  r < rows(g)
+// where row() may go through the slot->token table (dispatch) and epi may scale by the gate probability and write the
+// token's row, or add the expert outputs to the dense branch (combine).
+//
+// v_mfma_f32_16x16x4_f32, fp32 all the way.  A lane (c = lane % 16, kg = lane / 16) holds four consecutive k
+// (4 kg .. 4 kg + 3 of a 16-deep block) of one activation row, and four consecutive columns 4c .. 4c + 3 of the weight
+// rows with the same k: matrix instruction (j, i) multiplies element j of the first with element i of the second, so
+// every operand is a 16-byte access, no value is moved between lanes, and a lane ends with four consecutive columns
+// of four rows (16-byte stores).
+//
+// Two kernels:
+//   * f32_tile_kernel, groups of more than 32 rows: bound by the fp32 matrix cores (157 TFLOP/s).  64 x 128 or
+//     128 x 64 tiles of four 32 x 64 waves, 32-deep chunks double-buffered in LDS (52 KB: three work-groups per CU, so
+//     that one's barrier and memory waits are another's matrix time; a chunk is 2048 matrix clocks against 24 KB of
+//     operands, 12 B per clock and CU).  Weight rows of 256 bytes are read without bank conflicts as they are;
+//     activation rows are padded to 160 bytes (2 x odd 16-byte units), which sends the 16 lanes of one LDS pass
+//     (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
+//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP): 627 us on vector ALUs before.
+//   * f32_rows_kernel, groups of at most 32 rows: a read of the weights, bound by latency when they are few.  A
+//     work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from memory into
+//     registers, three blocks ahead, and add up through LDS in wave order.
+//     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before.
+#include <type_traits>
+
+#include "moe_internal.h"
+
+namespace moe {
+
+namespace {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+// Finishes columns n .. n + 3 of row r of group g (acc without the bias on entry).
+template <int EPI>
+__device__ __forceinline__ void f32_finish(const GemmArgs& a, int g, int r, int n, f32x4_t v) {
+    const float* bias = static_cast<const float*>(a.bias);
+    if (bias) v += *reinterpret_cast<const f32x4_t*>(bias + (size_t)g * a.N + n);
+    size_t orow = (size_t)g * a.o_group_stride + r;
+    if (EPI == EPI_GELU) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = gelu_tanh(v[i]);
+    } else if (EPI == EPI_SCATTER) {
+        orow = (size_t)a.scatter_map[(size_t)g * a.max_rows + r];
+        v *= a.gate_w[orow * a.top_k];
+    } else if (EPI == EPI_COMBINE) {
+        for (int j = 0; j < a.top_k; ++j) {
+            const int s = a.slot_idx[orow * a.top_k + j];
+            if (s < 0) continue;
+            const int e = a.expert_idx[orow * a.top_k + j];
+            const float gw = a.gate_w[orow * a.top_k + j];
+            const f32x4_t y = *reinterpret_cast<const f32x4_t*>(static_cast<const float*>(a.ye) + ((size_t)e * a.C + s) * a.N + n);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = fmaf(gw, y[i], v[i]);
+        }
+    }
+    *reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + orow * a.N + n) = v;
+}
+
+// EPI_SCATTER leaves the rows of dropped tokens unwritten: zero them, spread over all work-groups.
+__device__ __forceinline__ void f32_zero_dropped(const GemmArgs& a, int tid, int nthreads) {
+    for (int t = blockIdx.x; t < a.T; t += gridDim.x) {
+        if (a.slot_idx[(size_t)t * a.top_k] >= 0) continue;
+        f32x4_t* o = reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + (size_t)t * a.N);
+        for (int i = tid; i < a.N / 4; i += nthreads) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+}
+
+__device__ __forceinline__ int f32_rows_of(const GemmArgs& a, int g) { return a.rows ? min(a.rows[g], a.max_rows) : a.fixed_rows; }
+// activation row of (g, r)
+__device__ __forceinline__ const float* f32_arow(const GemmArgs& a, int g, int r) {
+    const long long ar = a.row_map ? (long long)a.row_map[(size_t)g * a.max_rows + r] : (long long)g * a.a_group_stride + r;
+    return static_cast<const float*>(a.A) + (size_t)ar * a.K;
+}
+
+// ---- more than 32 rows per group -----------------------------------------------------------------------------
+constexpr int kFK = 32;                       // k per chunk
+constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
+
+// WMW x WNW waves of 32 rows x 64 columns
+template <int WMW, int WNW, int EPI>
+__global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a, const int n_tiles, const int m_tiles) {
+    static_assert(WMW * WNW == 4, "four waves");
+    constexpr int TM = WMW * 32, TN = WNW * 64;
+    constexpr int A_BYTES = TM * kFStride, BUF = A_BYTES + kFK * TN * 4;
+    constexpr int NPA = TM * kFK / 4 / 256, NPB = TN * kFK / 4 / 256;      // 16-byte pieces per thread and chunk
+    __shared__ __attribute__((aligned(16))) char lds[2 * BUF];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kg = lane >> 4;
+    const int wm = w / WNW, wn = w % WNW;
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, 256);
+    // column tiles innermost: with a multiple of 8 of them all row tiles of a column tile run on one XCD and share its
+    // weights in that L2, and every XCD has the same work however unevenly the rows fall on the groups
+    const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles % m_tiles, g = blockIdx.x / n_tiles / m_tiles;
+    const int rows = f32_rows_of(a, g), m0 = mt * TM, n0 = nt * TN;
+    if (m0 >= rows) return;
+
+    const float* a_src[NPA];
+    int a_k[NPA];
+    uint32_t a_dst[NPA];
+#pragma unroll
+    for (int i = 0; i < NPA; ++i) {
+        const int p = tid + i * 256, r = p / (kFK / 4), kp = p % (kFK / 4);
+        a_src[i] = f32_arow(a, g, min(m0 + r, rows - 1));                  // rows past the end repeat the last one
+        a_k[i] = kp * 4;
+        a_dst[i] = r * kFStride + kp * 16;
+    }
+    const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
+    const int b_k = tid / (TN / 4), b_n = min(n0 + tid % (TN / 4) * 4, a.N - 4);   // columns past the end: never stored
+    constexpr int B_STEP = 256 / (TN / 4);                                 // k-rows between two pieces of a thread
+    f32x4_t areg[NPA], breg[NPB];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < NPA; ++i) areg[i] = *reinterpret_cast<const f32x4_t*>(a_src[i] + min(k0 + a_k[i], a.K - 4));
+#pragma unroll
+        for (int i = 0; i < NPB; ++i)
+            breg[i] = *reinterpret_cast<const f32x4_t*>(B + (size_t)min(k0 + b_k + i * B_STEP, a.K - 1) * a.N + b_n);
+    };
+    auto store = [&](int k0, int buf) {              // zeros past K (a multiple of 4: all four of a piece or none)
+        char* base = lds + buf * BUF;
+#pragma unroll
+        for (int i = 0; i < NPA; ++i)
+            *reinterpret_cast<f32x4_t*>(base + a_dst[i]) = k0 + a_k[i] < a.K ? areg[i] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < NPB; ++i) *reinterpret_cast<f32x4_t*>(base + A_BYTES + (tid + i * 256) * 16) = breg[i];
+    };
+
+    f32x4_t acc[2][4];
+#pragma unroll
+    for (int ms = 0; ms < 2; ++ms)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    // a wave whose second (or both) 16-row sub-tiles lie past the last row leaves them out
+    const int nsub = __builtin_amdgcn_readfirstlane(max(0, min(2, (rows - m0 - wm * 32 + 15) / 16)));
+    auto multiply = [&](int buf, auto ms_count) {
+        constexpr int MS = decltype(ms_count)::value;
+        const char* ap = lds + buf * BUF + (wm * 32 + c) * kFStride + kg * 16;
+        const char* bp = lds + buf * BUF + A_BYTES + (kg * 4 * TN + wn * 64 + c * 4) * 4;
+#pragma unroll
+        for (int kb = 0; kb < kFK / 16; ++kb) {
+            f32x4_t av[MS], bv[4];
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms) av[ms] = *reinterpret_cast<const f32x4_t*>(ap + ms * 16 * kFStride + kb * 64);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bv[j] = *reinterpret_cast<const f32x4_t*>(bp + (kb * 16 + j) * TN * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms)
+                        acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ms][j], bv[j][i], acc[ms][i], 0, 0, 0);
+        }
+    };
+
+    const int chunks = (a.K + kFK - 1) / kFK;
+    load(0);
+    store(0, 0);
+    __syncthreads();
+    for (int ch = 0; ch < chunks; ++ch) {
+        load((ch + 1) * kFK);                        // past the end: in bounds (clamped), not used
+        if (nsub == 2) multiply(ch & 1, std::integral_constant<int, 2>());
+        else if (nsub == 1) multiply(ch & 1, std::integral_constant<int, 1>());
+        store((ch + 1) * kFK, (ch + 1) & 1);         // its readers passed the barrier below one chunk ago
+        __syncthreads();
+    }
+
+    const int n = n0 + wn * 64 + c * 4;
+    if (n >= a.N) return;
+#pragma unroll
+    for (int ms = 0; ms < 2; ++ms)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int row = m0 + wm * 32 + ms * 16 + kg * 4 + r;
+            if (row < rows) f32_finish<EPI>(a, g, row, n, f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]});
+        }
+}
+
+// ---- at most 32 rows per group -------------------------------------------------------------------------------
+constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
+constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
+
+template <int MS, int EPI>
+__global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
+    __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves][MS * 16][16];
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kg = lane >> 4;
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
+    const int nt = blockIdx.x % n_tiles, g = blockIdx.x / n_tiles;
+    const int rows = f32_rows_of(a, g), n0 = nt * 64;
+    if (rows <= 0) return;
+
+    const float* a_src[MS];
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms) a_src[ms] = f32_arow(a, g, min(ms * 16 + c, rows - 1));
+    const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N + min(n0 + c * 4, a.N - 4);
+    struct Block {
+        f32x4_t av[MS], bv[4];
+    };
+    auto load = [&](Block& b, int kb) {
+        const int k = kb * 16 + kg * 4;                      // K is a multiple of 4: a lane's four k are all inside or all outside
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms) b.av[ms] = *reinterpret_cast<const f32x4_t*>(a_src[ms] + min(k, a.K - 4));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) b.bv[j] = *reinterpret_cast<const f32x4_t*>(B + (size_t)min(k + j, a.K - 1) * a.N);
+    };
+    f32x4_t acc[MS][4];
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const int blocks = (a.K + 15) / 16;
+    Block st[kFAhead];
+#pragma unroll
+    for (int s = 0; s < kFAhead; ++s) load(st[s], w + s * kFWaves);        // past the end: in bounds (clamped), meets zeros
+    for (int kb = w; kb < blocks; kb += kFAhead * kFWaves) {
+#pragma unroll
+        for (int s = 0; s < kFAhead; ++s) {
+            const bool in = (kb + s * kFWaves) * 16 + kg * 4 < a.K;
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms)
+                if (!in) st[s].av[ms] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms)
+                        acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[s].av[ms][j], st[s].bv[j][i], acc[ms][i], 0, 0, 0);
+            load(st[s], kb + (s + kFAhead) * kFWaves);
+            __builtin_amdgcn_sched_barrier(0);           // the refill stays here, kFAhead blocks ahead of its use
+        }
+    }
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
+    __syncthreads();
+    const int row = tid / 16, n = n0 + (tid & 15) * 4;
+    if (row >= rows || row >= MS * 16 || n >= a.N) return;
+    f32x4_t v = part[0][row][tid & 15];
+#pragma unroll
+    for (int s = 1; s < kFWaves; ++s) v += part[s][row][tid & 15];
+    f32_finish<EPI>(a, g, row, n, v);
+}
+
+template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
+    long long blocks;
+    if (a.max_rows <= 32) {
+        const int n_tiles = (a.N + 63) / 64;
+        blocks = (long long)a.G * n_tiles;
+        if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;
+        if (a.max_rows <= 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), dim3((unsigned)blocks), dim3(kFWaves * 64), 0, s, a, n_tiles);
+        else hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), dim3((unsigned)blocks), dim3(kFWaves * 64), 0, s, a, n_tiles);
+    } else {
+        const bool narrow = a.N <= 64;                       // one 64-column tile: all four waves along the rows
+        const int n_tiles = narrow ? 1 : (a.N + 127) / 128, tm = narrow ? 128 : 64, m_tiles = (a.max_rows + tm - 1) / tm;
+        blocks = (long long)a.G * n_tiles * m_tiles;
+        if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;
+        if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), dim3((unsigned)blocks), dim3(256), 0, s, a, n_tiles, m_tiles);
+        else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), dim3((unsigned)blocks), dim3(256), 0, s, a, n_tiles, m_tiles);
+    }
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
+}  // namespace
+
+int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s) {
+    if (a.max_rows <= 0 || a.G <= 0) return MOE_OK;
+    if (a.K % 4 || a.N % 4) return MOE_ERR_INVALID_ARG;
+    switch (epi) {
+        case EPI_STORE: return launch_epi<EPI_STORE>(a, s);
+        case EPI_GELU: return launch_epi<EPI_GELU>(a, s);
+        case EPI_SCATTER: return launch_epi<EPI_SCATTER>(a, s);
+        case EPI_COMBINE: return launch_epi<EPI_COMBINE>(a, s);
+        default: return MOE_ERR_INVALID_ARG;
+    }
+}
+
+}  // namespace moe

@@ -114,25 +114,7 @@ int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const i
                    const float* gate_w, const void* addend, void* out,
                    int T, int k, int C, int d, hipStream_t s);
 
-// Grouped GEMM  out[g, r, :] = epi( A[row(g,r), :] . B[g] + bias[g] )  for r < rows(g).
-struct GemmArgs {
-    const void* A;            // activations, row-major, leading dimension K
-    const void* B;            // [G, K, N] weights
-    const void* bias;         // [G, N] or nullptr
-    void* out;                // row-major, leading dimension N
-    const int32_t* rows;      // [G] device row counts, or nullptr -> fixed_rows for every group
-    const int32_t* row_map;   // [G, max_rows] A-row index per (g, r) (negative = skip), or nullptr
-    int32_t fixed_rows;
-    int32_t max_rows;         // upper bound of rows(g): sizes the grid
-    int32_t G, K, N;
-    int64_t a_group_stride;   // in rows; A-row of (g, r) = g*a_group_stride + r when row_map == nullptr
-    int64_t o_group_stride;   // in rows; out-row of (g, r) = g*o_group_stride + r
-    int32_t gelu;             // 1: gelu_tanh after the bias
-    int32_t dtype;            // element type of A, B, bias, out
-};
-int launch_gemm_simple(const GemmArgs& a, hipStream_t s);
-
-// bf16 MFMA weight-streaming grouped GEMM (ffn_mfma.hip).
+// What a grouped GEMM does with a finished row.
 enum WsEpilogue {
     EPI_STORE = 0,    // out[g*o_group_stride + r, :] = acc + bias
     EPI_GELU = 1,     // out[g*o_group_stride + r, :] = gelu_tanh(acc + bias)
@@ -140,6 +122,34 @@ enum WsEpilogue {
     EPI_COMBINE = 3,  // out[r, :] = acc + bias + sum_j keep_j g_j ye[e_j, slot_j, :]   (dense branch + combine)
     EPI_PARTIAL = 4   // partial[ks, g*o_group_stride + r, :] = acc   (split-K, fp32, no bias)
 };
+// fp32 grouped GEMM on the fp32 matrix cores (gemm_f32.hip); K and N multiples of 4, no EPI_PARTIAL.
+struct GemmArgs {
+    const void* A;            // activations, row-major, leading dimension K
+    const void* B;            // [G, K, N] weights
+    const void* bias;         // [G, N] or nullptr
+    void* out;                // row-major, leading dimension N
+    const int32_t* rows;      // [G] device row counts, or nullptr -> fixed_rows for every group
+    const int32_t* row_map;   // [G, max_rows] A-row index per (g, r), or nullptr
+    int32_t fixed_rows;
+    int32_t max_rows;         // upper bound of rows(g): sizes the grid
+    int32_t G, K, N;
+    int64_t a_group_stride;   // in rows; A-row of (g, r) = g*a_group_stride + r when row_map == nullptr
+    int64_t o_group_stride;   // in rows; out-row of (g, r) = g*o_group_stride + r
+    // EPI_SCATTER
+    const int32_t* scatter_map;    // [G, max_rows] token per expert row
+    int32_t T;                     // tokens; those with slot_idx < 0 get zero rows (top_k == 1)
+    // EPI_SCATTER / EPI_COMBINE
+    const float* gate_w;           // [T, top_k]
+    const int32_t* slot_idx;       // [T, top_k]
+    int32_t top_k;
+    // EPI_COMBINE
+    const void* ye;                // [E, C, N]
+    const int32_t* expert_idx;     // [T, top_k]
+    int32_t C;
+};
+int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s);
+
+// bf16 MFMA weight-streaming grouped GEMM (ffn_mfma.hip).
 struct WsGemmArgs {
     const uint16_t* A;         // activations, leading dimension K
     const uint16_t* B;         // [G, K, N], or the same weights in fragment order (packed != 0)
