@@ -12,12 +12,15 @@
 //
 // Two kernels:
 //   * f32_tile_kernel, groups of more than 32 rows: bound by the fp32 matrix cores (157 TFLOP/s).  64 x 128 or
-//     128 x 64 tiles of four 32 x 64 waves, 32-deep chunks double-buffered in LDS (52 KB: three work-groups per CU, so
-//     that one's barrier and memory waits are another's matrix time; a chunk is 2048 matrix clocks against 24 KB of
-//     operands, 12 B per clock and CU).  Weight rows of 256 bytes are read without bank conflicts as they are;
-//     activation rows are padded to 160 bytes (2 x odd 16-byte units), which sends the 16 lanes of one LDS pass
-//     (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
-//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP): 627 us on vector ALUs before.
+//     128 x 64 tiles of four 32 x 64 sub-tiles, each by two waves that halve every 32-deep chunk of K between them (one
+//     work-group of eight waves has a compute unit to itself at the usual sizes, and one wave per SIMD left every LDS
+//     and barrier wait exposed).  Chunks are double-buffered in LDS, fragments in registers; loads, LDS reads and LDS
+//     writes of later chunks are placed between the matrix instructions of this one.  Weight rows of 256 bytes are read
+//     without bank conflicts as they are; activation rows are padded to 160 bytes (2 x odd 16-byte units), which
+//     sends the 16 lanes of one LDS pass (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
+//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 80 + 71 us
+//     (85 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
+//     vector ALUs, before: 162 + 465.
 //   * f32_rows_kernel, groups of at most 32 rows: a read of the weights, bound by latency when they are few.  A
 //     work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from memory into
 //     registers, three blocks ahead, and add up through LDS in wave order.
@@ -78,17 +81,17 @@ __device__ __forceinline__ const float* f32_arow(const GemmArgs& a, int g, int r
 constexpr int kFK = 32;                       // k per chunk
 constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
 
-// WMW x WNW waves of 32 rows x 64 columns
+// WMW x WNW pairs of waves of 32 rows x 64 columns; wave 0 of a pair takes the first half of every chunk, wave 1 the second
 template <int WMW, int WNW, int EPI>
-__global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a, const int n_tiles, const int m_tiles) {
-    static_assert(WMW * WNW == 4, "four waves");
+__global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, const int n_tiles, const int m_tiles) {
+    static_assert(WMW * WNW == 4, "four pairs of waves");
     constexpr int TM = WMW * 32, TN = WNW * 64;
     constexpr int A_BYTES = TM * kFStride, BUF = A_BYTES + kFK * TN * 4;
-    constexpr int NPA = TM * kFK / 4 / 256, NPB = TN * kFK / 4 / 256;      // 16-byte pieces per thread and chunk
+    constexpr int NPA = TM * kFK / 4 / 512, NPB = TN * kFK / 4 / 512;      // 16-byte pieces per thread and chunk
     __shared__ __attribute__((aligned(16))) char lds[2 * BUF];
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kg = lane >> 4;
-    const int wm = w / WNW, wn = w % WNW;
-    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, 256);
+    const int kh = w >> 2, wm = (w & 3) / WNW, wn = (w & 3) % WNW;
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, 512);
     // column tiles innermost: with a multiple of 8 of them all row tiles of a column tile run on one XCD and share its
     // weights in that L2, and every XCD has the same work however unevenly the rows fall on the groups
     const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles % m_tiles, g = blockIdx.x / n_tiles / m_tiles;
@@ -100,80 +103,142 @@ __global__ __launch_bounds__(256) void f32_tile_kernel(const GemmArgs a, const i
     uint32_t a_dst[NPA];
 #pragma unroll
     for (int i = 0; i < NPA; ++i) {
-        const int p = tid + i * 256, r = p / (kFK / 4), kp = p % (kFK / 4);
+        const int p = tid + i * 512, r = p / (kFK / 4), kp = p % (kFK / 4);
         a_src[i] = f32_arow(a, g, min(m0 + r, rows - 1));                  // rows past the end repeat the last one
         a_k[i] = kp * 4;
         a_dst[i] = r * kFStride + kp * 16;
     }
+    // Weight rows through a buffer descriptor that starts at the chunk: the lane's offsets never change, and rows past K
+    // come back as zeros.
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
-    const int b_k = tid / (TN / 4), b_n = min(n0 + tid % (TN / 4) * 4, a.N - 4);   // columns past the end: never stored
-    constexpr int B_STEP = 256 / (TN / 4);                                 // k-rows between two pieces of a thread
-    f32x4_t areg[NPA], breg[NPB];
-    auto load = [&](int k0) {
+    constexpr int B_STEP = 512 / (TN / 4);                                 // k-rows between two pieces of a thread
+    const int b_off = (tid / (TN / 4) * a.N + min(n0 + tid % (TN / 4) * 4, a.N - 4)) * 4;   // columns past the end: never stored
+    struct Chunk {
+        f32x4_t a[NPA], b[NPB];
+    };
+    auto load = [&](Chunk& q, int k0) {
 #pragma unroll
-        for (int i = 0; i < NPA; ++i) areg[i] = *reinterpret_cast<const f32x4_t*>(a_src[i] + min(k0 + a_k[i], a.K - 4));
+        for (int i = 0; i < NPA; ++i) q.a[i] = *reinterpret_cast<const f32x4_t*>(a_src[i] + min(k0 + a_k[i], a.K - 4));
+        const int k_in = __builtin_amdgcn_readfirstlane(min(k0, a.K));
+        const int left = __builtin_amdgcn_readfirstlane(min(a.K - k_in, kFK));       // rows of the chunk inside K
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B + (size_t)k_in * a.N), 0, left * a.N * 4, 0x00027000);
 #pragma unroll
         for (int i = 0; i < NPB; ++i)
-            breg[i] = *reinterpret_cast<const f32x4_t*>(B + (size_t)min(k0 + b_k + i * B_STEP, a.K - 1) * a.N + b_n);
+            q.b[i] = __builtin_bit_cast(f32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, b_off + i * B_STEP * a.N * 4, 0, 0));
     };
-    auto store = [&](int k0, int buf) {              // zeros past K (a multiple of 4: all four of a piece or none)
+    auto store = [&](const Chunk& q, int k0, int buf) {              // zeros past K (a multiple of 4: all four of a piece or none)
         char* base = lds + buf * BUF;
 #pragma unroll
         for (int i = 0; i < NPA; ++i)
-            *reinterpret_cast<f32x4_t*>(base + a_dst[i]) = k0 + a_k[i] < a.K ? areg[i] : f32x4_t{0.f, 0.f, 0.f, 0.f};
+            *reinterpret_cast<f32x4_t*>(base + a_dst[i]) = k0 + a_k[i] < a.K ? q.a[i] : f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int i = 0; i < NPB; ++i) *reinterpret_cast<f32x4_t*>(base + A_BYTES + (tid + i * 256) * 16) = breg[i];
+        for (int i = 0; i < NPB; ++i) *reinterpret_cast<f32x4_t*>(base + A_BYTES + (tid + i * 512) * 16) = q.b[i];
     };
 
-    f32x4_t acc[2][4];
+    const int chunks = (a.K + kFK - 1) / kFK;
+    // The rest exists once per number MS of 16-row sub-tiles that a wave works on (sub-tiles past the last row are left
+    // out; the choice is the wave's): branches inside one loop would move the accumulators around at every chunk.
+    auto run = [&](auto ms_count) {
+        constexpr int MS = decltype(ms_count)::value, NA = MS > 0 ? MS : 1;
+        f32x4_t acc[NA][4];
 #pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
+        for (int ms = 0; ms < NA; ++ms)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    // a wave whose second (or both) 16-row sub-tiles lie past the last row leaves them out
-    const int nsub = __builtin_amdgcn_readfirstlane(max(0, min(2, (rows - m0 - wm * 32 + 15) / 16)));
-    auto multiply = [&](int buf, auto ms_count) {
-        constexpr int MS = decltype(ms_count)::value;
-        const char* ap = lds + buf * BUF + (wm * 32 + c) * kFStride + kg * 16;
-        const char* bp = lds + buf * BUF + A_BYTES + (kg * 4 * TN + wn * 64 + c * 4) * 4;
+            for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        struct Frags {
+            f32x4_t a[NA], b[4];
+        };
+        auto read = [&](Frags& f, int buf) {
+            if (MS == 0) return;
+            const char* ap = lds + buf * BUF + (wm * 32 + c) * kFStride + kh * 64 + kg * 16;
+            const char* bp = lds + buf * BUF + A_BYTES + ((kh * 16 + kg * 4) * TN + wn * 64 + c * 4) * 4;
 #pragma unroll
-        for (int kb = 0; kb < kFK / 16; ++kb) {
-            f32x4_t av[MS], bv[4];
+            for (int ms = 0; ms < MS; ++ms) f.a[ms] = *reinterpret_cast<const f32x4_t*>(ap + ms * 16 * kFStride);
 #pragma unroll
-            for (int ms = 0; ms < MS; ++ms) av[ms] = *reinterpret_cast<const f32x4_t*>(ap + ms * 16 * kFStride + kb * 64);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bv[j] = *reinterpret_cast<const f32x4_t*>(bp + (kb * 16 + j) * TN * 4);
+            for (int j = 0; j < 4; ++j) f.b[j] = *reinterpret_cast<const f32x4_t*>(bp + j * TN * 4);
+        };
+        auto multiply = [&](const Frags& f) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
                     for (int ms = 0; ms < MS; ++ms)
-                        acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[ms][j], bv[j][i], acc[ms][i], 0, 0, 0);
+                        acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(f.a[ms][j], f.b[j][i], acc[ms][i], 0, 0, 0);
+        };
+        // In step ch the fragments of chunk ch are in registers and chunk ch + 1 is in LDS; its fragments are read while
+        // ch is multiplied, ch + 2 goes from registers into the buffer that ch has left, ch + 3 is fetched.
+        Chunk q0, q1;
+        Frags f0, f1;
+        load(q0, 0);
+        load(q1, kFK);
+        store(q0, 0, 0);
+        load(q0, 2 * kFK);                               // past the end: in bounds (clamped), not used
+        store(q1, kFK, 1);
+        lds_barrier();
+        read(f0, 0);
+        auto step = [&](const Frags& cur, Frags& nxt, Chunk& ready, Chunk& refill, int ch) {
+            lds_barrier();                               // ch + 1 is in LDS, and everybody has the fragments of ch
+            read(nxt, (ch + 1) & 1);
+            load(refill, (ch + 3) * kFK);
+            multiply(cur);
+            store(ready, (ch + 2) * kFK, ch & 1);
+            // everything else goes into the shadow of the matrix instructions (32 clocks each)
+            if (MS == 2) {
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);      // matrix
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);      // LDS read
+                }
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);      // vector ALU
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);      // global load
+                }
+                __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);      // LDS write
+                    __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);           // nothing of the next step (a wait for its loads) moves up here
+        };
+        int ch = 0;
+        for (; ch + 2 <= chunks; ch += 2) {
+            step(f0, f1, q0, q1, ch);
+            step(f1, f0, q1, q0, ch + 1);
         }
+        if (ch < chunks) step(f0, f1, q0, q1, ch);
+        lds_barrier();
+
+        // the two halves of a pair's sums meet in LDS (the chunks' readers are done)
+        f32x4_t* red = reinterpret_cast<f32x4_t*>(lds) + (w & 3) * 8 * 64 + lane;
+        static_assert(4 * 8 * 64 * 16 <= 2 * BUF, "partial sums fit");
+        if (kh == 1) {
+#pragma unroll
+            for (int q = 0; q < 4 * MS; ++q) red[q * 64] = acc[q / 4][q % 4];
+        }
+        lds_barrier();
+        const int n = n0 + wn * 64 + c * 4;
+        if (kh == 1 || n >= a.N) return;
+#pragma unroll
+        for (int q = 0; q < 4 * MS; ++q) acc[q / 4][q % 4] += red[q * 64];
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = m0 + wm * 32 + ms * 16 + kg * 4 + r;
+                if (row < rows) f32_finish<EPI>(a, g, row, n, f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]});
+            }
     };
-
-    const int chunks = (a.K + kFK - 1) / kFK;
-    load(0);
-    store(0, 0);
-    __syncthreads();
-    for (int ch = 0; ch < chunks; ++ch) {
-        load((ch + 1) * kFK);                        // past the end: in bounds (clamped), not used
-        if (nsub == 2) multiply(ch & 1, std::integral_constant<int, 2>());
-        else if (nsub == 1) multiply(ch & 1, std::integral_constant<int, 1>());
-        store((ch + 1) * kFK, (ch + 1) & 1);         // its readers passed the barrier below one chunk ago
-        __syncthreads();
-    }
-
-    const int n = n0 + wn * 64 + c * 4;
-    if (n >= a.N) return;
-#pragma unroll
-    for (int ms = 0; ms < 2; ++ms)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = m0 + wm * 32 + ms * 16 + kg * 4 + r;
-            if (row < rows) f32_finish<EPI>(a, g, row, n, f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]});
-        }
+    const int nsub = __builtin_amdgcn_readfirstlane(max(0, min(2, (rows - m0 - wm * 32 + 15) / 16)));
+    if (nsub == 2) run(std::integral_constant<int, 2>());
+    else if (nsub == 1) run(std::integral_constant<int, 1>());
+    else run(std::integral_constant<int, 0>());
 }
 
 // ---- at most 32 rows per group -------------------------------------------------------------------------------
@@ -257,8 +322,8 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
         const int n_tiles = narrow ? 1 : (a.N + 127) / 128, tm = narrow ? 128 : 64, m_tiles = (a.max_rows + tm - 1) / tm;
         blocks = (long long)a.G * n_tiles * m_tiles;
         if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;
-        if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), dim3((unsigned)blocks), dim3(256), 0, s, a, n_tiles, m_tiles);
-        else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), dim3((unsigned)blocks), dim3(256), 0, s, a, n_tiles, m_tiles);
+        if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), dim3((unsigned)blocks), dim3(512), 0, s, a, n_tiles, m_tiles);
+        else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), dim3((unsigned)blocks), dim3(512), 0, s, a, n_tiles, m_tiles);
     }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
