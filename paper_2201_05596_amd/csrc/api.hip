@@ -83,6 +83,8 @@ struct FfnPlan {
     int ksplit2;        // split-K factor of GEMM-2 (1 = none)
     bool tiled;         // more than 64 rows per expert: the tiled (matrix-core-bound) kernel
     int NBUF;           // weight super-fragments kept in flight per wave, plus one
+    int nf1, nf2;       // 16-column fragments per work-group of the few-weights kernel, 0: not that kernel
+    int slots;          // launch-order entries that may have rows, 0: all
 };
 
 FfnPlan plan_ffn(const moe_shape_t* s) {
@@ -99,7 +101,13 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     const long long touched = s->E < (long long)s->T * s->top_k ? s->E : (long long)s->T * s->top_k;
     const long long m_tiles = (s->capacity + p.MT - 1) / p.MT;
     const long long waves = touched * ((s->d_model + 127) / 128) * m_tiles;
-    if (waves < 1024 && !p.tiled) {
+    const long long kept = (long long)s->T * s->top_k;
+    const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
+    if (!p.tiled) {
+        p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed);
+        p.nf2 = rows_pick_gemm2(touched, s->capacity, kept, s->d_ffn, s->d_model, packed, waves < 1024);
+    }
+    if (waves < 1024 && !p.tiled && !p.nf2) {
         const int chunks = (s->d_ffn + wsgemm_chunk_k(p.MT) - 1) / wsgemm_chunk_k(p.MT);
         long long ks = (2048 + waves - 1) / waves;
         if (ks > 8) ks = 8;
@@ -269,18 +277,34 @@ int run_dense_f32(const moe_shape_t* s, const void* x, const void* Wd1, const vo
 inline const uint16_t* u16(const void* p) { return static_cast<const uint16_t*>(p); }
 inline uint16_t* u16(void* p) { return static_cast<uint16_t*>(p); }
 
-// Expert GEMM-1 on the MFMA kernel: h[e, r, :] = gelu_tanh(A_row(e, r) W1[e] + b1[e]).
+// Expert GEMM-1 on the MFMA kernels: h[e, r, :] = gelu_tanh(A_row(e, r) W1[e] + b1[e]).
 // row_map == nullptr: A rows are xin[e*C + r]; otherwise xin[row_map[e*C + r]] (dispatch fused in).
+WsGemmArgs expert_gemm1_args(const moe_shape_t* s, const FfnPlan& p, const void* xin, const int32_t* row_map,
+                             const int32_t* rows, const int32_t* order, const void* W1, const void* b1, void* h) {
+    WsGemmArgs a{};
+    a.A = u16(xin); a.B = u16(W1); a.bias = u16(b1); a.rows = rows; a.order = order; a.row_map = row_map;
+    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS; a.slots = p.slots;
+    a.max_rows = s->capacity; a.map_stride = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
+    a.a_group_stride = s->capacity; a.out = u16(h); a.o_group_stride = s->capacity; a.ksplit = 1;
+    return a;
+}
+// First product of the dense branch of Residual-MoE: hd = gelu_tanh(x Wd1 + bd1)
+WsGemmArgs dense_gemm1_args(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, void* hd) {
+    WsGemmArgs a{};
+    a.A = u16(x); a.B = u16(Wd1); a.bias = u16(bd1); a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1;
+    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
+    a.K = s->d_model; a.N = s->d_ffn; a.out = u16(hd); a.ksplit = 1;
+    return a;
+}
+
 int run_expert_gemm1(const moe_shape_t* s, const FfnPlan& p, const void* xin, const int32_t* row_map,
                      const int32_t* rows, const int32_t* order, const void* W1, const void* b1, void* h,
                      hipStream_t st) {
-    WsGemmArgs a{};
-    a.A = u16(xin); a.B = u16(W1); a.bias = u16(b1); a.rows = rows; a.order = order; a.row_map = row_map;
-    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
-    a.max_rows = s->capacity; a.map_stride = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
-    a.a_group_stride = s->capacity; a.out = u16(h); a.o_group_stride = s->capacity; a.ksplit = 1;
+    const WsGemmArgs a = expert_gemm1_args(s, p, xin, row_map, rows, order, W1, b1, h);
     prof_pre(ST_GEMM1, st);
-    const int rc = p.tiled ? launch_tgemm(a, EPI_GELU, st) : launch_wsgemm(a, EPI_GELU, p.MT, p.NW1, p.NBUF, st);
+    const int rc = p.nf1     ? launch_rows(a, nullptr, EPI_GELU, p.nf1, st)
+                   : p.tiled ? launch_tgemm(a, EPI_GELU, st)
+                             : launch_wsgemm(a, EPI_GELU, p.MT, p.NW1, p.NBUF, st);
     prof_mark(ST_GEMM1, st);
     return rc;
 }
@@ -296,7 +320,7 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     // that the short tiles of the light ones fill the end (the second list).  GEMM-1 and the streaming kernel keep
     // the list that alternates busy and light experts.
     a.order = order && p.tiled ? order + s->E + 1 : order;
-    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
+    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS; a.slots = p.slots;
     a.max_rows = s->capacity; a.G = s->E; a.K = s->d_ffn; a.N = s->d_model;
     a.a_group_stride = s->capacity; a.out = u16(dst); a.o_group_stride = s->capacity; a.ksplit = p.ksplit2;
     a.scatter_map = slot_token; a.scatter_stride = s->capacity; a.zero_slot_idx = slot_idx; a.T = s->T;
@@ -304,7 +328,9 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     prof_pre(ST_GEMM2, st);
     if (p.ksplit2 == 1) {
         const int epi = scatter ? EPI_SCATTER : EPI_STORE;
-        const int rc1 = p.tiled ? launch_tgemm(a, epi, st) : launch_wsgemm(a, epi, p.MT, p.NW2, p.NBUF, st);
+        const int rc1 = p.nf2     ? launch_rows(a, nullptr, epi, p.nf2, st)
+                        : p.tiled ? launch_tgemm(a, epi, st)
+                                  : launch_wsgemm(a, epi, p.MT, p.NW2, p.NBUF, st);
         prof_mark(ST_GEMM2, st);
         return rc1;
     }
@@ -324,28 +350,34 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     return rc;
 }
 
-// Dense branch of Residual-MoE on the MFMA kernel, with the combine fused into its second GEMM:
+// Dense branch of Residual-MoE on the MFMA kernels, with the combine fused into its second GEMM:
 // out[t, :] = gelu_tanh(x[t] Wd1 + bd1) Wd2 + bd2 + sum_j keep_j g_j ye[e_j, slot_j, :].
+// first_done: hd is there already (the first product shared a launch with the experts').
 int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, const void* Wd2,
-                     const void* bd2, void* hd, const void* ye, const int32_t* expert_idx, const int32_t* slot_idx,
-                     const float* gate_w, void* out, hipStream_t st) {
-    int MT, NW;
-    WsGemmArgs a{};
-    a.A = u16(x); a.B = u16(Wd1); a.bias = u16(bd1); a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1;
-    a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
-    a.K = s->d_model; a.N = s->d_ffn; a.out = u16(hd); a.ksplit = 1;
-    wsgemm_pick_tile(s->T, 1, s->d_ffn, &MT, &NW);
+                     const void* bd2, void* hd, bool first_done, const void* ye, const int32_t* expert_idx,
+                     const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
+    int MT, NW, rc = MOE_OK;
+    WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
     const bool tiled = s->T > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
-    prof_pre(ST_DENSE1, st);
-    int rc = tiled ? launch_tgemm(a, EPI_GELU, st) : launch_wsgemm(a, EPI_GELU, MT, NW, 2, st);
-    prof_mark(ST_DENSE1, st);
-    if (rc != MOE_OK) return rc;
+    if (!first_done) {
+        const int nf = rows_pick_dense(s->T, s->d_ffn, a.packed);
+        wsgemm_pick_tile(s->T, 1, s->d_ffn, &MT, &NW);
+        prof_pre(ST_DENSE1, st);
+        rc = nf      ? launch_rows(a, nullptr, EPI_GELU, nf, st)
+             : tiled ? launch_tgemm(a, EPI_GELU, st)
+                     : launch_wsgemm(a, EPI_GELU, MT, NW, 2, st);
+        prof_mark(ST_DENSE1, st);
+        if (rc != MOE_OK) return rc;
+    }
     a.A = u16(hd); a.B = u16(Wd2); a.bias = u16(bd2); a.K = s->d_ffn; a.N = s->d_model; a.out = u16(out);
     a.ye = u16(ye); a.expert_idx = expert_idx; a.slot_idx = slot_idx; a.gate_w = gate_w; a.top_k = s->top_k;
     a.C = s->capacity;
+    const int nf = rows_pick_dense(s->T, s->d_model, a.packed);
     wsgemm_pick_tile(s->T, 1, s->d_model, &MT, &NW);
     prof_pre(ST_DENSE2, st);
-    rc = tiled ? launch_tgemm(a, EPI_COMBINE, st) : launch_wsgemm(a, EPI_COMBINE, MT, NW, 2, st);
+    rc = nf      ? launch_rows(a, nullptr, EPI_COMBINE, nf, st)
+         : tiled ? launch_tgemm(a, EPI_COMBINE, st)
+                 : launch_wsgemm(a, EPI_COMBINE, MT, NW, 2, st);
     prof_mark(ST_DENSE2, st);
     return rc;
 }
@@ -623,7 +655,8 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
     int32_t* order = at<int32_t>(ws, L.order);
     rc = run_gate(shape, x, Wg, bg, logits, expert_idx, slot_idx, gate_w, rows, slot_token, order, ws, L, true, st);
     if (rc != MOE_OK) return rc;
-    const FfnPlan plan = plan_ffn(shape);
+    FfnPlan plan = plan_ffn(shape);
+    plan.slots = (int)((long long)T * k < E ? (long long)T * k : E);
     if (!plan.mfma) {
         // fp32 layer: rows gathered inside GEMM-1; combine inside GEMM-2 (top-1), the dense branch's second GEMM
         // (residual) or, for top-2, a kernel of its own
@@ -647,7 +680,18 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
         if (rc != MOE_ERR_UNSUPPORTED) return rc;
     }
     // bf16: dispatch is fused into GEMM-1 (rows gathered through slot_token) ...
-    rc = run_expert_gemm1(shape, plan, x, slot_token, rows, order, W1, b1, at<void>(ws, L.h), st);
+    bool dense1_done = false;
+    if (shape->residual && plan.nf1 && T <= 16 && rows_pick_dense(T, f, shape->flags & MOE_FLAG_PACKED_WEIGHTS)) {
+        // ... which takes the dense branch's first product along when both read little but weights
+        const WsGemmArgs d1 = dense_gemm1_args(shape, x, Wd1, bd1, at<void>(ws, L.hd));
+        prof_pre(ST_GEMM1, st);
+        rc = launch_rows(expert_gemm1_args(shape, plan, x, slot_token, rows, order, W1, b1, at<void>(ws, L.h)), &d1, EPI_GELU,
+                         plan.nf1, st);
+        prof_mark(ST_GEMM1, st);
+        dense1_done = true;
+    } else {
+        rc = run_expert_gemm1(shape, plan, x, slot_token, rows, order, W1, b1, at<void>(ws, L.h), st);
+    }
     if (rc != MOE_OK) return rc;
     // ... and, for top-1 Standard-MoE, combine into GEMM-2 (scale by the gate weight, write the token's row)
     if (k == 1 && !shape->residual)
@@ -657,8 +701,8 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
                           at<void>(ws, L.ye), at<float>(ws, L.partial), st);
     if (rc != MOE_OK) return rc;
     if (shape->residual)
-        return run_dense_branch(shape, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd), at<void>(ws, L.ye), expert_idx,
-                                slot_idx, gate_w, out, st);
+        return run_dense_branch(shape, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd), dense1_done, at<void>(ws, L.ye),
+                                expert_idx, slot_idx, gate_w, out, st);
     prof_pre(ST_COMBINE, st);
     rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, nullptr, out, T, k, C, d, st);
     prof_mark(ST_COMBINE, st);
@@ -720,6 +764,7 @@ int run_linear(const uint16_t* x, const uint16_t* W, const uint16_t* bias, uint1
     WsGemmArgs a{};
     a.A = x; a.B = W; a.bias = bias; a.fixed_rows = T; a.max_rows = T; a.G = 1; a.K = K; a.N = N; a.out = out;
     a.o_group_stride = T; a.a_group_stride = T; a.ksplit = 1;
+    if (T <= 32) return launch_rows(a, nullptr, EPI_STORE, 2, st);   // 64 rows: two launches 151 us, one 158 (d = 1024)
     int MT, NW;
     wsgemm_pick_tile(T, 1, N, &MT, &NW);
     const long long waves = (long long)((N + 127) / 128) * ((T + MT - 1) / MT);

@@ -141,20 +141,43 @@ __device__ __forceinline__ void load_bias8(const WsGemmArgs& a, int g, int n_lan
     unpack_bias8(load_bias_raw(a, g, n_lane), bias);
 }
 
+// NC (8, 4, 2 or 1) consecutive 16-bit values as one access
+template <int NC> struct Bf16Vec;
+template <> struct Bf16Vec<8> { typedef uint4 type; };
+template <> struct Bf16Vec<4> { typedef uint2 type; };
+template <> struct Bf16Vec<2> { typedef uint32_t type; };
+template <> struct Bf16Vec<1> { typedef uint16_t type; };
+__device__ __forceinline__ uint32_t raw_dword(const uint4& v, int q) { return dw(v, q); }
+__device__ __forceinline__ uint32_t raw_dword(const uint2& v, int q) { return q == 0 ? v.x : v.y; }
+__device__ __forceinline__ uint32_t raw_dword(const uint32_t& v, int) { return v; }
+__device__ __forceinline__ uint32_t raw_dword(const uint16_t& v, int) { return v; }
+// fp32 value i of NC loaded bf16 values
+template <typename V> __device__ __forceinline__ float bf16_of(const V& v, int i) {
+    const uint32_t d = raw_dword(v, i / 2);
+    return __uint_as_float(i & 1 ? d & 0xffff0000u : d << 16);
+}
+template <int NC> __device__ __forceinline__ void load_bias(const WsGemmArgs& a, int g, int n, float (&bias)[NC]) {
+    typename Bf16Vec<NC>::type v{};
+    if (a.bias) v = *reinterpret_cast<const typename Bf16Vec<NC>::type*>(a.bias + (size_t)g * a.N + n);
+#pragma unroll
+    for (int i = 0; i < NC; ++i) bias[i] = bf16_of(v, i);
+}
+
 // Token and gate probability of expert row `row` of group g (top-1 combine fused into GEMM-2)
 __device__ __forceinline__ void scatter_lookup(const WsGemmArgs& a, int g, int row, int& t, float& gw) {
     t = a.scatter_map[(size_t)g * a.scatter_stride + row];
     gw = a.gate_w[(size_t)t * a.top_k];
 }
 
-// Finishes NC (8 or 4) consecutive columns n_lane.. of row `row` (index inside group g): v = acc + bias on entry.
+// Finishes NC (8, 4, 2 or 1) consecutive columns n_lane.. of row `row` (index inside group g): v = acc + bias on entry.
 // EPI_SCATTER: (t, gw) = scatter_lookup of the row, fetched by the caller.
 template <int EPI, int NC = 8>
 __device__ __forceinline__ void finish_row(const WsGemmArgs& a, int g, int row, int ks, int n_lane, float (&v)[NC],
                                            int t = 0, float gw = 1.f) {
-    static_assert(NC == 8 || NC == 4, "columns per lane");
+    typedef typename Bf16Vec<NC>::type Vec;
     const long long grow = (long long)g * a.o_group_stride + row;   // row in [G, o_group_stride]
-    if (EPI == EPI_PARTIAL) {
+    if constexpr (EPI == EPI_PARTIAL) {
+        static_assert(NC >= 4, "16-byte stores");
         float* o = a.partial + ((size_t)ks * a.partial_rows + grow) * a.N + n_lane;
 #pragma unroll
         for (int q = 0; q < NC / 4; ++q)
@@ -177,35 +200,27 @@ __device__ __forceinline__ void finish_row(const WsGemmArgs& a, int g, int row, 
             const int e = a.expert_idx[grow * a.top_k + j];
             const float gw = a.gate_w[grow * a.top_k + j];
             const uint16_t* yp = a.ye + ((size_t)e * a.C + s) * a.N + n_lane;
-            uint32_t y[NC / 2];
-            if (NC == 8) {
-                const uint4 yv = *reinterpret_cast<const uint4*>(yp);
-                y[0] = yv.x; y[1] = yv.y; y[NC / 2 - 2] = yv.z; y[NC / 2 - 1] = yv.w;
-            } else {
-                const uint2 yv = *reinterpret_cast<const uint2*>(yp);
-                y[0] = yv.x; y[1] = yv.y;
-            }
+            const Vec y = *reinterpret_cast<const Vec*>(yp);
 #pragma unroll
-            for (int q = 0; q < NC / 2; ++q) {
-                v[2 * q] = fmaf(gw, __uint_as_float(y[q] << 16), v[2 * q]);
-                v[2 * q + 1] = fmaf(gw, __uint_as_float(y[q] & 0xffff0000u), v[2 * q + 1]);
-            }
+            for (int i = 0; i < NC; ++i) v[i] = fmaf(gw, bf16_of(y, i), v[i]);
         }
     }
-    uint32_t o[NC / 2];
+    uint32_t o[(NC + 1) / 2];
 #pragma unroll
-    for (int q = 0; q < NC / 2; ++q) o[q] = pack_bf16x2(v[2 * q], v[2 * q + 1]);
+    for (int q = 0; q < (NC + 1) / 2; ++q) o[q] = pack_bf16x2(v[2 * q], NC > 1 ? v[(2 * q + 1) % NC] : 0.f);
     // h and the layer output are written once and read much later or never: streaming stores keep them
     // from displacing the activation rows in L2.  Expert outputs and split-K partials are read back at once.
     uint16_t* dst = a.out + orow * a.N + n_lane;
-    if (NC == 8) {
-        const uint4 ov = make_uint4(o[0], o[1], o[NC / 2 - 2], o[NC / 2 - 1]);
+    if constexpr (NC == 8) {
+        const uint4 ov = make_uint4(o[0], o[1], o[2], o[3]);
         if (EPI == EPI_STORE) *reinterpret_cast<uint4*>(dst) = ov;
         else store_stream16(dst, ov);
-    } else {
+    } else if constexpr (NC == 4) {
         const uint2 ov = make_uint2(o[0], o[1]);
         if (EPI == EPI_STORE) *reinterpret_cast<uint2*>(dst) = ov;
         else __builtin_nontemporal_store(__builtin_bit_cast(unsigned long long, ov), reinterpret_cast<unsigned long long*>(dst));
+    } else {                                                        // a piece of a line that other work-groups complete
+        *reinterpret_cast<Vec*>(dst) = static_cast<Vec>(o[0]);
     }
 }
 

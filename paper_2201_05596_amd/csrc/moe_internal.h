@@ -160,6 +160,7 @@ struct WsGemmArgs {
     const int32_t* row_map;    // [G, map_stride]: A-row of (g, r), or nullptr -> g*a_group_stride + r
     int32_t fixed_rows, max_rows, map_stride;
     int32_t G, K, N;
+    int32_t slots;             // entries of `order` that may have rows (the others certainly have none); 0: all
     long long a_group_stride;
     uint16_t* out;             // leading dimension N
     long long o_group_stride;
@@ -184,6 +185,14 @@ bool wsgemm_supported(int K, int N);
 void wsgemm_pick_tile(int max_rows, int G, int N, int* MT, int* NW);
 int launch_wsgemm(const WsGemmArgs& a, int epi, int MT, int NW, int NBUF, hipStream_t s);
 int wsgemm_chunk_k(int MT);
+
+// Products that read few weights (ffn_rows.hip): 16 NF columns per work-group, K split over its waves; ksplit must be 1.
+// b: a second product of the same K, N and packing in the same launch (not with EPI_SCATTER), or nullptr.
+int launch_rows(const WsGemmArgs& a, const WsGemmArgs* b, int epi, int NF, hipStream_t s);
+// NF for a product, or 0 where another kernel does better.  touched: experts that can have rows; kept: rows of all of them
+int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed);
+int rows_pick_gemm2(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves);
+int rows_pick_dense(int T, int N, bool packed);
 
 // Tiled variant for groups with many rows (ffn_tile.hip); same arguments, ksplit must be 1.
 int launch_tgemm(const WsGemmArgs& a, int epi, hipStream_t s);
