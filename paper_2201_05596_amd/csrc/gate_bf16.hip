@@ -279,7 +279,7 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
 #pragma unroll
             for (int j = 0; j < KK; ++j) {
                 const int e = lane < TM ? e_sh[j * TM + lane] : -1;
-                const int rank = wave_rank_by_expert(e, lane, h_sh + j * TN);
+                const int rank = wave_rank_by_expert(e, lane, E, h_sh + j * TN);
                 if (e >= 0) slot_idx[(size_t)(t0 + lane) * KK + j] = rank;
             }
         }
@@ -302,47 +302,94 @@ __global__ __launch_bounds__(256) void gate_bf16_kernel(const uint16_t* __restri
     gate_bf16_body<MA, NE, K>(lds, x, frags, bg, logits, T, d, E, ET, expert_idx, slot_idx, gate_w, hist);
 }
 
-// The whole gate of a decode step (at most 256 tokens) in ONE launch: the work-groups compute the logits tile by tile
-// (experts split over work-groups, so that many CUs share the read of the gate weights); every work-group then
-// publishes a flag, and the one with the highest index waits for all flags and runs the whole routing on the finished
-// logits.  The flags hold the call's epoch (never 0, and not repeated by the host from one call to the next), so they
-// need no clearing beforehand: what nobody or an earlier call left there is not this call's epoch, and the waiting
-// work-group puts every flag it has seen back to 0, which also makes a replayed graph launch (same epoch) safe.  Hand-over across the XCDs'
-// separate L2s: the writers release at device scope after their stores (write-back of the L2), the reader acquires at
-// device scope before its loads (invalidate).  The wait cannot hang: work-groups are started in index order, so all
-// others are running or done when the last one starts (and the whole grid, at most 64 work-groups, fits on the chip
-// at once); it is bounded all the same, and gives up (leaving wrong tables, never a hung GPU) after about 10^6 polls.
-template <int MA, int NE, int RK, int NV>
-__global__ __launch_bounds__(256) void gate_decode_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags,
-                                                          const float* __restrict__ bg, float* __restrict__ logits, int T,
-                                                          int d, int E, int ET, int C, int32_t* __restrict__ expert_idx,
-                                                          int32_t* __restrict__ slot_idx, float* __restrict__ gate_w,
-                                                          int32_t* __restrict__ expert_rows, int32_t* __restrict__ slot_token,
-                                                          int32_t* __restrict__ expert_order, uint32_t* __restrict__ flags,
-                                                          uint32_t epoch) {
+// The whole gate of a decode step (at most 256 tokens) in ONE launch.  Bound by latencies: the gate weights' round trip,
+// the hand-over, the chain of the routing.  A work-group of 16 waves computes the logits of 16 MA tokens for one tile of
+// 16 experts, the waves sharing K between them, so that up to d = 2048 all operands are fetched in one round trip (four
+// waves needed three); experts and tokens are split over work-groups so that many CUs share the read of the gate weights.
+// Every work-group then publishes a flag, and the one with the highest index waits for all flags and runs the whole routing
+// on the finished logits.  The flags hold the call's epoch (never 0, and not repeated by the host from one call to the
+// next), so they need no clearing beforehand: what nobody or an earlier call left there is not this call's epoch, and the
+// waiting work-group puts every flag it has seen back to 0, which also makes a replayed graph launch (same epoch) safe.
+// Hand-over across the XCDs' separate L2s: logits and flags are written with device-scope stores (through the L2), a
+// work-group waits for its logits stores to complete before it writes its flag, and the reader acquires at device scope
+// (invalidate) before its loads.  The wait cannot hang: work-groups are started in index order, so all others are running or
+// done when the last one starts (and the whole grid, at most 64 work-groups, fits on the chip at once); it is bounded all
+// the same, and gives up (leaving wrong tables, never a hung GPU) after about 10^6 polls.
+// One token, d = 1024, 128 experts: 12.4 us with four waves and a routing by 256 threads; 64 tokens, d = 2048: 23.2.
+constexpr int kDecodeWaves = 16, kDecodeBlocks = 4;      // waves; k-blocks in flight per wave
+template <int MA, int RK, int NV>
+__global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ bg, float* __restrict__ logits,
+    int T, int d, int E, int ET, int C, int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
+    float* __restrict__ gate_w, int32_t* __restrict__ expert_rows, int32_t* __restrict__ slot_token,
+    int32_t* __restrict__ expert_order, uint32_t* __restrict__ flags, uint32_t epoch) {
+    static_assert(kDecodeWaves * 64 == kSingleThreads, "the routing uses the same work-group");
+    constexpr int TM = 16 * MA;
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    gate_bf16_body<MA, NE, 0>(lds, x, frags, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr);
-    const int nblocks = gridDim.x * gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
-    __syncthreads();                                   // every thread's logits stores are issued
-    if (threadIdx.x == 0) {
-        __atomic_thread_fence(__ATOMIC_RELEASE);       // device scope: this work-group's stores become visible ...
-        __hip_atomic_store(flags + bid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ... before its flag
+    float* part = reinterpret_cast<float*>(lds);                 // [kDecodeWaves][TM][16]
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, kg = lane >> 4, et = blockIdx.y, t0 = blockIdx.x * TM;
+    const int KB = d / kKB, nkb = KB > w ? (KB - w + kDecodeWaves - 1) / kDecodeWaves : 0;   // k-blocks w, w + 16, ...
+    const int o_row = tid >> 4, o_col = et * 16 + (tid & 15);    // the logit that this thread finishes
+    const float bias = bg && o_col < E ? bg[o_col] : 0.f;
+    f32x4_t acc[MA];
+#pragma unroll
+    for (int m = 0; m < MA; ++m) acc[m] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    const uint16_t* a_src[MA];                                   // token rows, clamped: results past T are never stored
+#pragma unroll
+    for (int m = 0; m < MA; ++m) a_src[m] = x + (size_t)min(t0 + 16 * m + c, T - 1) * d + kg * 8;
+    const uint16_t* b_src = frags + (size_t)et * 3 * kFragElems + lane * 8;
+    for (int i0 = 0; i0 < nkb; i0 += kDecodeBlocks) {
+        bf16x8_t a[kDecodeBlocks][MA], b[kDecodeBlocks][3];
+#pragma unroll
+        for (int i = 0; i < kDecodeBlocks; ++i) {
+            const int kb = w + min(i0 + i, nkb - 1) * kDecodeWaves;          // past the end: in bounds, not multiplied
+#pragma unroll
+            for (int m = 0; m < MA; ++m) a[i][m] = *reinterpret_cast<const bf16x8_t*>(a_src[m] + kb * kKB);
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                b[i][q] = *reinterpret_cast<const bf16x8_t*>(b_src + ((size_t)kb * ET * 3 + q) * kFragElems);
+        }
+        __builtin_amdgcn_sched_barrier(0);                       // all loads go out before the first use
+#pragma unroll
+        for (int i = 0; i < kDecodeBlocks; ++i) {
+            if (i0 + i >= nkb) break;
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+#pragma unroll
+                for (int m = 0; m < MA; ++m) acc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i][m], b[i][q], acc[m], 0, 0, 0);
+        }
     }
+#pragma unroll
+    for (int m = 0; m < MA; ++m)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[(w * TM + 16 * m + 4 * kg + r) * 16 + c] = acc[m][r];   // D: column lane % 16, rows 4 kg + r
+    __syncthreads();
+    if (o_row < TM && t0 + o_row < T && o_col < E) {
+        float v = bias;
+#pragma unroll
+        for (int s = 0; s < kDecodeWaves; ++s) v += part[s * TM * 16 + tid];
+        __hip_atomic_store(logits + (size_t)(t0 + o_row) * E + o_col, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    const int nblocks = gridDim.x * gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's logits have left the L2 ...
+    __syncthreads();                                   // ... and every thread's of the work-group ...
+    if (tid == 0) __hip_atomic_store(flags + bid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ... before its flag
     if (bid != nblocks - 1) return;
-    if ((int)threadIdx.x < nblocks) {
+    if (tid < nblocks) {
         int polls = 0;
-        while (__hip_atomic_load(flags + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch && polls < (1 << 20)) {
-            __builtin_amdgcn_s_sleep(2);
+        while (__hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch && polls < (1 << 20)) {
+            __builtin_amdgcn_s_sleep(1);
             ++polls;
         }
     }
-    __atomic_thread_fence(__ATOMIC_ACQUIRE);           // device scope: nothing read below comes from a stale cache line
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); // nothing read below comes from a stale cache line
     // Each flag goes back to 0 (never an epoch) once it has been seen: a captured launch that is replayed carries the
     // same epoch every time and must not find it in the flags of its own previous run.
-    if ((int)threadIdx.x < nblocks) __hip_atomic_store(flags + threadIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < nblocks) __hip_atomic_store(flags + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     route_single_body<RK, NV>(reinterpret_cast<int32_t*>(lds), logits, T, E, C, expert_idx, slot_idx, gate_w, expert_rows,
-                              slot_token, expert_order, nullptr);
+                              slot_token, expert_order);
 }
 
 template <int MA, int NE, int K>
@@ -420,24 +467,15 @@ int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packe
 // differs from what any earlier call left in `flags`.
 bool gate_decode_supported(int T, int d, int E) { return gate_bf16_supported(d, E) && T <= kRouteTokens; }
 
-template <int RK, int NV>
+template <int MA, int RK, int NV>
 static int launch_decode_cfg(const uint16_t* x, const uint16_t* frags, const float* bg, float* logits, int T, int d, int E,
                              int ET, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
                              int32_t* slot_token, int32_t* expert_order, uint32_t* flags, uint32_t epoch, hipStream_t s) {
-    constexpr int MA = 2, NE = 1;                       // smallest tile: most work-groups (at most 8 x 8)
-    const size_t route = route_single_lds_ints(E, RK) * sizeof(int32_t);
-    const size_t smem = route > (size_t)GateLds<MA, NE, 0>::BYTES ? route : (size_t)GateLds<MA, NE, 0>::BYTES;
-    const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET / NE);
-    if (grid.x * grid.y > 64) return MOE_ERR_INVALID_ARG;
-    static size_t attr_bytes = 0;                       // one per instantiation
-    if (smem > attr_bytes) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_decode_kernel<MA, NE, RK, NV>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_bytes = smem;
-    }
-    hipLaunchKernelGGL((gate_decode_kernel<MA, NE, RK, NV>), grid, dim3(256), smem, s, x, frags, bg, logits, T, d, E, ET, C,
-                       expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order, flags, epoch);
+    const size_t route = route_single_lds_ints(E, RK) * sizeof(int32_t), sums = (size_t)kDecodeWaves * 16 * MA * 16 * 4;
+    const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET);              // smallest tiles: most work-groups (at most 8 x 8)
+    if (grid.x * grid.y > kGateFlagInts) return MOE_ERR_INVALID_ARG;
+    hipLaunchKernelGGL((gate_decode_kernel<MA, RK, NV>), grid, dim3(kDecodeWaves * 64), route > sums ? route : sums, s, x, frags,
+                       bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order, flags, epoch);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -455,8 +493,10 @@ int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, co
     }
     const uint16_t* xb = static_cast<const uint16_t*>(x);
 #define MOE_DECODE_CASE(kk, nv) \
-    return launch_decode_cfg<kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows, \
-                                     slot_token, expert_order, flags, epoch, s)
+    return T <= 128 ? launch_decode_cfg<1, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
+                                                   expert_rows, slot_token, expert_order, flags, epoch, s)              \
+                    : launch_decode_cfg<2, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
+                                                   expert_rows, slot_token, expert_order, flags, epoch, s)
     if (k == 1) {
         if (E <= 16) MOE_DECODE_CASE(1, 1);
         if (E <= 32) MOE_DECODE_CASE(1, 2);

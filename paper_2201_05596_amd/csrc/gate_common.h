@@ -109,21 +109,22 @@ __device__ __forceinline__ void token_gate_mem(const float* __restrict__ row, in
     gate_weights<K>(group_sum(s), g1, g2, w1, w2);
 }
 
-// Rank of each lane's token among the wave's tokens that chose the same expert (e < 0: no token), by
-// ballots: returns the number of lower lanes with the same e; the lowest lane of every group of equal e
-// adds the group's size to count[e] (LDS or global, one writer per expert and wave).
-__device__ __forceinline__ int wave_rank_by_expert(int e, int lane, int32_t* count) {
+// Rank of each lane's token among the wave's tokens that chose the same expert (e < 0: no token): the lanes with the
+// same e are found bit by bit with ballots, whatever e is (E <= 2^bits); returns the number of lower ones; the lowest lane
+// of every group of equal e writes the group's size to count[e] (LDS or global, one writer per expert and wave).
+// One pass of `bits` ballots instead of one ballot and one lane exchange per distinct expert: 28 of those among 32 tokens
+// of 128 experts.
+__device__ __forceinline__ int wave_rank_by_expert(int e, int lane, int E, int32_t* count) {
     const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
-    int rank = 0;
-    unsigned long long todo = __ballot(e >= 0);
-    while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const int le = __shfl(e, leader, kWave);
-        const unsigned long long m = __ballot(e == le);
-        if (e == le) rank = __popcll(m & lt_mask);
-        if (lane == leader) count[le] = __popcll(m);
-        todo &= ~m;
+    const int bits = 32 - __clz(E);                       // E >= 1; covers 0 .. E - 1
+    unsigned long long same = __ballot(e >= 0);
+    for (int i = 0; i < bits; ++i) {
+        const bool one = e >> i & 1;
+        const unsigned long long ones = __ballot(one);
+        same &= one ? ones : ~ones;
     }
+    const int rank = __popcll(same & lt_mask);
+    if (e >= 0 && rank == 0) count[e] = __popcll(same);
     return rank;
 }
 

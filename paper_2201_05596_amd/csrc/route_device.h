@@ -8,125 +8,60 @@
 namespace moe {
 
 // ------------------------------------------------------------------------------------------
-// Routing, kernel 1 of 2: per block of 256 tokens
-//   phase A  16 lanes per token: top-k by logit (lowest index on ties), softmax weight(s)
-//   phase B  one lane per token: rank of the token among the wave's tokens that chose the same
-//            expert, by ballot; per-wave histogram
-//   phase C  prefix over the block's waves; block histogram to global scratch; the rank inside
-//            the block is parked in slot_idx until kernel 2 adds the block's base.
-// scratch layout: hist[block][choice][E]
+// Top-k and gate weights of the tokens t0 .. t0 + n - 1 (n <= TB) by a block of NT threads, 16 lanes per token, and the
+// chosen experts in e_sh [K][TB] (-1: no token).  NV > 0: rows of at most 16 NV logits, fetched for all rounds at once.
 // ------------------------------------------------------------------------------------------
-// SINGLE (at most 256 tokens, one block): the block's totals stay in LDS (tot_sh [K][E]) and the ranks in registers
-// (my_e, my_slot: expert and rank within the expert's choice-j tokens of this thread's token), nothing is parked
-// in global memory.
-template <int K, int NV, bool SINGLE = false>
-__device__ __forceinline__ void route_local_body(int32_t* smem, const float* __restrict__ logits, int T, int E,
-                                                 int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
-                                                 float* __restrict__ gate_w, int32_t* __restrict__ hist,
-                                                 int32_t* tot_sh = nullptr, int* my_e_out = nullptr,
-                                                 int* my_slot_out = nullptr) {
-    constexpr int NW = kRouteTokens / kWave;
-    int32_t* e_sh = smem;                          // [K][256] chosen expert per token of the block
-    int32_t* whist = smem + K * kRouteTokens;      // [NW][K][E]
-
-    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
-    const int tb = SINGLE ? 0 : blockIdx.x * kRouteTokens;     // SINGLE: whichever block runs it, the tokens are 0..T-1
-
-    for (int i = tid; i < NW * K * E; i += kRouteTokens) whist[i] = 0;
-
-    // phase A: 16 lanes per token, 16 tokens of the block at a time.  When the row fits in registers
-    // (E <= 128) the logits of all 16 rounds are fetched first, in one memory round trip.
-    {
-        const int grp = tid >> 4, sub = tid & 15;
-        constexpr int ROUNDS = kRouteTokens / 16;
-        auto publish = [&](int tl, Best g1, Best g2, float w1, float w2) {
-            const int t = tb + tl;
-            if (sub == 0) {
-                const bool ok = t < T;
-                e_sh[tl] = ok ? g1.i : -1;
-                if (K == 2) e_sh[kRouteTokens + tl] = ok ? g2.i : -1;
-                if (ok) {
-                    expert_idx[(size_t)t * K] = g1.i;
-                    gate_w[(size_t)t * K] = w1;
-                    if (K == 2) {
-                        expert_idx[(size_t)t * K + 1] = g2.i;
-                        gate_w[(size_t)t * K + 1] = w2;
-                    }
-                }
-            }
-        };
-        if (NV > 0) {
-            constexpr int NVV = NV > 0 ? NV : 1;
-            float v[ROUNDS][NVV];
-            const int live_rounds = min(ROUNDS, (T - tb + 15) / 16);      // rounds that hold a token (uniform over the block)
-#pragma unroll
-            for (int it = 0; it < ROUNDS; ++it) {
-                if (it >= live_rounds) break;
-                const float* row = logits + (size_t)min(tb + it * 16 + grp, T - 1) * E;   // clamped: lanes stay in the shuffles
-#pragma unroll
-                for (int i = 0; i < NVV; ++i) v[it][i] = row[min(sub + 16 * i, E - 1)];
-            }
-#pragma unroll
-            for (int it = 0; it < ROUNDS; ++it) {
-                if (it >= live_rounds) {                                   // no token: only the table entries
-                    if (sub == 0) {
-                        e_sh[it * 16 + grp] = -1;
-                        if (K == 2) e_sh[kRouteTokens + it * 16 + grp] = -1;
-                    }
-                    continue;
-                }
-#pragma unroll
-                for (int i = 0; i < NVV; ++i) v[it][i] = sub + 16 * i < E ? v[it][i] : -INFINITY;
-                Best g1, g2;
-                float w1, w2;
-                token_gate_regs<K, NVV>(v[it], sub, g1, g2, w1, w2);
-                publish(it * 16 + grp, g1, g2, w1, w2);
-            }
-        } else {
-#pragma unroll 4
-            for (int it = 0; it < ROUNDS; ++it) {
-                const int tl = it * 16 + grp;
-                Best g1, g2;
-                float w1, w2;
-                token_gate_mem<K>(logits + (size_t)min(tb + tl, T - 1) * E, E, sub, g1, g2, w1, w2);
-                publish(tl, g1, g2, w1, w2);
+template <int K, int NV, int NT, int TB>
+__device__ __forceinline__ void choose_experts(int32_t* e_sh, const float* __restrict__ logits, int t0, int n, int T, int E,
+                                               int32_t* __restrict__ expert_idx, float* __restrict__ gate_w) {
+    constexpr int PER = NT / 16, ROUNDS = (TB + PER - 1) / PER;
+    static_assert(TB % PER == 0 || PER > TB, "whole rounds");
+    const int tid = threadIdx.x, grp = tid >> 4, sub = tid & 15;
+    auto publish = [&](int tl, Best g1, Best g2, float w1, float w2) {
+        if (sub != 0 || tl >= TB) return;
+        const bool ok = tl < n;
+        e_sh[tl] = ok ? g1.i : -1;
+        if (K == 2) e_sh[TB + tl] = ok ? g2.i : -1;
+        if (ok) {
+            const size_t o = (size_t)(t0 + tl) * K;
+            expert_idx[o] = g1.i;
+            gate_w[o] = w1;
+            if (K == 2) {
+                expert_idx[o + 1] = g2.i;
+                gate_w[o + 1] = w2;
             }
         }
-    }
-    __syncthreads();
-
-    // phase B
-    int my_e[K], my_rank[K];
+    };
+    if (NV > 0) {
+        constexpr int NVV = NV > 0 ? NV : 1;
+        float v[ROUNDS][NVV];
+        const int live_rounds = (n + PER - 1) / PER;                 // rounds that hold a token (uniform over the block)
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        my_e[j] = e_sh[j * kRouteTokens + tid];
-        my_rank[j] = wave_rank_by_expert(my_e[j], lane, whist + (w * K + j) * E);
-    }
-    __syncthreads();
-
-    // phase C
-    for (int i = tid; i < K * E; i += kRouteTokens) {
-        const int j = i / E, e = i % E;
-        int run = 0;
+        for (int it = 0; it < ROUNDS; ++it) {
+            if (it >= live_rounds) break;
+            const float* row = logits + (size_t)min(t0 + it * PER + grp, T - 1) * E;      // clamped: lanes stay in the moves
 #pragma unroll
-        for (int ww = 0; ww < NW; ++ww) {
-            const int c = whist[(ww * K + j) * E + e];
-            whist[(ww * K + j) * E + e] = run;
-            run += c;
+            for (int i = 0; i < NVV; ++i) v[it][i] = row[min(sub + 16 * i, E - 1)];
         }
-        if (SINGLE) tot_sh[j * E + e] = run;
-        else hist[((size_t)blockIdx.x * K + j) * E + e] = run;
-    }
-    __syncthreads();
-    const int t = tb + tid;
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-        const int slot = t < T ? my_rank[j] + whist[(w * K + j) * E + my_e[j]] : 0;
-        if (SINGLE) {
-            my_e_out[j] = my_e[j];
-            my_slot_out[j] = slot;
-        } else if (t < T) {
-            slot_idx[(size_t)t * K + j] = slot;
+        for (int it = 0; it < ROUNDS; ++it) {
+            if (it >= live_rounds) {                                 // no token: only the table entries
+                publish(it * PER + grp, Best{}, Best{}, 0.f, 0.f);
+                continue;
+            }
+#pragma unroll
+            for (int i = 0; i < NVV; ++i) v[it][i] = sub + 16 * i < E ? v[it][i] : -INFINITY;
+            Best g1, g2;
+            float w1, w2;
+            token_gate_regs<K, NVV>(v[it], sub, g1, g2, w1, w2);
+            publish(it * PER + grp, g1, g2, w1, w2);
+        }
+    } else {
+        for (int it = 0; it < ROUNDS; ++it) {
+            Best g1, g2;
+            float w1, w2;
+            token_gate_mem<K>(logits + (size_t)min(t0 + it * PER + grp, T - 1) * E, E, sub, g1, g2, w1, w2);
+            publish(it * PER + grp, g1, g2, w1, w2);
         }
     }
 }
@@ -204,22 +139,51 @@ __device__ __forceinline__ void write_expert_order(const int32_t* rows /* LDS */
     }
 }
 
-// At most 256 tokens: the whole routing by one block of 256 threads, whose block-local ranks are already global ones;
-// totals and ranks stay in LDS and registers, one memory round trip (the logits).  smem: route_single_lds_ints(E, K) ints.
+// At most 256 tokens: the whole routing by one block of kSingleThreads threads, whose block-local ranks are already
+// global ones; totals and ranks stay in LDS and registers, one memory round trip (the logits).  The block is as large as
+// they come: the tokens' top-k is a chain of cross-lane moves, and four rounds of 64 tokens take a quarter of sixteen
+// rounds of 16.  smem: route_single_lds_ints(E, K) ints.
+constexpr int kSingleThreads = 1024;
 template <int K, int NV>
 __device__ __forceinline__ void route_single_body(int32_t* smem, const float* __restrict__ logits, int T, int E, int C,
                                                   int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
                                                   float* __restrict__ gate_w, int32_t* __restrict__ expert_rows,
-                                                  int32_t* __restrict__ slot_token, int32_t* __restrict__ expert_order,
-                                                  int32_t* __restrict__ hist) {
-    constexpr int NW = kRouteTokens / kWave;
-    int32_t* tot_sh = smem + K * kRouteTokens + NW * K * E;     // [K][E] tokens per (choice, expert)
+                                                  int32_t* __restrict__ slot_token, int32_t* __restrict__ expert_order) {
+    constexpr int NW = kRouteTokens / kWave, NT = kSingleThreads;
+    int32_t* e_sh = smem;                                       // [K][256] chosen expert per token
+    int32_t* whist = smem + K * kRouteTokens;                   // [NW][K][E] tokens per (wave of tokens, choice, expert)
+    int32_t* tot_sh = whist + NW * K * E;                       // [K][E] tokens per (choice, expert)
     int32_t* rows_sh = tot_sh + K * E;                          // [E]
     int32_t* sorted = rows_sh + E;                              // [E + 2]
-    const int tid = threadIdx.x;
-    int my_e[K], my_slot[K];
-    route_local_body<K, NV, true>(smem, logits, T, E, expert_idx, slot_idx, gate_w, hist, tot_sh, my_e, my_slot);
-    for (int e = tid; e < E; e += kRouteTokens) {
+    const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
+    for (int i = tid; i < NW * K * E; i += NT) whist[i] = 0;
+    choose_experts<K, NV, NT, kRouteTokens>(e_sh, logits, 0, T, T, E, expert_idx, gate_w);
+    __syncthreads();
+
+    int my_e[K], my_rank[K];
+    if (tid < kRouteTokens) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            my_e[j] = e_sh[j * kRouteTokens + tid];
+            my_rank[j] = wave_rank_by_expert(my_e[j], lane, E, whist + (w * K + j) * E);
+        }
+    }
+    __syncthreads();
+
+    // prefix over the waves of tokens
+    for (int i = tid; i < K * E; i += NT) {
+        const int j = i / E, e = i % E;
+        int run = 0;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) {
+            const int c = whist[(ww * K + j) * E + e];
+            whist[(ww * K + j) * E + e] = run;
+            run += c;
+        }
+        tot_sh[i] = run;
+    }
+    __syncthreads();
+    for (int e = tid; e < E; e += NT) {
         const int rows = min(tot_sh[e] + (K == 2 ? tot_sh[E + e] : 0), C);
         rows_sh[e] = rows;
         expert_rows[e] = rows;
@@ -228,15 +192,15 @@ __device__ __forceinline__ void route_single_body(int32_t* smem, const float* __
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int e = my_e[j];
-            const int loc = my_slot[j] + (j == 1 ? tot_sh[e] : 0);   // second choices rank behind all first ones
+            const int loc = my_rank[j] + whist[(w * K + j) * E + e] + (j == 1 ? tot_sh[e] : 0);   // second choices behind all first ones
             if (loc < C) slot_token[(size_t)e * C + loc] = tid;
             slot_idx[(size_t)tid * K + j] = loc < C ? loc : -1;
         }
     }
     __syncthreads();
-    for (long long i = tid; i < (long long)E * C; i += kRouteTokens)
-        if ((int)(i % C) >= rows_sh[i / C]) slot_token[i] = -1;
-    if (expert_order) write_expert_order(rows_sh, E, expert_order, sorted, tid, kRouteTokens);
+    for (uint32_t i = tid; i < (uint32_t)E * C; i += NT)        // E * C < 2^31
+        if ((int)(i % (uint32_t)C) >= rows_sh[i / (uint32_t)C]) slot_token[i] = -1;
+    if (expert_order) write_expert_order(rows_sh, E, expert_order, sorted, tid, NT);
 }
 // LDS ints of route_single_body: chosen experts, per-wave histograms, totals, rows, order scratch
 __host__ __device__ inline size_t route_single_lds_ints(int E, int k) {
