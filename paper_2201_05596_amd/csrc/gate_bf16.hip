@@ -257,7 +257,7 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
             for (int i = 0; i < NE; ++i) v[i] = sub + 16 * i < E ? tile[tl * STRIDE + sub + 16 * i] : -INFINITY;
             Best g1, g2;
             float w1, w2;
-            token_gate_regs<KK, NE>(v, sub, g1, g2, w1, w2);
+            token_gate_regs<KK, NE>(v, E, sub, g1, g2, w1, w2);
             if (sub == 0) {
                 const int t = t0 + tl;
                 const bool ok = t < T;

@@ -14,6 +14,9 @@ struct Best {
 __device__ __forceinline__ Best better(Best a, Best b) {
     return (b.v > a.v || (b.v == a.v && b.i < a.i)) ? b : a;
 }
+constexpr int kNoExpert = 0x7fffffff;
+// later of a lane's experts against its best so far; a masked expert (-inf) is still one, so it beats none at all
+__device__ __forceinline__ bool beats(float v, const Best& b) { return v > b.v || (v == b.v && b.i == kNoExpert); }
 // All-reduce inside aligned groups of 16 lanes (one DPP "row") with data-parallel-primitive moves:
 // swap inside pairs, swap pairs inside quads, mirror the two quads of each half row, mirror the two
 // half rows.  After step i every aligned group of 2^i lanes holds one common value, which is what
@@ -69,18 +72,19 @@ __device__ __forceinline__ void gate_weights(float s, Best g1, Best g2, float& w
 }
 
 // Top-K experts and gate weights of one token, computed by a group of 16 lanes; lane `sub` looks
-// at experts sub, sub+16, ...  Every lane of the group returns the same result.
+// at experts sub, sub+16, ...  Every lane of the group returns the same result, experts below E whatever the logits are (NaN
+// is no choice: a token with nothing else gets expert E - 1).
 // Register version: the lane's NV logits are already loaded (padding = -inf).
 template <int K, int NV>
-__device__ __forceinline__ void token_gate_regs(const float (&v)[NV], int sub, Best& g1, Best& g2, float& w1,
+__device__ __forceinline__ void token_gate_regs(const float (&v)[NV], int E, int sub, Best& g1, Best& g2, float& w1,
                                                 float& w2) {
-    const Best none{-INFINITY, 0x7fffffff};
+    const Best none{-INFINITY, kNoExpert};
     Best b1 = none, b2 = none;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int e = sub + 16 * i;
-        if (v[i] > b1.v) { b2 = b1; b1.v = v[i]; b1.i = e; }
-        else if (v[i] > b2.v) { b2.v = v[i]; b2.i = e; }
+        if (beats(v[i], b1)) { b2 = b1; b1.v = v[i]; b1.i = e; }
+        else if (beats(v[i], b2)) { b2.v = v[i]; b2.i = e; }
     }
     g1 = group_best(b1);
     g2 = none;
@@ -89,17 +93,19 @@ __device__ __forceinline__ void token_gate_regs(const float (&v)[NV], int sub, B
 #pragma unroll
     for (int i = 0; i < NV; ++i) s += fast_exp(v[i] - g1.v);       // exp(-inf) = 0 for the padding
     gate_weights<K>(group_sum(s), g1, g2, w1, w2);
+    g1.i = min(g1.i, E - 1);
+    g2.i = min(g2.i, E - 1);
 }
 // Any E: two passes over the row in memory.
 template <int K>
 __device__ __forceinline__ void token_gate_mem(const float* __restrict__ row, int E, int sub, Best& g1, Best& g2,
                                                float& w1, float& w2) {
-    const Best none{-INFINITY, 0x7fffffff};
+    const Best none{-INFINITY, kNoExpert};
     Best b1 = none, b2 = none;
     for (int e = sub; e < E; e += 16) {
         const float v = row[e];
-        if (v > b1.v) { b2 = b1; b1.v = v; b1.i = e; }
-        else if (v > b2.v) { b2.v = v; b2.i = e; }
+        if (beats(v, b1)) { b2 = b1; b1.v = v; b1.i = e; }
+        else if (beats(v, b2)) { b2.v = v; b2.i = e; }
     }
     g1 = group_best(b1);
     g2 = none;
@@ -107,6 +113,8 @@ __device__ __forceinline__ void token_gate_mem(const float* __restrict__ row, in
     float s = 0.f;
     for (int e = sub; e < E; e += 16) s += fast_exp(row[e] - g1.v);
     gate_weights<K>(group_sum(s), g1, g2, w1, w2);
+    g1.i = min(g1.i, E - 1);
+    g2.i = min(g2.i, E - 1);
 }
 
 // Rank of each lane's token among the wave's tokens that chose the same expert (e < 0: no token): the lanes with the

@@ -53,7 +53,7 @@ __device__ __forceinline__ void choose_experts(int32_t* e_sh, const float* __res
             for (int i = 0; i < NVV; ++i) v[it][i] = sub + 16 * i < E ? v[it][i] : -INFINITY;
             Best g1, g2;
             float w1, w2;
-            token_gate_regs<K, NVV>(v[it], sub, g1, g2, w1, w2);
+            token_gate_regs<K, NVV>(v[it], E, sub, g1, g2, w1, w2);
             publish(it * PER + grp, g1, g2, w1, w2);
         }
     } else {
