@@ -38,8 +38,8 @@ __device__ __forceinline__ int a_swizzle(int row) { return (0x78 >> (((row >> 2)
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
-// NWM waves along the rows x 2 along the columns; each owns WM rows x WN columns (WN = 128, or 64 for products
-// with so few columns that 256-column tiles would leave CUs without work)
+// NWM waves along the rows x 2 along the columns; each owns WM rows x WN columns (WN = 128, or 64 where 256-column
+// tiles would leave CUs without work)
 template <int WM, int NWM, int NS_, int WN> struct TileCfg {
     static constexpr int NWAVES = NWM * 2;
     static constexpr int BM = NWM * WM;
@@ -382,54 +382,75 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false>(a, b, s);
 }
 
-// Tile shapes.  256 x 256 (4 x 2 waves of 64 x 128: the accumulators take 128 registers, which the compiler updates
-// in place; 128 rows per wave fill the file and cost copies) wherever that gives every CU a tile.  Products with few
-// columns (N = d_model in GEMM-2) get 256 x 128 tiles of 4 x 2 waves of 64 x 64 instead: as many tiles, but eight waves
-// per CU rather than the four of a 128 x 256 tile, which is what hides the LDS and barrier latencies.  Groups of at
-// most 128 rows: 128 x 256 tiles; for short K as 2 x 2 waves of 64 x 128, 3 stages, two work-groups per CU; for long K
-// (few, long tiles: one per CU) as 4 x 2 waves of 32 x 128 with 6 stages of 24 KB -- eight waves hide the latencies
-// better than four there (c3b GEMM-2: 113 against 116 us), for short K the two work-groups do (121 against 127 us).
-enum TileShape { TILE_128x256, TILE_256x256, TILE_256x128 };
-static TileShape pick_tile(int max_rows, int G, int N) {
-    if (max_rows <= 128) return TILE_128x256;
-    const long long row_tiles = (long long)G * ((max_rows + 255) / 256);
-    if (row_tiles * ((N + 255) / 256) >= 256) return TILE_256x256;
-    if (row_tiles * ((N + 127) / 128) >= 256) return TILE_256x128;
-    return TILE_128x256;
+// Tile shapes, for one product or for two in one launch (same K, N and packing: all tiles are counted together):
+//   256 x 256   4 x 2 waves of 64 x 128 (the accumulators take 128 registers, which the compiler updates in place; 128
+//               rows per wave fill the file and cost copies), one work-group per CU: least traffic per flop
+//   128 x 256   4 x 2 waves of 32 x 128, 5 or 6 stages, one work-group per CU
+//   128 x 256   2 x 2 waves of 64 x 128, 3 stages, two work-groups per CU: one's epilogue and barriers under the other's
+//               matrix work, which short K needs (TILE_128x256_PAIRED)
+//   128 x 128   4 x 2 waves of 32 x 64, 6 stages, one work-group per CU: most work-groups
+// Few tiles leave CUs idle, small tiles cost more per flop, so the time of a launch is the number of rounds times a
+// tile's time.  Relative tile times, from products that ran one round of each on one machine (16 experts x 2 x 128 rows x
+// 8192 x 2048: 256 x 256 on 128 CUs 351 us for the layer, 128 x 256 on 256 CUs 298, 128 x 128 in two rounds 350;
+// the same with 1024 columns: 156 / 126 / 112): 0.77 : 0.56 : 0.42; a 256-row tile with at most 128 rows counts 0.6; two
+// paired tiles on a CU 0.84 (32 steps of K: 43 us against 39.5).  A partial last round costs half a round more on average.
+// Against the largest tile that gives every CU one: 1500 tokens, 16 experts, 1024 / 4096 122 -> 101 us, 2048 / 8192
+// 270 -> 226; 3000 tokens, 32 experts 166 -> 142; paired with 1500 rows of a dense branch 140 -> 117; 4000 tokens, top-1
+// of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 427 through the first product.
+enum TileShape { TILE_256x256, TILE_128x256, TILE_128x256_PAIRED, TILE_128x128 };
+struct TileCount {
+    double tiles256 = 0, tiles128 = 0, tiles128x128 = 0;     // tiles of each shape
+    int max_rows = 0, min_rows = 1 << 30;
+    void add(const WsGemmArgs& a) {
+        const double n256 = (a.N + 255) / 256, n128 = (a.N + 127) / 128, rows128 = (a.max_rows + 127) / 128;
+        const int last = a.max_rows % 256;
+        tiles256 += a.G * n256 * (a.max_rows / 256 + (last == 0 ? 0 : last <= 128 ? 0.6 : 1));
+        tiles128 += a.G * n256 * rows128;
+        tiles128x128 += a.G * n128 * rows128;
+        if (a.max_rows > max_rows) max_rows = a.max_rows;
+        if (a.max_rows < min_rows) min_rows = a.max_rows;
+    }
+};
+static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
+    TileCount c;
+    c.add(a);
+    if (b) c.add(*b);
+    auto rounds = [](double tiles) { return tiles <= 256 ? 1 : tiles / 256 == (int)(tiles / 256) ? tiles / 256 : tiles / 256 + 0.5; };
+    const double t256 = c.min_rows > 128 ? rounds(c.tiles256) * 0.77 : 1e30, t128 = rounds(c.tiles128) * 0.56;
+    const double t128x128 = rounds(c.tiles128x128) * 0.42;
+    const bool paired_ok = a.K <= 2048 && c.tiles128 > 256;              // short K, and two tiles for some CU
+    if (t128x128 < t256 && t128x128 < t128) return TILE_128x128;
+    if (t128 < t256) return paired_ok ? TILE_128x256_PAIRED : TILE_128x256;
+    // rows just past a multiple of 256 pay for a second, mostly empty tile (not with up to 256 rows: there the 128-row
+    // tiles would stream every weight twice for a few rows; 64 experts x 157 rows at most, 125 on average: 279 -> 318)
+    const double t_paired = (int)((c.tiles128 + 511) / 512) * 0.84;
+    return paired_ok && c.max_rows > 256 && t_paired < t256 ? TILE_128x256_PAIRED : TILE_256x256;
 }
 
-// Two products in one launch (same K, N and packing; the tile is picked for the tiles of both together).  Both with
-// groups of more than 128 rows: 256-row tiles, the large 256 x 256 one if the pair has enough tiles for it.  One of
-// them with groups of at most 128 rows: 128 x 256 tiles for both, but only if the other product alone could not fill
-// the chip with 256 x 256 tiles (a product with few columns), since 128-row tiles are the less efficient ones.
-static bool pair_shape(const WsGemmArgs& a, const WsGemmArgs& b, TileShape* shape) {
+// Two products in one launch: twice the tiles, so that a product with few columns can use a large tile.  Not with so few
+// that 256-row tiles of 128 columns leave CUs idle: the second products' outputs meet in a kernel of their own, rounded,
+// while the dense branch alone adds the experts' rows in its epilogue.  With groups of at most 128 rows in one of them
+// only if the other product alone could not fill the chip with 256 x 256 tiles: those keep their rate, and the 128-row
+// tiles that both would get are the less efficient ones.
+static bool pair_fits(const WsGemmArgs& a, const WsGemmArgs& b) {
     if (a.K != b.K || a.N != b.N || (a.packed != 0) != (b.packed != 0) || a.ksplit != 1 || b.ksplit != 1) return false;
-    const long long n256 = (a.N + 255) / 256;
-    if (a.max_rows <= 128 || b.max_rows <= 128) {
-        const WsGemmArgs& big = a.max_rows <= 128 ? b : a;
-        if (big.max_rows <= 128 || (long long)big.G * ((big.max_rows + 255) / 256) * n256 >= 256) return false;
-        *shape = TILE_128x256;
-        return true;
-    }
-    const long long row_tiles = (long long)a.G * ((a.max_rows + 255) / 256) + (long long)b.G * ((b.max_rows + 255) / 256);
-    if (row_tiles * n256 >= 256) *shape = TILE_256x256;
-    else if (row_tiles * ((a.N + 127) / 128) >= 256) *shape = TILE_256x128;
-    else return false;
-    return true;
+    if (a.max_rows > 128 && b.max_rows > 128)
+        return ((long long)a.G * ((a.max_rows + 255) / 256) + (long long)b.G * ((b.max_rows + 255) / 256)) * ((a.N + 127) / 128) >= 256;
+    const WsGemmArgs& big = a.max_rows <= 128 ? b : a;
+    return big.max_rows > 128 && (long long)big.G * ((big.max_rows + 255) / 256) * ((a.N + 255) / 256) < 256;
 }
 bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b) {
-    TileShape t;
-    return tgemm_supported(a.K, a.N) && pair_shape(a, b, &t);
+    return tgemm_supported(a.K, a.N) && pair_fits(a, b);
 }
 
 template <int EPI>
 static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    TileShape shape = pick_tile(a.max_rows, a.G, a.N);
-    if (b && !pair_shape(a, *b, &shape)) return MOE_ERR_INVALID_ARG;
-    switch (shape) {
+    if (b && !pair_fits(a, *b)) return MOE_ERR_INVALID_ARG;
+    switch (pick_tile(a, b)) {
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);
-        case TILE_256x128: return launch_t<64, 4, 5, EPI, 64>(a, b, s);
-        default: return a.K <= 2048 ? launch_t<64, 2, 3, EPI, 128>(a, b, s) : launch_t<32, 4, 5, EPI, 128>(a, b, s);
+        case TILE_128x256: return launch_t<32, 4, 5, EPI, 128>(a, b, s);
+        case TILE_128x256_PAIRED: return launch_t<64, 2, 3, EPI, 128>(a, b, s);
+        default: return launch_t<32, 4, 6, EPI, 64>(a, b, s);
     }
 }
 
