@@ -392,6 +392,9 @@ int run_residual_paired(const moe_shape_t* s, const FfnPlan& p, const void* x, c
                         void* hd, void* ye, void* dense_out, const int32_t* expert_idx, const int32_t* slot_idx,
                         const float* gate_w, void* out, hipStream_t st) {
     if (!p.tiled || s->T <= 128) return MOE_ERR_UNSUPPORTED;
+    // Shapes with an inner dimension off the 32-deep stages keep the combine inside the dense branch's product, which adds
+    // the experts' rows to unrounded sums.
+    if (s->d_model % 32 || s->d_ffn % 32) return MOE_ERR_UNSUPPORTED;
     const int packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
     WsGemmArgs e1{}, d1{}, e2{}, d2{};
     e1.A = u16(x); e1.B = u16(W1); e1.bias = u16(b1); e1.rows = rows; e1.order = order; e1.row_map = slot_token;

@@ -17,7 +17,8 @@
 // and does not put a full vmcnt(0) wait in front of every LDS read; completion is tracked by hand
 // (in-order vmcnt: 8 loads per wave and stage).
 // v_mfma_f32_16x16x32_bf16, fp32 accumulation; epilogues shared with the streaming kernel.
-// Requires K to be a multiple of 32 (no zero fill is possible on the way into LDS).
+// K is a multiple of 8; a lane whose 16 bytes of the last stage lie past K loads zeros from a constant instead (weights too,
+// unless they are packed and hold zeros there): nothing is filled in on the way into LDS.
 #include "ffn_common.h"
 #include <type_traits>
 
@@ -35,6 +36,8 @@ __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_wave_base) 
 // unit 4*(m%4) + slot, so the four lanes of a pass that share m%4 need four different slots.  Taking
 // slot = kg ^ f(m/4) with f = {0, 2, 3, 1} does that for every pass.
 __device__ __forceinline__ int a_swizzle(int row) { return (0x78 >> (((row >> 2) & 3) * 2)) & 3; }
+
+__device__ __align__(16) const uint32_t kZero16[4] = {0, 0, 0, 0};   // what lanes past K load
 
 template <int N> __device__ __forceinline__ void wait_vmcnt() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 
@@ -68,7 +71,7 @@ template <int WM, int NWM, int NS_, int WN> struct TileCfg {
     static constexpr int LDS_BYTES = RING + BM * 8;
 };
 
-template <int WM, int NWM, int NSX, int EPI, int WN, bool PACKED>
+template <int WM, int NWM, int NSX, int EPI, int WN, bool PACKED, bool RAGGED>
 __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU)) void tgemm_kernel(const WsGemmArgs a0,
                                                                                                    const WsGemmArgs a1,
                                                                                                    const int split) {
@@ -158,22 +161,26 @@ __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU))
     const int p_ng = (a.N + 127) / 128;
     const int p_grp = min(n0 / 128 + (w * NIB) / 8, p_ng - 1);             // clamped group: loaded, never stored
     const uint16_t* b_src = PACKED
-        ? a.B + (((size_t)g * (a.K / kTK) * p_ng + p_grp) * 8 + (w * NIB) % 8) * 512 + lane * 8
+        ? a.B + (((size_t)g * ((a.K + kTK - 1) / kTK) * p_ng + p_grp) * 8 + (w * NIB) % 8) * 512 + lane * 8
         : a.B + (size_t)g * a.K * a.N + (size_t)b_row * a.N + min(n0 + b_piece * 8, a.N - 8);   // clamped column
     const size_t b_step2 = PACKED ? (size_t)512 : (size_t)RPI * a.N;        // from one load of a stage to the next
     const size_t b_kstep = PACKED ? (size_t)p_ng * 4096 : (size_t)kTK * a.N;   // from one stage to the next
-    const int steps = a.K / kTK;
-    auto issue = [&](int step) {                                // all loads of one stage, this wave's share
+    const int steps = (a.K + kTK - 1) / kTK;
+    // All loads of one stage, this wave's share.  RAGGED: K ends inside the last stage, some of whose lanes lie past it.
+    auto issue = [&](int step) {
         const int st = min(step, steps - 1);                    // past the end: harmless re-read, keeps the count uniform
         const uint32_t base = lds0 + (step % NS) * STAGE;
         const int k0 = st * kTK;
+        const uint16_t* zeros = reinterpret_cast<const uint16_t*>(kZero16);
+        const int a_kp = ((lane & 3) ^ a_swizzle(lane >> 2)) * 8;             // a_swizzle(r) == a_swizzle(lane >> 2) above
 #pragma unroll
         for (int i = 0; i < NIA; ++i)
-            dma16(a_src[i] + k0, __builtin_amdgcn_readfirstlane(base + (w * NIA + i) * 1024));
+            dma16(RAGGED && k0 + a_kp >= a.K ? zeros : a_src[i] + k0, __builtin_amdgcn_readfirstlane(base + (w * NIA + i) * 1024));
         const uint16_t* bp = b_src + (size_t)st * b_kstep;
 #pragma unroll
         for (int i = 0; i < NIB; ++i)
-            dma16(bp + i * b_step2, __builtin_amdgcn_readfirstlane(base + A_BYTES + (w * NIB + i) * 1024));
+            dma16(RAGGED && !PACKED && k0 + b_row + i * RPI >= a.K ? zeros : bp + i * b_step2,
+                  __builtin_amdgcn_readfirstlane(base + A_BYTES + (w * NIB + i) * 1024));
     };
 
     f32x4_t acc[NA][NCF];
@@ -250,12 +257,7 @@ __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU))
     // other waves (their shares have landed too, and nobody reads the buffer of stage s-1 any more),
     // refills that buffer with stage s+NS-1, then reads the fragments of stage s+1 from LDS while the
     // matrix cores work on stage s: LDS reads and MFMAs of a wave overlap instead of alternating.
-#pragma unroll
-    for (int s = 0; s < NS - 1; ++s) issue(s);
     Frags f0, f1;
-    wait_vmcnt<(NS - 2) * PER_STAGE>();
-    __builtin_amdgcn_s_barrier();
-    read_frags(f0, 0);
     auto step = [&](const Frags& cur, Frags& nxt, int s) {
         wait_vmcnt<(NS - 3) * PER_STAGE>();
         __builtin_amdgcn_s_barrier();
@@ -279,6 +281,11 @@ __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU))
             if (MFMAS > PER * GROUPS) __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - PER * GROUPS, 0);
         }
     };
+#pragma unroll
+    for (int s = 0; s < NS - 1; ++s) issue(s);
+    wait_vmcnt<(NS - 2) * PER_STAGE>();
+    __builtin_amdgcn_s_barrier();
+    read_frags(f0, 0);
     int s = 0;
     for (; s + 2 <= steps; s += 2) {
         step(f0, f1, s);
@@ -354,7 +361,7 @@ __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU))
 }
 
 // b == nullptr: one product; otherwise the two products share the launch (same K, N, packing)
-template <int WM, int NWM, int NSX, int EPI, int WN, bool PACKED>
+template <int WM, int NWM, int NSX, int EPI, int WN, bool PACKED, bool RAGGED>
 static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     constexpr int BM = NWM * WM, TBN = 2 * WN;
     const int n_tiles = (a.N + TBN - 1) / TBN;
@@ -368,18 +375,20 @@ static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
                   "the promised work-groups per CU must fit its LDS together");
     static bool attr_set = false;            // one flag per instantiation
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED, RAGGED>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
             return MOE_ERR_HIP;
         attr_set = true;
     }
-    hipLaunchKernelGGL((tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED>), dim3((unsigned)blocks), dim3(NWM * 128), smem, s, a,
+    hipLaunchKernelGGL((tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED, RAGGED>), dim3((unsigned)blocks), dim3(NWM * 128), smem, s, a,
                        b ? *b : a, (int)blocks_a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 template <int WM, int NWM, int NSX, int EPI, int WN>
 static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false>(a, b, s);
+    if (a.K % kTK)            // instances of their own: whole stages are not charged for the selects
+        return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s);
+    return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
 }
 
 // Tile shapes, for one product or for two in one launch (same K, N and packing: all tiles are counted together):
@@ -454,7 +463,7 @@ static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s)
     }
 }
 
-bool tgemm_supported(int K, int N) { return K % kTK == 0 && K >= kTK && N % 8 == 0 && N >= 8; }
+bool tgemm_supported(int K, int N) { return K % 8 == 0 && K >= 8 && N % 8 == 0 && N >= 8; }
 
 static int launch_tgemm_any(const WsGemmArgs& a, const WsGemmArgs* b, int epi, hipStream_t s) {
     if (a.G <= 0 || a.max_rows <= 0) return b ? MOE_ERR_INVALID_ARG : MOE_OK;

@@ -184,7 +184,7 @@ struct WsGemmArgs {
 bool wsgemm_supported(int K, int N);
 void wsgemm_pick_tile(int max_rows, int G, int N, int* MT, int* NW);
 int launch_wsgemm(const WsGemmArgs& a, int epi, int MT, int NW, int NBUF, hipStream_t s);
-int wsgemm_chunk_k(int MT);
+int wsgemm_chunk_k(int MT);   // k-extent of one LDS chunk = granularity of split-K
 
 // Products that read few weights (ffn_rows.hip): 16 NF columns per work-group, K split over its waves; ksplit must be 1.
 // b: a second product of the same K, N and packing in the same launch (not with EPI_SCATTER), or nullptr.
@@ -199,7 +199,7 @@ int launch_tgemm(const WsGemmArgs& a, int epi, hipStream_t s);
 // two grouped products in one launch (same K, N, packing, epilogue; both with 256-row tiles): twice the tiles
 bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b);
 int launch_tgemm_pair(const WsGemmArgs& a, const WsGemmArgs& b, int epi, hipStream_t s);
-bool tgemm_supported(int K, int N);   // K a multiple of 32   // k-extent of one LDS chunk = granularity of split-K
+bool tgemm_supported(int K, int N);
 
 // Weights in the fragment order of v_mfma_f32_16x16x32_bf16's second operand (pack.hip).  Element (k, n) of group g
 // goes to  ((((g*KB + k/32)*NG + n/128)*8 + n%8)*64 + (k%32/8)*16 + (n%128)/8)*8 + k%8,  KB = ceil(K/32),

@@ -21,3 +21,15 @@ def test_tiled_layer(C, T, d, f, E, k, residual):
     print(f"case C={C} T={T} d={d} f={f} E={E} k={k} residual={residual}", flush=True)
     cfg = CONFIGS["c3a"].scaled(name="tiles", T=T, d_model=d, d_ffn=f, E=E, top_k=k, residual=residual, seed=7)
     U.check_layer(make_inputs(cfg, "cuda", bias_std=0.05), capacity=C)
+
+
+# the inner dimension ends inside a 32-deep stage, in the first product (d) or the second (f)
+RAGGED = [(70, 200, 8, 72, 3, 1, False), (130, 300, 40, 104, 3, 1, True), (300, 700, 1000, 264, 3, 2, False),
+          (256, 1100, 72, 1000, 5, 1, True), (200, 3000, 120, 4104, 16, 1, False), (100, 500, 200, 3016, 8, 2, True)]
+
+
+@pytest.mark.parametrize("C,T,d,f,E,k,residual", RAGGED)
+def test_tiled_layer_ragged_k(C, T, d, f, E, k, residual):
+    print(f"case C={C} T={T} d={d} f={f} E={E} k={k} residual={residual}", flush=True)
+    cfg = CONFIGS["c3a"].scaled(name="tiles", T=T, d_model=d, d_ffn=f, E=E, top_k=k, residual=residual, seed=8)
+    U.check_layer(make_inputs(cfg, "cuda", bias_std=0.05), capacity=C)
