@@ -103,16 +103,15 @@ inline long long tile_grid_blocks(const WsGemmArgs& a, int n_tiles, int inner_n)
     return ((long long)a.G * n_tiles + kXcd - 1) / kXcd * kXcd * inner_n;
 }
 
-// Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them, spread over
-// all work-groups (a dropped token has no other writer).
+// Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them, spread over the waves of all
+// work-groups (a dropped token has no other writer).  A wave looks at 16 tokens at once: one token after the other, a
+// work-group of a small grid waited for up to 16 memory round trips before its first tile (8192 tokens, 512 work-groups).
 __device__ __forceinline__ void zero_dropped_rows(const WsGemmArgs& a, int tid, int nthreads) {
     if (!a.zero_slot_idx) return;
-    for (int t = blockIdx.x; t < a.T; t += gridDim.x) {
-        if (a.zero_slot_idx[t] < 0) {
-            uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
-            for (int i = tid; i < a.N / 8; i += nthreads) o[i] = make_uint4(0, 0, 0, 0);
-        }
-    }
+    for_dropped_tokens(a.zero_slot_idx, 1, a.T, tid, nthreads, [&](int t, int lane) {
+        uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
+        for (int i = lane; i < a.N / 8; i += kWave) o[i] = make_uint4(0, 0, 0, 0);
+    });
 }
 
 // 16-byte loads and stores with the non-temporal hint: data that passes through once (expert weights at a

@@ -63,11 +63,10 @@ __device__ __forceinline__ void f32_finish(const GemmArgs& a, int g, int r, int 
 
 // EPI_SCATTER leaves the rows of dropped tokens unwritten: zero them, spread over all work-groups.
 __device__ __forceinline__ void f32_zero_dropped(const GemmArgs& a, int tid, int nthreads) {
-    for (int t = blockIdx.x; t < a.T; t += gridDim.x) {
-        if (a.slot_idx[(size_t)t * a.top_k] >= 0) continue;
+    for_dropped_tokens(a.slot_idx, a.top_k, a.T, tid, nthreads, [&](int t, int lane) {
         f32x4_t* o = reinterpret_cast<f32x4_t*>(static_cast<float*>(a.out) + (size_t)t * a.N);
-        for (int i = tid; i < a.N / 4; i += nthreads) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int i = lane; i < a.N / 4; i += kWave) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    });
 }
 
 __device__ __forceinline__ int f32_rows_of(const GemmArgs& a, int g) { return a.rows ? min(a.rows[g], a.max_rows) : a.fixed_rows; }

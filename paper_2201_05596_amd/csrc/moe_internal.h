@@ -47,6 +47,18 @@ __device__ __forceinline__ float gelu_tanh(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
+// zero(t, lane) by a whole wave for every token t < T whose first choice has no slot; 16 tokens per wave at a time, dealt to
+// the work-groups first and to their waves then.
+template <typename F>
+__device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int top_k, int T, int tid, int nthreads, F zero) {
+    const int lane = tid % kWave;
+    for (int c = blockIdx.x + gridDim.x * __builtin_amdgcn_readfirstlane(tid / kWave); c < (T + 15) / 16; c += gridDim.x * (nthreads / kWave)) {
+        const int t = c * 16 + lane;
+        const bool dropped = lane < 16 && t < T && slot_idx[(size_t)t * top_k] < 0;
+        for (unsigned long long m = __ballot(dropped); m; m &= m - 1) zero(c * 16 + __ffsll((long long)m) - 1, lane);
+    }
+}
+
 template <typename T> struct Elem;
 template <> struct Elem<float> {
     static __device__ __forceinline__ float load(const float* p) { return *p; }
