@@ -21,6 +21,73 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+// A row by one work-group, its pieces of 8 elements held in registers from the sum to the result (NP per thread): one
+// memory round trip and the two sums across the waves.  A wave per row with three passes over it, below, left 64 rows to 16
+// work-groups: 10.7 us for 64 rows of 2048 with the residual add, 6.6 without.
+template <int NP>
+__global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ r,
+                                                                const float* __restrict__ gamma, const float* __restrict__ beta,
+                                                                uint16_t* __restrict__ sum_out, uint16_t* __restrict__ y, int d,
+                                                                float eps) {
+    __shared__ float part[2][4];
+    const int tid = threadIdx.x, pieces = d / 8;
+    const size_t row = (size_t)blockIdx.x * d;
+    float f[NP][8], gm[NP][8], bt[NP][8];
+    uint4 xv[NP], rv[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {                      // all loads first; past the end: the last piece, not counted
+        const int i = min(tid + p * 256, pieces - 1);
+        xv[p] = reinterpret_cast<const uint4*>(x + row)[i];
+        if (r) rv[p] = reinterpret_cast<const uint4*>(r + row)[i];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            *reinterpret_cast<float4*>(&gm[p][4 * q]) = reinterpret_cast<const float4*>(gamma)[2 * i + q];
+            *reinterpret_cast<float4*>(&bt[p][4 * q]) = reinterpret_cast<const float4*>(beta)[2 * i + q];
+        }
+    }
+    auto block_sum = [&](float v, float (&sh)[4]) {
+        v = wave_sum(v);
+        if (tid % kWave == 0) sh[tid / kWave] = v;
+        __syncthreads();
+        return (sh[0] + sh[1]) + (sh[2] + sh[3]);
+    };
+    float sum = 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int i = tid + p * 256;
+        unpack8(xv[p], f[p]);
+        if (r) {
+            float g[8];
+            unpack8(rv[p], g);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) f[p][q] += g[q];
+            const uint4 o = pack8(f[p]);
+            unpack8(o, f[p]);                           // the row as it is stored
+            if (sum_out && i < pieces) reinterpret_cast<uint4*>(sum_out + row)[i] = o;
+        } else if (sum_out && i < pieces) {
+            reinterpret_cast<uint4*>(sum_out + row)[i] = xv[p];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sum += i < pieces ? f[p][q] : 0.f;
+    }
+    const float mean = block_sum(sum, part[0]) / (float)d;
+    float sq = 0.f;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) sq += tid + p * 256 < pieces ? (f[p][q] - mean) * (f[p][q] - mean) : 0.f;
+    const float rstd = rsqrtf(block_sum(sq, part[1]) / (float)d + eps);
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+        const int i = tid + p * 256;
+        if (i >= pieces) break;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) f[p][q] = (f[p][q] - mean) * rstd * gm[p][q] + bt[p][q];
+        reinterpret_cast<uint4*>(y + row)[i] = pack8(f[p]);
+    }
+}
+
+// The same for rows of more than 4096 elements.
 // y[t,:] = LayerNorm(s[t,:]) * gamma + beta with s = x (+ r), one wave per row; s is also written to `sum_out` when
 // given (rounded to bf16 first: the statistics are those of the stored row).  d is a multiple of 8.
 __global__ __launch_bounds__(256) void add_layernorm_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ r,
@@ -75,7 +142,11 @@ __global__ __launch_bounds__(256) void add_layernorm_kernel(const uint16_t* __re
 
 int launch_add_layernorm(const uint16_t* x, const uint16_t* r, const float* gamma, const float* beta, uint16_t* sum_out,
                          uint16_t* y, int T, int d, float eps, hipStream_t s) {
-    hipLaunchKernelGGL(add_layernorm_kernel, dim3((T + 3) / 4), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, T, d, eps);
+    if (d <= 2048)
+        hipLaunchKernelGGL(add_layernorm_row_kernel<1>, dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps);
+    else if (d <= 4096)
+        hipLaunchKernelGGL(add_layernorm_row_kernel<2>, dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps);
+    else hipLaunchKernelGGL(add_layernorm_kernel, dim3((T + 3) / 4), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, T, d, eps);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -109,7 +180,10 @@ int launch_add_rows(const uint16_t* a, const uint16_t* b, uint16_t* out, long lo
 // and leave one partial (m, l, o[DH]) per chunk, merged by attn_merge_kernel.  The chunk that holds position pos[b]
 // takes the new key/value from qkv, never from the cache, so the write of the new rows into the cache (by chunk 0)
 // races with nobody.
+// Bound by the read of the cache: kAttnAhead steps are loaded together and meet in one rescaling of the running softmax
+// (one step at a time, load after use, ran at 5 TB/s: 108 us for 64 sequences of 2048 positions at most, 16 heads of 128).
 constexpr int kAttnChunk = 256;
+constexpr int kAttnAhead = 4;
 
 template <int DH>
 __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ cache_k,
@@ -142,31 +216,46 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
 #pragma unroll
     for (int i = 0; i < 8; ++i) o[i] = 0.f;
     const int p0 = split * kAttnChunk + w * (kAttnChunk / 4);
-    for (int step = 0; step < kAttnChunk / 4 / PPW; ++step) {
-        const int p = p0 + step * PPW + grp;
+    const uint4 knew = *reinterpret_cast<const uint4*>(qrow + d + sub * 8);       // the new token itself
+    const uint4 vnew = *reinterpret_cast<const uint4*>(qrow + 2 * d + sub * 8);
+    static_assert(kAttnChunk / 4 / PPW % kAttnAhead == 0, "whole rounds");
+    for (int step = 0; step < kAttnChunk / 4 / PPW; step += kAttnAhead) {
         if (p0 + step * PPW > npast) break;                          // uniform over the wave
-        const bool valid = p <= npast;
-        const int pc = min(p, max(npast - 1, 0));                    // clamped cache position (in bounds; unused if !valid)
-        uint4 kraw = *reinterpret_cast<const uint4*>(kc + (size_t)pc * DH + sub * 8);
-        uint4 vraw = *reinterpret_cast<const uint4*>(vc + (size_t)pc * DH + sub * 8);
-        if (p == npast || npast == 0) {                              // the new token itself
-            kraw = *reinterpret_cast<const uint4*>(qrow + d + sub * 8);
-            vraw = *reinterpret_cast<const uint4*>(qrow + 2 * d + sub * 8);
+        uint4 kraw[kAttnAhead], vraw[kAttnAhead];
+#pragma unroll
+        for (int u = 0; u < kAttnAhead; ++u) {
+            const int pc = min(p0 + (step + u) * PPW + grp, max(npast - 1, 0));   // clamped cache position (in bounds; unused past npast)
+            kraw[u] = *reinterpret_cast<const uint4*>(kc + (size_t)pc * DH + sub * 8);
+            vraw[u] = *reinterpret_cast<const uint4*>(vc + (size_t)pc * DH + sub * 8);
         }
-        float kf[8], vf[8];
-        unpack8(kraw, kf);
-        unpack8(vraw, vf);
-        float s = 0.f;
+        float s[kAttnAhead], mn = m;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) s = fmaf(q[i], kf[i], s);
+        for (int u = 0; u < kAttnAhead; ++u) {
+            const int p = p0 + (step + u) * PPW + grp;
+            float kf[8];
+            unpack8(p == npast ? knew : kraw[u], kf);
+            s[u] = 0.f;
 #pragma unroll
-        for (int msk = 1; msk < LPP; msk <<= 1) s += __shfl_xor(s, msk);
-        if (valid) {
-            const float mn = fmaxf(m, s);
-            const float c = __expf(m - mn), e = __expf(s - mn);      // m = -inf at first: c = 0
-            l = l * c + e;
+            for (int i = 0; i < 8; ++i) s[u] = fmaf(q[i], kf[i], s[u]);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) o[i] = fmaf(o[i], c, e * vf[i]);
+            for (int msk = 1; msk < LPP; msk <<= 1) s[u] += __shfl_xor(s[u], msk);
+            if (p > npast) s[u] = -INFINITY;
+            mn = fmaxf(mn, s[u]);
+        }
+        if (mn > -INFINITY) {                                        // false: nothing yet for this lane group
+            const float c = __expf(m - mn);                          // m = -inf at first: c = 0
+            l *= c;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) o[i] *= c;
+#pragma unroll
+            for (int u = 0; u < kAttnAhead; ++u) {
+                const float e = __expf(s[u] - mn);                   // exp(-inf) = 0 past npast
+                float vf[8];
+                unpack8(p0 + (step + u) * PPW + grp >= npast ? vnew : vraw[u], vf);   // past npast: anything finite
+                l += e;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) o[i] = fmaf(e, vf[i], o[i]);
+            }
             m = mn;
         }
     }
@@ -198,13 +287,30 @@ __global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict_
                                                         int nsplit) {
     const int bh = blockIdx.x, b = bh / H, h = bh % H, t = threadIdx.x;
     const float* p = partial + (size_t)bh * nsplit * (DH + 2);
-    float M = -INFINITY;
-    for (int s = 0; s < nsplit; ++s) M = fmaxf(M, p[s * (DH + 2)]);
-    float L = 0.f, O = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
-        const float c = __expf(p[s * (DH + 2)] - M);
-        L = fmaf(p[s * (DH + 2) + 1], c, L);
-        O = fmaf(p[s * (DH + 2) + 2 + t], c, O);
+    // eight chunks' partials in flight; a chunk without positions holds m = -inf and zeros
+    float M = -INFINITY, L = 0.f, O = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        float m[8], l[8], o[8], mn = M;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float* ps = p + min(s0 + u, nsplit - 1) * (DH + 2);
+            m[u] = s0 + u < nsplit ? ps[0] : -INFINITY;
+            l[u] = ps[1];
+            o[u] = ps[2 + t];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mn = fmaxf(mn, m[u]);
+        if (mn == -INFINITY) continue;
+        const float c = __expf(M - mn);
+        L *= c;
+        O *= c;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float e = __expf(m[u] - mn);
+            L = fmaf(l[u], e, L);
+            O = fmaf(o[u], e, O);
+        }
+        M = mn;
     }
     attn[(size_t)b * H * DH + h * DH + t] = f32_to_bf16(O / L);
 }
