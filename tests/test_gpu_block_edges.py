@@ -32,3 +32,9 @@ def test_unused_cache_rows_are_never_used():
         cache.masked_fill_(rows, float("nan"))
     res = _run_block(bi, False)
     assert torch.equal(ref["out"], res["out"]) and torch.equal(ref["x1"], res["x1"])
+
+
+def test_decode_block_large_cache():
+    """Caches of more than 256 MB together are read with the non-temporal hint; here with 64 elements per head."""
+    cfg = CONFIGS["c4"].scaled(name="b-large", T=33, d_model=1024, d_ffn=256, E=4, capacity_factor=4.0)
+    print(_check_block(make_block_inputs(cfg, 16, 2200, DEV), packed_too=False), flush=True)
