@@ -6,10 +6,8 @@
 // capacity), and a scatter, all driven by a dense token-to-expert mapping table
 // instead of one-hot masks.  The paper parallelises the cumsum with a Blelloch
 // scan on its hardware; here the count is done with 64-wide wavefront ballots
-// (rank inside a wave), a per-block histogram and a prefix over blocks, which
+// (rank inside a wave), a per-tile histogram and a prefix over tiles, which
 // is deterministic (no atomics) and needs two small launches.
-#include <cstdlib>
-
 #include "route_device.h"
 
 namespace moe {
