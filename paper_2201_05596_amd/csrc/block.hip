@@ -235,6 +235,7 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
             vraw[u] = load_cache16<STREAM>(vc + (size_t)pc * DH + sub * 8);
         }
         float s[kAttnAhead], mn = m;
+        bool some = false;
 #pragma unroll
         for (int u = 0; u < kAttnAhead; ++u) {
             const int p = p0 + (step + u) * PPW + grp;
@@ -246,9 +247,10 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
 #pragma unroll
             for (int msk = 1; msk < LPP; msk <<= 1) s[u] += __shfl_xor(s[u], msk);
             if (p > npast) s[u] = -INFINITY;
+            some = some || !(s[u] == -INFINITY);                     // NaN is a score: it has to reach l (fmaxf passes it over)
             mn = fmaxf(mn, s[u]);
         }
-        if (mn > -INFINITY) {                                        // false: nothing yet for this lane group
+        if (some) {                                                  // false: no position for this lane group
             const float c = __expf(m - mn);                          // m = -inf at first: c = 0
             l *= c;
 #pragma unroll
@@ -274,12 +276,11 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
         float M = -INFINITY;
         for (int j = 0; j < NG; ++j) M = fmaxf(M, m_sh[j]);
         float L = 0.f, O = 0.f;
-        if (M > -INFINITY) {
-            for (int j = 0; j < NG; ++j) {
-                const float c = __expf(m_sh[j] - M);                 // empty groups: exp(-inf) = 0
-                L = fmaf(l_sh[j], c, L);
-                O = fmaf(o_sh[j][tid], c, O);
-            }
+        for (int j = 0; j < NG; ++j) {
+            // empty groups: exp(-inf) = 0; M = -inf: nothing but empty groups and such whose scores were all NaN (l is NaN)
+            const float c = m_sh[j] == M ? 1.f : __expf(m_sh[j] - M);
+            L = fmaf(l_sh[j], c, L);
+            O = fmaf(o_sh[j][tid], c, O);
         }
         float* dst = partial + ((size_t)bh * nsplit + split) * (DH + 2);
         dst[2 + tid] = O;
@@ -293,7 +294,8 @@ __global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict_
                                                         int nsplit) {
     const int bh = blockIdx.x, b = bh / H, h = bh % H, t = threadIdx.x;
     const float* p = partial + (size_t)bh * nsplit * (DH + 2);
-    // eight chunks' partials in flight; a chunk without positions holds m = -inf and zeros
+    // eight chunks' partials in flight; a chunk without positions holds m = -inf and zeros, one whose scores are all NaN
+    // m = -inf and NaN
     float M = -INFINITY, L = 0.f, O = 0.f;
     for (int s0 = 0; s0 < nsplit; s0 += 8) {
         float m[8], l[8], o[8], mn = M;
@@ -306,13 +308,12 @@ __global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict_
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) mn = fmaxf(mn, m[u]);
-        if (mn == -INFINITY) continue;
-        const float c = __expf(M - mn);
+        const float c = M == mn ? 1.f : __expf(M - mn);
         L *= c;
         O *= c;
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
-            const float e = __expf(m[u] - mn);
+            const float e = s0 + u >= nsplit ? 0.f : m[u] == mn ? 1.f : __expf(m[u] - mn);
             L = fmaf(l[u], e, L);
             O = fmaf(o[u], e, O);
         }
