@@ -259,7 +259,8 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
             for (int u = 0; u < kAttnAhead; ++u) {
                 const float e = __expf(s[u] - mn);                   // exp(-inf) = 0 past npast
                 float vf[8];
-                unpack8(p0 + (step + u) * PPW + grp >= npast ? vnew : vraw[u], vf);   // past npast: anything finite
+                const int p = p0 + (step + u) * PPW + grp;
+                unpack8(p < npast ? vraw[u] : p == npast ? vnew : make_uint4(0, 0, 0, 0), vf);   // past npast: 0 times 0
                 l += e;
 #pragma unroll
                 for (int i = 0; i < 8; ++i) o[i] = fmaf(e, vf[i], o[i]);
@@ -303,8 +304,8 @@ __global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict_
         for (int u = 0; u < 8; ++u) {
             const float* ps = p + min(s0 + u, nsplit - 1) * (DH + 2);
             m[u] = s0 + u < nsplit ? ps[0] : -INFINITY;
-            l[u] = ps[1];
-            o[u] = ps[2 + t];
+            l[u] = s0 + u < nsplit ? ps[1] : 0.f;
+            o[u] = s0 + u < nsplit ? ps[2 + t] : 0.f;            // not the last chunk's once more: 0 times infinity is NaN
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) mn = fmaxf(mn, m[u]);

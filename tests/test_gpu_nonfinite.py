@@ -48,3 +48,25 @@ def test_nan_in_the_new_key(dh):
     got = _run_block(bi)["x1"]
     lost = [p for b, p in enumerate(POS) if not bool(torch.isnan(got[b]).all())]
     assert not lost, f"NaN key of the new token is lost at positions {lost}"
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("where", ["first", "last", "new"])
+def test_infinity_in_a_value(dh, where):
+    """An infinite value with a positive weight: infinite attention output, so x1 is infinite with the signs of Wo's row."""
+    print(f"case dh={dh} {where}", flush=True)
+    bi = _block(dh)
+    ref = _run_block(bi)["x1"]
+    if where == "new":
+        bi.bqkv[4 * dh + 3] = INF                                   # columns q | k | v of 2 dh each: element 3 of head 0
+        hit = set(range(len(POS)))
+    else:
+        hit = {b for b, p in enumerate(POS) if p > 0 and (b % 2 == 0 or p == 2499)}   # 2499: the last chunk too
+        for b in hit:
+            bi.k_cache[b, 0] = 0.0                                  # equal scores but the new token's: no weight underflows
+            bi.v_cache[b, 0, 0 if where == "first" else POS[b] - 1, 3] = INF
+    want = torch.where(bi.Wo[3] > 0, INF, -INF).to(ref.dtype)
+    assert bool((bi.Wo[3] != 0).all())
+    got = _run_block(bi)["x1"]
+    for b, p in enumerate(POS):
+        assert torch.equal(got[b], want if b in hit else ref[b]), f"sequence with {p} positions"
