@@ -247,7 +247,8 @@ constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wa
 template <int MS, int EPI>
 __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
     __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves][MS * 16][16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, c = lane & 15, kg = lane >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
     const int nt = blockIdx.x % n_tiles, g = blockIdx.x / n_tiles;
     const int rows = f32_rows_of(a, g), n0 = nt * 64;
@@ -273,27 +274,40 @@ __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a
 #pragma unroll
         for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     const int blocks = (a.K + 15) / 16;
-    Block st[kFAhead];
-#pragma unroll
-    for (int s = 0; s < kFAhead; ++s) load(st[s], w + s * kFWaves);        // past the end: in bounds (clamped), meets zeros
-    for (int kb = w; kb < blocks; kb += kFAhead * kFWaves) {
-#pragma unroll
-        for (int s = 0; s < kFAhead; ++s) {
-            const bool in = (kb + s * kFWaves) * 16 + kg * 4 < a.K;
+    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + kFWaves - 1) / kFWaves : 0);   // blocks w, w + 8, ...
+    auto multiply = [&](Block& b, int kb) {
+        if (kb * 16 + 16 > a.K) {                            // K ends inside: zeros on both sides (0 times infinity is NaN)
+            const bool in = kb * 16 + kg * 4 < a.K;
 #pragma unroll
             for (int ms = 0; ms < MS; ++ms)
-                if (!in) st[s].av[ms] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                if (!in) b.av[ms] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < 4; ++j)
+                if (!in) b.bv[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-                    for (int ms = 0; ms < MS; ++ms)
-                        acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[s].av[ms][j], st[s].bv[j][i], acc[ms][i], 0, 0, 0);
-            load(st[s], kb + (s + kFAhead) * kFWaves);
-            __builtin_amdgcn_sched_barrier(0);           // the refill stays here, kFAhead blocks ahead of its use
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int ms = 0; ms < MS; ++ms)
+                    acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.av[ms][j], b.bv[j][i], acc[ms][i], 0, 0, 0);
+    };
+    Block st[kFAhead];
+#pragma unroll
+    for (int s = 0; s < kFAhead; ++s) load(st[s], w + s * kFWaves);        // past the end: in bounds (clamped), never multiplied
+    int q = 0;
+    for (; q + kFAhead <= mine; q += kFAhead) {
+#pragma unroll
+        for (int s = 0; s < kFAhead; ++s) {
+            multiply(st[s], w + (q + s) * kFWaves);
+            load(st[s], w + (q + s + kFAhead) * kFWaves);
+            __builtin_amdgcn_sched_barrier(0);               // the refill stays here, kFAhead blocks ahead of its use
         }
     }
+#pragma unroll
+    for (int s = 0; s < kFAhead; ++s)
+        if (q + s < mine) multiply(st[s], w + (q + s) * kFWaves);
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms)
 #pragma unroll

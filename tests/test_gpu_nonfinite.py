@@ -3,8 +3,9 @@ remainder, and nothing that takes no part (positions, rows of K past the end) ma
 import pytest
 import torch
 
+from tests import gpu_util as U
 from tests.test_gpu_block import DEV, _run_block
-from workloads import CONFIGS, make_block_inputs
+from workloads import CONFIGS, make_block_inputs, make_inputs
 
 pytestmark = pytest.mark.gpu
 NAN, INF = float("nan"), float("inf")
@@ -70,3 +71,31 @@ def test_infinity_in_a_value(dh, where):
     got = _run_block(bi)["x1"]
     for b, p in enumerate(POS):
         assert torch.equal(got[b], want if b in hit else ref[b]), f"sequence with {p} positions"
+
+
+# dtype, capacity, d, f: at most 16, 32 and more rows per expert, K (d, then f) of whole blocks, ragged, less than a block
+LAST_ROW = [("f32", 1, 4, 4), ("f32", 12, 64, 256), ("f32", 16, 20, 72), ("f32", 30, 36, 132), ("f32", 60, 64, 128), ("f32", 60, 36, 100)]
+
+
+@pytest.mark.parametrize("dtype,C,d,f", LAST_ROW)
+@pytest.mark.parametrize("second", [False, True])
+def test_infinity_in_the_last_weight_row(dtype, C, d, f, second):
+    """An infinite weight in the last row of W1 or W2: the sums that it takes part in are infinite, as any order of additions
+    gives them, and the others what they were."""
+    print(f"case {dtype} C={C} d={d} f={f} second={second}", flush=True)
+    cfg = (CONFIGS["c1"] if dtype == "f32" else CONFIGS["c4"]).scaled(name="last-row", T=C, d_model=d, d_ffn=f, E=1, top_k=1, seed=9)
+    inp = make_inputs(cfg, DEV, bias_std=0.05)
+    inp.x[:, -1] = inp.x[:, -1].abs() + 0.5
+    ref = U.gpu_forward(inp, C)["out"].clone()
+    if second:                                           # h[:, f - 1] > 0 through its bias: column 2 of the output is -inf
+        inp.W1[0, :, -1] = 0.0
+        inp.b1[0, -1] = 1.0
+        inp.W2[0, -1, 2] = -INF
+        got = U.gpu_forward(inp, C)["out"]
+        assert bool((got[:, 2] == -INF).all()) and bool(torch.isfinite(got[:, torch.arange(d) != 2].float()).all())
+    else:                                                # h[:, 1] = +inf: every output is infinite with W2's sign
+        inp.W1[0, -1, 1] = INF
+        got = U.gpu_forward(inp, C)["out"]
+        assert bool((inp.W2[0, 1] != 0).all())
+        assert torch.equal(got, torch.where(inp.W2[0, 1] > 0, INF, -INF).to(got.dtype).expand_as(got))
+    assert bool(torch.isfinite(ref.float()).all())
