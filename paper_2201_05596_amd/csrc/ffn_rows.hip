@@ -106,6 +106,13 @@ __global__ __launch_bounds__(kRWaves * 64) void rows_kernel(const WsGemmArgs a0,
 #pragma unroll
             for (int ms = 0; ms < MS; ++ms)
                 if (!in) b.av[ms] = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
+            if constexpr (!PACKED) {                             // zeros on both sides: 0 times infinity is NaN
+                if (kb * 32 + 32 > a.K) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        if (!in) b.braw[j] = BRaw{};
+                }
+            }
             if constexpr (PACKED) {                              // zeros past K by themselves
 #pragma unroll
                 for (int f = 0; f < NF; ++f)

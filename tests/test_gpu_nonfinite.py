@@ -74,7 +74,8 @@ def test_infinity_in_a_value(dh, where):
 
 
 # dtype, capacity, d, f: at most 16, 32 and more rows per expert, K (d, then f) of whole blocks, ragged, less than a block
-LAST_ROW = [("f32", 1, 4, 4), ("f32", 12, 64, 256), ("f32", 16, 20, 72), ("f32", 30, 36, 132), ("f32", 60, 64, 128), ("f32", 60, 36, 100)]
+LAST_ROW = [("f32", 1, 4, 4), ("f32", 12, 64, 256), ("f32", 16, 20, 72), ("f32", 30, 36, 132), ("f32", 60, 64, 128), ("f32", 60, 36, 100),
+            ("bf16", 1, 8, 8), ("bf16", 12, 40, 136), ("bf16", 16, 72, 264), ("bf16", 9, 1000, 1032)]
 
 
 @pytest.mark.parametrize("dtype,C,d,f", LAST_ROW)
