@@ -2,6 +2,7 @@
 // Every check happens on the host before the first HIP call.
 #include <vector>
 
+#include "call_tag.h"
 #include "moe_internal.h"
 
 using namespace moe;
@@ -132,7 +133,10 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.logits = take(T * E * 4);
     L.wg_frags = take(s->dtype == MOE_BF16 ? gate_bf16_ws_bytes(s->d_model, s->E) : 0);
     L.hist = take(route_scratch_ints(s->T, s->E, s->top_k) * 4);
-    L.flags = take(kGateFlagInts * 4);                 // hand-over flags of the one-launch decode gate
+    // hand-over flags of the one-launch decode gate: it leaves no histograms, so they reach back into that region
+    static_assert(kGateFlags * 8 <= 2 * kAlign, "at least one unit of histograms before the extra one");
+    take(kAlign);
+    L.flags = off - kGateFlags * 8;
     L.expert_idx = take(T * k * 4);
     L.slot_idx = take(T * k * 4);
     L.gate_w = take(T * k * 4);
@@ -213,13 +217,11 @@ int run_gate(const moe_shape_t* s, const void* x, const float* Wg, const float* 
     }
     if (s->dtype == MOE_BF16 && gate_decode_supported(s->T, s->d_model, s->E)) {
         // decode: logits and the whole routing in one launch (counted under ST_LOGITS)
-        static uint32_t epoch = 0;                     // never repeats: a flag left by an earlier call is never "done"
-        epoch = epoch + 1 == 0 ? 1 : epoch + 1;
         const bool packed = s->flags & MOE_FLAG_PACKED_GATE;
         if (profile) prof_pre(ST_LOGITS, st);
         rc = launch_gate_decode(x, packed ? nullptr : Wg, packed ? Wg : nullptr, bg, logits, s->T, s->d_model, s->E,
                                 s->top_k, s->capacity, expert_idx, slot_idx, gate_w, rows, slot_token, order,
-                                at<void>(ws, L.wg_frags), at<uint32_t>(ws, L.flags), epoch, st);
+                                at<void>(ws, L.wg_frags), at<uint64_t>(ws, L.flags), next_call_tag(), st);
         if (profile) prof_mark(ST_LOGITS, st);
         return rc;
     }

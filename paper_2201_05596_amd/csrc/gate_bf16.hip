@@ -307,9 +307,10 @@ __global__ __launch_bounds__(256) void gate_bf16_kernel(const uint16_t* __restri
 // 16 experts, the waves sharing K between them, so that up to d = 2048 all operands are fetched in one round trip (four
 // waves needed three); experts and tokens are split over work-groups so that many CUs share the read of the gate weights.
 // Every work-group then publishes a flag, and the one with the highest index waits for all flags and runs the whole routing
-// on the finished logits.  The flags hold the call's epoch (never 0, and not repeated by the host from one call to the
-// next), so they need no clearing beforehand: what nobody or an earlier call left there is not this call's epoch, and the
-// waiting work-group puts every flag it has seen back to 0, which also makes a replayed graph launch (same epoch) safe.
+// on the finished logits.  The flags lie in scratch memory that may hold anything, so a flag is the call's 64-bit tag: never
+// 0, never repeated by the process, and not to be met by accident (next_call_tag; a small count of calls was, in memory that
+// held indices or histograms before).  The waiting work-group puts every flag it has seen back to 0, which also makes a
+// replayed graph launch (same tag) safe.
 // Hand-over across the XCDs' separate L2s: logits and flags are written with device-scope stores (through the L2), a
 // work-group waits for its logits stores to complete before it writes its flag, and the reader acquires at device scope
 // (invalidate) before its loads.  The wait cannot hang: work-groups are started in index order, so all others are running or
@@ -322,7 +323,7 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
     const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ bg, float* __restrict__ logits,
     int T, int d, int E, int ET, int C, int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
     float* __restrict__ gate_w, int32_t* __restrict__ expert_rows, int32_t* __restrict__ slot_token,
-    int32_t* __restrict__ expert_order, uint32_t* __restrict__ flags, uint32_t epoch) {
+    int32_t* __restrict__ expert_order, uint64_t* __restrict__ flags, uint64_t tag) {
     static_assert(kDecodeWaves * 64 == kSingleThreads, "the routing uses the same work-group");
     constexpr int TM = 16 * MA;
     extern __shared__ __attribute__((aligned(16))) char lds[];
@@ -374,19 +375,19 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
     const int nblocks = gridDim.x * gridDim.y, bid = blockIdx.y * gridDim.x + blockIdx.x;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's logits have left the L2 ...
     __syncthreads();                                   // ... and every thread's of the work-group ...
-    if (tid == 0) __hip_atomic_store(flags + bid, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ... before its flag
+    if (tid == 0) __hip_atomic_store(flags + bid, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ... before its flag
     if (bid != nblocks - 1) return;
     if (tid < nblocks) {
         int polls = 0;
-        while (__hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch && polls < (1 << 20)) {
+        while (__hip_atomic_load(flags + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != tag && polls < (1 << 20)) {
             __builtin_amdgcn_s_sleep(1);
             ++polls;
         }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent"); // nothing read below comes from a stale cache line
-    // Each flag goes back to 0 (never an epoch) once it has been seen: a captured launch that is replayed carries the
-    // same epoch every time and must not find it in the flags of its own previous run.
-    if (tid < nblocks) __hip_atomic_store(flags + tid, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Each flag goes back to 0 (never a tag) once it has been seen: a captured launch that is replayed carries the
+    // same tag every time and must not find it in the flags of its own previous run.
+    if (tid < nblocks) __hip_atomic_store(flags + tid, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     route_single_body<RK, NV>(reinterpret_cast<int32_t*>(lds), logits, T, E, C, expert_idx, slot_idx, gate_w, expert_rows,
                               slot_token, expert_order);
@@ -463,25 +464,25 @@ int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packe
     return MOE_ERR_INVALID_ARG;
 }
 
-// The decode gate in one launch: bf16 tokens, at most 256 of them.  flags: 64 uint32 of scratch; epoch: a value that
-// differs from what any earlier call left in `flags`.
+// The decode gate in one launch: bf16 tokens, at most 256 of them.  flags: kGateFlags words of scratch, whatever they hold;
+// tag: next_call_tag().
 bool gate_decode_supported(int T, int d, int E) { return gate_bf16_supported(d, E) && T <= kRouteTokens; }
 
 template <int MA, int RK, int NV>
 static int launch_decode_cfg(const uint16_t* x, const uint16_t* frags, const float* bg, float* logits, int T, int d, int E,
                              int ET, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
-                             int32_t* slot_token, int32_t* expert_order, uint32_t* flags, uint32_t epoch, hipStream_t s) {
+                             int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s) {
     const size_t route = route_single_lds_ints(E, RK) * sizeof(int32_t), sums = (size_t)kDecodeWaves * 16 * MA * 16 * 4;
     const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET);              // smallest tiles: most work-groups (at most 8 x 8)
-    if (grid.x * grid.y > kGateFlagInts) return MOE_ERR_INVALID_ARG;
+    if (grid.x * grid.y > kGateFlags) return MOE_ERR_INVALID_ARG;
     hipLaunchKernelGGL((gate_decode_kernel<MA, RK, NV>), grid, dim3(kDecodeWaves * 64), route > sums ? route : sums, s, x, frags,
-                       bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order, flags, epoch);
+                       bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order, flags, tag);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
 int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T, int d,
                        int E, int k, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
-                       int32_t* slot_token, int32_t* expert_order, void* frag_ws, uint32_t* flags, uint32_t epoch,
+                       int32_t* slot_token, int32_t* expert_order, void* frag_ws, uint64_t* flags, uint64_t tag,
                        hipStream_t s) {
     if (!gate_decode_supported(T, d, E) || (!frag_ws && !Wg_packed) || !flags || k < 1 || k > 2) return MOE_ERR_INVALID_ARG;
     const int KB = d / kKB, ET = padded_expert_tiles(E);
@@ -494,9 +495,9 @@ int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, co
     const uint16_t* xb = static_cast<const uint16_t*>(x);
 #define MOE_DECODE_CASE(kk, nv) \
     return T <= 128 ? launch_decode_cfg<1, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
-                                                   expert_rows, slot_token, expert_order, flags, epoch, s)              \
+                                                   expert_rows, slot_token, expert_order, flags, tag, s)              \
                     : launch_decode_cfg<2, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
-                                                   expert_rows, slot_token, expert_order, flags, epoch, s)
+                                                   expert_rows, slot_token, expert_order, flags, tag, s)
     if (k == 1) {
         if (E <= 16) MOE_DECODE_CASE(1, 1);
         if (E <= 32) MOE_DECODE_CASE(1, 2);
