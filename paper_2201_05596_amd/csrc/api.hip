@@ -82,6 +82,7 @@ struct FfnPlan {
     bool mfma;          // false: the fp32 kernels (fp32 layers)
     int MT, NW1, NW2;   // row tile; waves per work-group of GEMM-1 / GEMM-2
     int ksplit2;        // split-K factor of GEMM-2 (1 = none)
+    int ksplit_room;    // split-K factor that the workspace has room for
     bool tiled;         // more than 64 rows per expert: the tiled (matrix-core-bound) kernel
     int NBUF;           // weight super-fragments kept in flight per wave, plus one
     int nf1, nf2;       // 16-column fragments per work-group of the few-weights kernel, 0: not that kernel
@@ -91,7 +92,7 @@ struct FfnPlan {
 FfnPlan plan_ffn(const moe_shape_t* s) {
     FfnPlan p{};
     p.mfma = s->dtype == MOE_BF16 && wsgemm_supported(s->d_model, s->d_ffn);
-    p.ksplit2 = 1;
+    p.ksplit2 = p.ksplit_room = 1;
     p.NBUF = 2;
     if (!p.mfma) return p;
     p.tiled = s->capacity > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
@@ -108,12 +109,17 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
         p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed);
         p.nf2 = rows_pick_gemm2(touched, s->capacity, kept, s->d_ffn, s->d_model, packed, waves < 1024);
     }
-    if (waves < 1024 && !p.tiled && !p.nf2) {
+    // The room for partial sums is that of the streaming kernel's split whether or not the call takes it, so that a
+    // workspace sized for packed weights serves the same shape with plain ones (the few-weights kernel's rule knows them
+    // apart) and no size depends on which kernel is the faster one.
+    const bool whole_stages = s->d_model % 32 == 0 && s->d_ffn % 32 == 0;
+    if (waves < 1024 && !(s->capacity > 64 && whole_stages)) {
         const int chunks = (s->d_ffn + wsgemm_chunk_k(p.MT) - 1) / wsgemm_chunk_k(p.MT);
         long long ks = (2048 + waves - 1) / waves;
         if (ks > 8) ks = 8;
         if (ks > chunks) ks = chunks;
-        p.ksplit2 = (int)(ks < 1 ? 1 : ks);
+        p.ksplit_room = (int)(ks < 1 ? 1 : ks);
+        if (!p.tiled && !p.nf2) p.ksplit2 = p.ksplit_room;
     }
     return p;
 }
@@ -147,7 +153,7 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
     L.dense = take(s->residual && plan.mfma ? T * d * es : 0);   // the dense branch's output where it is not combined in place
-    L.partial = take(plan.ksplit2 > 1 ? (size_t)plan.ksplit2 * E * C * d * 4 : 0);
+    L.partial = take(plan.ksplit_room > 1 ? (size_t)plan.ksplit_room * E * C * d * 4 : 0);
     L.total = off;
     return L;
 }

@@ -1,0 +1,20 @@
+"""Workspace sizes on the CPU: one shape, one size, whichever layout the weights have."""
+import itertools
+
+import pytest
+
+from paper_2201_05596_amd import binding as B
+
+
+@pytest.mark.parametrize("d,f", [(256, 1024), (1000, 4000), (2048, 8192), (4096, 16384)])
+def test_size_does_not_depend_on_the_layout_of_the_weights(d, f):
+    for T, E, k, C, residual in itertools.product((1, 16, 64, 200), (1, 8, 64), (1, 2), (1, 16, 17, 64, 100), (False, True)):
+        if k > E:
+            continue
+        sizes = {B.moe_workspace_bytes(B.make_shape(T, d, f, E, k, C, "bf16", residual, flags)) for flags in (0, B.MOE_FLAG_PACKED_WEIGHTS)}
+        assert len(sizes) == 1, f"T={T} E={E} top_k={k} capacity={C} residual={residual}: {sizes}"
+        block = B.MoeBlockShape(d // 64, 128)
+        if d % 64 == 0:
+            sizes = {B.moe_decode_block_workspace_bytes(B.make_shape(T, d, f, E, k, C, "bf16", residual, flags), block)
+                     for flags in (0, B.MOE_FLAG_PACKED_WEIGHTS)}
+            assert len(sizes) == 1
