@@ -82,7 +82,7 @@ constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
 
 // WMW x WNW pairs of waves of 32 rows x 64 columns; wave 0 of a pair takes the first half of every chunk, wave 1 the second
 template <int WMW, int WNW, int EPI>
-__global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, const int n_tiles, const int m_tiles) {
+__global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, const int n_tiles) {
     static_assert(WMW * WNW == 4, "four pairs of waves");
     constexpr int TM = WMW * 32, TN = WNW * 64;
     constexpr int A_BYTES = TM * kFStride, BUF = A_BYTES + kFK * TN * 4;
@@ -93,7 +93,7 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, cons
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, 512);
     // column tiles innermost: with a multiple of 8 of them all row tiles of a column tile run on one XCD and share its
     // weights in that L2, and every XCD has the same work however unevenly the rows fall on the groups
-    const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles % m_tiles, g = blockIdx.x / n_tiles / m_tiles;
+    const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles, g = blockIdx.y;
     const int rows = f32_rows_of(a, g), m0 = mt * TM, n0 = nt * TN;
     if (m0 >= rows) return;
 
@@ -240,7 +240,7 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, cons
     else run(std::integral_constant<int, 0>());
 }
 
-// ---- at most 32 rows per group -------------------------------------------------------------------------------
+// ---- at most 32 rows per tile --------------------------------------------------------------------------------
 constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
 
@@ -250,13 +250,13 @@ __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
-    const int nt = blockIdx.x % n_tiles, g = blockIdx.x / n_tiles;
-    const int rows = f32_rows_of(a, g), n0 = nt * 64;
-    if (rows <= 0) return;
+    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
+    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * MS * 16, n0 = nt * 64;
+    if (m0 >= rows) return;
 
     const float* a_src[MS];
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms) a_src[ms] = f32_arow(a, g, min(ms * 16 + c, rows - 1));
+    for (int ms = 0; ms < MS; ++ms) a_src[ms] = f32_arow(a, g, min(m0 + ms * 16 + c, rows - 1));
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N + min(n0 + c * 4, a.N - 4);
     struct Block {
         f32x4_t av[MS], bv[4];
@@ -315,29 +315,26 @@ __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a
             part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
     __syncthreads();
     const int row = tid / 16, n = n0 + (tid & 15) * 4;
-    if (row >= rows || row >= MS * 16 || n >= a.N) return;
+    if (m0 + row >= rows || row >= MS * 16 || n >= a.N) return;
     f32x4_t v = part[0][row][tid & 15];
 #pragma unroll
     for (int s = 1; s < kFWaves; ++s) v += part[s][row][tid & 15];
-    f32_finish<EPI>(a, g, row, n, v);
+    f32_finish<EPI>(a, g, m0 + row, n, v);
 }
 
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
-    long long blocks;
-    if (a.max_rows <= 32) {
-        const int n_tiles = (a.N + 63) / 64;
-        blocks = (long long)a.G * n_tiles;
-        if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;
-        if (a.max_rows <= 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), dim3((unsigned)blocks), dim3(kFWaves * 64), 0, s, a, n_tiles);
-        else hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), dim3((unsigned)blocks), dim3(kFWaves * 64), 0, s, a, n_tiles);
-    } else {
-        const bool narrow = a.N <= 64;                       // one 64-column tile: all four waves along the rows
-        const int n_tiles = narrow ? 1 : (a.N + 127) / 128, tm = narrow ? 128 : 64, m_tiles = (a.max_rows + tm - 1) / tm;
-        blocks = (long long)a.G * n_tiles * m_tiles;
-        if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;
-        if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), dim3((unsigned)blocks), dim3(512), 0, s, a, n_tiles, m_tiles);
-        else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), dim3((unsigned)blocks), dim3(512), 0, s, a, n_tiles, m_tiles);
-    }
+    // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
+    const bool few = a.max_rows <= 32, narrow = a.N <= 64;   // one 64-column tile: all four pairs along the rows
+    const int tm = few ? (a.max_rows <= 16 ? 16 : 32) : narrow ? 128 : 64, tn = few || narrow ? 64 : 128;
+    const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
+    const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;
+    if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)tiles, (unsigned)a.G), block(512);
+    static_assert(kFWaves * 64 == 512, "all kernels have the same work-group");
+    if (few && tm == 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles);
+    else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
+    else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
+    else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 

@@ -52,10 +52,12 @@ __device__ __forceinline__ float gelu_tanh(float z) {
 template <typename F>
 __device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int top_k, int T, int tid, int nthreads, F zero) {
     const int lane = tid % kWave;
-    for (int c = blockIdx.x + gridDim.x * __builtin_amdgcn_readfirstlane(tid / kWave); c < (T + 15) / 16; c += gridDim.x * (nthreads / kWave)) {
-        const int t = c * 16 + lane;
-        const bool dropped = lane < 16 && t < T && slot_idx[(size_t)t * top_k] < 0;
-        for (unsigned long long m = __ballot(dropped); m; m &= m - 1) zero(c * 16 + __ffsll((long long)m) - 1, lane);
+    const long long blocks = (long long)gridDim.x * gridDim.y, block = (long long)blockIdx.y * gridDim.x + blockIdx.x;
+    const int pieces = (int)(((long long)T + 15) / 16);
+    for (long long c = block + blocks * __builtin_amdgcn_readfirstlane(tid / kWave); c < pieces; c += blocks * (nthreads / kWave)) {
+        const int t0 = (int)c * 16;
+        const bool dropped = lane < 16 && t0 + lane < T && slot_idx[(size_t)(t0 + lane) * top_k] < 0;
+        for (unsigned long long m = __ballot(dropped); m; m &= m - 1) zero(t0 + __ffsll((long long)m) - 1, lane);
     }
 }
 
