@@ -21,7 +21,8 @@
 //     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 80 + 71 us
 //     (85 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
 //     vector ALUs, before: 162 + 465.
-//   * f32_rows_kernel, groups of at most 32 rows: a read of the weights, bound by latency when they are few.  A
+//   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products of 2^24 columns or more, whose 32-row
+//     chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency when they are few.  A
 //     work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from memory into
 //     registers, three blocks ahead, and add up through LDS in wave order.
 //     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before.
@@ -324,7 +325,7 @@ __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a
 
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
-    const bool few = a.max_rows <= 32, narrow = a.N <= 64;   // one 64-column tile: all four pairs along the rows
+    const bool few = a.max_rows <= 32 || a.N >= 1 << 24, narrow = a.N <= 64;   // one 64-column tile: all four pairs along the rows
     const int tm = few ? (a.max_rows <= 16 ? 16 : 32) : narrow ? 128 : 64, tn = few || narrow ? 64 : 128;
     const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
     const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;
