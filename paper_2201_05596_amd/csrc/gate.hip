@@ -231,33 +231,53 @@ int launch_gate_logits(const void* x, int dtype, const float* Wg, const float* b
 // ------------------------------------------------------------------------------------------
 // Routing, kernel 1 of 2, a block per TB tokens: top-k and gate weights, the rank of each token among the tile's
 // tokens that chose the same expert (parked in slot_idx until kernel 2 adds the tile's base), the tile's histogram
-// hist[tile][choice][E].  Latency-bound, so tiles are small and many: blocks of 256 tokens (16 dependent rounds of top-k
-// each) took 38.7 us for 777 tokens, 128 experts, top-2.
+// hist[tile][choice][E].  Latency-bound with few tokens, so tiles are small and many: blocks of 256 threads for 256 tokens
+// (16 dependent rounds of top-k each) took 38.7 us for 777 tokens, 128 experts, top-2.  But every block of kernel 2 reads
+// the histograms of all tiles, which grows with the square of T: from 32768 tokens on a tile has 256 tokens and 1024 threads.
+// Both kernels, us, small tiles / tiles of 256: 64 experts, top-2, 32768 tokens 18.3 / 13.2, 131072 79 / 30; 128 experts,
+// top-2, 8192 14.2 / 16.8, 16384 18.5 / 15.7, 262144 524 / 118; 512 experts 16384 61 / 71, 32768 78 / 77, 262144 755 / 387.
 // ------------------------------------------------------------------------------------------
-constexpr int route_tile_tokens(int NV) { return NV > 0 ? 32 : 64; }    // E > 128: kernel 2 keeps k E 256 / TB sums in LDS
-template <int K, int NV>
-__global__ __launch_bounds__(256) void route_tile_kernel(const float* __restrict__ logits, int T, int E,
-                                                         int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
-                                                         float* __restrict__ gate_w, int32_t* __restrict__ hist) {
-    constexpr int TB = route_tile_tokens(NV);
-    static_assert(TB <= kWave && kRouteTokens % TB == 0, "one wave ranks a tile");
+constexpr int kSmallRouteTiles = 32768;        // tokens below which tiles are small
+template <int K, int NV, int TB>
+__global__ __launch_bounds__(TB == kRouteTokens ? 1024 : 256) void route_tile_kernel(const float* __restrict__ logits, int T, int E,
+                                                                                     int32_t* __restrict__ expert_idx,
+                                                                                     int32_t* __restrict__ slot_idx,
+                                                                                     float* __restrict__ gate_w,
+                                                                                     int32_t* __restrict__ hist) {
+    constexpr int NT = TB == kRouteTokens ? 1024 : 256, NW = (TB + kWave - 1) / kWave;    // waves that rank 64 tokens each
+    static_assert(kRouteTokens % TB == 0, "whole tiles in a block of kernel 2");
     extern __shared__ int32_t smem[];
     int32_t* e_sh = smem;                          // [K][TB]
-    int32_t* h_sh = smem + K * TB;        // [K][E]
-    const int tid = threadIdx.x, t0 = blockIdx.x * TB;
-    for (int i = tid; i < K * E; i += 256) h_sh[i] = 0;
-    choose_experts<K, NV, 256, TB>(e_sh, logits, t0, min(TB, T - t0), T, E, expert_idx, gate_w);
+    int32_t* h_sh = smem + K * TB;                 // [NW][K][E]
+    const int tid = threadIdx.x, t0 = blockIdx.x * TB, w = tid / kWave;
+    for (int i = tid; i < NW * K * E; i += NT) h_sh[i] = 0;
+    choose_experts<K, NV, NT, TB>(e_sh, logits, t0, min(TB, T - t0), T, E, expert_idx, gate_w);
     __syncthreads();
-    if (tid < kWave) {
+    int my_e[K], rank[K];
+    if (tid < NW * kWave) {
 #pragma unroll
         for (int j = 0; j < K; ++j) {
-            const int e = tid < TB ? e_sh[j * TB + tid] : -1;
-            const int rank = wave_rank_by_expert(e, tid, E, h_sh + j * E);
-            if (e >= 0) slot_idx[(size_t)(t0 + tid) * K + j] = rank;
+            my_e[j] = tid < TB ? e_sh[j * TB + tid] : -1;
+            rank[j] = wave_rank_by_expert(my_e[j], tid % kWave, E, h_sh + (w * K + j) * E);
         }
     }
     __syncthreads();
-    for (int i = tid; i < K * E; i += 256) hist[(size_t)blockIdx.x * K * E + i] = h_sh[i];
+    for (int i = tid; i < K * E; i += NT) {        // the tile's histogram, and the tokens of the waves before each
+        int run = 0;
+#pragma unroll
+        for (int ww = 0; ww < NW; ++ww) {
+            const int c = h_sh[ww * K * E + i];
+            h_sh[ww * K * E + i] = run;
+            run += c;
+        }
+        hist[(size_t)blockIdx.x * K * E + i] = run;
+    }
+    __syncthreads();
+    if (tid < TB) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (my_e[j] >= 0) slot_idx[(size_t)(t0 + tid) * K + j] = rank[j] + h_sh[(w * K + j) * E + my_e[j]];
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -281,11 +301,11 @@ int launch_expert_order(const int32_t* expert_rows, int E, int C, int32_t* order
 }
 
 constexpr int kMaxFine = 8;      // fine blocks per 256 tokens at most (32-token tiles)
-constexpr int kFinThreads = 1024;   // four times the tokens of a block: the sums over all tiles are most of its work
+constexpr int kFinThreads = 1024;   // at most; four times the tokens of a block: the sums over all tiles are most of its work
 
 // row groups that share a column's sum: all threads, but few enough that adding up their results stays short
-__host__ __device__ inline int finalize_row_groups(int ncol) {
-    const int r = ncol >= kFinThreads ? 1 : kFinThreads / ncol;
+__host__ __device__ inline int finalize_row_groups(int ncol, int nthreads) {
+    const int r = ncol >= nthreads ? 1 : nthreads / ncol;
     return r < 16 ? r : 16;
 }
 
@@ -307,12 +327,12 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
 
     // the tiles' histograms are summed with all threads: R row groups each take every R-th tile,
     // partial sums meet in LDS
-    const int R = finalize_row_groups(ncol);
-    for (int idx = tid; idx < R * ncol; idx += kFinThreads) {
+    const int nt = blockDim.x, nfine = (T + TB - 1) / TB, R = finalize_row_groups(ncol, nt);
+    for (int idx = tid; idx < R * ncol; idx += nt) {
         const int col = idx % ncol, rg = idx / ncol;
         int pre = 0, tot = 0;
         // every TB-token block's histogram once; those of 256-token blocks before this one also count as "before me"
-        const int nfine = (T + TB - 1) / TB, first_own = b * q;
+        const int first_own = b * q;
 #pragma unroll 16
         for (int fb = rg; fb < nfine; fb += R) {
             const int v = hist[(size_t)fb * ncol + col];
@@ -323,7 +343,7 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
         part[(R + rg) * ncol + col] = tot;
     }
     __syncthreads();
-    for (int e = tid; e < E; e += kFinThreads) {
+    for (int e = tid; e < E; e += nt) {
         int pre[K], tot[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -382,14 +402,14 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
     const long long chunk = (total_slots + nblocks - 1) / nblocks;
     const long long lo = (long long)b * chunk;
     const long long hi = min(lo + chunk, total_slots);
-    for (uint32_t i = (uint32_t)lo + tid; i < hi; i += kFinThreads)        // E * C < 2^31
+    for (uint32_t i = (uint32_t)lo + tid; i < hi; i += nt)        // E * C < 2^31
         if ((int)(i % (uint32_t)C) >= rows_sh[i / (uint32_t)C]) slot_token[i] = -1;
     // The rows per expert and the launch order are the work of one block: with an order to write, of an extra block
     // behind the last one (no tokens, no slots: everything above ran empty for it), so that the ranking does not
     // lengthen a block that also has tokens to place.
     if (b == (expert_order ? nblocks : 0)) {
-        for (int e = tid; e < E; e += kFinThreads) expert_rows[e] = rows_sh[e];
-        if (expert_order) write_expert_order(rows_sh, E, expert_order, part, tid, kFinThreads);   // part: free by now
+        for (int e = tid; e < E; e += nt) expert_rows[e] = rows_sh[e];
+        if (expert_order) write_expert_order(rows_sh, E, expert_order, part, tid, nt);   // part: free by now
     }
 }
 
@@ -419,9 +439,9 @@ __global__ __launch_bounds__(kSingleThreads) void route_single_kernel(const floa
     route_single_body<K, NV>(smem, logits, T, E, C, expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order);
 }
 
-size_t route_finalize_lds_bytes(int E, int k, int TB) {
+size_t route_finalize_lds_bytes(int E, int k, int TB, int nthreads) {
     const int ncol = k * E;
-    const int R = finalize_row_groups(ncol);
+    const int R = finalize_row_groups(ncol, nthreads);
     size_t ints = (size_t)(kRouteTokens / TB) * ncol + E + 2 * (size_t)R * ncol;
     if (ints < (size_t)(kRouteTokens / TB) * ncol + 2 * (size_t)E + 2) ints = (size_t)(kRouteTokens / TB) * ncol + 2 * (size_t)E + 2;
     return ints * sizeof(int32_t);
@@ -431,13 +451,17 @@ int launch_route_finalize(int T, int E, int k, int C, int TB, const int32_t* exp
                           int32_t* expert_rows, int32_t* slot_token, int32_t* expert_order, const int32_t* hist,
                           hipStream_t s) {
     const int nb = (T + kRouteTokens - 1) / kRouteTokens;
-    const size_t sm = route_finalize_lds_bytes(E, k, TB);
+    // Many tokens and few columns: little to add up per block, and small blocks are more of them on the chip at once (top-1, both
+    // kernels, 1024 / 256 threads: 8 experts, 524288 tokens 56 / 34 us; 64 experts, 98304 20.4 / 16.2, 524288 107 / 90; top-2 of
+    // 128 experts, 65536 21.7 / 24.6).
+    const int nt = T >= kSmallRouteTiles && k * E <= 64 ? 256 : kFinThreads;
+    const size_t sm = route_finalize_lds_bytes(E, k, TB, nt);
     const int grid = nb + (expert_order ? 1 : 0);               // + the block that ranks the experts
     if (k == 1)
-        hipLaunchKernelGGL((route_finalize_kernel<1>), dim3(grid), dim3(kFinThreads), sm, s, T, E, C, nb, TB, expert_idx,
+        hipLaunchKernelGGL((route_finalize_kernel<1>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, TB, expert_idx,
                            slot_idx, expert_rows, slot_token, expert_order, hist);
     else
-        hipLaunchKernelGGL((route_finalize_kernel<2>), dim3(grid), dim3(kFinThreads), sm, s, T, E, C, nb, TB, expert_idx,
+        hipLaunchKernelGGL((route_finalize_kernel<2>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, TB, expert_idx,
                            slot_idx, expert_rows, slot_token, expert_order, hist);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
@@ -472,12 +496,18 @@ int launch_route(const float* logits, int T, int E, int k, int C, int32_t* exper
 #undef MOE_ROUTE_SINGLE
         return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
     }
-    const int TB = route_tile_tokens(E <= 128 ? 1 : 0);
-    const size_t sm = sizeof(int32_t) * ((size_t)k * TB + (size_t)k * E);
+    const int TB = T >= kSmallRouteTiles ? kRouteTokens : E <= 128 ? 32 : 64;   // E > 128: kernel 2 keeps k E 256 / TB sums in LDS
+    const size_t sm = sizeof(int32_t) * ((size_t)k * TB + (size_t)((TB + kWave - 1) / kWave) * k * E);
     const unsigned tiles = (unsigned)((T + TB - 1) / TB);
-#define MOE_ROUTE_TILE(K, NV)                                                                                    \
-    hipLaunchKernelGGL((route_tile_kernel<K, NV>), dim3(tiles), dim3(256), sm, s, logits, T, E, expert_idx, slot_idx, \
-                       gate_w, scratch)
+#define MOE_ROUTE_TILE(K, NV)                                                                                             \
+    do {                                                                                                                  \
+        if (TB == kRouteTokens)                                                                                           \
+            hipLaunchKernelGGL((route_tile_kernel<K, NV, kRouteTokens>), dim3(tiles), dim3(1024), sm, s, logits, T, E,    \
+                               expert_idx, slot_idx, gate_w, scratch);                                                    \
+        else                                                                                                              \
+            hipLaunchKernelGGL((route_tile_kernel<K, NV, (NV > 0 ? 32 : 64)>), dim3(tiles), dim3(256), sm, s, logits, T,  \
+                               E, expert_idx, slot_idx, gate_w, scratch);                                                 \
+    } while (0)
     if (k == 1) {
         if (E <= 16) MOE_ROUTE_TILE(1, 1);
         else if (E <= 32) MOE_ROUTE_TILE(1, 2);
