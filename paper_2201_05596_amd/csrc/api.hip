@@ -87,6 +87,7 @@ struct FfnPlan {
     int NBUF;           // weight super-fragments kept in flight per wave, plus one
     int nf1, nf2;       // 16-column fragments per work-group of the few-weights kernel, 0: not that kernel
     int slots;          // launch-order entries that may have rows, 0: all
+    int expect;         // rows per expert if the tokens fall evenly on them
 };
 
 FfnPlan plan_ffn(const moe_shape_t* s) {
@@ -104,6 +105,7 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     const long long m_tiles = (s->capacity + p.MT - 1) / p.MT;
     const long long waves = touched * ((s->d_model + 127) / 128) * m_tiles;
     const long long kept = (long long)s->T * s->top_k;
+    p.expect = (int)((kept + s->E - 1) / s->E < s->capacity ? (kept + s->E - 1) / s->E : s->capacity);
     const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
     if (!p.tiled) {
         p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed);
@@ -292,7 +294,7 @@ WsGemmArgs expert_gemm1_args(const moe_shape_t* s, const FfnPlan& p, const void*
     WsGemmArgs a{};
     a.A = u16(xin); a.B = u16(W1); a.bias = u16(b1); a.rows = rows; a.order = order; a.row_map = row_map;
     a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS; a.slots = p.slots;
-    a.max_rows = s->capacity; a.map_stride = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
+    a.max_rows = s->capacity; a.expect_rows = p.expect; a.map_stride = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
     a.a_group_stride = s->capacity; a.out = u16(h); a.o_group_stride = s->capacity; a.ksplit = 1;
     return a;
 }
@@ -329,7 +331,7 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     // the list that alternates busy and light experts.
     a.order = order && p.tiled ? order + s->E + 1 : order;
     a.packed = s->flags & MOE_FLAG_PACKED_WEIGHTS; a.slots = p.slots;
-    a.max_rows = s->capacity; a.G = s->E; a.K = s->d_ffn; a.N = s->d_model;
+    a.max_rows = s->capacity; a.expect_rows = p.expect; a.G = s->E; a.K = s->d_ffn; a.N = s->d_model;
     a.a_group_stride = s->capacity; a.out = u16(dst); a.o_group_stride = s->capacity; a.ksplit = p.ksplit2;
     a.scatter_map = slot_token; a.scatter_stride = s->capacity; a.zero_slot_idx = slot_idx; a.T = s->T;
     a.gate_w = gate_w; a.top_k = s->top_k;
@@ -358,6 +360,15 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     return rc;
 }
 
+// does the dense branch of so many tokens go to the tiled kernel (where the few-weights one does not take it)?
+bool dense_tiled(const moe_shape_t* s) {
+    return s->T > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
+}
+// does the dense branch's first product share the launch of the experts' in the few-weights kernel?
+bool dense1_shared(const moe_shape_t* s, const FfnPlan& p) {
+    return s->residual && p.nf1 && s->T <= 16 && rows_pick_dense(s->T, s->d_ffn, s->flags & MOE_FLAG_PACKED_WEIGHTS);
+}
+
 // Dense branch of Residual-MoE on the MFMA kernels, with the combine fused into its second GEMM:
 // out[t, :] = gelu_tanh(x[t] Wd1 + bd1) Wd2 + bd2 + sum_j keep_j g_j ye[e_j, slot_j, :].
 // first_done: hd is there already (the first product shared a launch with the experts').
@@ -366,7 +377,7 @@ int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const
                      const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
     int MT, NW, rc = MOE_OK;
     WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
-    const bool tiled = s->T > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
+    const bool tiled = dense_tiled(s);
     if (!first_done) {
         const int nf = rows_pick_dense(s->T, s->d_ffn, a.packed);
         wsgemm_pick_tile(s->T, 1, s->d_ffn, &MT, &NW);
@@ -390,30 +401,33 @@ int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const
     return rc;
 }
 
-// Residual-MoE with experts and dense branch both on 256-row tiles: the experts' and the dense branch's products of
+// the second product of the FFN half that `a` is the first one of, on its output
+WsGemmArgs second_half(WsGemmArgs a, const void* h, const void* W2, const void* b2, void* out) {
+    a.A = u16(h); a.B = u16(W2); a.bias = u16(b2); a.row_map = nullptr; a.out = u16(out);
+    const int K = a.K;
+    a.K = a.N; a.N = K;
+    return a;
+}
+// Do the experts' and the dense branch's second products share a launch?  Shapes with an inner dimension off the 32-deep
+// stages keep the combine inside the dense branch's product, which adds the experts' rows to unrounded sums.
+bool residual_pairs(const moe_shape_t* s, const FfnPlan& p) {
+    if (!p.tiled || s->T <= 128 || s->d_model % 32 || s->d_ffn % 32) return false;
+    return tgemm_pair_fusable(second_half(expert_gemm1_args(s, p, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr), nullptr, nullptr, nullptr, nullptr),
+                              second_half(dense_gemm1_args(s, nullptr, nullptr, nullptr, nullptr), nullptr, nullptr, nullptr, nullptr));
+}
+
+// Residual-MoE with experts and dense branch both on the tiled kernel: the experts' and the dense branch's products of
 // each FFN half share one launch (same inner and outer sizes), so that the second half, with only d_model columns,
-// has twice the tiles and can use the large tile; the combine then is a kernel of its own on the two outputs.
+// has more tiles and can use a larger one; the combine then is a kernel of its own on the two outputs.
 // Returns MOE_ERR_UNSUPPORTED (nothing launched) when the pair does not fit that pattern.
 int run_residual_paired(const moe_shape_t* s, const FfnPlan& p, const void* x, const int32_t* slot_token,
                         const int32_t* rows, const int32_t* order, const void* W1, const void* b1, const void* W2,
                         const void* b2, const void* Wd1, const void* bd1, const void* Wd2, const void* bd2, void* h,
                         void* hd, void* ye, void* dense_out, const int32_t* expert_idx, const int32_t* slot_idx,
                         const float* gate_w, void* out, hipStream_t st) {
-    if (!p.tiled || s->T <= 128) return MOE_ERR_UNSUPPORTED;
-    // Shapes with an inner dimension off the 32-deep stages keep the combine inside the dense branch's product, which adds
-    // the experts' rows to unrounded sums.
-    if (s->d_model % 32 || s->d_ffn % 32) return MOE_ERR_UNSUPPORTED;
-    const int packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
-    WsGemmArgs e1{}, d1{}, e2{}, d2{};
-    e1.A = u16(x); e1.B = u16(W1); e1.bias = u16(b1); e1.rows = rows; e1.order = order; e1.row_map = slot_token;
-    e1.packed = packed; e1.max_rows = s->capacity; e1.map_stride = s->capacity; e1.G = s->E; e1.K = s->d_model;
-    e1.N = s->d_ffn; e1.a_group_stride = s->capacity; e1.out = u16(h); e1.o_group_stride = s->capacity; e1.ksplit = 1;
-    d1.A = u16(x); d1.B = u16(Wd1); d1.bias = u16(bd1); d1.fixed_rows = s->T; d1.max_rows = s->T; d1.G = 1;
-    d1.packed = packed; d1.K = s->d_model; d1.N = s->d_ffn; d1.out = u16(hd); d1.ksplit = 1;
-    e2 = e1; e2.A = u16(h); e2.B = u16(W2); e2.bias = u16(b2); e2.row_map = nullptr; e2.K = s->d_ffn; e2.N = s->d_model;
-    e2.out = u16(ye);
-    d2 = d1; d2.A = u16(hd); d2.B = u16(Wd2); d2.bias = u16(bd2); d2.K = s->d_ffn; d2.N = s->d_model; d2.out = u16(dense_out);
-    if (!tgemm_pair_fusable(e2, d2)) return MOE_ERR_UNSUPPORTED;
+    if (!residual_pairs(s, p)) return MOE_ERR_UNSUPPORTED;
+    const WsGemmArgs e1 = expert_gemm1_args(s, p, x, slot_token, rows, order, W1, b1, h), d1 = dense_gemm1_args(s, x, Wd1, bd1, hd);
+    const WsGemmArgs e2 = second_half(e1, h, W2, b2, ye), d2 = second_half(d1, hd, Wd2, bd2, dense_out);
     int rc;
     if (tgemm_pair_fusable(e1, d1)) {
         prof_pre(ST_GEMM1, st);
@@ -600,7 +614,7 @@ int moe_expert_ffn_slice(const moe_shape_t* shape, const void* xe, const int32_t
     WsGemmArgs a{};
     a.A = at<uint16_t>(ws, L.h); a.B = u16(W2s); a.rows = expert_rows; a.order = order;
     a.packed = shape->flags & MOE_FLAG_PACKED_WEIGHTS;
-    a.max_rows = shape->capacity; a.G = shape->E; a.K = shape->d_ffn; a.N = shape->d_model;
+    a.max_rows = shape->capacity; a.expect_rows = plan.expect; a.G = shape->E; a.K = shape->d_ffn; a.N = shape->d_model;
     a.a_group_stride = shape->capacity; a.o_group_stride = shape->capacity; a.ksplit = 1;
     a.partial = ye_partial; a.partial_rows = (long long)shape->E * shape->capacity;
     return plan.tiled ? launch_tgemm(a, EPI_PARTIAL, st) : launch_wsgemm(a, EPI_PARTIAL, plan.MT, plan.NW2, plan.NBUF, st);
@@ -692,7 +706,7 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
     }
     // bf16: dispatch is fused into GEMM-1 (rows gathered through slot_token) ...
     bool dense1_done = false;
-    if (shape->residual && plan.nf1 && T <= 16 && rows_pick_dense(T, f, shape->flags & MOE_FLAG_PACKED_WEIGHTS)) {
+    if (dense1_shared(shape, plan)) {
         // ... which takes the dense branch's first product along when both read little but weights
         const WsGemmArgs d1 = dense_gemm1_args(shape, x, Wd1, bd1, at<void>(ws, L.hd));
         prof_pre(ST_GEMM1, st);
@@ -730,6 +744,43 @@ int moe_layer_forward(const moe_shape_t* shape, const void* x, const float* Wg, 
                                          ws_bytes, stream);
     g_prof.cur = -1;       // stage events belong to this call only: a later moe_expert_ffn must not add to them
     return rc;
+}
+
+// Which kernel each product of a bf16 moe_layer_forward call takes, from the shape alone; for the tests of the dispatch, not
+// part of the interface (moe.h does not declare it).  kernels: expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2, each
+// 0 = none, 1..4 = few-weights kernel with that many 16-column fragments, 100 S + rows = streaming kernel with tiles of that
+// many rows and K split S ways, 1000 rows + columns = tiled kernel (+ 1: two work-groups per compute unit).
+// shared: do the experts' and the dense product of the first / second half run in one launch?
+int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2]) {
+    const int rc = check_shape(shape);
+    if (rc != MOE_OK) return rc;
+    const FfnPlan p = plan_ffn(shape);
+    if (!p.mfma) return MOE_ERR_UNSUPPORTED;
+    for (int i = 0; i < 4; ++i) kernels[i] = 0;
+    shared[0] = shared[1] = 0;
+    const WsGemmArgs e1 = expert_gemm1_args(shape, p, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+    const WsGemmArgs d1 = dense_gemm1_args(shape, nullptr, nullptr, nullptr, nullptr);
+    const WsGemmArgs e2 = second_half(e1, nullptr, nullptr, nullptr, nullptr), d2 = second_half(d1, nullptr, nullptr, nullptr, nullptr);
+    if (shape->residual && residual_pairs(shape, p)) {
+        shared[0] = tgemm_pair_fusable(e1, d1);
+        shared[1] = 1;
+        kernels[0] = tgemm_shape(e1, shared[0] ? &d1 : nullptr);
+        kernels[2] = shared[0] ? kernels[0] : tgemm_shape(d1, nullptr);
+        kernels[1] = kernels[3] = tgemm_shape(e2, &d2);
+        return MOE_OK;
+    }
+    kernels[0] = p.nf1 ? p.nf1 : p.tiled ? tgemm_shape(e1, nullptr) : 100 + p.MT;
+    kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_shape(e2, nullptr) : 100 * p.ksplit2 + p.MT;
+    if (!shape->residual) return MOE_OK;
+    shared[0] = dense1_shared(shape, p);
+    for (int i = 0; i < 2; ++i) {
+        const WsGemmArgs& a = i ? d2 : d1;
+        const int nf = rows_pick_dense(shape->T, a.N, a.packed);
+        int MT, NW;
+        wsgemm_pick_tile(shape->T, 1, a.N, &MT, &NW);
+        kernels[2 + i] = i == 0 && shared[0] ? p.nf1 : nf ? nf : dense_tiled(shape) ? tgemm_shape(a, nullptr) : 100 + MT;
+    }
+    return MOE_OK;
 }
 
 // ---- one decode step of a whole decoder block ---------------------------------------------------------------------

@@ -397,6 +397,7 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 //   128 x 256   4 x 2 waves of 32 x 128, 5 or 6 stages, one work-group per CU
 //   128 x 256   2 x 2 waves of 64 x 128, 3 stages, two work-groups per CU: one's epilogue and barriers under the other's
 //               matrix work, which short K needs (TILE_128x256_PAIRED)
+//   256 x 128   4 x 2 waves of 64 x 64, 5 stages, one work-group per CU
 //   128 x 128   4 x 2 waves of 32 x 64, 6 stages, one work-group per CU: most work-groups
 // Few tiles leave CUs idle, small tiles cost more per flop, so the time of a launch is the number of rounds times a
 // tile's time.  Relative tile times, from products that ran one round of each on one machine (16 experts x 2 x 128 rows x
@@ -406,11 +407,24 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 // Against the largest tile that gives every CU one: 1500 tokens, 16 experts, 1024 / 4096 122 -> 101 us, 2048 / 8192
 // 270 -> 226; 3000 tokens, 32 experts 166 -> 142; paired with 1500 rows of a dense branch 140 -> 117; 4000 tokens, top-1
 // of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 427 through the first product.
-enum TileShape { TILE_256x256, TILE_128x256, TILE_128x256_PAIRED, TILE_128x128 };
+// All this counts tiles by the groups' room for rows, which the routing need not fill.  Where 256 x 256 tiles are too few for
+// the chip and 256 x 128 ones are not, one product takes the latter if its groups are expected to hold so few rows that the
+// second of two 128-row tiles is empty or nearly so (half the 128 x 256 work-groups would have nothing to do, or read every
+// weight for a handful of rows: 8 experts, 4096 / 16384, packed, room for 130 rows, 832 tokens: GEMM-2 302 us on 128 x 256, 227
+// on 256 x 128; 682 tokens and room for 256: 272 / 206; at 200 rows in 200 128 x 256 is the faster one, by 10 %; at 160 the
+// former by 11 % with packed weights, the latter by 5 % with plain ones: 32 experts, 1024 / 4096, layer 170 / 180), or if the
+// choice would be 256 x 256 and the rows expected are one round of 256 x 128 (2 experts, 4096 / 4096, room for 1200 rows,
+// 800 tokens: 94 / 68).
+enum TileShape { TILE_256x256, TILE_128x256, TILE_128x256_PAIRED, TILE_256x128, TILE_128x128 };
 struct TileCount {
     double tiles256 = 0, tiles128 = 0, tiles128x128 = 0;     // tiles of each shape
-    int max_rows = 0, min_rows = 1 << 30;
+    long long row_tiles = 0, full_row_tiles = 0;             // 256-row tiles: with room for rows, with rows expected
+    int max_rows = 0, min_rows = 1 << 30, expect = 0;
     void add(const WsGemmArgs& a) {
+        const int rows = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
+        row_tiles += (long long)a.G * ((a.max_rows + 255) / 256);
+        full_row_tiles += (long long)a.G * ((rows + 255) / 256);
+        if (rows > expect) expect = rows;
         const double n256 = (a.N + 255) / 256, n128 = (a.N + 127) / 128, rows128 = (a.max_rows + 127) / 128;
         const int last = a.max_rows % 256;
         tiles256 += a.G * n256 * (a.max_rows / 256 + (last == 0 ? 0 : last <= 128 ? 0.6 : 1));
@@ -420,20 +434,38 @@ struct TileCount {
         if (a.max_rows < min_rows) min_rows = a.max_rows;
     }
 };
-static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
-    TileCount c;
-    c.add(a);
-    if (b) c.add(*b);
+static TileShape pick_by_rounds(const WsGemmArgs& a, const TileCount& c) {
     auto rounds = [](double tiles) { return tiles <= 256 ? 1 : tiles / 256 == (int)(tiles / 256) ? tiles / 256 : tiles / 256 + 0.5; };
     const double t256 = c.min_rows > 128 ? rounds(c.tiles256) * 0.77 : 1e30, t128 = rounds(c.tiles128) * 0.56;
     const double t128x128 = rounds(c.tiles128x128) * 0.42;
     const bool paired_ok = a.K <= 2048 && c.tiles128 > 256;              // short K, and two tiles for some CU
     if (t128x128 < t256 && t128x128 < t128) return TILE_128x128;
     if (t128 < t256) return paired_ok ? TILE_128x256_PAIRED : TILE_128x256;
-    // rows just past a multiple of 256 pay for a second, mostly empty tile (not with up to 256 rows: there the 128-row
-    // tiles would stream every weight twice for a few rows; 64 experts x 157 rows at most, 125 on average: 279 -> 318)
+    // rows just past a multiple of 256 pay for a second, mostly empty tile (not with up to 256 rows in either product: there
+    // the 128-row tiles would stream every weight twice for a few rows; 64 experts x 157 rows at most, 125 on average: 279 ->
+    // 318; 16 experts with room for 130 rows and 1664 rows of a dense branch, 2048 / 8192: GEMM-1 156 -> 232)
     const double t_paired = (int)((c.tiles128 + 511) / 512) * 0.84;
-    return paired_ok && c.max_rows > 256 && t_paired < t256 ? TILE_128x256_PAIRED : TILE_256x256;
+    return paired_ok && c.min_rows > 256 && t_paired < t256 ? TILE_128x256_PAIRED : TILE_256x256;
+}
+static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
+    TileCount c;
+    c.add(a);
+    if (b) c.add(*b);
+    const TileShape shape = pick_by_rounds(a, c);
+    const long long n256 = (a.N + 255) / 256, n128 = (a.N + 127) / 128;
+    if (!b && a.max_rows > 128 && c.row_tiles * n256 < 256 && c.row_tiles * n128 >= 256 &&
+        (c.expect <= (a.packed ? 160 : 144) || (shape == TILE_256x256 && c.full_row_tiles * n128 <= 256)))
+        return TILE_256x128;
+    return shape;
+}
+int tgemm_shape(const WsGemmArgs& a, const WsGemmArgs* b) {
+    switch (pick_tile(a, b)) {
+        case TILE_256x256: return 256256;
+        case TILE_128x256: return 128256;
+        case TILE_128x256_PAIRED: return 128257;
+        case TILE_256x128: return 256128;
+        default: return 128128;
+    }
 }
 
 // Two products in one launch: twice the tiles, so that a product with few columns can use a large tile.  Not with so few
@@ -459,6 +491,7 @@ static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s)
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);
         case TILE_128x256: return launch_t<32, 4, 5, EPI, 128>(a, b, s);
         case TILE_128x256_PAIRED: return launch_t<64, 2, 3, EPI, 128>(a, b, s);
+        case TILE_256x128: return launch_t<64, 4, 5, EPI, 64>(a, b, s);
         default: return launch_t<32, 4, 6, EPI, 64>(a, b, s);
     }
 }

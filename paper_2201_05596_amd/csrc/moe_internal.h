@@ -173,6 +173,7 @@ struct WsGemmArgs {
     const int32_t* order;      // [G + 1] groups in launch order (busiest first), then the tile-dealing flag; or nullptr -> identity
     const int32_t* row_map;    // [G, map_stride]: A-row of (g, r), or nullptr -> g*a_group_stride + r
     int32_t fixed_rows, max_rows, map_stride;
+    int32_t expect_rows;       // tiled kernel: rows of a group if the tokens fall evenly on them; 0: max_rows
     int32_t G, K, N;
     int32_t slots;             // entries of `order` that may have rows (the others certainly have none); 0: all
     long long a_group_stride;
@@ -210,10 +211,11 @@ int rows_pick_dense(int T, int N, bool packed);
 
 // Tiled variant for groups with many rows (ffn_tile.hip); same arguments, ksplit must be 1.
 int launch_tgemm(const WsGemmArgs& a, int epi, hipStream_t s);
-// two grouped products in one launch (same K, N, packing, epilogue; both with 256-row tiles): twice the tiles
+// two grouped products in one launch (same K, N, packing, epilogue): more tiles, one shape for both
 bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b);
 int launch_tgemm_pair(const WsGemmArgs& a, const WsGemmArgs& b, int epi, hipStream_t s);
 bool tgemm_supported(int K, int N);
+int tgemm_shape(const WsGemmArgs& a, const WsGemmArgs* b);   // the tile shape that these products get, as 1000 rows + columns (+ 1: two per CU)
 
 // Weights in the fragment order of v_mfma_f32_16x16x32_bf16's second operand (pack.hip).  Element (k, n) of group g
 // goes to  ((((g*KB + k/32)*NG + n/128)*8 + n%8)*64 + (k%32/8)*16 + (n%128)/8)*8 + k%8,  KB = ceil(K/32),

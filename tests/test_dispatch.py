@@ -1,0 +1,26 @@
+"""The choice of kernels on the CPU, at shapes where both sides were measured (us beside each case: this choice / the other)."""
+import pytest
+
+from tests.plan_util import plan
+
+T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
+
+
+@pytest.mark.parametrize("T,d,f,E,k,C,residual,which,kernel", [
+    # room for few more than 128 rows, or for many more than there are: 256 x 128 tiles where 256 x 256 ones are too few
+    (832, 4096, 16384, 8, 1, 130, False, 1, T256N),      # 227 / 302 (128 x 256)
+    (682, 4096, 16384, 8, 1, 256, False, 1, T256N),      # 206 / 272
+    (2080, 2048, 8192, 16, 1, 130, False, 1, T256N),     # 121 / 167
+    (4160, 1024, 4096, 32, 1, 130, False, 1, T256N),     # 71 / 92
+    (800, 4096, 4096, 2, 1, 1200, False, 1, T256N),      # 68 / 94 (256 x 256)
+    # rows that fill their tiles: as before
+    (4001, 1024, 4096, 32, 2, 251, False, 1, T128),
+    (8192, 1024, 4096, 32, 1, 256, True, 0, T256),
+    (16384, 4096, 16384, 64, 2, 640, False, 0, T256),
+    (1500, 1024, 4096, 16, 1, 117, False, 1, T128N),
+    # two products in a launch, the experts' with few more than 128 rows: not two small tiles per compute unit
+    (1664, 2048, 8192, 16, 1, 130, True, 0, T256),       # 156 / 232
+    (3328, 1024, 4096, 32, 1, 130, True, 0, T256),       # 95 / 126
+])
+def test_tile_shape(T, d, f, E, k, C, residual, which, kernel):
+    assert plan(T, d, f, E, k, C, residual, packed=True)[0][which] == kernel
