@@ -15,7 +15,7 @@ GEMM1, GEMM2, DENSE1, DENSE2 = range(4)
 CASES = [
     (257, 2056, 64, 1000, 16, 1, False, GEMM1, T256N, False), (257, 2056, 1000, 64, 16, 1, False, GEMM2, T256N, False),
     (257, 1028, 1000, 64, 16, 2, False, GEMM2, T256N, False), (150, 4500, 40, 1000, 32, 1, False, GEMM1, T256N, False),
-    (160, 5000, 1000, 40, 32, 1, False, GEMM2, T256N, False), (130, 2000, 1000, 72, 32, 2, False, GEMM2, T256N, False),
+    (160, 4500, 1000, 40, 32, 1, False, GEMM2, T256N, False), (130, 2000, 1000, 72, 32, 2, False, GEMM2, T256N, False),
 ]
 
 
