@@ -97,6 +97,15 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     p.NBUF = 2;
     if (!p.mfma) return p;
     p.tiled = s->capacity > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
+    // Few experts, an inner dimension off the 32-deep stages and a long second product: on the tiled kernel that one leaves most
+    // of the chip idle, the streaming kernel splits its K (1000 / 4000, plain, 2 experts x 156 rows: layer 92 us tiled, 78
+    // streamed; 2008 / 8032, 1 x 128: 161 / 116; 72 / 2088, 8 x 160: 57 / 47).  The tiled one is the faster with more rows (1 x
+    // 1000 of 1000: 97 / 120), from about 64 tiles of 128 x 128 on (4 x 400: 99 / 137; 64 experts x 65 of 72 / 2088: 60 / 72) and
+    // where the second product is not much the longer one (4 x 128 of 1000 / 1000: 54 / 63).  Whole stages are not asked here:
+    // they always went to the tiled kernel.
+    const bool whole_stages = s->d_model % 32 == 0 && s->d_ffn % 32 == 0;
+    const long long tiles2 = (long long)s->E * ((s->capacity + 127) / 128) * ((s->d_model + 127) / 128);
+    if (!whole_stages && s->capacity <= 512 && s->E <= 32 && tiles2 <= 64 && s->d_ffn >= s->d_model + 2000) p.tiled = false;
     wsgemm_pick_tile(s->capacity, s->E, s->d_ffn, &p.MT, &p.NW1);
     int mt2;
     wsgemm_pick_tile(s->capacity, s->E, s->d_model, &mt2, &p.NW2);
@@ -107,14 +116,13 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     const long long kept = (long long)s->T * s->top_k;
     p.expect = (int)((kept + s->E - 1) / s->E < s->capacity ? (kept + s->E - 1) / s->E : s->capacity);
     const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
-    if (!p.tiled) {
+    if (s->capacity <= 64) {
         p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed);
         p.nf2 = rows_pick_gemm2(touched, s->capacity, kept, s->d_ffn, s->d_model, packed, waves < 1024);
     }
     // The room for partial sums is that of the streaming kernel's split whether or not the call takes it, so that a
     // workspace sized for packed weights serves the same shape with plain ones (the few-weights kernel's rule knows them
     // apart) and no size depends on which kernel is the faster one.
-    const bool whole_stages = s->d_model % 32 == 0 && s->d_ffn % 32 == 0;
     if (waves < 1024 && !(s->capacity > 64 && whole_stages)) {
         const int chunks = (s->d_ffn + wsgemm_chunk_k(p.MT) - 1) / wsgemm_chunk_k(p.MT);
         long long ks = (2048 + waves - 1) / waves;

@@ -24,3 +24,18 @@ T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
 ])
 def test_tile_shape(T, d, f, E, k, C, residual, which, kernel):
     assert plan(T, d, f, E, k, C, residual, packed=True)[0][which] == kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,C,packed,kernel", [
+    # inner dimension off 32, few experts: the streaming kernel with K split for the second product (layer / on tiles)
+    (124, 1000, 4000, 2, 156, False, 864),       # 78 / 92
+    (102, 2008, 8032, 1, 128, False, 864),       # 116 / 161
+    (102, 2008, 8032, 1, 128, True, 864),        # 110 / 148
+    # many rows or many tiles, and whole stages
+    (800, 1000, 4000, 1, 1000, False, T128N),    # 97 / 120 (streaming)
+    (1280, 1000, 4000, 4, 400, False, T128N),    # 99 / 137
+    (409, 1000, 1000, 4, 128, False, T128N),     # 54 / 63
+    (3200, 1000, 4000, 16, 250, True, T128N), (124, 1024, 4096, 2, 156, False, T128N),
+])
+def test_ragged_inner_dimension(T, d, f, E, C, packed, kernel):
+    assert plan(T, d, f, E, 1, C, False, packed)[0][1] == kernel
