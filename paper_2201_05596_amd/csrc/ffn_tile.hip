@@ -408,13 +408,15 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 // 270 -> 226; 3000 tokens, 32 experts 166 -> 142; paired with 1500 rows of a dense branch 140 -> 117; 4000 tokens, top-1
 // of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 427 through the first product.
 // All this counts tiles by the groups' room for rows, which the routing need not fill.  Where 256 x 256 tiles are too few for
-// the chip and 256 x 128 ones are not, one product takes the latter if its groups are expected to hold so few rows that the
-// second of two 128-row tiles is empty or nearly so (half the 128 x 256 work-groups would have nothing to do, or read every
-// weight for a handful of rows: 8 experts, 4096 / 16384, packed, room for 130 rows, 832 tokens: GEMM-2 302 us on 128 x 256, 227
-// on 256 x 128; 682 tokens and room for 256: 272 / 206; at 200 rows in 200 128 x 256 is the faster one, by 10 %; at 160 the
-// former by 11 % with packed weights, the latter by 5 % with plain ones: 32 experts, 1024 / 4096, layer 170 / 180), or if the
-// choice would be 256 x 256 and the rows expected are one round of 256 x 128 (2 experts, 4096 / 4096, room for 1200 rows,
-// 800 tokens: 94 / 68).
+// the chip, 256 x 128 ones are not, and the expected rows are one round of them (16 experts, 520 / 2080, room for 156 rows:
+// in two rounds layer 64 -> 68), one product takes the latter
+//   - if its groups are expected to hold so few rows that the second of two 128-row tiles is empty or nearly so (half the
+//     128 x 256 work-groups would have nothing to do, or read every weight for a handful of rows).  8 experts, 4096 / 16384,
+//     packed, GEMM-2: room for 130 rows, 832 tokens 302 us on 128 x 256, 227 on 256 x 128; room for 256, 682 tokens 272 / 206.  At
+//     200 rows in 200 128 x 256 is the faster one by 10 %; at 160 the former by 11 % with packed weights, the latter by 5 % with
+//     plain ones (32 experts, 1024 / 4096: layer 170 / 180);
+//   - if the choice would be 256 x 256: 2 experts, 4096 / 4096, room for 1200 rows, 800 tokens: 94 / 68.  Small products only with
+//     half a round (8 experts, 256 x 1024, room for 1200 rows: 3200 tokens -20 %, 7680 +20 %; 512 x 2048 -20 %, +6 %).
 enum TileShape { TILE_256x256, TILE_128x256, TILE_128x256_PAIRED, TILE_256x128, TILE_128x128 };
 struct TileCount {
     double tiles256 = 0, tiles128 = 0, tiles128x128 = 0;     // tiles of each shape
@@ -453,8 +455,9 @@ static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
     if (b) c.add(*b);
     const TileShape shape = pick_by_rounds(a, c);
     const long long n256 = (a.N + 255) / 256, n128 = (a.N + 127) / 128;
-    if (!b && a.max_rows > 128 && c.row_tiles * n256 < 256 && c.row_tiles * n128 >= 256 &&
-        (c.expect <= (a.packed ? 160 : 144) || (shape == TILE_256x256 && c.full_row_tiles * n128 <= 256)))
+    if (!b && a.max_rows > 128 && c.row_tiles * n256 < 256 && c.row_tiles * n128 >= 256 && c.full_row_tiles * n128 <= 256 &&
+        (c.expect <= (a.packed ? 160 : 144) ||
+         (shape == TILE_256x256 && (c.full_row_tiles * n128 <= 128 || (a.K >= 1024 && a.N >= 1024)))))
         return TILE_256x128;
     return shape;
 }

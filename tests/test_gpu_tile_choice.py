@@ -18,7 +18,7 @@ CASES = [
     (65, 32, 64, 64, 1, 1, False, GEMM1, T128N, False), (520, 260, 40, 40, 1, 1, False, GEMM1, T128N, False),
     (130, 4290, 64, 200, 66, 1, False, GEMM1, T128, False), (130, 4290, 40, 200, 66, 1, False, GEMM1, T128, False),
     (65, 2145, 64, 1000, 66, 1, False, GEMM1, T128X2, False), (65, 2145, 40, 1000, 66, 1, False, GEMM1, T128X2, False),
-    (257, 257, 64, 8192, 2, 1, False, GEMM1, T256N, False), (130, 2145, 40, 1000, 33, 1, False, GEMM1, T256N, False),
+    (257, 257, 64, 8192, 2, 1, False, GEMM1, T256N, False), (130, 2080, 40, 1000, 32, 1, False, GEMM1, T256N, False),
     (130, 4290, 64, 264, 66, 1, False, GEMM1, T256, False), (130, 4290, 40, 264, 66, 1, False, GEMM1, T256, False),
     # two first products in a launch
     (65, 130, 64, 64, 2, 1, True, GEMM1, T128N, True), (65, 130, 64, 8192, 4, 1, True, GEMM1, T128, True),
@@ -27,14 +27,14 @@ CASES = [
     (65, 32, 64, 64, 1, 1, False, GEMM2, T128N, False), (520, 260, 40, 40, 1, 1, False, GEMM2, T128N, False),
     (130, 4290, 200, 64, 66, 1, False, GEMM2, T128, False), (130, 4290, 200, 40, 66, 1, False, GEMM2, T128, False),
     (65, 520, 4104, 64, 16, 1, False, GEMM2, T128X2, False), (65, 520, 4104, 40, 16, 1, False, GEMM2, T128X2, False),
-    (257, 2056, 1000, 64, 16, 1, False, GEMM2, T256N, False), (130, 2145, 1000, 40, 33, 1, False, GEMM2, T256N, False),
+    (257, 2056, 1000, 64, 16, 1, False, GEMM2, T256N, False), (130, 2080, 1000, 40, 32, 1, False, GEMM2, T256N, False),
     (130, 4290, 264, 64, 66, 1, False, GEMM2, T256, False), (130, 4290, 264, 40, 66, 1, False, GEMM2, T256, False),
     # store epilogue (second product, top-2 or beside a dense branch); K = f whole and ragged
     (65, 32, 64, 64, 1, 1, True, GEMM2, T128N, False), (520, 260, 40, 40, 1, 1, True, GEMM2, T128N, False),
     (130, 4290, 200, 64, 66, 2, False, GEMM2, T128, False), (130, 4290, 200, 40, 66, 2, False, GEMM2, T128, False),
     (65, 520, 4104, 64, 16, 2, False, GEMM2, T128X2, False), (65, 520, 4104, 40, 16, 2, False, GEMM2, T128X2, False),
     (257, 1028, 1000, 64, 16, 2, False, GEMM2, T256N, False), (257, 2056, 1000, 64, 16, 1, True, GEMM2, T256N, False),
-    (130, 1072, 1000, 40, 33, 2, False, GEMM2, T256N, False),
+    (130, 1040, 1000, 40, 32, 2, False, GEMM2, T256N, False),
     (130, 4290, 264, 64, 66, 2, False, GEMM2, T256, False), (130, 4290, 264, 40, 66, 2, False, GEMM2, T256, False),
     # two second products in a launch
     (65, 130, 64, 64, 2, 1, True, GEMM2, T128N, True), (65, 130, 8192, 64, 4, 1, True, GEMM2, T128, True),
@@ -58,7 +58,7 @@ def test_tile_choice(C, T, d, f, E, k, residual, product, kernel, shared):
 
 
 @pytest.mark.parametrize("C,d,f,E,kernel", [(65, 64, 64, 3, T128N), (130, 200, 40, 66, T128), (70, 4104, 64, 16, T128X2), (257, 1000, 64, 16, T256N),
-                                            (144, 1000, 40, 33, T256N), (130, 264, 40, 66, T256)])
+                                            (144, 1000, 40, 32, T256N), (130, 264, 40, 66, T256)])
 def test_slice_on_every_tile(C, d, f, E, kernel):
     """moe_expert_ffn_slice leaves fp32 partial sums: with one slice and the sum of it, the expert FFN's result."""
     print(f"case C={C} d={d} f={f} E={E}", flush=True)
