@@ -117,8 +117,8 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     p.expect = (int)((kept + s->E - 1) / s->E < s->capacity ? (kept + s->E - 1) / s->E : s->capacity);
     const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
     if (s->capacity <= 64) {
-        p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed);
-        p.nf2 = rows_pick_gemm2(touched, s->capacity, kept, s->d_ffn, s->d_model, packed, waves < 1024);
+        p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed, s->residual && s->T <= 16);
+        p.nf2 = rows_pick_gemm2(s->E, touched, s->capacity, kept, s->d_ffn, s->d_model, packed, waves < 1024);
     }
     // The room for partial sums is that of the streaming kernel's split whether or not the call takes it, so that a
     // workspace sized for packed weights serves the same shape with plain ones (the few-weights kernel's rule knows them

@@ -246,29 +246,47 @@ static int rows_columns(long long groups, int max_rows, int N, bool packed) {
 
 // Experts' first product, against the streaming kernel.  That one has a wave per 128 columns: with slots x N up to 48 K
 // columns it leaves compute units idle (1 token, 1024 x 4096: 22.8 -> 5 us in this kernel; 2048 x 8192, 2 tokens 87 -> 39
-// with both products; plain weights 12 tokens of d = 1024: 67.1 / 67.0, 16: 70.8 / 75.8).  Beyond, packed weights with K
-// >= 2048 still gain (64 tokens, 128 experts 544 -> 533; 128 tokens 889 -> 878; 200 tokens, 32 experts 362 -> 369) and
-// K = 1024 loses (64 tokens, 128 experts 166 -> 171: two rounds of loads per wave do not pay for a work-group).
-int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed) {
+// with both products; plain weights 12 tokens of d = 1024: 67.1 / 67.0, 16: 70.8 / 75.8).  Beyond, with packed weights and K >=
+// 2048, what decides is how many experts the tokens reach: the streaming kernel deals whole experts to the eight XCDs, so a
+// number that is no multiple of eight leaves some XCDs idle at the end.  While the tokens are few enough to miss experts
+// (up to two choices per expert) this kernel wins (2048 x 8192: 64 tokens, 32 experts 158 / 150; 64, 64: 204 / 194; 16, 16:
+// 65 / 53; 64 tokens, 128 experts, of which 52 are reached: layer 519 / 506; where they happen to be 48: 242 / 246 for the
+// product); with all of a multiple of eight experts reached, or fewer than eight of them, the streaming one does (128 tokens,
+// 8 experts 44 / 52; 64, 16: 86 / 88).  K = 1024 loses (64 tokens, 128 experts layer 166 -> 171: two rounds of loads per wave
+// do not pay for a work-group).  with_dense: the dense branch's first product comes along in the launch, which pays for it
+// (block of 10 tokens, top-2 of 8 experts, 2048 / 8192: 122 / 138).
+int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool with_dense) {
     if (max_rows > 16) return 0;
-    if (touched * N > 48 * 1024 && (!packed || K < 2048 || kept > 128)) return 0;
+    if (touched * N > 48 * 1024) {
+        if (!packed || K < 2048 || kept > 128) return 0;
+        if (!with_dense && kept > 2 * touched && (touched % 8 == 0 || touched < 8)) return 0;
+    }
     const int nf = rows_columns(touched, max_rows, N, packed);
     return packed ? nf : 4;                                    // plain rows of 64 bytes: 4 tokens, d = 2048, 110 against 91
 }
 
 // Experts' second product, against the streaming kernel with K split over work-groups and a kernel that adds up
-// (few_waves): 64 tokens, 128 experts, d = 1024 166 -> 156, 96 tokens, 64 experts 158 -> 151; 48 tokens, d = 2048
-// 464 -> 445; 256 tokens, 32 experts, top-2 (up to 32 rows each), d = 2048 382 -> 373.  With K < 8192 it is within 1 %
-// either way from 128 rows on (120.2 / 119.0, 122.6 / 121.2, 216 / 218) and, where the streaming kernel needs no split,
-// within 3 %: that one stays there.  With K < 8192 16 columns are the best split (32 experts, 32 rows, d = 1024:
-// 75.2 / 79.3 / 83.9 with 16 / 32 / 64), many short work-groups of which four share a compute unit; longer ones want
-// more (d = 2048: 245 / 242 / 251; 256 rows of 32 experts, top-2: 457 / 395 / 373).
-// Plain weights (rows of 64 bytes, so twice the lines are touched): one or two experts only (93 -> 81, 94 -> 93).
-int rows_pick_gemm2(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves) {
+// (few_waves): 64 tokens, 128 experts, d = 1024 166 -> 156, 96 tokens, 64 experts 158 -> 151; 48 tokens, d = 2048 464 ->
+// 445; 256 tokens, 32 experts, top-2 (up to 32 rows each), d = 2048 382 -> 373.  With K < 8192 it is within 1 % either
+// way from 128 rows on (120.2 / 119.0, 122.6 / 121.2, 216 / 218) and, where the streaming kernel needs no split, within
+// 3 %: that one stays there.  With K < 8192 16 columns are the best split (32 experts, 32 rows, d = 1024: 75.2 / 79.3 /
+// 83.9 with 16 / 32 / 64), many short work-groups of which four share a compute unit; longer ones want more (d = 2048:
+// 245 / 242 / 251; 256 rows of 32 experts, top-2: 457 / 395 / 373; K = 16384, 8 experts, 128 tokens 226 / 205 / 170; 12
+// tokens, layer with 32 / 64 columns 225 / 241).  Every work-group reads the rows of its expert again, so many rows per
+// expert, few columns per work-group and a long K lose to the streaming kernel's one pass: product with K = 8192, N =
+// 2048, 1 expert of 64 rows 45 / 32, 4 of 64 54 / 41, of 32 38 / 36; K = 16384, N = 4096, 2 experts of 24 rows 62 / 54,
+// 1 of 64 82 / 50; K = 4096, N = 1024, 1 of 64 26.5 / 22.5.
+// Plain weights (rows of 64 bytes, so twice the lines are touched): one or two experts only, and with a long K only out of at
+// least eight (fewer are spread over the XCDs by columns: K = 8192, 2 experts of 16 rows 31 / 27, K = 16384, 1 of 16 54 / 40; 2
+// tokens out of 8 experts, 2048 / 8192: layer 44 / 59).
+int rows_pick_gemm2(int E, long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves) {
     if (!few_waves || kept > (K >= 8192 ? 256 : 96)) return 0;
-    if (!packed) return max_rows <= 16 && touched * N <= 4096 ? 2 : 0;
-    const int nf = rows_columns(touched, max_rows, N, packed);
-    return max_rows > 16 ? nf : K < 8192 ? 1 : nf < 2 ? nf : 2;
+    if (!packed) return (K < 8192 || E >= 8) && max_rows <= 16 && touched * N <= 4096 ? 2 : 0;
+    int nf = rows_columns(touched, max_rows, N, packed);
+    if (max_rows <= 16) return K < 8192 ? 1 : nf > 2 && (K < 16384 || kept < 8 * touched) ? 2 : nf;
+    if (K < 8192) return K >= 4096 && kept > 48 * touched ? 0 : nf;
+    if (kept > 16 * touched && (max_rows > 32 || nf == 2)) return 0;
+    return kept > 24 * touched && nf < 4 ? 0 : nf;
 }
 
 // Dense branch, against the streaming kernel (up to 64 tokens: one wave per 128 columns; GEMM-2 of 16 tokens, d = 2048:

@@ -205,8 +205,8 @@ int wsgemm_chunk_k(int MT);   // k-extent of one LDS chunk = granularity of spli
 // b: a second product of the same K, N and packing in the same launch (not with EPI_SCATTER), or nullptr.
 int launch_rows(const WsGemmArgs& a, const WsGemmArgs* b, int epi, int NF, hipStream_t s);
 // NF for a product, or 0 where another kernel does better.  touched: experts that can have rows; kept: rows of all of them
-int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed);
-int rows_pick_gemm2(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves);
+int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool with_dense);
+int rows_pick_gemm2(int E, long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves);
 int rows_pick_dense(int T, int N, bool packed);
 
 // Tiled variant for groups with many rows (ffn_tile.hip); same arguments, ksplit must be 1.

@@ -13,6 +13,7 @@ T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
     (2080, 2048, 8192, 16, 1, 130, False, 1, T256N),     # 121 / 167
     (4160, 1024, 4096, 32, 1, 130, False, 1, T256N),     # 71 / 92
     (800, 4096, 4096, 2, 1, 1200, False, 1, T256N),      # 68 / 94 (256 x 256)
+    (2000, 520, 2080, 16, 1, 156, False, 0, T256),       # 64 / 68 in two rounds of 256 x 128 (layer)
     # rows that fill their tiles: as before
     (4001, 1024, 4096, 32, 2, 251, False, 1, T128),
     (8192, 1024, 4096, 32, 1, 256, True, 0, T256),
@@ -39,3 +40,19 @@ def test_tile_shape(T, d, f, E, k, C, residual, which, kernel):
 ])
 def test_ragged_inner_dimension(T, d, f, E, C, packed, kernel):
     assert plan(T, d, f, E, 1, C, False, packed)[0][1] == kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,C,packed,which,kernel", [
+    # first product beyond 48 K columns: the few-weights kernel while some experts are missed, the streaming one (116) when not
+    (64, 2048, 8192, 128, 1, True, 0, 4), (64, 2048, 8192, 64, 4, True, 0, 4), (64, 2048, 8192, 32, 8, True, 0, 4),
+    (128, 2048, 8192, 8, 16, True, 0, 116), (64, 2048, 8192, 16, 8, True, 0, 116), (96, 2048, 8192, 8, 12, True, 0, 116),
+    (96, 2048, 8192, 12, 16, True, 0, 4),
+    # second product: many rows per expert, few columns per work-group, long K: streaming with K split
+    (64, 2048, 8192, 1, 64, True, 1, 864), (256, 2048, 8192, 4, 64, True, 1, 864), (48, 4096, 16384, 2, 24, True, 1, 832),
+    (64, 1024, 4096, 1, 64, True, 1, 864), (32, 2048, 8192, 2, 16, False, 1, 816),
+    (128, 2048, 8192, 32, 8, True, 1, 2), (16, 2048, 8192, 64, 1, True, 1, 2), (128, 4096, 16384, 8, 16, True, 1, 4),
+    (2, 2048, 8192, 8, 1, False, 1, 2), (64, 128, 512, 1, 64, True, 1, 1), (12, 4096, 16384, 8, 2, True, 1, 2),
+    (32, 1024, 4096, 2, 32, True, 1, 1), (4, 1024, 4096, 1, 4, False, 1, 2),
+])
+def test_few_rows(T, d, f, E, C, packed, which, kernel):
+    assert plan(T, d, f, E, 1, C, False, packed)[0][which] == kernel
