@@ -332,7 +332,9 @@ int launch_attn_decode(const uint16_t* qkv, uint16_t* cache_k, uint16_t* cache_v
     const int nsplit = attn_nsplit(Lmax);
     const dim3 grid((unsigned)(T * H), (unsigned)nsplit);
     // Caches beyond the 256 MB Infinity Cache stream past it (blocks of 64 sequences, d = 2048, 2048 positions: 705 -> 687 us;
-    // 128, d = 1024, 1500: 216 -> 206); smaller ones are read from there at the next step (32, d = 1024, 2000: 132 -> 134).
+    // 128, d = 1024, 1500: 216 -> 206); smaller ones are read from there at the next step (32, d = 1024, 2000: 132 -> 134).  The rule
+    // sees the room for positions only: short sequences in a large cache pay for the hint (up to 256 of 2048 positions, block
+    // without much of a feed-forward part: 108.6 -> 112.5; all 2048: 202 -> 184).
     const bool stream = (long long)T * H * Lmax * dh * 4 > 256ll << 20;
 #define MOE_ATTN(DH, STREAM) \
     hipLaunchKernelGGL((attn_decode_kernel<DH, STREAM>), grid, dim3(256), 0, s, qkv, cache_k, cache_v, pos, partial, H, Lmax, nsplit)

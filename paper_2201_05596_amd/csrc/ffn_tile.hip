@@ -2,8 +2,8 @@
 // the dense branch of Residual-MoE (paper Sec. 4.1.1), where the products are bound by the matrix
 // cores, not by weight traffic.
 //
-// A work-group of NWM x 2 waves owns a (NWM*64) x (2*WN) output tile; a wave owns 64 x WN of it (WN = 128, or 64
-// for products with few columns).  Both operands pass through LDS in 32-deep k-stages, 3 to 6 stages deep, filled by direct
+// A work-group of NWM x 2 waves owns a (NWM*WM) x (2*WN) output tile; a wave owns WM x WN of it (WM = 64 or 32, WN = 128
+// or 64).  Both operands pass through LDS in 32-deep k-stages, 3 to 6 stages deep, filled by direct
 // global->LDS loads (global_load_lds_dwordx4: 16 bytes per lane, a wave writes 1 KB of contiguous
 // LDS per instruction, no staging registers), so all stages but one are always in flight:
 //   * weights: 32 k-rows x 2*WN columns, K-major exactly as in memory (a wave instruction copies
@@ -50,9 +50,9 @@ template <int WM, int NWM, int NS_, int WN> struct TileCfg {
     static constexpr int B_BYTES = kTK * TBN * 2;              // weight bytes per stage (16 or 8 KB)
     static constexpr int A_BYTES = BM * 64;                    // activation bytes per stage
     static constexpr int STAGE = A_BYTES + B_BYTES;
-    // 256-row tiles: 4 stages of 32 KB, one work-group of 8 waves per CU.  128-row tiles: 5 stages of 24 KB and one
-    // work-group of 4 waves per CU, or 3 stages and at most 256 registers per lane, so that two work-groups share a
-    // CU and one multiplies while the other waits at its barrier: much faster for short K (8192 x 1024 x 4096:
+    // 256-row tiles: 4 stages of 32 KB (256 columns) or 5 of 24 KB (128), one work-group of 8 waves per CU.  128-row tiles: 6
+    // stages of 24 KB (16 KB with 128 columns) and one work-group of 8 waves per CU, or of 4 waves with 3 stages and at most
+    // 256 registers per lane, so that two work-groups share a CU and one multiplies while the other waits at its barrier: much faster for short K (8192 x 1024 x 4096:
     // 92 against 141 us), slightly slower for long K, where the deeper ring counts.
     static constexpr int NS = NS_;
     static constexpr int WGS_PER_CU = NS_ * (NWM * WM * 64 + B_BYTES) + NWM * WM * 8 <= 80 * 1024 && NWM == 2 ? 2 : 1;
@@ -352,11 +352,13 @@ __global__ __launch_bounds__(NWM * 128, (TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU))
             }
         }
     }
-    if (!done) {
-        if (nsub > 2) run(std::integral_constant<int, MSUB>(), No(), Yes());
-        else if (nsub == 2) run(std::integral_constant<int, 2>(), No(), Yes());
-        else if (nsub == 1) run(std::integral_constant<int, 1>(), No(), Yes());
-        else run(std::integral_constant<int, 0>(), No(), Yes());
+    if constexpr (!Cfg::HAS_LIGHT || BM > Cfg::L_ROWS) {        // 128-row tiles of 256 columns are always light ones
+        if (!done) {
+            if (nsub > 2) run(std::integral_constant<int, MSUB>(), No(), Yes());
+            else if (nsub == 2) run(std::integral_constant<int, 2>(), No(), Yes());
+            else if (nsub == 1) run(std::integral_constant<int, 1>(), No(), Yes());
+            else run(std::integral_constant<int, 0>(), No(), Yes());
+        }
     }
 }
 
@@ -394,7 +396,7 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 // Tile shapes, for one product or for two in one launch (same K, N and packing: all tiles are counted together):
 //   256 x 256   4 x 2 waves of 64 x 128 (the accumulators take 128 registers, which the compiler updates in place; 128
 //               rows per wave fill the file and cost copies), one work-group per CU: least traffic per flop
-//   128 x 256   4 x 2 waves of 32 x 128, 5 or 6 stages, one work-group per CU
+//   128 x 256   4 x 2 waves of 32 x 128, 6 stages, one work-group per CU
 //   128 x 256   2 x 2 waves of 64 x 128, 3 stages, two work-groups per CU: one's epilogue and barriers under the other's
 //               matrix work, which short K needs (TILE_128x256_PAIRED)
 //   256 x 128   4 x 2 waves of 64 x 64, 5 stages, one work-group per CU
@@ -492,7 +494,7 @@ static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s)
     if (b && !pair_fits(a, *b)) return MOE_ERR_INVALID_ARG;
     switch (pick_tile(a, b)) {
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);
-        case TILE_128x256: return launch_t<32, 4, 5, EPI, 128>(a, b, s);
+        case TILE_128x256: return launch_t<32, 4, 6, EPI, 128>(a, b, s);
         case TILE_128x256_PAIRED: return launch_t<64, 2, 3, EPI, 128>(a, b, s);
         case TILE_256x128: return launch_t<64, 4, 5, EPI, 64>(a, b, s);
         default: return launch_t<32, 4, 6, EPI, 64>(a, b, s);

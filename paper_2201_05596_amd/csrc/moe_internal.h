@@ -61,16 +61,6 @@ __device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int 
     }
 }
 
-template <typename T> struct Elem;
-template <> struct Elem<float> {
-    static __device__ __forceinline__ float load(const float* p) { return *p; }
-    static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
-};
-template <> struct Elem<uint16_t> {
-    static __device__ __forceinline__ float load(const uint16_t* p) { return bf16_to_f32(*p); }
-    static __device__ __forceinline__ void store(uint16_t* p, float v) { *p = f32_to_bf16(v); }
-};
-
 // ---- launchers (each returns MOE_OK or MOE_ERR_HIP) ---------------------------------------
 
 // logits[t,e] = bg[e] + sum_i x[t,i] Wg[i,e]

@@ -1,5 +1,6 @@
-"""Every tile shape of the tiled kernel (256 x 256, 128 x 256 one and two per compute unit, 128 x 128), one product and two
-in a launch, at the edges of its tiles, through moe_layer_forward against the oracle, plain and packed weights."""
+"""The tiled kernel at the edges of its tiles (rows, columns, an inner dimension that ends inside a stage), one product and two
+in a launch, through moe_layer_forward against the oracle, plain and packed weights.  Which tile shape a case gets is the
+dispatch's business here; test_gpu_tile_choice.py takes every shape with every epilogue."""
 import pytest
 
 from tests import gpu_util as U
@@ -11,7 +12,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (65, 150, 128, 256, 3, 1, False), (127, 300, 96, 136, 2, 2, False), (128, 300, 160, 264, 4, 1, True), (129, 400, 128, 1032, 3, 1, False),
     (257, 1100, 64, 520, 4, 1, False), (383, 1500, 96, 128, 3, 2, False), (120, 2300, 1024, 64, 16, 1, True),
-    (200, 3000, 128, 4096, 16, 1, False),          # 128 x 256 tiles, more than 256 of them, short K: two per compute unit
+    (200, 3000, 128, 4096, 16, 1, False),          # 256 x 256 tiles, one round, and 128 x 128 ones
     (313, 4000, 64, 8200, 12, 1, False), (320, 2600, 128, 8192, 6, 1, True), (256, 1300, 64, 4104, 4, 1, True),
 ]
 
