@@ -250,7 +250,7 @@ static int rows_columns(long long groups, int max_rows, int N, bool packed) {
 // 2048, what decides is how many experts the tokens reach: the streaming kernel deals whole experts to the eight XCDs, so a
 // number that is no multiple of eight leaves some XCDs idle at the end.  While the tokens are few enough to miss experts
 // (up to two choices per expert) this kernel wins (2048 x 8192: 64 tokens, 32 experts 158 / 150; 64, 64: 204 / 194; 16, 16:
-// 65 / 53; 64 tokens, 128 experts, of which 52 are reached: layer 519 / 506; where they happen to be 48: 242 / 246 for the
+// 65 / 53; 64 tokens, 128 experts, of which about 51 are reached: layer 519 / 506; where they happen to be 48: 242 / 246 for the
 // product); with all of a multiple of eight experts reached, or fewer than eight of them, the streaming one does (128 tokens,
 // 8 experts 44 / 52; 64, 16: 86 / 88).  K = 1024 loses (64 tokens, 128 experts layer 166 -> 171: two rounds of loads per wave
 // do not pay for a work-group).  with_dense: the dense branch's first product comes along in the launch, which pays for it

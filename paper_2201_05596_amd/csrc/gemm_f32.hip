@@ -18,14 +18,14 @@
 //     writes of later chunks are placed between the matrix instructions of this one.  Weight rows of 256 bytes are read
 //     without bank conflicts as they are; activation rows are padded to 160 bytes (2 x odd 16-byte units), which
 //     sends the 16 lanes of one LDS pass (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
-//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 80 + 71 us
-//     (85 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
+//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 81 + 75 us
+//     (83 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
 //     vector ALUs, before: 162 + 465.
 //   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products of 2^24 columns or more, whose 32-row
 //     chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency when they are few.  A
 //     work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from memory into
 //     registers, three blocks ahead, and add up through LDS in wave order.
-//     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before.
+//     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before, 5.5 + 7.4 here.
 #include <type_traits>
 
 #include "moe_internal.h"
