@@ -81,7 +81,8 @@ typedef struct {
 } moe_shape_t;
 
 /* Upper bound, in bytes, of the workspace any entry point needs for this
- * shape.  Returns 0 for an invalid shape.  Pure host arithmetic. */
+ * shape, the same whether the weights are packed or not.  Returns 0 for an
+ * invalid shape.  Pure host arithmetic. */
 size_t moe_workspace_bytes(const moe_shape_t* shape);
 
 /* Static string for a status code. */

@@ -406,9 +406,9 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 // 8192 x 2048: 256 x 256 on 128 CUs 351 us for the layer, 128 x 256 on 256 CUs 298, 128 x 128 in two rounds 350;
 // the same with 1024 columns: 156 / 126 / 112): 0.77 : 0.56 : 0.42; a 256-row tile with at most 128 rows counts 0.6; two
 // paired tiles on a CU 0.84 (32 steps of K: 43 us against 39.5).  A partial last round costs half a round more on average.
-// Against the largest tile that gives every CU one: 1500 tokens, 16 experts, 1024 / 4096 122 -> 101 us, 2048 / 8192
-// 270 -> 226; 3000 tokens, 32 experts 166 -> 142; paired with 1500 rows of a dense branch 140 -> 117; 4000 tokens, top-1
-// of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 427 through the first product.
+// Against the largest tile that gives every CU one, layers on packed weights: 1500 tokens, 16 experts, 1024 / 4096 129 -> 95 us,
+// 2048 / 8192 277 -> 223; 3000 tokens, 32 experts 168 -> 138; paired with 1500 rows of a dense branch 146 -> 115; 4000 tokens,
+// top-1 of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 419 through the first product.
 // All this counts tiles by the groups' room for rows, which the routing need not fill.  Where 256 x 256 tiles are too few for
 // the chip, 256 x 128 ones are not, and the expected rows are one round of them (16 experts, 520 / 2080, room for 156 rows:
 // in two rounds layer 64 -> 68), one product takes the latter
