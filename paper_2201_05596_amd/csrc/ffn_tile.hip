@@ -17,6 +17,7 @@
 // and does not put a full vmcnt(0) wait in front of every LDS read; completion is tracked by hand
 // (in-order vmcnt: 8 loads per wave and stage).
 // v_mfma_f32_16x16x32_bf16, fp32 accumulation; epilogues shared with the streaming kernel.
+// Packed weights take this kernel only for the 128-column tiles; their 256-column tiles run on ffn_wide.hip.
 // K is a multiple of 8; a lane whose 16 bytes of the last stage lie past K loads zeros from a constant instead (weights too,
 // unless they are packed and hold zeros there): nothing is filled in on the way into LDS.
 #include "ffn_common.h"
@@ -388,9 +389,12 @@ static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 }
 template <int WM, int NWM, int NSX, int EPI, int WN>
 static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    if (a.K % kTK)            // instances of their own: whole stages are not charged for the selects
-        return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s);
-    return a.packed ? launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
+    // K off 32: instances of their own, whole stages are not charged for the selects
+    if constexpr (WN == 64) {
+        if (a.packed) return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s);
+    }
+    if (a.packed) return MOE_ERR_INVALID_ARG;                    // 256 columns: launch_wide
+    return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
 }
 
 // Tile shapes, for one product or for two in one launch (same K, N and packing: all tiles are counted together):
@@ -492,7 +496,13 @@ bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b) {
 template <int EPI>
 static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     if (b && !pair_fits(a, *b)) return MOE_ERR_INVALID_ARG;
-    switch (pick_tile(a, b)) {
+    const TileShape shape = pick_tile(a, b);
+    if (a.packed && (shape == TILE_256x256 || shape == TILE_128x256 || shape == TILE_128x256_PAIRED)) {
+        // packed weights: all shapes of 256 columns on the four-wave kernel
+        const bool long_groups = a.max_rows > 256 && (!b || b->max_rows > 256);
+        return launch_wide(a, b, shape == TILE_256x256 || (shape == TILE_128x256_PAIRED && long_groups) ? 256 : 128, EPI, s);
+    }
+    switch (shape) {
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);
         case TILE_128x256: return launch_t<32, 4, 6, EPI, 128>(a, b, s);
         case TILE_128x256_PAIRED: return launch_t<64, 2, 3, EPI, 128>(a, b, s);

@@ -207,6 +207,9 @@ int launch_tgemm_pair(const WsGemmArgs& a, const WsGemmArgs& b, int epi, hipStre
 bool tgemm_supported(int K, int N);
 int tgemm_shape(const WsGemmArgs& a, const WsGemmArgs* b);   // the tile shape that these products get, as 1000 rows + columns (+ 1: two per CU)
 
+// 256-column tiles of 256 or 128 rows on packed weights (ffn_wide.hip); b: a second product in the launch, or nullptr
+int launch_wide(const WsGemmArgs& a, const WsGemmArgs* b, int tile_rows, int epi, hipStream_t s);
+
 // Weights in the fragment order of v_mfma_f32_16x16x32_bf16's second operand (pack.hip).  Element (k, n) of group g
 // goes to  ((((g*KB + k/32)*NG + n/128)*8 + n%8)*64 + (k%32/8)*16 + (n%128)/8)*8 + k%8,  KB = ceil(K/32),
 // NG = ceil(N/128); positions past K or N hold zeros.  A lane's 16 bytes are then 8 consecutive k of one column,
