@@ -1,0 +1,9 @@
+// Instances of the four-wave tile kernel (ffn_wide.h).
+#include "ffn_wide.h"
+
+namespace moe {
+
+template int launch_wide_epi<EPI_STORE>(const WsGemmArgs&, const WsGemmArgs*, int, hipStream_t);
+template int launch_wide_epi<EPI_PARTIAL>(const WsGemmArgs&, const WsGemmArgs*, int, hipStream_t);
+
+}  // namespace moe

@@ -157,6 +157,7 @@ int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s);
 struct WsGemmArgs {
     const uint16_t* A;         // activations, leading dimension K
     const uint16_t* B;         // [G, K, N], or the same weights in fragment order (packed != 0)
+    int32_t stream;            // four-wave tile kernel: weights that only one row tile reads are not worth caching
     int32_t packed;            // B is [G, ceil(K/32), ceil(N/128), 8, 64, 8] as written by launch_pack_weights
     const uint16_t* bias;      // [G, N] or nullptr
     const int32_t* rows;       // [G] device row counts or nullptr -> fixed_rows
