@@ -20,11 +20,12 @@
 //     sends the 16 lanes of one LDS pass (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
 //     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 81 + 75 us
 //     (83 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
-//     vector ALUs, before: 162 + 465.
-//   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products of 2^24 columns or more, whose 32-row
-//     chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency when they are few.  A
-//     work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from memory into
-//     registers, three blocks ahead, and add up through LDS in wave order.
+//     vector ALUs, before: 162 + 465.  At most 128 registers (132 if left alone), so that two work-groups share a compute unit
+//     where there are more tiles than units: 8192 tokens, 512/2048, 8 experts 308 -> 298 us (layer).
+//   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products with few tiles and those of 2^24 columns or
+//     more, whose 32-row chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency
+//     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
+//     memory into registers, three blocks ahead, and add up through LDS in wave order.
 //     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before, 5.5 + 7.4 here.
 #include <type_traits>
 
@@ -83,7 +84,7 @@ constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
 
 // WMW x WNW pairs of waves of 32 rows x 64 columns; wave 0 of a pair takes the first half of every chunk, wave 1 the second
 template <int WMW, int WNW, int EPI>
-__global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, const int n_tiles) {
+__global__ __launch_bounds__(512, WNW == 1 ? 2 : 4) void f32_tile_kernel(const GemmArgs a, const int n_tiles) {
     static_assert(WMW * WNW == 4, "four pairs of waves");
     constexpr int TM = WMW * 32, TN = WNW * 64;
     constexpr int A_BYTES = TM * kFStride, BUF = A_BYTES + kFK * TN * 4;
@@ -246,7 +247,7 @@ constexpr int kFWaves = 8;                    // waves of a work-group = ways K 
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
 
 template <int MS, int EPI>
-__global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
+__global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
     __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves][MS * 16][16];
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -325,7 +326,14 @@ __global__ __launch_bounds__(kFWaves * 64) void f32_rows_kernel(const GemmArgs a
 
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
-    const bool few = a.max_rows <= 32 || a.N >= 1 << 24, narrow = a.N <= 64;   // one 64-column tile: all four pairs along the rows
+    // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
+    // flop, so the line is where two of them on every unit hold all (layers, us, second product on 64 x 128 / on 32 x 64: 1024
+    // tokens, 512/2048, 8 experts, 256 small tiles 106 / 67; 300 tokens, 4 experts with a dense branch, both second products
+    // 196 / 110; 2048 tokens, 8 experts, 512 tiles 124 / 105; 1536 tokens, top-2, 960 tiles 165 / 203.  First products: 700
+    // tokens, 256/1024, 16 experts, 512 tiles 65.4 / 62.9; 512 tokens, 512/2048, 4 experts, 640 tiles 104 / 108).
+    const long long small_tiles = ((long long)a.max_rows + 31) / 32 * (((long long)a.N + 63) / 64) * a.G;
+    const bool few = a.max_rows <= 32 || small_tiles <= 512 || a.N >= 1 << 24;
+    const bool narrow = a.N <= 64;                               // one 64-column tile: all four pairs along the rows
     const int tm = few ? (a.max_rows <= 16 ? 16 : 32) : narrow ? 128 : 64, tn = few || narrow ? 64 : 128;
     const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
     const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;

@@ -20,3 +20,17 @@ def test_f32_layer(C, T, d, f, E, k, residual):
     print(f"case C={C} T={T} d={d} f={f} E={E} k={k} residual={residual}", flush=True)
     cfg = CONFIGS["c1"].scaled(name="f32", T=T, d_model=d, d_ffn=f, E=E, top_k=k, residual=residual, seed=5)
     U.check_layer(make_inputs(cfg, "cuda", bias_std=0.05), capacity=C)
+
+
+# the same with more than 512 tiles of 32 x 64 in one or both expert products, or in the dense branch's (fewer of them are
+# another kernel's): 64- and 128-row tiles, one row more or less, and the last launch of the few (512 tiles)
+MANY_TILES = [
+    (33, 400, 64, 516, 32, 1, False), (65, 900, 60, 772, 14, 2, True), (129, 2600, 196, 132, 26, 1, False),
+    (65, 5000, 64, 68, 180, 1, False), (1030, 4100, 196, 132, 4, 1, True), (128, 500, 132, 256, 4, 1, False),
+    (512, 1500, 64, 512, 4, 1, False),
+]
+
+
+@pytest.mark.parametrize("C,T,d,f,E,k,residual", MANY_TILES)
+def test_f32_layer_many_tiles(C, T, d, f, E, k, residual):
+    test_f32_layer(C, T, d, f, E, k, residual)
