@@ -83,12 +83,34 @@ struct FfnPlan {
     int MT, NW1, NW2;   // row tile; waves per work-group of GEMM-1 / GEMM-2
     int ksplit2;        // split-K factor of GEMM-2 (1 = none)
     int ksplit_room;    // split-K factor that the workspace has room for
-    bool tiled;         // more than 64 rows per expert: the tiled (matrix-core-bound) kernel
+    bool tiled;         // the tiled kernel: more than 64 rows per expert, or packed weights and enough tiles (few_rows_tiled)
+    bool tiled1;        // the tiled kernel for GEMM-1, whatever GEMM-2 takes
     int NBUF;           // weight super-fragments kept in flight per wave, plus one
     int nf1, nf2;       // 16-column fragments per work-group of the few-weights kernel, 0: not that kernel
     int slots;          // launch-order entries that may have rows, 0: all
     int expect;         // rows per expert if the tokens fall evenly on them
 };
+
+// Experts with room for at most 64 rows: both kernels read the weights once, and on packed ones the tiled kernel does it
+// faster (whole 32 KB blocks by direct loads, no sums of partial results) as long as there are tiles for the compute units
+// however unevenly the rows fall on the experts: its tiles are as long as K, where the streaming kernel splits that.
+// Layers, us or per cent of the streaming kernel's time:
+//   first product (d_ffn columns): from 3 rows per expert on, 8 of fewer than 32 experts.  64 experts x 22 .. 45 rows (1024/4096)
+//     with skewed routing -12 .. -14 %, 32 x 24 -5 %, 2048/8192 64 x 58 -5 %, even routing -3 .. +0 %; 92 tokens of 64 experts
+//     144 / 152;
+//   both products: from 512 tiles in the second one on, with 7/4 rows per expert (so that few are missed).  128 x 33 rows
+//     (1024/4096) skewed 135 / 104, even 382 / 374; 2048/8192 64 x 58 skewed 247 / 206, 64 x 24 even 668 / 643; 256 tokens of 128
+//     experts 313 / 303, 164 tokens 250 / 252.  With half the tiles even routing gains (64 x 64, 1024/4096, 235 / 206) but a few
+//     busy experts lose (64 x 45 85 / 94, 64 x 7 60 / 75, 40 x 55 72 / 93), and so does 4096/16384 (64 x 5 skewed 800 / 844).  The
+//     dense branch's few tiles of a shared second launch are as long: with at most 128 rows 526 / 538 (75 tokens, 64 experts,
+//     2048/8192), with 151 230 / 180;
+//   more than 48 rows on a short K leave the set-up and epilogue of a tile too little to hide behind: 128 x 64 (1024/4096)
+//     394 / 404, 128 x 33 .. 38 -0.1 .. -2 %.
+bool few_rows_short(const moe_shape_t* s) { return !(s->flags & MOE_FLAG_PACKED_WEIGHTS) || (s->capacity > 48 && s->d_model < 2048); }
+bool few_rows_tiled(const moe_shape_t* s, long long kept) {
+    if (few_rows_short(s) || (s->residual && s->T <= 128)) return false;
+    return (long long)s->E * ((s->d_model + 255) / 256) >= 512 && s->d_ffn <= 8192 && 4 * kept >= 7ll * s->E;
+}
 
 FfnPlan plan_ffn(const moe_shape_t* s) {
     FfnPlan p{};
@@ -96,7 +118,10 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     p.ksplit2 = p.ksplit_room = 1;
     p.NBUF = 2;
     if (!p.mfma) return p;
-    p.tiled = s->capacity > 64 && tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
+    const long long kept = (long long)s->T * s->top_k, touched = s->E < kept ? s->E : kept;
+    p.expect = (int)((kept + s->E - 1) / s->E < s->capacity ? (kept + s->E - 1) / s->E : s->capacity);
+    const bool tiles_fit = tgemm_supported(s->d_model, s->d_ffn) && tgemm_supported(s->d_ffn, s->d_model);
+    p.tiled = tiles_fit && (s->capacity > 64 || few_rows_tiled(s, kept));
     // Few experts, an inner dimension off the 32-deep stages and a long second product: on the tiled kernel that one leaves most
     // of the chip idle, the streaming kernel splits its K (1000 / 4000, plain, 2 experts x 156 rows: layer 92 us tiled, 78
     // streamed; 2008 / 8032, 1 x 128: 161 / 116; 72 / 2088, 8 x 160: 57 / 47).  The tiled one is the faster with more rows (1 x
@@ -106,15 +131,13 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     const bool whole_stages = s->d_model % 32 == 0 && s->d_ffn % 32 == 0;
     const long long tiles2 = (long long)s->E * ((s->capacity + 127) / 128) * ((s->d_model + 127) / 128);
     if (!whole_stages && s->capacity <= 512 && s->E <= 32 && tiles2 <= 64 && s->d_ffn >= s->d_model + 2000) p.tiled = false;
+    p.tiled1 = p.tiled || (tiles_fit && s->capacity <= 64 && s->E >= 16 && p.expect >= (s->E >= 32 ? 3 : 8) && !few_rows_short(s));
     wsgemm_pick_tile(s->capacity, s->E, s->d_ffn, &p.MT, &p.NW1);
     int mt2;
     wsgemm_pick_tile(s->capacity, s->E, s->d_model, &mt2, &p.NW2);
     // GEMM-2 has few output columns; when that leaves the chip short of waves, split K
-    const long long touched = s->E < (long long)s->T * s->top_k ? s->E : (long long)s->T * s->top_k;
     const long long m_tiles = (s->capacity + p.MT - 1) / p.MT;
     const long long waves = touched * ((s->d_model + 127) / 128) * m_tiles;
-    const long long kept = (long long)s->T * s->top_k;
-    p.expect = (int)((kept + s->E - 1) / s->E < s->capacity ? (kept + s->E - 1) / s->E : s->capacity);
     const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
     if (s->capacity <= 64) {
         p.nf1 = rows_pick_gemm1(touched, s->capacity, kept, s->d_model, s->d_ffn, packed, s->residual && s->T <= 16);
@@ -321,7 +344,7 @@ int run_expert_gemm1(const moe_shape_t* s, const FfnPlan& p, const void* xin, co
     const WsGemmArgs a = expert_gemm1_args(s, p, xin, row_map, rows, order, W1, b1, h);
     prof_pre(ST_GEMM1, st);
     const int rc = p.nf1     ? launch_rows(a, nullptr, EPI_GELU, p.nf1, st)
-                   : p.tiled ? launch_tgemm(a, EPI_GELU, st)
+                   : p.tiled1 ? launch_tgemm(a, EPI_GELU, st)
                              : launch_wsgemm(a, EPI_GELU, p.MT, p.NW1, p.NBUF, st);
     prof_mark(ST_GEMM1, st);
     return rc;
@@ -777,7 +800,7 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
         kernels[1] = kernels[3] = tgemm_shape(e2, &d2);
         return MOE_OK;
     }
-    kernels[0] = p.nf1 ? p.nf1 : p.tiled ? tgemm_shape(e1, nullptr) : 100 + p.MT;
+    kernels[0] = p.nf1 ? p.nf1 : p.tiled1 ? tgemm_shape(e1, nullptr) : 100 + p.MT;
     kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_shape(e2, nullptr) : 100 * p.ksplit2 + p.MT;
     if (!shape->residual) return MOE_OK;
     shared[0] = dense1_shared(shape, p);
