@@ -132,14 +132,26 @@ __global__ __launch_bounds__(kWideThreads, 1) void wide_kernel(const WsGemmArgs 
         // activations: wave w, load i copies 128 bytes of rows (w*ACT + i)*8 ..+7; lane -> row +lane/8, 16-byte slot lane%8,
         // which holds k-piece slot ^ (row/2 % 8).  The loads i..i+3 share one LDS base: load i adds 1 KB (i%4) to both
         // addresses, which the pointer takes back here.
+        // All of a tile's table look-ups and its bias are asked for before the first is waited for: with the choice between
+        // table and group inside the loop the compiler made each row's look-up a memory round trip of its own.
+        const int n_lane = n0 + wn * 128 + c * 8;                // this lane's eight columns
+        const bool has_bias = EPI != EPI_PARTIAL && a.bias != nullptr;
+        const uint4 bias_raw = has_bias ? *reinterpret_cast<const uint4*>(a.bias + (size_t)g * a.N + min(n_lane, a.N - 8)) : make_uint4(0, 0, 0, 0);
         const uint16_t* a_src[ACT];
         const int a_piece = (lane & 7);
+        int a_row[ACT];
+#pragma unroll
+        for (int i = 0; i < ACT; ++i) a_row[i] = m0 + min((w * ACT + i) * 8 + (lane >> 3), nrows - 1);   // rows past the end alias the last valid one
+        if (a.row_map) {
+            const int32_t* map = a.row_map + (size_t)g * a.map_stride;
+#pragma unroll
+            for (int i = 0; i < ACT; ++i) a_row[i] = map[a_row[i]];
+        }
+        const uint16_t* a_group = a.A + (a.row_map ? (size_t)0 : (size_t)g * a.a_group_stride * a.K);
 #pragma unroll
         for (int i = 0; i < ACT; ++i) {
             const int rt = (w * ACT + i) * 8 + (lane >> 3);
-            const int r = m0 + min(rt, nrows - 1);               // rows past the end alias the last valid one
-            const long long row = a.row_map ? (long long)a.row_map[(size_t)g * a.map_stride + r] : (long long)g * a.a_group_stride + r;
-            a_src[i] = a.A + (size_t)row * a.K + (a_piece ^ ((rt >> 1) & 7)) * 8 - (i & 3) * 512;
+            a_src[i] = a_group + (size_t)a_row[i] * a.K + (a_piece ^ ((rt >> 1) & 7)) * 8 - (i & 3) * 512;
         }
         // weights: wave w copies fragments 4w..4w+3 of the tile's sixteen in each of a chunk's two 32-deep steps
         const int p_ng = (a.N + 127) / 128, kb_n = (a.K + 31) / 32;
@@ -183,9 +195,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void wide_kernel(const WsGemmArgs 
         };
 
 
-        const int n_lane = n0 + wn * 128 + c * 8;                // this lane's eight columns
-        float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if (EPI != EPI_PARTIAL && n_lane < a.N) load_bias8(a, g, n_lane, bias);
+        float bias[8];
+        unpack_bias8(bias_raw, bias);
 #pragma unroll
         for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(bias[j]));   // waited for here, not behind the direct loads
         f32x4_t acc[ACT][8];
@@ -263,6 +274,16 @@ __global__ __launch_bounds__(kWideThreads, 1) void wide_kernel(const WsGemmArgs 
         if (n_lane >= a.N) return;
         int kg_e = kg;
         asm volatile("" : "+v"(kg_e));                           // the address is formed here, not kept through the main loop
+        // top-1 combine: tokens and gate weights of all the lane's rows in two round trips, not two for each row
+        int tok[EPI == EPI_SCATTER ? ACT * 4 : 1];
+        float gate[EPI == EPI_SCATTER ? ACT * 4 : 1];
+        if constexpr (EPI == EPI_SCATTER) {
+            const int32_t* map = a.scatter_map + (size_t)g * a.scatter_stride + m0;
+#pragma unroll
+            for (int q = 0; q < ACT * 4; ++q) tok[q] = map[min((2 * (q / 4) + wm) * 16 + kg_e * 4 + q % 4, nrows - 1)];
+#pragma unroll
+            for (int q = 0; q < ACT * 4; ++q) gate[q] = a.gate_w[(size_t)tok[q] * a.top_k];
+        }
         uint16_t* dst = a.out + ((size_t)g * a.o_group_stride + m0 + wm * 16 + kg_e * 4) * a.N + n_lane;
 #pragma unroll
         for (int i = 0; i < ACT; ++i) {
@@ -283,10 +304,8 @@ __global__ __launch_bounds__(kWideThreads, 1) void wide_kernel(const WsGemmArgs 
                     dst += r < 3 ? (size_t)a.N : (size_t)a.N * 29;
                 } else {
                     if (rl >= nrows) continue;
-                    int t = 0;
-                    float gw = 1.f;
-                    if (EPI == EPI_SCATTER) scatter_lookup(a, g, m0 + rl, t, gw);
-                    finish_row<EPI, 8>(a, g, m0 + rl, 0, n_lane, v, t, gw);
+                    if constexpr (EPI == EPI_SCATTER) finish_row<EPI, 8>(a, g, m0 + rl, 0, n_lane, v, tok[4 * i + r], gate[4 * i + r]);
+                    else finish_row<EPI, 8>(a, g, m0 + rl, 0, n_lane, v);
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
