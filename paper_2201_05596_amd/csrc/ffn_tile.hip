@@ -27,9 +27,10 @@ namespace moe {
 
 constexpr int kTK = 32;            // k-rows per stage
 
-// 16 bytes per lane from global memory straight into LDS at lds_wave_base + lane*16
+// 16 bytes per lane from global memory straight into LDS at lds_wave_base + lane*16.  A direct load must not follow the write of
+// m0 at once: one wait state, which the compiler does not add inside a statement (tests/test_wide_hazards.py).
 __device__ __forceinline__ void dma16(const void* gptr, uint32_t lds_wave_base) {
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_wave_base) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(gptr), "s"(lds_wave_base) : "memory", "m0");
 }
 // A 64-lane 16-byte LDS read is served in four passes of 16 lanes, and the passes are not runs of
 // consecutive lanes: pass 0 takes lanes 0-3, 12-15, 20-23, 24-27, pass 1 lanes 4-7, 8-11, 16-19,

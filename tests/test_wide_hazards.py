@@ -1,7 +1,8 @@
-"""The matrix instructions of ffn_wide.h are inline asm: the compiler puts no wait states between them and the vector
-instructions around them.  The built code must leave the distances that the hardware needs (in wait states; an instruction is
-at least one): 2 from a vector instruction that writes a register to a matrix instruction that reads it, 11 from a matrix
-instruction to any other instruction that reads or writes its result (16 x 16 x 32 in bf16: 8 passes)."""
+"""Inline asm of the tiled kernels, around which the compiler puts no wait states: the built code must leave the distances that
+the hardware needs (in wait states; an instruction is at least one).  Matrix instructions of ffn_wide.h: 2 from a vector
+instruction that writes a register to a matrix instruction that reads it, 11 from a matrix instruction to any other instruction
+that reads or writes its result (16 x 16 x 32 in bf16: 8 passes).  Direct loads to LDS (ffn_wide.h, ffn_tile.hip): 1 from a write
+of m0, which holds their LDS address."""
 import os
 import re
 import subprocess
@@ -77,9 +78,27 @@ def find_hazards(code):
     return bad
 
 
+def find_m0_hazards(code):
+    """Direct loads whose predecessor in memory writes m0.  (A predecessor over a branch is the branch: a wait state.)"""
+    return [line for (_, before), (_, line) in zip(code, code[1:])
+            if "_lds_" in line.split()[0] and re.match(r"s_\S+ m0\b", before)]
+
+
+WIDE = ("wide_store", "wide_gelu", "wide_scatter", "wide_combine")
+
+
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    objs = [os.path.join(B.HERE, "_build", f"ffn_wide_{n}.o") for n in ("store", "gelu", "scatter", "combine")]
+    return disassemble(WIDE, tmp_path_factory)
+
+
+@pytest.fixture(scope="module")
+def tiled_kernels(tmp_path_factory):
+    return disassemble(("tile",), tmp_path_factory)
+
+
+def disassemble(names, tmp_path_factory):
+    objs = [os.path.join(B.HERE, "_build", f"ffn_{n}.o") for n in names]
     if not all(map(os.path.exists, objs)) or not os.path.exists(LLVM + "/llvm-objdump"):
         pytest.skip("needs the built object files and llvm-objdump")
     found = {}
@@ -98,7 +117,7 @@ def kernels(tmp_path_factory):
             elif current is not None and "//" in line:
                 body, _, tail = line.partition("//")
                 current.append((int(tail.strip().split(":")[0], 16), " ".join(body.split())))
-    return {n: c for n, c in found.items() if "wide_kernel" in n}
+    return {n: c for n, c in found.items() if "wide_kernel" in n or "tgemm_kernel" in n}
 
 
 def test_built_code_keeps_the_distances(kernels):
@@ -106,6 +125,13 @@ def test_built_code_keeps_the_distances(kernels):
     for name, code in kernels.items():
         assert sum(line.startswith("v_mfma") for _, line in code) >= 224
         assert not find_hazards(code), name
+
+
+def test_direct_loads_wait_for_m0(kernels, tiled_kernels):
+    assert kernels and tiled_kernels
+    for name, code in [*kernels.items(), *tiled_kernels.items()]:
+        assert sum("_lds_" in line.split()[0] for _, line in code) >= 8
+        assert not find_m0_hazards(code), name
 
 
 def test_finds_planted_hazards():
@@ -119,3 +145,10 @@ def test_finds_planted_hazards():
     assert hazards("v_mov_b32_e32 v4, v9", mfma) and hazards("v_accvgpr_write_b32 a3, v9", "s_nop 0", mfma)
     assert not hazards("v_mov_b32_e32 v4, v9", "s_nop 1", mfma)
     assert hazards("v_accvgpr_read_b32 v9, a0", "s_nop 1", mfma, "s_cbranch_scc1 65532")
+
+    def m0_hazards(*lines):
+        return find_m0_hazards([(4 * i, line) for i, line in enumerate(lines)])
+
+    load = "global_load_lds_dwordx4 v[2:3], off"
+    assert m0_hazards("s_mov_b32 m0, s3", load) and m0_hazards("s_nop 0", "s_add_u32 m0, s3, 0x400", load)
+    assert not m0_hazards("s_mov_b32 m0, s3", "s_nop 0", load) and not m0_hazards("s_mov_b32 s4, m0", load, load)
