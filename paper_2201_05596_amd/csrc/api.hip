@@ -101,9 +101,11 @@ struct FfnPlan {
 //   both products: from 512 tiles in the second one on, with 7/4 rows per expert (so that few are missed).  128 x 33 rows
 //     (1024/4096) skewed 135 / 104, even 382 / 374; 2048/8192 64 x 58 skewed 247 / 206, 64 x 24 even 668 / 643; 256 tokens of 128
 //     experts 313 / 303, 164 tokens 250 / 252.  With half the tiles even routing gains (64 x 64, 1024/4096, 235 / 206) but a few
-//     busy experts lose (64 x 45 85 / 94, 64 x 7 60 / 75, 40 x 55 72 / 93), and so does 4096/16384 (64 x 5 skewed 800 / 844).  The
-//     dense branch's few tiles of a shared second launch are as long: with at most 128 rows 526 / 538 (75 tokens, 64 experts,
-//     2048/8192), with 151 230 / 180;
+//     busy experts lose (64 x 45 85 / 94, 64 x 7 60 / 75, 40 x 55 72 / 93), and so does 4096/16384 (64 x 5 skewed 800 / 844).  Beside a
+//     dense branch, whose products keep launches of their own: 1000 tokens of 64 experts, 2048/8192, 786 / 777, skewed 327 / 313;
+//     3000 tokens, top-2 of 128, 1024/4096, 470 / 473, skewed 216 / 182; 151 tokens of 64 660 / 639, skewed 228 / 211.  With at most
+//     128 tokens such layers stay on the streaming kernel, though tiles are not slower there (112 tokens of 64 572 / 569, skewed
+//     221 / 209);
 //   more than 48 rows on a short K leave the set-up and epilogue of a tile too little to hide behind: 128 x 64 (1024/4096)
 //     394 / 404, 128 x 33 .. 38 -0.1 .. -2 %.
 bool few_rows_short(const moe_shape_t* s) { return !(s->flags & MOE_FLAG_PACKED_WEIGHTS) || (s->capacity > 48 && s->d_model < 2048); }
@@ -439,10 +441,11 @@ WsGemmArgs second_half(WsGemmArgs a, const void* h, const void* W2, const void* 
     a.K = a.N; a.N = K;
     return a;
 }
-// Do the experts' and the dense branch's second products share a launch?  Shapes with an inner dimension off the 32-deep
-// stages keep the combine inside the dense branch's product, which adds the experts' rows to unrounded sums.
+// Do the experts' and the dense branch's second products share a launch?  Experts with room for at most 64 rows and shapes with
+// an inner dimension off the 32-deep stages keep the combine inside the dense branch's product, which adds the experts' rows to
+// unrounded sums.
 bool residual_pairs(const moe_shape_t* s, const FfnPlan& p) {
-    if (!p.tiled || s->T <= 128 || s->d_model % 32 || s->d_ffn % 32) return false;
+    if (!p.tiled || s->capacity <= 64 || s->T <= 128 || s->d_model % 32 || s->d_ffn % 32) return false;
     return tgemm_pair_fusable(second_half(expert_gemm1_args(s, p, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr), nullptr, nullptr, nullptr, nullptr),
                               second_half(dense_gemm1_args(s, nullptr, nullptr, nullptr, nullptr), nullptr, nullptr, nullptr, nullptr));
 }

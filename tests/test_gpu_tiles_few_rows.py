@@ -18,7 +18,7 @@ CASES = [
     (5, 256, 96, 1288, 64, 1, False, True, False), (40, 2600, 64, 1000, 66, 1, False, True, False), (2, 256, 1024, 128, 128, 1, False, False, True),
     (33, 2100, 1032, 64, 104, 1, False, True, True), (20, 1300, 1032, 72, 104, 2, False, True, True), (16, 1600, 2056, 40, 64, 1, False, False, True),
     (64, 3000, 2048, 96, 64, 2, False, True, True), (49, 1000, 1024, 264, 128, 1, False, False, False),
-    (3, 128, 1024, 128, 128, 2, True, False, False), (3, 129, 1024, 128, 128, 2, True, True, True), (16, 1030, 1000, 72, 130, 2, True, False, True),
+    (3, 128, 1024, 128, 128, 2, True, False, False), (3, 129, 1024, 128, 128, 2, True, False, True), (16, 1030, 1000, 72, 130, 2, True, False, True),
     (48, 1000, 72, 264, 16, 1, True, True, False),
 ]
 
