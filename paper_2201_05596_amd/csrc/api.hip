@@ -783,7 +783,7 @@ int moe_layer_forward(const moe_shape_t* shape, const void* x, const float* Wg, 
 // Which kernel each product of a bf16 moe_layer_forward call takes, from the shape alone; for the tests of the dispatch, not
 // part of the interface (moe.h does not declare it).  kernels: expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2, each
 // 0 = none, 1..4 = few-weights kernel with that many 16-column fragments, 100 S + rows = streaming kernel with tiles of that
-// many rows and K split S ways, 1000 rows + columns = tiled kernel (+ 1: two work-groups per compute unit).
+// many rows and K split S ways, beyond that a tiled kernel (tgemm_code).
 // shared: do the experts' and the dense product of the first / second half run in one launch?
 int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2]) {
     const int rc = check_shape(shape);
@@ -798,13 +798,13 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
     if (shape->residual && residual_pairs(shape, p)) {
         shared[0] = tgemm_pair_fusable(e1, d1);
         shared[1] = 1;
-        kernels[0] = tgemm_shape(e1, shared[0] ? &d1 : nullptr);
-        kernels[2] = shared[0] ? kernels[0] : tgemm_shape(d1, nullptr);
-        kernels[1] = kernels[3] = tgemm_shape(e2, &d2);
+        kernels[0] = tgemm_code(e1, shared[0] ? &d1 : nullptr, EPI_GELU);
+        kernels[2] = shared[0] ? kernels[0] : tgemm_code(d1, nullptr, EPI_GELU);
+        kernels[1] = kernels[3] = tgemm_code(e2, &d2, EPI_STORE);
         return MOE_OK;
     }
-    kernels[0] = p.nf1 ? p.nf1 : p.tiled1 ? tgemm_shape(e1, nullptr) : 100 + p.MT;
-    kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_shape(e2, nullptr) : 100 * p.ksplit2 + p.MT;
+    kernels[0] = p.nf1 ? p.nf1 : p.tiled1 ? tgemm_code(e1, nullptr, EPI_GELU) : 100 + p.MT;
+    kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_code(e2, nullptr, shape->top_k == 1 && !shape->residual ? EPI_SCATTER : EPI_STORE) : 100 * p.ksplit2 + p.MT;
     if (!shape->residual) return MOE_OK;
     shared[0] = dense1_shared(shape, p);
     for (int i = 0; i < 2; ++i) {
@@ -812,7 +812,7 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
         const int nf = rows_pick_dense(shape->T, a.N, a.packed);
         int MT, NW;
         wsgemm_pick_tile(shape->T, 1, a.N, &MT, &NW);
-        kernels[2 + i] = i == 0 && shared[0] ? p.nf1 : nf ? nf : dense_tiled(shape) ? tgemm_shape(a, nullptr) : 100 + MT;
+        kernels[2 + i] = i == 0 && shared[0] ? p.nf1 : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
     }
     return MOE_OK;
 }

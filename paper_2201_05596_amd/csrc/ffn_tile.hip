@@ -390,11 +390,10 @@ static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 }
 template <int WM, int NWM, int NSX, int EPI, int WN>
 static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    // K off 32: instances of their own, whole stages are not charged for the selects
+    // K off 32: instances of their own, whole stages are not charged for the selects.  Packed weights: 128-column tiles only (pick_kernel)
     if constexpr (WN == 64) {
         if (a.packed) return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s);
     }
-    if (a.packed) return MOE_ERR_INVALID_ARG;                    // 256 columns: launch_wide
     return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
 }
 
@@ -468,8 +467,24 @@ static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
         return TILE_256x128;
     return shape;
 }
-int tgemm_shape(const WsGemmArgs& a, const WsGemmArgs* b) {
-    switch (pick_tile(a, b)) {
+// The kernel of a launch: this file's with a tile shape or, where packed weights get 256-column tiles, the four-wave one with
+// 256 or 128 rows.  A pair of products of which one has groups of at most 128 rows gets 256-row tiles there, those of the other one
+// first (half-filled tiles cost about 0.7 of a full one; all on 128-row tiles 157 us, 64 groups x 128 rows + 8192 rows, 4096 x
+// 1024: 150).
+struct TileKernel {
+    TileShape shape;
+    int wide_rows;           // rows of a four-wave tile, 0: this file's kernel
+};
+static TileKernel pick_kernel(const WsGemmArgs& a, const WsGemmArgs* b) {
+    const TileShape shape = pick_tile(a, b);
+    if (!a.packed || shape == TILE_256x128 || shape == TILE_128x128) return {shape, 0};
+    const bool mixed = b && (a.max_rows > 128) != (b->max_rows > 128), long_groups = a.max_rows > 256 && (!b || b->max_rows > 256);
+    return {shape, mixed || shape == TILE_256x256 || (shape == TILE_128x256_PAIRED && long_groups) ? 256 : 128};
+}
+int tgemm_code(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
+    const TileKernel k = pick_kernel(a, b);
+    if (k.wide_rows) return 1000 * k.wide_rows + 256 + 2 + wide_policy(a, b, k.wide_rows, epi);
+    switch (k.shape) {
         case TILE_256x256: return 256256;
         case TILE_128x256: return 128256;
         case TILE_128x256_PAIRED: return 128257;
@@ -497,13 +512,9 @@ bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b) {
 template <int EPI>
 static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     if (b && !pair_fits(a, *b)) return MOE_ERR_INVALID_ARG;
-    const TileShape shape = pick_tile(a, b);
-    if (a.packed && (shape == TILE_256x256 || shape == TILE_128x256 || shape == TILE_128x256_PAIRED)) {
-        // packed weights: all shapes of 256 columns on the four-wave kernel
-        const bool long_groups = a.max_rows > 256 && (!b || b->max_rows > 256);
-        return launch_wide(a, b, shape == TILE_256x256 || (shape == TILE_128x256_PAIRED && long_groups) ? 256 : 128, EPI, s);
-    }
-    switch (shape) {
+    const TileKernel k = pick_kernel(a, b);
+    if (k.wide_rows) return launch_wide(a, b, k.wide_rows, EPI, s);
+    switch (k.shape) {
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);
         case TILE_128x256: return launch_t<32, 4, 6, EPI, 128>(a, b, s);
         case TILE_128x256_PAIRED: return launch_t<64, 2, 3, EPI, 128>(a, b, s);

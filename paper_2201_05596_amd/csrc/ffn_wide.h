@@ -92,6 +92,7 @@ __device__ __forceinline__ void gelu_tanh8(float (&v)[8]) {
 // How the weights are read: through the caches, with the non-temporal hint, or as each tile's group needs it.  The hint is for
 // weights that one row tile reads and nobody will find in the 256 MB Infinity Cache later.
 enum WidePolicy { WIDE_CACHED, WIDE_STREAMED, WIDE_BY_GROUP };
+constexpr bool wide_hints(int epi) { return epi == EPI_STORE || epi == EPI_GELU || epi == EPI_SCATTER; }   // the epilogues that have the hint
 
 template <int BM, int EPI, bool RAGGED, int POLICY>
 __global__ __launch_bounds__(kWideThreads, 1) void wide_kernel(const WsGemmArgs a0, const WsGemmArgs a1, const int split) {
@@ -342,25 +343,19 @@ template <int BM, int EPI, bool RAGGED, int POLICY> static int launch_wide_p(con
     hipLaunchKernelGGL((wide_kernel<BM, EPI, RAGGED, POLICY>), dim3((unsigned)blocks), dim3(kWideThreads), kWideLds, s, a, b ? *b : a, (int)blocks_a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
-template <int BM, int EPI, bool RAGGED> static int launch_wide_r(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    if constexpr (EPI == EPI_STORE || EPI == EPI_GELU || EPI == EPI_SCATTER) {
-        if (a.stream && a.max_rows <= BM && (!b || (b->stream && b->max_rows <= BM)))
-            return launch_wide_p<BM, EPI, RAGGED, WIDE_STREAMED>(a, b, s);
+template <int BM, int EPI, bool RAGGED> static int launch_wide_r(const WsGemmArgs& a, const WsGemmArgs* b, int policy, hipStream_t s) {
+    if constexpr (wide_hints(EPI)) {
+        if (policy == WIDE_STREAMED) return launch_wide_p<BM, EPI, RAGGED, WIDE_STREAMED>(a, b, s);
         if constexpr (BM == 256) {
-            if (a.stream || (b && b->stream)) return launch_wide_p<BM, EPI, RAGGED, WIDE_BY_GROUP>(a, b, s);
+            if (policy == WIDE_BY_GROUP) return launch_wide_p<BM, EPI, RAGGED, WIDE_BY_GROUP>(a, b, s);
         }
     }
     return launch_wide_p<BM, EPI, RAGGED, WIDE_CACHED>(a, b, s);
 }
-// Both halves of an FFN have weights of this size: beyond 128 MB a pass evicts what the next one would have found in the
-// Infinity Cache.  (64 groups x 128 rows x 4096 x 1024, 537 MB: 105 -> 91 us with the hint, 16 rows 89 -> 79 = 6.8 TB/s; 32
-// groups x 16 rows, 268 MB read again and again 41 -> 48; weights that several row tiles read, 8192 x 4096 x 4096 193 -> 212.)
-inline bool wide_streams(const WsGemmArgs& a) { return (long long)a.G * a.K * a.N * 2 > (128ll << 20); }
-
-template <int EPI> int launch_wide_epi(const WsGemmArgs& a, const WsGemmArgs* b, int tile_rows, hipStream_t s) {
+template <int EPI> int launch_wide_epi(const WsGemmArgs& a, const WsGemmArgs* b, int tile_rows, int policy, hipStream_t s) {
     if (tile_rows == 256)
-        return a.K % kChunk ? launch_wide_r<256, EPI, true>(a, b, s) : launch_wide_r<256, EPI, false>(a, b, s);
-    return a.K % kChunk ? launch_wide_r<128, EPI, true>(a, b, s) : launch_wide_r<128, EPI, false>(a, b, s);
+        return a.K % kChunk ? launch_wide_r<256, EPI, true>(a, b, policy, s) : launch_wide_r<256, EPI, false>(a, b, policy, s);
+    return a.K % kChunk ? launch_wide_r<128, EPI, true>(a, b, policy, s) : launch_wide_r<128, EPI, false>(a, b, policy, s);
 }
 
 }  // namespace moe

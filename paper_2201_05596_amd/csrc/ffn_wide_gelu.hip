@@ -3,6 +3,6 @@
 
 namespace moe {
 
-template int launch_wide_epi<EPI_GELU>(const WsGemmArgs&, const WsGemmArgs*, int, hipStream_t);
+template int launch_wide_epi<EPI_GELU>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 
 }  // namespace moe

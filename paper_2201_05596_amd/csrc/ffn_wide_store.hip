@@ -3,7 +3,7 @@
 
 namespace moe {
 
-template int launch_wide_epi<EPI_STORE>(const WsGemmArgs&, const WsGemmArgs*, int, hipStream_t);
-template int launch_wide_epi<EPI_PARTIAL>(const WsGemmArgs&, const WsGemmArgs*, int, hipStream_t);
+template int launch_wide_epi<EPI_STORE>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
+template int launch_wide_epi<EPI_PARTIAL>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 
 }  // namespace moe

@@ -206,10 +206,13 @@ int launch_tgemm(const WsGemmArgs& a, int epi, hipStream_t s);
 bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b);
 int launch_tgemm_pair(const WsGemmArgs& a, const WsGemmArgs& b, int epi, hipStream_t s);
 bool tgemm_supported(int K, int N);
-int tgemm_shape(const WsGemmArgs& a, const WsGemmArgs* b);   // the tile shape that these products get, as 1000 rows + columns (+ 1: two per CU)
+// the kernel that these products get: 1000 rows + columns of its tiles; + 1: two work-groups per CU; + 2: the four-wave kernel,
+// weights through the caches, + 3: with the non-temporal hint, + 4: as each group needs it
+int tgemm_code(const WsGemmArgs& a, const WsGemmArgs* b, int epi);
 
 // 256-column tiles of 256 or 128 rows on packed weights (ffn_wide.hip); b: a second product in the launch, or nullptr
 int launch_wide(const WsGemmArgs& a, const WsGemmArgs* b, int tile_rows, int epi, hipStream_t s);
+int wide_policy(const WsGemmArgs& a, const WsGemmArgs* b, int tile_rows, int epi);   // how it reads the weights (WidePolicy)
 
 // Weights in the fragment order of v_mfma_f32_16x16x32_bf16's second operand (pack.hip).  Element (k, n) of group g
 // goes to  ((((g*KB + k/32)*NG + n/128)*8 + n%8)*64 + (k%32/8)*16 + (n%128)/8)*8 + k%8,  KB = ceil(K/32),

@@ -5,7 +5,8 @@ from paper_2201_05596_amd import binding as B
 
 
 def plan(T, d, f, E, k, C, residual=False, packed=False):
-    """([expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2], [first, second half shared]); codes as in csrc/api.hip."""
+    """([expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2], [first, second half shared]); codes as in csrc/api.hip and, of the tiled
+    kernels, at tgemm_code in csrc/moe_internal.h."""
     shape = B.make_shape(T, d, f, E, k, C, "bf16", residual, B.MOE_FLAG_PACKED_WEIGHTS if packed else 0)
     kernels, shared = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 2)()
     assert B.load_library().moe_test_plan(ctypes.byref(shape), kernels, shared) == 0

@@ -1,29 +1,42 @@
-"""The choice of kernels on the CPU, at shapes where both sides were measured (us beside each case: this choice / the other)."""
+"""The choice of kernels on the CPU, at shapes where both sides were measured (us beside each case: this choice / the others;
+tile shapes: of the product, on packed weights)."""
 import pytest
 
 from tests.plan_util import plan
 
 T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
+W256, W256H, W256G, W128, W128H = 256258, 256259, 256260, 128258, 128259     # four-wave kernel: cached, with the hint, by group
 
 
 @pytest.mark.parametrize("T,d,f,E,k,C,residual,which,kernel", [
     # room for few more than 128 rows, or for many more than there are: 256 x 128 tiles where 256 x 256 ones are too few
-    (832, 4096, 16384, 8, 1, 130, False, 1, T256N),      # 227 / 302 (128 x 256)
-    (682, 4096, 16384, 8, 1, 256, False, 1, T256N),      # 206 / 272
-    (2080, 2048, 8192, 16, 1, 130, False, 1, T256N),     # 121 / 167
-    (4160, 1024, 4096, 32, 1, 130, False, 1, T256N),     # 71 / 92
-    (800, 4096, 4096, 2, 1, 1200, False, 1, T256N),      # 68 / 94 (256 x 256)
-    (2000, 520, 2080, 16, 1, 156, False, 0, T256),       # 64 / 68 in two rounds of 256 x 128 (layer)
+    (832, 4096, 16384, 8, 1, 130, False, 1, T256N),      # 224 / 260 (128 x 256), 243 (256 x 256)
+    (682, 4096, 16384, 8, 1, 256, False, 1, T256N),      # 214 / 253, 235
+    (2080, 2048, 8192, 16, 1, 130, False, 1, T256N),     # 126 / 138, 136
+    (4160, 1024, 4096, 32, 1, 130, False, 1, T256N),     # 66 / 71, 76
+    (800, 4096, 4096, 2, 1, 1200, False, 1, T256N),      # 68 / 110, 80
+    (2000, 520, 2080, 16, 1, 156, False, 0, W256),       # 20 / 25 in two rounds of 256 x 128
     # rows that fill their tiles: as before
-    (4001, 1024, 4096, 32, 2, 251, False, 1, T128),
-    (8192, 1024, 4096, 32, 1, 256, True, 0, T256),
-    (16384, 4096, 16384, 64, 2, 640, False, 0, T256),
-    (1500, 1024, 4096, 16, 1, 117, False, 1, T128N),
+    (4001, 1024, 4096, 32, 2, 251, False, 1, W128),      # 80 / 93 (256 x 256)
+    (8192, 1024, 4096, 32, 1, 256, True, 0, W256G),
+    (16384, 4096, 16384, 64, 2, 640, False, 0, W256G),
+    (1500, 1024, 4096, 16, 1, 117, False, 1, T128N),     # 50 / 58 (128 x 256)
     # two products in a launch, the experts' with few more than 128 rows: not two small tiles per compute unit
-    (1664, 2048, 8192, 16, 1, 130, True, 0, T256),       # 156 / 232
-    (3328, 1024, 4096, 32, 1, 130, True, 0, T256),       # 95 / 126
+    (1664, 2048, 8192, 16, 1, 130, True, 0, W256G),      # 137 / 215
+    (3328, 1024, 4096, 32, 1, 130, True, 0, W256G),      # 84 / 116
 ])
 def test_tile_shape(T, d, f, E, k, C, residual, which, kernel):
+    assert plan(T, d, f, E, k, C, residual, packed=True)[0][which] == kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,k,C,residual,which,kernel", [
+    # packed weights, 256 columns: the four-wave kernel; weights of more than 128 MB that one row tile reads get the hint
+    (8192, 1024, 4096, 64, 1, 128, True, 0, W128H), (8192, 1024, 4096, 64, 1, 128, True, 1, W256G), (8192, 1024, 4096, 64, 1, 128, True, 2, W256),
+    (4001, 1024, 4096, 32, 2, 251, False, 0, W256H), (4001, 1024, 2048, 32, 2, 251, False, 0, W256),
+    # a pair of products: 256 rows where one has groups of at most 128, or by the choice of the shape
+    (130, 64, 8192, 4, 1, 65, True, 0, W256), (300, 256, 32, 64, 1, 300, True, 1, W128),
+])
+def test_four_wave_kernel(T, d, f, E, k, C, residual, which, kernel):
     assert plan(T, d, f, E, k, C, residual, packed=True)[0][which] == kernel
 
 

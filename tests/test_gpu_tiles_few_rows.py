@@ -9,7 +9,7 @@ from tests.plan_util import plan
 from workloads import CONFIGS, make_inputs
 
 pytestmark = pytest.mark.gpu
-TILES = (256256, 128256, 128257, 256128, 128128)
+TILES = (256258, 256259, 256260, 128258, 128259, 256128, 128128)      # on packed weights
 
 # capacity, T, d, f, E, top_k, residual, first and second product on tiles
 CASES = [
@@ -26,7 +26,7 @@ CASES = [
 def test_few_rows_on_tiles(C, T, d, f, E, k, residual, first, second):
     print(f"case C={C} T={T} d={d} f={f} E={E} k={k} residual={residual}", flush=True)
     kernels = plan(T, d, f, E, k, C, residual, packed=True)[0][:2]
-    assert [x in TILES for x in kernels] == [first, second] and not any(x in TILES for x in plan(T, d, f, E, k, C, residual)[0][:2])
+    assert [x in TILES for x in kernels] == [first, second] and all(x < 1000 for x in plan(T, d, f, E, k, C, residual)[0][:2])
     cfg = CONFIGS["c3a"].scaled(name="few", T=T, d_model=d, d_ffn=f, E=E, top_k=k, residual=residual, seed=11)
     U.check_layer(make_inputs(cfg, "cuda", bias_std=0.05), capacity=C)
 
