@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmoe_hip.so")
 SOURCES = ["api.hip", "gate.hip", "gate_bf16.hip", "layout.hip", "pack.hip", "block.hip", "gemm_f32.hip", "ffn_mfma.hip", "ffn_rows.hip", "ffn_tile.hip", "ffn_wide.hip",
-           "ffn_wide_store.hip", "ffn_wide_gelu.hip", "ffn_wide_scatter.hip", "ffn_wide_combine.hip"]
+           "ffn_wide_store.hip", "ffn_wide_gelu.hip", "ffn_wide_scatter.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -17,7 +17,7 @@
 // and does not put a full vmcnt(0) wait in front of every LDS read; completion is tracked by hand
 // (in-order vmcnt: 8 loads per wave and stage).
 // v_mfma_f32_16x16x32_bf16, fp32 accumulation; epilogues shared with the streaming kernel.
-// Packed weights take this kernel only for the 128-column tiles; their 256-column tiles run on ffn_wide.hip.
+// Packed weights take this kernel for 128-column tiles and the combine; their other 256-column tiles run on ffn_wide.hip.
 // K is a multiple of 8; a lane whose 16 bytes of the last stage lie past K loads zeros from a constant instead (weights too,
 // unless they are packed and hold zeros there): nothing is filled in on the way into LDS.
 #include "ffn_common.h"
@@ -390,8 +390,9 @@ static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 }
 template <int WM, int NWM, int NSX, int EPI, int WN>
 static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
-    // K off 32: instances of their own, whole stages are not charged for the selects.  Packed weights: 128-column tiles only (pick_kernel)
-    if constexpr (WN == 64) {
+    // K off 32: instances of their own, whole stages are not charged for the selects.  Packed weights: what pick_kernel()
+    // leaves to this kernel
+    if constexpr (WN == 64 || EPI == EPI_COMBINE) {
         if (a.packed) return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s);
     }
     return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
@@ -468,21 +469,23 @@ static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
     return shape;
 }
 // The kernel of a launch: this file's with a tile shape or, where packed weights get 256-column tiles, the four-wave one with
-// 256 or 128 rows.  A pair of products of which one has groups of at most 128 rows gets 256-row tiles there, those of the other one
+// 256 or 128 rows.  Not for the combine, whose epilogue waits for tables and expert rows token by token: one wave per SIMD exposes
+// that (dense second product, four waves / eight: 16384 tokens, 264/1056, top-2 46 / 38 us, 520/2080 79 / 72, 1000/1000 64 / 54;
+// 8192 tokens, 1000/4000 81 / 80; 2000 tokens 54 / 55).  A pair of products of which one has groups of at most 128 rows gets 256-row tiles there, those of the other one
 // first (half-filled tiles cost about 0.7 of a full one; all on 128-row tiles 157 us, 64 groups x 128 rows + 8192 rows, 4096 x
 // 1024: 150).
 struct TileKernel {
     TileShape shape;
     int wide_rows;           // rows of a four-wave tile, 0: this file's kernel
 };
-static TileKernel pick_kernel(const WsGemmArgs& a, const WsGemmArgs* b) {
+static TileKernel pick_kernel(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
     const TileShape shape = pick_tile(a, b);
-    if (!a.packed || shape == TILE_256x128 || shape == TILE_128x128) return {shape, 0};
+    if (!a.packed || epi == EPI_COMBINE || shape == TILE_256x128 || shape == TILE_128x128) return {shape, 0};
     const bool mixed = b && (a.max_rows > 128) != (b->max_rows > 128), long_groups = a.max_rows > 256 && (!b || b->max_rows > 256);
     return {shape, mixed || shape == TILE_256x256 || (shape == TILE_128x256_PAIRED && long_groups) ? 256 : 128};
 }
 int tgemm_code(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
-    const TileKernel k = pick_kernel(a, b);
+    const TileKernel k = pick_kernel(a, b, epi);
     if (k.wide_rows) return 1000 * k.wide_rows + 256 + 2 + wide_policy(a, b, k.wide_rows, epi);
     switch (k.shape) {
         case TILE_256x256: return 256256;
@@ -512,7 +515,7 @@ bool tgemm_pair_fusable(const WsGemmArgs& a, const WsGemmArgs& b) {
 template <int EPI>
 static int launch_t_epi(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     if (b && !pair_fits(a, *b)) return MOE_ERR_INVALID_ARG;
-    const TileKernel k = pick_kernel(a, b);
+    const TileKernel k = pick_kernel(a, b, EPI);
     if (k.wide_rows) return launch_wide(a, b, k.wide_rows, EPI, s);
     switch (k.shape) {
         case TILE_256x256: return launch_t<64, 4, 4, EPI, 128>(a, b, s);

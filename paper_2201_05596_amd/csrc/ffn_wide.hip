@@ -6,7 +6,6 @@ namespace moe {
 extern template int launch_wide_epi<EPI_STORE>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 extern template int launch_wide_epi<EPI_GELU>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 extern template int launch_wide_epi<EPI_SCATTER>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
-extern template int launch_wide_epi<EPI_COMBINE>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 extern template int launch_wide_epi<EPI_PARTIAL>(const WsGemmArgs&, const WsGemmArgs*, int, int, hipStream_t);
 
 // Both halves of an FFN have weights of this size: beyond 128 MB a pass evicts what the next one would have found in the
@@ -32,7 +31,6 @@ int launch_wide(const WsGemmArgs& first, const WsGemmArgs* second, int tile_rows
         case EPI_STORE: return launch_wide_epi<EPI_STORE>(a, pb, tile_rows, policy, s);
         case EPI_GELU: return launch_wide_epi<EPI_GELU>(a, pb, tile_rows, policy, s);
         case EPI_SCATTER: return second ? MOE_ERR_INVALID_ARG : launch_wide_epi<EPI_SCATTER>(a, pb, tile_rows, policy, s);   // zeroes rows grid-wide
-        case EPI_COMBINE: return launch_wide_epi<EPI_COMBINE>(a, pb, tile_rows, policy, s);
         case EPI_PARTIAL: return launch_wide_epi<EPI_PARTIAL>(a, pb, tile_rows, policy, s);
         default: return MOE_ERR_INVALID_ARG;
     }

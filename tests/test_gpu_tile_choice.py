@@ -46,9 +46,9 @@ CASES = [
     (300, 300, 256, 32, 64, 1, True, GEMM2, T128, True),
     # combine epilogue (the dense branch's second product in a launch of its own)
     (128, 256, 4104, 64, 2, 1, True, DENSE2, T128N, False), (128, 256, 4104, 40, 2, 1, True, DENSE2, T128N, False),
-    (300, 900, 4104, 64, 3, 1, True, DENSE2, T128, False), (300, 900, 4104, 40, 3, 1, True, DENSE2, T128, False),
-    (128, 3379, 8192, 64, 33, 1, True, DENSE2, (T128X2, W256), False), (128, 3379, 8192, 40, 33, 1, True, DENSE2, (T128X2, W256), False),
-    (300, 3600, 2056, 64, 12, 1, True, DENSE2, T256, False), (300, 3600, 2056, 40, 12, 1, True, DENSE2, T256, False),
+    (300, 900, 4104, 64, 3, 1, True, DENSE2, (T128, T128), False), (300, 900, 4104, 40, 3, 1, True, DENSE2, (T128, T128), False),
+    (128, 3379, 8192, 64, 33, 1, True, DENSE2, (T128X2, T128X2), False), (128, 3379, 8192, 40, 33, 1, True, DENSE2, (T128X2, T128X2), False),
+    (300, 3600, 2056, 64, 12, 1, True, DENSE2, (T256, T256), False), (300, 3600, 2056, 40, 12, 1, True, DENSE2, (T256, T256), False),
 ]
 
 

@@ -84,7 +84,7 @@ def find_m0_hazards(code):
             if "_lds_" in line.split()[0] and re.match(r"s_\S+ m0\b", before)]
 
 
-WIDE = ("wide_store", "wide_gelu", "wide_scatter", "wide_combine")
+WIDE = ("wide_store", "wide_gelu", "wide_scatter")
 
 
 @pytest.fixture(scope="module")
