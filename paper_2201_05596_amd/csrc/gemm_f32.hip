@@ -20,8 +20,11 @@
 //     sends the 16 lanes of one LDS pass (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
 //     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 81 + 75 us
 //     (83 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
-//     vector ALUs, before: 162 + 465.  At most 128 registers (132 if left alone), so that two work-groups share a compute unit
-//     where there are more tiles than units: 8192 tokens, 512/2048, 8 experts 308 -> 298 us (layer).
+//     vector ALUs, before: 162 + 465.  One work-group per compute unit, by its 132 registers (within 128 two fit): with two, a
+//     unit may hold two tiles while another has none, and a few rounds of tiles of unequal rows end later (layers, two / one: 1700
+//     tokens, 1024/1024, 8 experts with room for 430 rows 156 / 97 us; 1919 tokens, 1024/2048, 4 experts with room for 720, skewed
+//     185 / 160; 1000 tokens, 1024/4096, 16 experts, skewed 202 / 188).  Many full tiles would be a little faster with two (8192
+//     tokens, 512/2048, 8 experts 294 / 303).
 //   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products with few tiles and those of 2^24 columns or
 //     more, whose 32-row chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
@@ -84,7 +87,7 @@ constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
 
 // WMW x WNW pairs of waves of 32 rows x 64 columns; wave 0 of a pair takes the first half of every chunk, wave 1 the second
 template <int WMW, int WNW, int EPI>
-__global__ __launch_bounds__(512, WNW == 1 ? 2 : 4) void f32_tile_kernel(const GemmArgs a, const int n_tiles) {
+__global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, const int n_tiles) {
     static_assert(WMW * WNW == 4, "four pairs of waves");
     constexpr int TM = WMW * 32, TN = WNW * 64;
     constexpr int A_BYTES = TM * kFStride, BUF = A_BYTES + kFK * TN * 4;
