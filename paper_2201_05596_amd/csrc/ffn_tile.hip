@@ -17,7 +17,8 @@
 // and does not put a full vmcnt(0) wait in front of every LDS read; completion is tracked by hand
 // (in-order vmcnt: 8 loads per wave and stage).
 // v_mfma_f32_16x16x32_bf16, fp32 accumulation; epilogues shared with the streaming kernel.
-// Packed weights take this kernel for 128-column tiles and the combine; their other 256-column tiles run on ffn_wide.hip.
+// Packed weights take this kernel for 128-column tiles, the combine and two short tiles per CU (pick_kernel); their other
+// 256-column tiles run on ffn_wide.hip.
 // K is a multiple of 8; a lane whose 16 bytes of the last stage lie past K loads zeros from a constant instead (weights too,
 // unless they are packed and hold zeros there): nothing is filled in on the way into LDS.
 #include "ffn_common.h"
@@ -392,7 +393,7 @@ template <int WM, int NWM, int NSX, int EPI, int WN>
 static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     // K off 32: instances of their own, whole stages are not charged for the selects.  Packed weights: what pick_kernel()
     // leaves to this kernel
-    if constexpr (WN == 64 || EPI == EPI_COMBINE) {
+    if constexpr (WN == 64 || EPI == EPI_COMBINE || NWM == 2) {
         if (a.packed) return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, true, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, true, false>(a, b, s);
     }
     return a.K % kTK ? launch_tp<WM, NWM, NSX, EPI, WN, false, true>(a, b, s) : launch_tp<WM, NWM, NSX, EPI, WN, false, false>(a, b, s);
@@ -469,20 +470,44 @@ static TileShape pick_tile(const WsGemmArgs& a, const WsGemmArgs* b) {
     return shape;
 }
 // The kernel of a launch: this file's with a tile shape or, where packed weights get 256-column tiles, the four-wave one with
-// 256 or 128 rows.  Not for the combine, whose epilogue waits for tables and expert rows token by token: one wave per SIMD exposes
-// that (dense second product, four waves / eight: 16384 tokens, 264/1056, top-2 46 / 38 us, 520/2080 79 / 72, 1000/1000 64 / 54;
-// 8192 tokens, 1000/4000 81 / 80; 2000 tokens 54 / 55).  A pair of products of which one has groups of at most 128 rows gets 256-row tiles there, those of the other one
-// first (half-filled tiles cost about 0.7 of a full one; all on 128-row tiles 157 us, 64 groups x 128 rows + 8192 rows, 4096 x
-// 1024: 150).
+// 256 or 128 rows.  This file's keep
+//   - the combine, whose epilogue waits for tables and expert rows token by token: one wave per SIMD exposes that (dense second
+//     product, four waves / eight: 16384 tokens, 264/1056, top-2 46 / 38 us, 520/2080 79 / 72, 1000/1000 64 / 54; 8192 tokens,
+//     1000/4000 81 / 80; 2000 tokens 54 / 55);
+//   - two paired tiles per CU with K up to 512: set-up and epilogue of a short tile run under the other one (products, four waves
+//     with 128 rows, with 256 / paired: 128 experts x 75 rows with room for 300, 256 x 1024 36, 48 / 32 us; 16 x 867 with room for
+//     1084, 512 x 2048 85, 75 / 76; 32 x 238, room for 298, 45, 56 / 39; 64 x 64, room for 88, 256 x 1024 18, 20 / 18.5).
+// Rows of a four-wave tile where the choice is not 256 x 256:
+//   - two products of which one has groups of at most 128 rows: 256, the full tiles of the other product first (half-filled ones
+//     cost about 0.7 of a full one), unless 128-row tiles are a single round, up to one and a half where 256-row ones are no single
+//     one, or one of two tiles per CU where that was chosen (128 / 256 rows, 4096 x 1024: 32 groups x 64 rows + 2069 rows, 196 tiles
+//     of 128 rows 69 / 82; 40 x 78 + 3168, 260 of 128 and 212 of 256 120 / 87; 64 x 44 + 2773, 344 and 300 125 / 127, with skewed
+//     routing 52 / 77; 64 x 102 + 6446, 460 and 360 155 / 142; 64 x 128 + 8192 157 / 150.  1024 x 2048: 16 x 62 + 979, 192 of 128 24 /
+//     31; 32 x 76 + 2427, paired, 408 of 128, skewed 21 / 31; 64 x 45 + 2870, 696 of 128 71 / 66);
+//   - the paired choice with K beyond 512: 128, but 256 for groups of more than 384 rows that are expected to fill three quarters of
+//     their room (128 / 256: 16 x 750 of 800, 1024 x 4096, 125 / 112; 40 x 301 of 451, 1024 x 1024 beside a dense branch 71 / 63;
+//     64 x 256 of 260, 1024 x 4096, 203 / 224; 64 x 256 of 300, 2048 x 8192, 680 / 748; 16 x 405 of 809, skewed, 147 / 213).
 struct TileKernel {
     TileShape shape;
     int wide_rows;           // rows of a four-wave tile, 0: this file's kernel
 };
 static TileKernel pick_kernel(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
     const TileShape shape = pick_tile(a, b);
-    if (!a.packed || epi == EPI_COMBINE || shape == TILE_256x128 || shape == TILE_128x128) return {shape, 0};
-    const bool mixed = b && (a.max_rows > 128) != (b->max_rows > 128), long_groups = a.max_rows > 256 && (!b || b->max_rows > 256);
-    return {shape, mixed || shape == TILE_256x256 || (shape == TILE_128x256_PAIRED && long_groups) ? 256 : 128};
+    const bool paired = shape == TILE_128x256_PAIRED;
+    if (!a.packed || epi == EPI_COMBINE || shape == TILE_256x128 || shape == TILE_128x128 || (paired && a.K <= 512)) return {shape, 0};
+    if (shape == TILE_256x256) return {shape, 256};
+    if (b && (a.max_rows > 128) != (b->max_rows > 128)) {
+        TileCount c;
+        c.add(a);
+        c.add(*b);
+        const long long tiles256 = c.row_tiles * ((a.N + 255) / 256);
+        return {shape, c.tiles128 <= 256 || (c.tiles128 <= 384 && tiles256 > 256) || (paired && c.tiles128 <= 512) ? 128 : 256};
+    }
+    auto fills = [](const WsGemmArgs& p) {
+        const int expect = p.expect_rows > 0 && p.expect_rows < p.max_rows ? p.expect_rows : p.max_rows;
+        return p.max_rows > 384 && 4ll * expect > 3ll * p.max_rows;
+    };
+    return {shape, paired && fills(a) && (!b || fills(*b)) ? 256 : 128};
 }
 int tgemm_code(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
     const TileKernel k = pick_kernel(a, b, epi);

@@ -33,8 +33,18 @@ def test_tile_shape(T, d, f, E, k, C, residual, which, kernel):
     # packed weights, 256 columns: the four-wave kernel; weights of more than 128 MB that one row tile reads get the hint
     (8192, 1024, 4096, 64, 1, 128, True, 0, W128H), (8192, 1024, 4096, 64, 1, 128, True, 1, W256G), (8192, 1024, 4096, 64, 1, 128, True, 2, W256),
     (4001, 1024, 4096, 32, 2, 251, False, 0, W256H), (4001, 1024, 2048, 32, 2, 251, False, 0, W256),
-    # a pair of products: 256 rows where one has groups of at most 128, or by the choice of the shape
-    (130, 64, 8192, 4, 1, 65, True, 0, W256), (300, 256, 32, 64, 1, 300, True, 1, W128),
+    # a pair of products of which one has groups of at most 128 rows: us with 128 / 256 rows
+    (2069, 1024, 4096, 32, 1, 97, True, 1, W128),        # 69 / 82
+    (979, 1024, 2048, 16, 1, 77, True, 0, W128),         # 24 / 31
+    (2870, 1024, 2048, 64, 1, 68, True, 0, W256G),       # 71 / 66
+    (300, 256, 32, 64, 1, 300, True, 1, W128),
+    # two tiles per compute unit chosen: K up to 512 (four waves with 128, 256 rows / here), beyond it 128 or 256 rows
+    (9585, 256, 1024, 128, 2, 300, False, 0, T128X2),    # 36, 48 / 32
+    (13866, 512, 2048, 16, 1, 1084, True, 0, T128X2),    # 85, 75 / 76
+    (12000, 1024, 4096, 16, 1, 800, False, 0, W256),     # 125 / 112
+    (16384, 1024, 4096, 64, 1, 260, False, 0, W128),     # 203 / 224
+    (16384, 2048, 8192, 64, 1, 300, False, 0, W128),     # 680 / 748
+    (6466, 2048, 8192, 16, 1, 809, False, 0, W128),      # 147 / 213 (skewed routing)
 ])
 def test_four_wave_kernel(T, d, f, E, k, C, residual, which, kernel):
     assert plan(T, d, f, E, k, C, residual, packed=True)[0][which] == kernel

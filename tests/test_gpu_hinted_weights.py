@@ -18,7 +18,7 @@ CASES = [(K, C, T, 64, k, False, kernel, kernel) for K in (WHOLE, RAGGED)
                                  (300, 16768, 1, GROUP), (300, 8384, 2, GROUP))]
 CASES += [(HALF, 100, 4000, 64, 1, False, H128, H128), (HALF, 200, 4500, 64, 2, False, H256, H256),
           (HALF, 300, 16768, 64, 1, False, GROUP, GROUP),
-          (WHOLE, 100, 4000, 64, 1, True, GROUP, GROUP), (WHOLE, 300, 8384, 64, 2, True, GROUP, GROUP),
+          (WHOLE, 100, 9000, 64, 1, True, GROUP, GROUP), (WHOLE, 300, 8384, 64, 2, True, GROUP, GROUP),
           ((1032, 520), 24, 2400, 128, 1, False, H128, H128), ((1024, 528), 40, 2200, 128, 2, False, H128, H128)]
 
 

@@ -10,8 +10,8 @@ from workloads import CONFIGS, make_inputs
 
 pytestmark = pytest.mark.gpu
 T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
-W256, W128 = 256258, 128258                                    # packed weights, 256 columns: the four-wave kernel
-PACKED = {T256: W256, T256N: T256N, T128: W128, T128X2: W128, T128N: T128N}
+W256, W256G, W128 = 256258, 256260, 128258                     # packed weights, 256 columns: the four-wave kernel
+PACKED = {T256: W256, T256N: T256N, T128: W128, T128X2: T128X2, T128N: T128N}       # K up to 512
 GEMM1, GEMM2, DENSE1, DENSE2 = range(4)
 
 # capacity, T, d, f, E, top_k, residual, product, kernel on plain weights (with that on packed ones where PACKED has another), two
@@ -24,8 +24,8 @@ CASES = [
     (257, 257, 64, 8192, 2, 1, False, GEMM1, T256N, False), (130, 2080, 40, 1000, 32, 1, False, GEMM1, T256N, False),
     (130, 4290, 64, 264, 66, 1, False, GEMM1, T256, False), (130, 4290, 40, 264, 66, 1, False, GEMM1, T256, False),
     # two first products in a launch
-    (65, 130, 64, 64, 2, 1, True, GEMM1, T128N, True), (65, 130, 64, 8192, 4, 1, True, GEMM1, (T128, W256), True),
-    (65, 260, 64, 8192, 8, 1, True, GEMM1, (T128X2, W256), True), (257, 4240, 512, 512, 33, 1, True, GEMM1, T256, True),
+    (65, 130, 64, 64, 2, 1, True, GEMM1, T128N, True), (65, 130, 64, 8192, 4, 1, True, GEMM1, T128, True),
+    (65, 260, 64, 8192, 8, 1, True, GEMM1, T128X2, True), (257, 4240, 512, 512, 33, 1, True, GEMM1, T256, True),
     (300, 300, 256, 256, 64, 1, True, GEMM1, T128, True),
     # scatter epilogue (second product, top-1); K = f whole and ragged
     (65, 32, 64, 64, 1, 1, False, GEMM2, T128N, False), (520, 260, 40, 40, 1, 1, False, GEMM2, T128N, False),
@@ -41,13 +41,21 @@ CASES = [
     (130, 1040, 1000, 40, 32, 2, False, GEMM2, T256N, False),
     (130, 4290, 264, 64, 66, 2, False, GEMM2, T256, False), (130, 4290, 264, 40, 66, 2, False, GEMM2, T256, False),
     # two second products in a launch
-    (65, 130, 64, 64, 2, 1, True, GEMM2, T128N, True), (65, 130, 8192, 64, 4, 1, True, GEMM2, (T128, W256), True),
-    (65, 260, 8192, 64, 8, 1, True, GEMM2, (T128X2, W256), True), (257, 257, 8192, 64, 2, 1, True, GEMM2, T256, True),
+    (65, 130, 64, 64, 2, 1, True, GEMM2, T128N, True), (65, 130, 8192, 64, 4, 1, True, GEMM2, T128, True),
+    (65, 260, 8192, 64, 8, 1, True, GEMM2, T128X2, True), (257, 257, 8192, 64, 2, 1, True, GEMM2, T256, True),
     (300, 300, 256, 32, 64, 1, True, GEMM2, T128, True),
+    # packed weights, two paired tiles per compute unit chosen with K beyond 512: four waves with 128 or 256 rows; and pairs of
+    # groups of at most 128 rows with a dense branch, in a round of 128-row tiles and beyond
+    (65, 1248, 520, 1032, 64, 1, False, GEMM1, (T128X2, W128), False), (65, 1248, 1032, 520, 64, 1, False, GEMM2, (T128X2, W128), False),
+    (600, 11520, 520, 520, 64, 1, False, GEMM1, (T128X2, W128), False), (400, 5760, 576, 2048, 16, 1, True, GEMM1, (T128X2, W256), True),
+    (384, 3686, 576, 1024, 32, 1, True, GEMM1, (T128X2, W128), True), (384, 1843, 2048, 1024, 16, 1, True, GEMM2, (T128X2, W128), True),
+    (100, 300, 576, 1024, 64, 1, True, GEMM1, (T128X2, W128), True), (100, 300, 1024, 1024, 64, 1, True, GEMM2, (T128X2, W128), True),
+    (80, 3000, 576, 2112, 40, 1, True, GEMM1, (T128X2, W256), True), (80, 300, 576, 2112, 64, 1, True, GEMM1, (T128X2, W256G), True),
+    (80, 300, 2112, 1024, 64, 1, True, GEMM2, (T128X2, W256G), True),
     # combine epilogue (the dense branch's second product in a launch of its own)
     (128, 256, 4104, 64, 2, 1, True, DENSE2, T128N, False), (128, 256, 4104, 40, 2, 1, True, DENSE2, T128N, False),
     (300, 900, 4104, 64, 3, 1, True, DENSE2, (T128, T128), False), (300, 900, 4104, 40, 3, 1, True, DENSE2, (T128, T128), False),
-    (128, 3379, 8192, 64, 33, 1, True, DENSE2, (T128X2, T128X2), False), (128, 3379, 8192, 40, 33, 1, True, DENSE2, (T128X2, T128X2), False),
+    (128, 3379, 8192, 64, 33, 1, True, DENSE2, T128X2, False), (128, 3379, 8192, 40, 33, 1, True, DENSE2, T128X2, False),
     (300, 3600, 2056, 64, 12, 1, True, DENSE2, (T256, T256), False), (300, 3600, 2056, 40, 12, 1, True, DENSE2, (T256, T256), False),
 ]
 

@@ -9,7 +9,7 @@ from tests.plan_util import plan
 from workloads import CONFIGS, make_inputs
 
 pytestmark = pytest.mark.gpu
-TILES = (256258, 256259, 256260, 128258, 128259, 256128, 128128)      # on packed weights
+TILES = (256258, 256259, 256260, 128258, 128259, 128257, 256128, 128128)      # on packed weights
 
 # capacity, T, d, f, E, top_k, residual, first and second product on tiles
 CASES = [
