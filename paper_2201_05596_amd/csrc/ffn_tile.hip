@@ -412,18 +412,20 @@ static int launch_t(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
 // 8192 x 2048: 256 x 256 on 128 CUs 351 us for the layer, 128 x 256 on 256 CUs 298, 128 x 128 in two rounds 350;
 // the same with 1024 columns: 156 / 126 / 112): 0.77 : 0.56 : 0.42; a 256-row tile with at most 128 rows counts 0.6; two
 // paired tiles on a CU 0.84 (32 steps of K: 43 us against 39.5).  A partial last round costs half a round more on average.
-// Against the largest tile that gives every CU one, layers on packed weights: 1500 tokens, 16 experts, 1024 / 4096 129 -> 95 us,
-// 2048 / 8192 277 -> 223; 3000 tokens, 32 experts 168 -> 138; paired with 1500 rows of a dense branch 146 -> 115; 4000 tokens,
-// top-1 of 16 experts at 1.25 (313 rows), 2048 / 8192: 462 -> 419 through the first product.
+// These are the eight-wave kernel's.  On packed weights, where the 256-column tiles are the four-wave kernel's, the same products
+// take 170 : 138 : 103 us (0.77 : 0.62 : 0.47), a half-filled 256-row tile 0.78 of a full one, and "paired" stands for the choice
+// that pick_kernel() makes of it; the shapes are chosen by the same ratios.  Both sides there now (us, layers on packed weights
+// against the largest tile that gives every CU one): 1500 tokens, 16 experts, 1024 / 4096 98 / 90, 2048 / 8192 227 / 216; 3000
+// tokens, 32 experts 136 / 126; 8192 tokens, 32 experts, 8192 x 2048 second product on 256 x 256 214, on 128 x 256 262.
 // All this counts tiles by the groups' room for rows, which the routing need not fill.  Where 256 x 256 tiles are too few for
 // the chip, 256 x 128 ones are not, and the expected rows are one round of them (16 experts, 520 / 2080, room for 156 rows:
-// in two rounds layer 64 -> 68), one product takes the latter
+// in two rounds layer 64 -> 69), one product takes the latter
 //   - if its groups are expected to hold so few rows that the second of two 128-row tiles is empty or nearly so (half the
 //     128 x 256 work-groups would have nothing to do, or read every weight for a handful of rows).  8 experts, 4096 / 16384,
-//     packed, GEMM-2: room for 130 rows, 832 tokens 302 us on 128 x 256, 227 on 256 x 128; room for 256, 682 tokens 272 / 206.  At
-//     200 rows in 200 128 x 256 is the faster one by 10 %; at 160 the former by 11 % with packed weights, the latter by 5 % with
-//     plain ones (32 experts, 1024 / 4096: layer 170 / 180);
-//   - if the choice would be 256 x 256: 2 experts, 4096 / 4096, room for 1200 rows, 800 tokens: 94 / 68.  Small products only with
+//     packed, GEMM-2: room for 130 rows, 832 tokens 260 us on 128 x 256, 224 on 256 x 128; room for 256, 682 tokens 253 / 214.  At
+//     200 rows in 200 128 x 256 is the faster one (257 / 305); at 160 they are equal with packed weights (32 experts, 1024 / 4096:
+//     73 / 74), with plain ones 128 x 256 by 5 % (layer 170 / 180);
+//   - if the choice would be 256 x 256: 2 experts, 4096 / 4096, room for 1200 rows, 800 tokens: 80 / 68.  Small products only with
 //     half a round (8 experts, 256 x 1024, room for 1200 rows: 3200 tokens -20 %, 7680 +20 %; 512 x 2048 -20 %, +6 %).
 enum TileShape { TILE_256x256, TILE_128x256, TILE_128x256_PAIRED, TILE_256x128, TILE_128x128 };
 struct TileCount {
@@ -452,8 +454,8 @@ static TileShape pick_by_rounds(const WsGemmArgs& a, const TileCount& c) {
     if (t128x128 < t256 && t128x128 < t128) return TILE_128x128;
     if (t128 < t256) return paired_ok ? TILE_128x256_PAIRED : TILE_128x256;
     // rows just past a multiple of 256 pay for a second, mostly empty tile (not with up to 256 rows in either product: there
-    // the 128-row tiles would stream every weight twice for a few rows; 64 experts x 157 rows at most, 125 on average: 279 ->
-    // 318; 16 experts with room for 130 rows and 1664 rows of a dense branch, 2048 / 8192: GEMM-1 156 -> 232)
+    // the 128-row tiles would stream every weight twice for a few rows; 64 experts x 157 rows at most, 125 on average: 233 ->
+    // 285; 16 experts with room for 130 rows and 1664 rows of a dense branch, 2048 / 8192: GEMM-1 137 -> 214)
     const double t_paired = (int)((c.tiles128 + 511) / 512) * 0.84;
     return paired_ok && c.min_rows > 256 && t_paired < t256 ? TILE_128x256_PAIRED : TILE_256x256;
 }
@@ -524,8 +526,8 @@ int tgemm_code(const WsGemmArgs& a, const WsGemmArgs* b, int epi) {
 // Two products in one launch: twice the tiles, so that a product with few columns can use a large tile.  Not with so few
 // that 256-row tiles of 128 columns leave CUs idle: the second products' outputs meet in a kernel of their own, rounded,
 // while the dense branch alone adds the experts' rows in its epilogue.  With groups of at most 128 rows in one of them
-// only if the other product alone could not fill the chip with 256 x 256 tiles: those keep their rate, and the 128-row
-// tiles that both would get are the less efficient ones.
+// only if the other product alone could not fill the chip with 256 x 256 tiles: those keep their rate in a launch of their own,
+// where the pair's choice counts 128-row tiles.
 static bool pair_fits(const WsGemmArgs& a, const WsGemmArgs& b) {
     if (a.K != b.K || a.N != b.N || (a.packed != 0) != (b.packed != 0) || a.ksplit != 1 || b.ksplit != 1) return false;
     if (a.max_rows > 128 && b.max_rows > 128)

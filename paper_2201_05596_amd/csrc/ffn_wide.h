@@ -3,16 +3,18 @@
 //
 // A work-group owns BM rows x 256 columns, each of its four waves every other 16-row sub-tile of 128 columns.  The
 // accumulators of a full tile take 256 registers per lane (the accumulation half of the file), the operand fragments of two
-// 32-deep steps the other half.
+// 32-deep steps the other half.  (The 256-row store and GELU instances have two or three values too many: written to scratch memory
+// before the main loop and read back in the epilogue.)
 //
 // What bounds it: on random operands the chip runs at its power limit (1.8 - 2.0 GHz instead of 2.4), so bytes moved per flop
 // count twice, as time and as clock.  128 x 128 per wave reads 64 KB of fragments from LDS per 32-deep step of a tile, eight
 // waves of 64 x 128 read 96.  Activations come in chunks of 64 k: a load takes 128 bytes of a row, a whole cache line; 32-deep
 // stages ask for every line twice (loads alone, 8192 x 4096 x 4096: 17.8 TB/s from L2 with 64-byte pieces, 23.2 with 128).  One
 // barrier per 64 k.  Products alone, against the eight-wave kernel of 32-deep stages: 8192 x 4096 x 4096 204 -> 190 us (1.45
-// PFLOP/s), 8 x 2048 x 4096 x 1024 105 -> 96, 64 groups of 256 x 4096 x 1024 146 -> 131, with bias + GELU 32 groups of 256 x 1024
-// x 4096 79 -> 76; 128-row tiles: 64 x 128 x 1024 x 4096 with GELU 122 -> 116, 32 x 256 x 4096 x 1024 94 -> 79, 8 x 1024 x
-// 4096 x 1024 63 -> 58.  Layers: 8192 tokens, 1024 / 4096, 32 experts beside a dense branch 314 -> 292 us, 64 experts 403 -> 377.
+// PFLOP/s; two of them in moe_expert_ffn 435 -> 394), 8 x 2048 x 4096 x 1024 105 -> 96, 64 groups of 256 x 4096 x 1024 146 -> 131,
+// with bias + GELU 32 groups of 256 x 1024 x 4096 79 -> 76; 128-row tiles: 64 x 128 x 1024 x 4096 with GELU 122 -> 116, 32 x 256 x
+// 4096 x 1024 94 -> 79, 8 x 1024 x 4096 x 1024 63 -> 58.  Layers: 8192 tokens, 1024 / 4096, 32 experts beside a dense branch 314 ->
+// 292 us, 64 experts 403 -> 377.
 // With one wave per SIMD nothing covers a wave's own waits, so every load, LDS read and scalar instruction sits between two
 // matrix instructions, and the epilogue's exp and rcp are taken eight at a time.
 #pragma once
@@ -77,7 +79,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt_barrier() {      // 
 __device__ __forceinline__ void gelu_tanh8(float (&v)[8]) {
     float p[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) p[j] = fmaf(v[j] * v[j], -0.10294324f, -2.3022082f);
+    for (int j = 0; j < 8; ++j) p[j] = fmaf(v[j] * v[j], kGelu3, kGelu1);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 8; ++j) p[j] = __builtin_amdgcn_exp2f(v[j] * p[j]);

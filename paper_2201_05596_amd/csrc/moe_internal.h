@@ -40,10 +40,10 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 
 // gelu_tanh(z) = 0.5 z (1 + tanh(u)), u = sqrt(2/pi) (z + 0.044715 z^3).  Since tanh(u) = 2 sigmoid(2u) - 1 this is
 // z sigmoid(2u) = z / (1 + exp(-2u)): one exp2 and one rcp on the hardware units, five multiply-adds.
+constexpr float kGelu1 = -2.3022082f, kGelu3 = -0.10294324f;   // -2u log2(e) = z (kGelu1 + kGelu3 z^2)
 __device__ __forceinline__ float gelu_tanh(float z) {
     const float z2 = z * z;
-    // -2u log2(e) = z (c1 + c3 z^2)
-    const float e = __builtin_amdgcn_exp2f(z * fmaf(z2, -0.10294324f, -2.3022082f));
+    const float e = __builtin_amdgcn_exp2f(z * fmaf(z2, kGelu3, kGelu1));
     return z * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
