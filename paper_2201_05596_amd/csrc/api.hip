@@ -288,7 +288,7 @@ int run_expert_ffn_f32(const moe_shape_t* s, const void* xin, const int32_t* row
                        const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
     GemmArgs a{};
     a.A = xin; a.B = W1; a.bias = b1; a.out = h; a.rows = rows; a.row_map = row_map;
-    a.max_rows = s->capacity; a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
+    a.max_rows = s->capacity; a.expect_rows = (int)(((long long)s->T * s->top_k + s->E - 1) / s->E); a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
     a.a_group_stride = s->capacity; a.o_group_stride = s->capacity;
     prof_pre(ST_GEMM1, st);
     int rc = launch_gemm_f32(a, EPI_GELU, st);

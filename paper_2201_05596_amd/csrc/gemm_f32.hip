@@ -10,16 +10,25 @@
 // every operand is a 16-byte access, no value is moved between lanes, and a lane ends with four consecutive columns
 // of four rows (16-byte stores).
 //
-// Two kernels:
-//   * f32_tile_kernel, groups of more than 32 rows: bound by the fp32 matrix cores (157 TFLOP/s).  64 x 128 or
+// Three kernels:
+//   * f32_split_kernel, groups of more than 32 rows and K beyond 128: bound by the bf16 matrix cores and the vector ALUs beside them.  An
+//     fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, so six of the nine products of pieces (the
+//     other three are below 2^-26 of it) give an fp32 product at 2.6 times the fp32 matrix rate.  64 x 128 tiles; pairs of
+//     waves of 64 x 64 split K, v_mfma_f32_32x32x16_bf16 (a matrix instruction keeps the vector ALU from issuing for 8 clocks, so
+//     that six others fit beside one of 32 clocks, two beside one of 16 x 16 x 32).  Activations are split once per tile and go
+//     through LDS, weights straight into the registers of the wave that multiplies them.  Errors against 64 bits, of the FFN:
+//     512/2048, 8 experts x 480 rows 6.6e-7 -> 3.9e-7, x 256 4.3e-7 -> 3.5e-7, 256/1024, 16 x 256 3.1e-7 -> 2.5e-7.
+//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP): 81 + 75 us on f32_tile_kernel, 58 + 50 here; with both operands' pieces
+//     through LDS 76 + 59 (every piece is written and read at half the rate it is used at).
+//   * f32_tile_kernel, the same with shorter K or at most 64 columns: bound by the fp32 matrix cores (157 TFLOP/s).  64 x 128 or
 //     128 x 64 tiles of four 32 x 64 sub-tiles, each by two waves that halve every 32-deep chunk of K between them (one
 //     work-group of eight waves has a compute unit to itself at the usual sizes, and one wave per SIMD left every LDS
 //     and barrier wait exposed).  Chunks are double-buffered in LDS, fragments in registers; loads, LDS reads and LDS
 //     writes of later chunks are placed between the matrix instructions of this one.  Weight rows of 256 bytes are read
 //     without bank conflicts as they are; activation rows are padded to 160 bytes (2 x odd 16-byte units), which
 //     sends the 16 lanes of one LDS pass (0-3, 12-15 of one kg, 4-11 of the next) to 16 different units.
-//     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP, 3.2 tiles per compute unit in GEMM-1, 0.8 in GEMM-2): 81 + 75 us
-//     (83 TFLOP/s; 2048 matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
+//     12.9 GFLOP in products of 512 x 2048 and 2048 x 512, 3.2 and 0.8 tiles per compute unit: 81 + 75 us (83 TFLOP/s; 2048
+//     matrix clocks of a chunk in about 2600).  Four waves with nothing placed: 88 + 101; on the
 //     vector ALUs, before: 162 + 465.  One work-group per compute unit, by its 132 registers (within 128 two fit): with two, a
 //     unit may hold two tiles while another has none, and a few rounds of tiles of unequal rows end later (layers, two / one: 1700
 //     tokens, 1024/1024, 8 experts with room for 430 rows 156 / 97 us; 1919 tokens, 1024/2048, 4 experts with room for 720, skewed
@@ -81,7 +90,7 @@ __device__ __forceinline__ const float* f32_arow(const GemmArgs& a, int g, int r
     return static_cast<const float*>(a.A) + (size_t)ar * a.K;
 }
 
-// ---- more than 32 rows per group -----------------------------------------------------------------------------
+// ---- more than 32 rows per group, short K or few columns ------------------------------------------------------
 constexpr int kFK = 32;                       // k per chunk
 constexpr int kFStride = kFK * 4 + 32;        // bytes per activation row in LDS
 
@@ -245,6 +254,304 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, cons
     else run(std::integral_constant<int, 0>());
 }
 
+// ---- more than 32 rows per group, long K: on the bf16 matrix instructions --------------------------------------
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x16_t __attribute__((ext_vector_type(16)));
+constexpr int kSRows = 64, kSCols = 128;      // of a tile: two waves of 64 columns
+
+// The matrix instruction takes pieces below 2^-126 for zero.  That cannot show in a sum of at least 2^-70 over operands of at most 2^20
+// (2^11 products, each off by less than 2^-105: 2^-24 of it); tiles with other sums or operands are multiplied unsplit.
+constexpr float kSplitSmallest = 0x1p-70f, kSplitLargest = 0x1p20f;
+
+// Four pairs of fp32 values as three times four pairs of bf16: a value is piece 0 + piece 1 + piece 2 exactly (3 x 8 significant
+// bits, each piece the nearest bf16 of what is left).  Infinities, NaN and values that round to infinity leave NaN in the later pieces.
+__device__ __forceinline__ void split_pairs(float (&x)[4][2], uint32_t (&piece)[3][4], float& largest) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) largest = fmaxf(fmaxf(largest, fabsf(x[i][0])), fabsf(x[i][1]));
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {                            // piece by piece, so that no instruction waits for the one before it
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            piece[q][i] = pack_bf16x2(x[i][0], x[i][1]);
+            asm("" : "+v"(piece[q][i]));                     // one conversion for both values, not one more for the first alone
+        }
+        if (q == 2) break;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            x[i][0] -= __uint_as_float(piece[q][i] << 16);
+            x[i][1] -= __uint_as_float(piece[q][i] & 0xffff0000u);
+        }
+    }
+}
+
+// 16 rows x 64 columns from (m0, n0) on the fp32 matrix instructions, straight from memory, finished: for the tiles that hold an
+// infinity, a NaN or an overflow, whose pieces do not add up.
+template <int EPI> __device__ void f32_unsplit(const GemmArgs& a, int g, int rows, int m0, int n0, int lane) {
+    const int c = lane & 15, kg = lane >> 4, n = n0 + c * 4;
+    const float* A = f32_arow(a, g, min(m0 + c, rows - 1));
+    const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N + min(n, a.N - 4);
+    f32x4_t acc[2][4] = {};                                  // every other 16 k: half as many steps that round a sum
+    for (int k0 = 0; k0 < a.K; k0 += 32) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k0 + h * 16 + kg * 4;              // K is a multiple of 4: a lane's four k are all inside or all outside
+            f32x4_t av = {}, bv[4] = {};
+            if (k < a.K) {
+                av = *reinterpret_cast<const f32x4_t*>(A + k);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) bv[j] = *reinterpret_cast<const f32x4_t*>(B + (size_t)(k + j) * a.N);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[h][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[j], bv[j][i], acc[h][i], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[0][i] += acc[1][i];
+    if (n >= a.N) return;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int row = m0 + kg * 4 + r;
+        if (row < rows) f32_finish<EPI>(a, g, row, n, f32x4_t{acc[0][0][r], acc[0][1][r], acc[0][2][r], acc[0][3][r]});
+    }
+}
+
+template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + 16; }   // partial sums and a flag; less before
+
+// P pairs of waves split K between them, 32 deep in turn; wave 2 q + wn has columns 64 wn .. + 63 of the tile and pair q's K.
+template <int P, int EPI>
+__global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a, const int n_tiles) {
+    constexpr int FRAG = 1024, PAIR = 2 * 2 * 3 * FRAG, BUF = P * PAIR, STEP = P * 32;      // STEP: k per step of the loop
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    static_assert(2 * BUF <= split_lds<P>() - 16, "two buffers of activation pieces");
+    int* const flag = reinterpret_cast<int*>(lds + split_lds<P>() - 16);
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, half = lane >> 5;
+    const int q = w >> 1, wn = w & 1;
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, P * 128);
+    // column tiles innermost: with a multiple of 8 of them all row tiles of a column tile run on one XCD and share its
+    // weights in that L2, and every XCD has the same work however unevenly the rows fall on the groups
+    const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles, g = blockIdx.y;
+    const int rows = f32_rows_of(a, g), m0 = mt * kSRows, n0 = nt * kSCols;
+    if (m0 >= rows) return;
+    if (tid == 0) *flag = 0;
+
+    // Activations: four threads take 32 k of a row, eight each, and put the pieces into LDS as fragments [row block][16 k][piece] of
+    // v_mfma_f32_32x32x16_bf16.  Row r's 16 bytes of k-octet o stand at (o % 2) * 32 + (r ^ x(o)): x sends the lanes of one LDS
+    // write to different banks.
+    auto swizzle = [](int o) { return (o & 1) * 10 + (o >> 1) * 4; };
+    const int oct = tid & 3, a_r = (tid & 127) >> 2;
+    const float* a_src[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a_src[i] = f32_arow(a, g, min(m0 + a_r + i * 32, rows - 1));      // rows past the end repeat the last one
+    char* const a_dst = lds + q * PAIR + (oct >> 1) * 3 * FRAG + ((oct & 1) * 32 + (a_r ^ swizzle(oct))) * 16;
+    auto load_a = [&](f32x4_t (&r)[2], int i, int t) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) r[h] = *reinterpret_cast<const f32x4_t*>(a_src[i] + min(t * STEP + q * 32 + oct * 8 + h * 4, a.K - 4));
+    };
+    float largest = 0.f;                                     // of the operands that this thread splits
+    // The matrix instruction rounds its sums down, not to nearest: every other pair of waves sums the products negated.
+    const float sign = q % 2 ? -1.f : 1.f;
+    // Past K the weights are zeros, the activations any of the row's (an infinity there makes NaN, and those sums are taken again).
+    auto store_a = [&](const f32x4_t (&r)[2], int i, int t) {
+        float x[4][2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = sign * r[j / 4][j % 4];
+        uint32_t u[3][4];
+        split_pairs(x, u, largest);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(a_dst + (t & 1) * BUF + (i * 6 + p) * FRAG) = make_uint4(u[p][0], u[p][1], u[p][2], u[p][3]);
+    };
+    // Weights go straight into the registers of the wave that multiplies them: eight rows of two neighbouring columns per lane, which
+    // are its column of two fragments, through a buffer descriptor that starts at the 16 rows of a half step (rows past K come
+    // back as zeros).
+    const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
+    const int b_off = (half * 8 * a.N + min(n0 + wn * 64 + c * 2, a.N - 2)) * 4;        // columns past the end: never stored
+    // rows 4 h .. 4 h + 3 of a lane's eight in half step s of step t; a half step's pieces of two columns
+    typedef uint32_t Pieces[2][3][4];
+    auto load_b = [&](float (&r)[8][2], int h, int t, int s) {
+        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+        const int k_in = __builtin_amdgcn_readfirstlane(min(t * STEP + q * 32 + s * 16, a.K));
+        const int left = __builtin_amdgcn_readfirstlane(min(a.K - k_in, 16));
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B + (size_t)k_in * a.N), 0, left * a.N * 4, 0x00027000);
+#pragma unroll
+        for (int j = 4 * h; j < 4 * h + 4; ++j) {
+            const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, b_off + j * a.N * 4, 0, 0));
+            r[j][0] = __uint_as_float(v[0]);
+            r[j][1] = __uint_as_float(v[1]);
+        }
+    };
+    auto split_b = [&](const float (&r)[8][2], int h, Pieces& f) {
+        float x[4][2];
+        uint32_t u[3][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {                        // pairs 0, 1: rows of the first column, 2, 3: of the second
+            x[i][0] = r[4 * h + i % 2 * 2][i / 2];
+            x[i][1] = r[4 * h + i % 2 * 2 + 1][i / 2];
+        }
+        split_pairs(x, u, largest);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) f[i / 2][p][2 * h + i % 2] = u[p][i];
+    };
+
+    const int steps = (a.K + STEP - 1) / STEP;
+    // The loop exists once per number MS of row blocks that hold rows.
+    auto run = [&](auto ms_count) {
+        constexpr int MS = decltype(ms_count)::value;
+        f32x16_t acc[MS][2];
+#pragma unroll
+        for (int i = 0; i < MS * 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[i / 2][i % 2][j] = 0.f;
+        auto read_a = [&](bf16x8_t (&f)[MS][3], int t, int s) {
+            const char* p0 = lds + (t & 1) * BUF + q * PAIR + s * 3 * FRAG + (half * 32 + (c ^ swizzle(2 * s + half))) * 16;
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) f[ms][p] = *reinterpret_cast<const bf16x8_t*>(p0 + (ms * 6 + p) * FRAG);
+        };
+        // the six products of pieces that reach into the 24 bits of the sum, the smallest first
+        auto multiply = [&](const bf16x8_t (&fa)[MS][3], const Pieces& fb, int from, int to) {
+            constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+            for (int t = from; t < to; ++t)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms) {
+                        const uint32_t* f = fb[i][PB[t]];
+                        acc[ms][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ms][PA[t]], __builtin_bit_cast(bf16x8_t, make_uint4(f[0], f[1], f[2], f[3])), acc[ms][i], 0, 0, 0);
+                    }
+        };
+        // Everything else goes into the shadow of the matrix instructions (32 clocks each, 24 of them free for six others), evenly: the
+        // waves of a SIMD go through a step together.  A third of a half step each time.  Loads come when what they overwrite has been
+        // split: any earlier they would get registers of their own, and copies.
+        auto place = [&](auto third) {
+            constexpr int TH = decltype(third)::value;
+            if (MS == 2) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                   // matrix
+                    if (TH == 0 && i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
+                    if (TH == 0 ? i < 4 : TH == 1 ? i >= 2 && i < 4 : i >= 2 && i < 6) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
+                    __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);                                   // vector ALU
+                    if (TH == 0 && i >= 5) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);            // LDS write
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // Step t enters with its first half's fragments in registers, t's activations and the first block of t + 1's in LDS; what is
+        // fetched is used a step later.
+        float b0[8][2], b1[8][2];
+        f32x4_t ra[2][2], first[2][2];
+        bf16x8_t fa0[MS][3], fa1[MS][3];
+        Pieces fb0, fb1;
+        // (issued in the loop's order: the loop waits for all but so many)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) load_a(first[i], i, 0);
+        load_b(b0, 0, 0, 0);
+        load_b(b0, 1, 0, 0);
+        load_a(ra[0], 0, 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) store_a(first[i], i, 0);
+        split_b(b0, 0, fb0);
+        split_b(b0, 1, fb0);
+        store_a(ra[0], 0, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(ra[1], 1, 1);
+        load_b(b1, 0, 0, 1);
+        load_b(b1, 1, 0, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(ra[0], 0, 2);
+        load_b(b0, 0, 1, 0);
+        lds_barrier();
+        read_a(fa0, 0, 0);
+        for (int t = 0; t < steps; ++t) {
+            multiply(fa0, fb0, 0, 2);
+            read_a(fa1, t, 1);
+            load_b(b0, 1, t + 1, 0);
+            store_a(ra[1], 1, t + 1);
+            place(std::integral_constant<int, 0>());
+            multiply(fa0, fb0, 2, 4);
+            load_a(ra[1], 1, t + 2);
+            split_b(b1, 0, fb1);
+            place(std::integral_constant<int, 1>());
+            multiply(fa0, fb0, 4, 6);
+            load_b(b1, 0, t + 1, 1);
+            split_b(b1, 1, fb1);
+            place(std::integral_constant<int, 2>());
+            lds_barrier();                               // t + 1 is in LDS, and everybody has the fragments of t
+            multiply(fa1, fb1, 0, 2);
+            read_a(fa0, t + 1, 0);
+            load_b(b1, 1, t + 1, 1);
+            store_a(ra[0], 0, t + 2);
+            place(std::integral_constant<int, 0>());
+            multiply(fa1, fb1, 2, 4);
+            load_a(ra[0], 0, t + 3);
+            split_b(b0, 0, fb0);
+            place(std::integral_constant<int, 1>());
+            multiply(fa1, fb1, 4, 6);
+            load_b(b0, 0, t + 2, 0);
+            split_b(b0, 1, fb0);
+            place(std::integral_constant<int, 2>());
+        }
+
+        // the pairs' sums meet in LDS, in the order of the pairs
+        lds_barrier();
+        float* const part = reinterpret_cast<float*>(lds);
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int r = ms * 32 + 8 * (j / 4) + 4 * half + j % 4;                  // D: that row, column lane % 32
+                *reinterpret_cast<float2*>(part + ((size_t)q * kSRows + r) * kSCols + wn * 64 + c * 2) = make_float2(acc[ms][0][j], acc[ms][1][j]);
+            }
+        lds_barrier();
+        constexpr int NV = MS * 32 * kSCols / 4 / (P * 128);
+        f32x4_t v[NV];
+        bool bad = !(largest <= kSplitLargest);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int r = (tid + i * P * 128) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
+            v[i] = *reinterpret_cast<const f32x4_t*>(part + (size_t)r * kSCols + n);
+#pragma unroll
+            for (int p = 1; p < P; ++p) {
+                const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + ((size_t)p * kSRows + r) * kSCols + n);
+                v[i] = p % 2 ? v[i] - u : v[i] + u;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[i][j]) <= 3.4028234e38f) || (fabsf(v[i][j]) < kSplitSmallest && v[i][j] != 0.f);
+        }
+        if (__ballot(bad)) *flag = 1;
+        lds_barrier();
+        if (*flag) {
+            for (int i = q; i < 4; i += P) f32_unsplit<EPI>(a, g, rows, m0 + i * 16, n0 + wn * 64, lane);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int r = (tid + i * P * 128) / (kSCols / 4), n = n0 + tid % (kSCols / 4) * 4;
+            if (m0 + r < rows && n < a.N) f32_finish<EPI>(a, g, m0 + r, n, v[i]);
+        }
+    };
+    if (rows - m0 > 32) run(std::integral_constant<int, 2>());
+    else run(std::integral_constant<int, 1>());
+}
+
+template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
+    static bool attr_set = false;            // one flag per instantiation
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_split_kernel<P, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<P>()) != hipSuccess)
+            return MOE_ERR_HIP;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((f32_split_kernel<P, EPI>), grid, dim3(P * 128), split_lds<P>(), s, a, n_tiles);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 // ---- at most 32 rows per tile --------------------------------------------------------------------------------
 constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
@@ -330,10 +637,9 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
     // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
-    // flop, so the line is where two of them on every unit hold all (layers, us, second product on 64 x 128 / on 32 x 64: 1024
-    // tokens, 512/2048, 8 experts, 256 small tiles 106 / 67; 300 tokens, 4 experts with a dense branch, both second products
-    // 196 / 110; 2048 tokens, 8 experts, 512 tiles 124 / 105; 1536 tokens, top-2, 960 tiles 165 / 203.  First products: 700
-    // tokens, 256/1024, 16 experts, 512 tiles 65.4 / 62.9; 512 tokens, 512/2048, 4 experts, 640 tiles 104 / 108).
+    // flop, so the line is where two of them on every unit hold all (products, us, 32 x 64 / 64 x 128 split: 2048 x 512, 256 small
+    // tiles 27 / 35, 512 tiles 58 / 39 full, but 27 / 36 where skewed routing leaves half of them empty, 640 tiles 84 / 44; 512 x
+    // 2048, 256 tiles 9.5 / 13.7, 512 tiles 18.2 / 14.9, 640 24.4 / 15.3; 256 x 1024, 512 tiles 10.3 / 10.8, 640 13.5 / 11.0).
     const long long small_tiles = ((long long)a.max_rows + 31) / 32 * (((long long)a.N + 63) / 64) * a.G;
     const bool few = a.max_rows <= 32 || small_tiles <= 512 || a.N >= 1 << 24;
     const bool narrow = a.N <= 64;                               // one 64-column tile: all four pairs along the rows
@@ -341,12 +647,22 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
     const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;
     if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
+    // Split pieces or fp32 products, two small or one large work-group per compute unit (products, us, fp32 / split with four pairs / with
+    // two): the split kernel's set-up and epilogue want a long K (8 groups x 2000 rows 64 x 256 12.7 / 19.5 / 13.6; 31 x 265, 128 x 512
+    // 23.4 / 27.6 / 24.2; 4 x 2000, 200 x 800 43.6 / 47.9 / 38.3; 8 x 2000, 200 x 100 12.4 / 12.8 / 13.2, 256 x 128 14.1 / 13.3 / 13.6) and
+    // more than half a tile of columns (8 x 8192, 256 x 64 29 / 47 / 35).  Two pairs leave room for a second work-group, whose products run
+    // under the first one's set-up and epilogue, but two of few tiles may meet on a unit while another has none (8 x 384, 512 x 2048,
+    // 768 tiles 60 / 50 / 44; 4 x 480 with room for 720, 2048 x 1024, 256 tiles 69 / 50 / 75; 31 x 132, 2048 x 512, 372 tiles 130 / 84 / 83).
+    const int expect = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
+    const long long live = (long long)a.G * ((expect + 63) / 64) * n_tiles;      // tiles if the rows fall evenly on the groups
     const dim3 grid((unsigned)tiles, (unsigned)a.G), block(512);
     static_assert(kFWaves * 64 == 512, "all kernels have the same work-group");
+    static_assert(kSRows == 64 && kSCols == 128, "the same tile");
     if (few && tm == 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles);
     else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
     else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
-    else hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
+    else if (a.K <= (live > 256 ? 128 : 255)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
+    else return live > 256 ? launch_split<2, EPI>(a, grid, n_tiles, s) : launch_split<4, EPI>(a, grid, n_tiles, s);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 

@@ -136,6 +136,7 @@ struct GemmArgs {
     const int32_t* row_map;   // [G, max_rows] A-row index per (g, r), or nullptr
     int32_t fixed_rows;
     int32_t max_rows;         // upper bound of rows(g): sizes the grid
+    int32_t expect_rows;      // rows of a group if the tokens fall evenly on them; 0: max_rows
     int32_t G, K, N;
     int64_t a_group_stride;   // in rows; A-row of (g, r) = g*a_group_stride + r when row_map == nullptr
     int64_t o_group_stride;   // in rows; out-row of (g, r) = g*o_group_stride + r

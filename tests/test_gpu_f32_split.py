@@ -1,0 +1,70 @@
+"""The fp32 kernel on split operands (more than 512 tiles of 32 x 64, K beyond 128, more than 64 columns) at the edges of its tiles and
+steps, and on operands that the split does not hold: infinities, NaN, values whose pieces are below or beyond the range."""
+import pytest
+import torch
+
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+EPS = 2.0 ** -24
+
+
+def _ffn(E, C, d, f, rows, edit=None, scale=1.0):
+    """moe_expert_ffn and the same in 64 bits; h in 64 bits too."""
+    m, g = U.amd(), torch.Generator(device="cuda").manual_seed(E * C + d)
+    n = lambda *s, std: torch.empty(s, device="cuda").normal_(0.0, std, generator=g)
+    xe, W1, W2, b1, b2 = n(E, C, d, std=scale), n(E, d, f, std=0.05 / scale), n(E, f, d, std=0.05), n(E, f, std=0.05), n(E, d, std=0.05)
+    if edit:
+        edit(xe, W1, W2)
+    r = torch.tensor(rows, dtype=torch.int32, device="cuda")
+    shape = m.make_shape(C, d, f, E, 1, C, "f32")
+    ye = torch.full_like(xe, 12345.0)
+    m.moe_expert_ffn(shape, xe, r, W1, b1, W2, b2, ye, m.alloc_workspace(shape, "cuda"))
+    torch.cuda.synchronize()
+    ref = torch.empty(E, C, d, dtype=torch.float64, device="cuda")
+    for e in range(E):
+        z = xe[e].double() @ W1[e].double() + b1[e].double()
+        ref[e] = torch.nn.functional.gelu(z, approximate="tanh") @ W2[e].double() + b2[e].double()
+    return ye, ref
+
+
+# rows with room for, K and N off the steps (64 and 128 k), half steps and tiles (64 rows, 128 columns); both numbers of wave pairs
+@pytest.mark.parametrize("E,C,d,f,rows", [
+    (4, 1100, 132, 260, [1100, 1, 33, 64]), (16, 70, 260, 516, [70, 65, 64, 63, 32, 33, 31, 1, 0] + [70] * 7), (2, 700, 516, 1028, [700, 129]),
+    (1, 2100, 148, 1156, [2049]), (8, 600, 196, 132, [600, 97, 96, 577, 0, 128, 300, 16]),
+])
+def test_edges(E, C, d, f, rows):
+    print(f"case E={E} C={C} d={d} f={f}", flush=True)
+    ye, ref = _ffn(E, C, d, f, rows)
+    for e, r in enumerate(rows):
+        if r:                                            # fp32 sums of f terms with random signs, each step rounded by up to 2^-23 of the sum
+            assert (ye[e, :r].double() - ref[e, :r]).abs().max() <= 2 * f ** 0.5 * 2 * EPS * ref[e, :r].abs().max()
+        assert bool((ye[e, r:] == 12345.0).all())
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
+def test_values_beyond_the_split(value):
+    """In one weight and one activation: what a sum of the same products holds; other rows, columns and tiles as without."""
+    print(f"case {value}", flush=True)
+    E, C, d, f = 4, 640, 256, 1024
+
+    def edit(xe, W1, W2):
+        W2[1, 700, 130] = value
+        xe[2, 333, 7] = value
+    clean, _ = _ffn(E, C, d, f, [C] * E)
+    ye, ref = _ffn(E, C, d, f, [C] * E, edit)
+    hit = torch.zeros_like(ye, dtype=torch.bool)
+    hit[1, :, 130], hit[2, 333] = True, True
+    bad = ~torch.isfinite(ref) | (ref.abs() > 3.4e38)
+    assert bool((bad <= hit).all())
+    assert bool((torch.isfinite(ye) == ~bad)[hit].all())
+    assert torch.equal(torch.isnan(ye), torch.isnan(ref)) or value == 3.4e38     # beyond the range: infinities of either sign may meet
+    assert (ye - clean)[~hit].abs().max() <= 4 * f ** 0.5 * EPS * clean.abs().max()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -118, 2.0 ** -100, 2.0 ** 100])
+def test_far_from_one(scale):
+    """Activations whose second and third pieces the matrix instruction would take for zero, under large weights; and the reverse."""
+    print(f"case {scale}", flush=True)
+    ye, ref = _ffn(4, 640, 256, 1024, [640] * 4, scale=scale)
+    assert (ye.double() - ref).abs().max() <= 2 * 1024 ** 0.5 * 2 * EPS * ref.abs().max()
