@@ -71,9 +71,11 @@ __global__ __launch_bounds__(256) void gate_prepare_kernel(const float* __restri
 
 template <int MA, int NE> struct GateCfg {
     static constexpr int PER = MA + 3 * NE;                                  // 16-byte loads per lane and k-block
-    // k-blocks held in registers: as many as fit beside the accumulators (4 registers per load and per tile)
-    static constexpr int D_WANT = 48 / PER < 3 ? 3 : (48 / PER > 6 ? 6 : 48 / PER);
-    static constexpr int D = 4 * (MA * NE + D_WANT * PER) <= 400 ? D_WANT : 2;
+    // k-blocks held in registers: as many as keep the CU's loads busy and divide the k-blocks of the usual widths (8 per wave with d =
+    // 1024).  The last D of a wave fetch nothing; re-reading the last one instead, 3 to 6 deep, was up to half of all loads (8192
+    // tokens, d = 1024, us: 32 experts 15.5 -> 9.4, 64 16.0 -> 13.4; 4001 tokens, top-2 of 32 13.6 -> 10.0; 777 tokens, logits
+    // alone, 128 experts 7.6 -> 5.4; 128 experts stay at 20: 0.85 MB per CU at 50 GB/s).
+    static constexpr int D = PER <= 16 ? 4 : 2;
 };
 
 // tile: MA token tiles (16 tokens each) x NE expert tiles; blockIdx.x = token tile, blockIdx.y = expert group;
@@ -145,16 +147,10 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
 #pragma unroll
             for (int i = 0; i < 3 * NE; ++i) st.r[MA + i] = *reinterpret_cast<const u32x4_t*>(bp + i * kFragElems);
         };
-        // `live` is false for the steps past the last k-block of a partly filled round: their token
-        // fragments are replaced by zeros, so the loop needs no branches.
-        auto mma = [&](const Stage& st, bool live) {
+        auto mma = [&](const Stage& st) {
             bf16x8_t af[MA];
 #pragma unroll
-            for (int m = 0; m < MA; ++m) {
-                const u32x4_t v = st.r[m];
-                const u32x4_t z = {live ? v.x : 0u, live ? v.y : 0u, live ? v.z : 0u, live ? v.w : 0u};
-                af[m] = __builtin_bit_cast(bf16x8_t, z);
-            }
+            for (int m = 0; m < MA; ++m) af[m] = __builtin_bit_cast(bf16x8_t, st.r[m]);
 #pragma unroll
             for (int e = 0; e < NE; ++e)
 #pragma unroll
@@ -167,18 +163,22 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
 
         Stage st[D];
 #pragma unroll
-        for (int s = 0; s < D - 1; ++s) load(st[s], s);
-        for (int s0 = 0; s0 < nkb; s0 += D) {
+        for (int s = 0; s < D; ++s) load(st[s], s);
+        int i = 0;
+        for (; i + D < nkb; i += D) {                             // the last round fetches nothing
 #pragma unroll
-            for (int i = 0; i < D; ++i) {
-                // the scheduling barriers pin "fetch the block D-1 ahead, then use the oldest": left alone,
+            for (int s = 0; s < D; ++s) {
+                // the scheduling barriers pin "use the oldest, then fetch the block D ahead": left alone,
                 // the compiler sinks the loads to their first use
-                load(st[(i + D - 1) % D], s0 + i + D - 1);
+                mma(st[s]);
                 __builtin_amdgcn_sched_barrier(0);
-                mma(st[i], s0 + i < nkb);
+                load(st[s], i + s + D);
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
+#pragma unroll
+        for (int s = 0; s < D; ++s)
+            if (i + s < nkb) mma(st[s]);
     }
 
     // ---- sum of the four partial tiles, always as (w0 + w2) + (w1 + w3) ------------------------------
@@ -344,7 +344,8 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
         bf16x8_t a[kDecodeBlocks][MA], b[kDecodeBlocks][3];
 #pragma unroll
         for (int i = 0; i < kDecodeBlocks; ++i) {
-            const int kb = w + min(i0 + i, nkb - 1) * kDecodeWaves;          // past the end: in bounds, not multiplied
+            if (i0 + i >= nkb) break;
+            const int kb = w + (i0 + i) * kDecodeWaves;
 #pragma unroll
             for (int m = 0; m < MA; ++m) a[i][m] = *reinterpret_cast<const bf16x8_t*>(a_src[m] + kb * kKB);
 #pragma unroll

@@ -609,7 +609,7 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
 #pragma unroll
     for (int s = 0; s < kFAhead; ++s) load(st[s], w + s * kFWaves);        // past the end: in bounds (clamped), never multiplied
     int q = 0;
-    for (; q + kFAhead <= mine; q += kFAhead) {
+    for (; q + kFAhead < mine; q += kFAhead) {               // the last round fetches nothing
 #pragma unroll
         for (int s = 0; s < kFAhead; ++s) {
             multiply(st[s], w + (q + s) * kFWaves);
