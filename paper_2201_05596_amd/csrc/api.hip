@@ -290,14 +290,21 @@ int run_expert_ffn_f32(const moe_shape_t* s, const void* xin, const int32_t* row
     a.A = xin; a.B = W1; a.bias = b1; a.out = h; a.rows = rows; a.row_map = row_map;
     a.max_rows = s->capacity; a.expect_rows = (int)(((long long)s->T * s->top_k + s->E - 1) / s->E); a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
     a.a_group_stride = s->capacity; a.o_group_stride = s->capacity;
+    GemmArgs b = a;
+    b.A = h; b.B = W2; b.bias = b2; b.out = out; b.row_map = nullptr; b.K = s->d_ffn; b.N = s->d_model;
+    b.scatter_map = scatter_map; b.T = s->T; b.gate_w = gate_w; b.slot_idx = slot_idx; b.top_k = s->top_k;
+    const int epi = scatter_map ? EPI_SCATTER : EPI_STORE;
     prof_pre(ST_GEMM1, st);
+    if (ffn_f32_fused(a)) {                   // counted under ST_GEMM1
+        const int rc = launch_ffn_f32(a, b, epi, st);
+        prof_mark(ST_GEMM1, st);
+        return rc;
+    }
     int rc = launch_gemm_f32(a, EPI_GELU, st);
     prof_mark(ST_GEMM1, st);
     if (rc != MOE_OK) return rc;
-    a.A = h; a.B = W2; a.bias = b2; a.out = out; a.row_map = nullptr; a.K = s->d_ffn; a.N = s->d_model;
-    a.scatter_map = scatter_map; a.T = s->T; a.gate_w = gate_w; a.slot_idx = slot_idx; a.top_k = s->top_k;
     prof_pre(ST_GEMM2, st);
-    rc = launch_gemm_f32(a, scatter_map ? EPI_SCATTER : EPI_STORE, st);
+    rc = launch_gemm_f32(b, epi, st);
     prof_mark(ST_GEMM2, st);
     return rc;
 }
@@ -309,14 +316,20 @@ int run_dense_f32(const moe_shape_t* s, const void* x, const void* Wd1, const vo
     GemmArgs a{};
     a.A = x; a.B = Wd1; a.bias = bd1; a.out = hd; a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1;
     a.K = s->d_model; a.N = s->d_ffn;
+    GemmArgs b = a;
+    b.A = hd; b.B = Wd2; b.bias = bd2; b.out = out; b.K = s->d_ffn; b.N = s->d_model;
+    b.ye = ye; b.expert_idx = expert_idx; b.slot_idx = slot_idx; b.gate_w = gate_w; b.top_k = s->top_k; b.C = s->capacity;
     prof_pre(ST_DENSE1, st);
+    if (ffn_f32_fused(a)) {                   // counted under ST_DENSE1
+        const int rc = launch_ffn_f32(a, b, EPI_COMBINE, st);
+        prof_mark(ST_DENSE1, st);
+        return rc;
+    }
     int rc = launch_gemm_f32(a, EPI_GELU, st);
     prof_mark(ST_DENSE1, st);
     if (rc != MOE_OK) return rc;
-    a.A = hd; a.B = Wd2; a.bias = bd2; a.out = out; a.K = s->d_ffn; a.N = s->d_model;
-    a.ye = ye; a.expert_idx = expert_idx; a.slot_idx = slot_idx; a.gate_w = gate_w; a.top_k = s->top_k; a.C = s->capacity;
     prof_pre(ST_DENSE2, st);
-    rc = launch_gemm_f32(a, EPI_COMBINE, st);
+    rc = launch_gemm_f32(b, EPI_COMBINE, st);
     prof_mark(ST_DENSE2, st);
     return rc;
 }

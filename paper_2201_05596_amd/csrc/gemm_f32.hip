@@ -10,7 +10,7 @@
 // every operand is a 16-byte access, no value is moved between lanes, and a lane ends with four consecutive columns
 // of four rows (16-byte stores).
 //
-// Three kernels:
+// Four kernels:
 //   * f32_split_kernel, groups of more than 32 rows and K beyond 128: bound by the bf16 matrix cores and the vector ALUs beside them.  An
 //     fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, so six of the nine products of pieces (the
 //     other three are below 2^-26 of it) give an fp32 product at 2.6 times the fp32 matrix rate.  64 x 128 tiles; pairs of
@@ -34,6 +34,7 @@
 //     tokens, 1024/1024, 8 experts with room for 430 rows 156 / 97 us; 1919 tokens, 1024/2048, 4 experts with room for 720, skewed
 //     185 / 160; 1000 tokens, 1024/4096, 16 experts, skewed 202 / 188).  Many full tiles would be a little faster with two (8192
 //     tokens, 512/2048, 8 experts 294 / 303).
+//   * f32_ffn_kernel, d_model up to 64: both products in one launch;
 //   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products with few tiles and those of 2^24 columns or
 //     more, whose 32-row chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
@@ -634,6 +635,129 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
     f32_finish<EPI>(a, g, m0 + row, n, v);
 }
 
+// ---- both products of a narrow FFN -------------------------------------------------------------------------
+// d_model up to 64: a work-group owns 16 MS rows and does both products; the intermediate never leaves its wave.  Wave w computes
+// columns 32 w .. + 31 of every 256 of the first product, two per lane, and they are just the K that it multiplies in the second: the
+// rows turn from one operand order into the other through a piece of LDS of its own, no barrier until the waves' sums meet.  All
+// weights of a round are asked for before the first is used.  Bound by latency with few rows, by the fp32 matrix cores with many.
+template <int MS, int EPI>
+__global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs a, const GemmArgs b) {
+    constexpr int HS = 36;                                       // floats per row of a wave's piece: 16 rows, 16 different units
+    __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves][MS * 16][16];
+    static_assert(HS * 4 <= 16 * 16, "a wave's rows of 32 columns fit where its sums go");
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (EPI == EPI_SCATTER) f32_zero_dropped(b, tid, kFWaves * 64);
+    const int g = blockIdx.y, rows = f32_rows_of(a, g), m0 = blockIdx.x * MS * 16;
+    if (m0 >= rows) return;
+    const int d = a.K, f = a.N;
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    typedef float f32x2_t __attribute__((ext_vector_type(2)));
+
+    f32x4_t x[4][MS];                                            // K of the first product: 16 deep blocks, zeros past it on both sides
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms) {
+        const float* src = f32_arow(a, g, min(m0 + ms * 16 + c, rows - 1));        // rows past the end repeat the last one
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f32x4_t v = *reinterpret_cast<const f32x4_t*>(src + min(q * 16 + kg * 4, d - 4));
+            x[q][ms] = q * 16 + kg * 4 < d ? v : zero;
+        }
+    }
+    const float* W1 = static_cast<const float*>(a.B) + (size_t)g * d * f;
+    const float* W2 = static_cast<const float*>(b.B) + (size_t)g * f * d + min(c * 4, d - 4);
+    const float* bias1 = static_cast<const float*>(a.bias);
+    float* const hs = reinterpret_cast<float*>(&part[w][0][0]);
+    f32x4_t acc[MS][4];
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[ms][i] = zero;
+    for (int n0 = w * 32; n0 < f; n0 += kFWaves * 32) {
+        const int n = n0 + c * 2, nc = min(n, f - 2);            // f is a multiple of 4: both columns inside or both outside
+        f32x2_t w1[4][4], bv = {0.f, 0.f};
+        f32x4_t w2[2][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = q * 16 + kg * 4;
+                const f32x2_t v = *reinterpret_cast<const f32x2_t*>(W1 + (size_t)min(k + j, d - 1) * f + nc);
+                w1[q][j] = k < d ? v : f32x2_t{0.f, 0.f};
+            }
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int k = n0 + q * 16 + kg * 4;
+                const f32x4_t v = *reinterpret_cast<const f32x4_t*>(W2 + (size_t)min(k + j, f - 1) * d);
+                w2[q][j] = k < f ? v : zero;
+            }
+        if (bias1) bv = *reinterpret_cast<const f32x2_t*>(bias1 + (size_t)g * f + nc);
+        f32x4_t h[4][MS][2];                                     // every 16 k on their own: as few steps that round a sum as in the split products
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms) h[q][ms][0] = h[q][ms][1] = zero;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms) h[q][ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][ms][j], w1[q][j][i], h[q][ms][i], 0, 0, 0);
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) h[0][ms][i] = (h[0][ms][i] + h[1][ms][i]) + (h[2][ms][i] + h[3][ms][i]);
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {                        // D: rows 4 kg + r, column c
+                const f32x2_t v = {gelu_tanh(h[0][ms][0][r] + bv[0]), gelu_tanh(h[0][ms][1][r] + bv[1])};
+                *reinterpret_cast<f32x2_t*>(hs + (ms * 16 + kg * 4 + r) * HS + c * 2) = n < f ? v : f32x2_t{0.f, 0.f};
+            }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();                         // another lane's values, the same wave's LDS operations: in order
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            f32x4_t hv[MS];
+#pragma unroll
+            for (int ms = 0; ms < MS; ++ms) hv[ms] = *reinterpret_cast<const f32x4_t*>(hs + (ms * 16 + c) * HS + q * 16 + kg * 4);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int ms = 0; ms < MS; ++ms) acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(hv[ms][j], w2[q][j][i], acc[ms][i], 0, 0, 0);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
+    __syncthreads();
+    const int row = tid / 16, n = (tid & 15) * 4;
+    if (m0 + row >= rows || row >= MS * 16 || n >= d) return;
+    f32x4_t v = part[0][row][tid & 15];
+#pragma unroll
+    for (int s = 1; s < kFWaves; ++s) v += part[s][row][tid & 15];
+    f32_finish<EPI>(b, g, m0 + row, n, v);
+}
+
+template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
+    const int tm = a.max_rows <= 16 ? 16 : 32;
+    const long long tiles = ((long long)a.max_rows + tm - 1) / tm;
+    if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)tiles, (unsigned)a.G), block(kFWaves * 64);
+    if (tm == 16) hipLaunchKernelGGL((f32_ffn_kernel<1, EPI>), grid, block, 0, s, a, b);
+    else hipLaunchKernelGGL((f32_ffn_kernel<2, EPI>), grid, block, 0, s, a, b);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
     // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
@@ -667,6 +791,22 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// d_model up to 64 in one launch, against the two products (layers, us): d_ffn = 256, 8 experts, 256 tokens 24.3 / 21.1, 2048 27.9 /
+// 24.2, 20000 52.5 / 46.1; 31 experts, top-2, 2048 tokens 38.5 / 31.8; 20/64 beside a dense branch, 1000 tokens 36.5 / 28.2.  Beyond
+// 1024 row tiles the products on their own are as fast (65536 tokens 96.1 / 97.2), and with a longer d_ffn one work-group's rounds
+// are the longer chain (256 tokens, 512: 25.0 / 26.0, 1024: 30.2 / 36.1).
+bool ffn_f32_fused(const GemmArgs& a) { return a.K <= 64 && a.N <= 256 && (long long)a.G * ((a.max_rows + 31) / 32) <= 1024; }
+int launch_ffn_f32(const GemmArgs& a, const GemmArgs& b, int epi, hipStream_t s) {
+    if (a.max_rows <= 0 || a.G <= 0) return MOE_OK;
+    if (a.K % 4 || a.N % 4 || !ffn_f32_fused(a) || b.K != a.N || b.N != a.K) return MOE_ERR_INVALID_ARG;
+    switch (epi) {
+        case EPI_STORE: return launch_ffn_epi<EPI_STORE>(a, b, s);
+        case EPI_SCATTER: return launch_ffn_epi<EPI_SCATTER>(a, b, s);
+        case EPI_COMBINE: return launch_ffn_epi<EPI_COMBINE>(a, b, s);
+        default: return MOE_ERR_INVALID_ARG;
+    }
+}
 
 int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s) {
     if (a.max_rows <= 0 || a.G <= 0) return MOE_OK;

@@ -153,6 +153,9 @@ struct GemmArgs {
     int32_t C;
 };
 int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s);
+// both products of an FFN in one launch: a is the first, b the second on its output (a.out and b.A are not used); epi: the second's
+bool ffn_f32_fused(const GemmArgs& a);
+int launch_ffn_f32(const GemmArgs& a, const GemmArgs& b, int epi, hipStream_t s);
 
 // bf16 MFMA weight-streaming grouped GEMM (ffn_mfma.hip).
 struct WsGemmArgs {
