@@ -229,12 +229,10 @@ int static_scratch(void** out) {
 
 // gate logits: bf16 tokens go to the bf16 matrix cores when the shape allows, everything else to the fp32 ones.
 // With MOE_FLAG_PACKED_GATE, Wg is the buffer moe_pack_gate wrote and no weight is split at call time.
-int run_gate_logits(const moe_shape_t* s, const void* x, const float* Wg, const float* bg, float* logits, void* ws,
-                    const WsLayout& L, hipStream_t st) {
+int run_gate_logits(const moe_shape_t* s, const void* x, const float* Wg, const float* bg, float* logits, hipStream_t st) {
     const bool packed = s->flags & MOE_FLAG_PACKED_GATE;
     if (s->dtype == MOE_BF16 && gate_bf16_supported(s->d_model, s->E))
-        return launch_gate_logits_bf16(x, packed ? nullptr : Wg, packed ? Wg : nullptr, bg, logits, s->T, s->d_model, s->E,
-                                       at<void>(ws, L.wg_frags), st);
+        return launch_gate_logits_bf16(x, packed ? nullptr : Wg, packed ? Wg : nullptr, bg, logits, s->T, s->d_model, s->E, st);
     return launch_gate_logits(x, s->dtype, Wg, bg, logits, s->T, s->d_model, s->E, st);
 }
 
@@ -266,12 +264,12 @@ int run_gate(const moe_shape_t* s, const void* x, const float* Wg, const float* 
         if (profile) prof_pre(ST_LOGITS, st);
         rc = launch_gate_decode(x, packed ? nullptr : Wg, packed ? Wg : nullptr, bg, logits, s->T, s->d_model, s->E,
                                 s->top_k, s->capacity, expert_idx, slot_idx, gate_w, rows, slot_token, order,
-                                at<void>(ws, L.wg_frags), at<uint64_t>(ws, L.flags), next_call_tag(), st);
+                                at<uint64_t>(ws, L.flags), next_call_tag(), st);
         if (profile) prof_mark(ST_LOGITS, st);
         return rc;
     }
     if (profile) prof_pre(ST_LOGITS, st);
-    rc = run_gate_logits(s, x, Wg, bg, logits, ws, L, st);
+    rc = run_gate_logits(s, x, Wg, bg, logits, st);
     if (profile) prof_mark(ST_LOGITS, st);
     if (rc != MOE_OK) return rc;
     if (profile) prof_pre(ST_ROUTE, st);

@@ -12,8 +12,9 @@
 //
 // Kernels:
 //   * gate_prepare_kernel writes the three pieces as ready-made MFMA B fragments (1 KB each: lane l
-//     holds k = 8*(l/16)..+7 of expert column l%16), ordered [k-block][expert tile][piece]: into the
-//     workspace at every call, or once into a buffer the caller keeps (packed gate weights);
+//     holds k = 8*(l/16)..+7 of expert column l%16), ordered [k-block][expert tile][piece]: once into a buffer the caller
+//     keeps (packed gate weights), or into the workspace at every call of 2048 tokens or more; with fewer, kernels that
+//     are given plain weights split them as they go;
 //   * gate_bf16_kernel: a work-group owns a tile of 16*MA tokens x 16*NE experts; its four waves
 //     split the k-blocks (wave w takes blocks w, w+4, ...) and each computes the whole tile for its
 //     blocks, so no operand byte is fetched twice by a work-group.  Every operand fragment is one
@@ -69,6 +70,42 @@ __global__ __launch_bounds__(256) void gate_prepare_kernel(const float* __restri
     }
 }
 
+// Eight weights of one column (k = 8*(lane/16) .. +7) as gate_prepare_kernel splits them, for the kernels that read plain weights: a
+// call of few tokens reads each weight so seldom that a launch for the split costs more than splitting as it goes (layers on plain
+// weights, us: one token, 1024/4096, 128 experts 34.6 -> 27.8; 200 tokens of 32 112.6 -> 107.9; 2000 of 128 370 -> 362).
+__device__ __forceinline__ void split_weights(const float (&v)[8], bf16x8_t (&piece)[3]) {
+    float x[8];
+    uint32_t u[3][4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = v[j];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            u[q][i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
+            asm("" : "+v"(u[q][i]));                              // one conversion for both values
+        }
+#pragma unroll
+        for (int i = 0; i < 4 && q < 2; ++i) {
+            x[2 * i] -= __uint_as_float(u[q][i] << 16);           // exact
+            x[2 * i + 1] -= __uint_as_float(u[q][i] & 0xffff0000u);
+        }
+        piece[q] = __builtin_bit_cast(bf16x8_t, make_uint4(u[q][0], u[q][1], u[q][2], u[q][3]));
+    }
+}
+// the weights themselves: column n of k-block kb, zero past E; Wg is [d, E]
+__device__ __forceinline__ void load_weights(const float* __restrict__ Wg, int kb, int kg, int n, int E, float (&v)[8]) {
+    const float* p = Wg + (size_t)(kb * kKB + kg * 8) * E + min(n, E - 1);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[(size_t)j * E];
+}
+__device__ __forceinline__ void zero_past(int n, int E, float (&v)[8]) {
+    if (n >= E) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = 0.f;
+    }
+}
+
 template <int MA, int NE> struct GateCfg {
     static constexpr int PER = MA + 3 * NE;                                  // 16-byte loads per lane and k-block
     // k-blocks held in registers: as many as keep the CU's loads busy and divide the k-blocks of the usual widths (8 per wave with d =
@@ -91,8 +128,8 @@ template <int MA, int NE, int K> struct GateLds {
     static constexpr int BYTES = MAIN + ROUTE;
 };
 
-template <int MA, int NE, int K>
-__device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags,
+template <int MA, int NE, int K, bool PLAIN>
+__device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ Wg,
                                                const float* __restrict__ bg, float* __restrict__ logits, int T, int d,
                                                int E, int ET, int32_t* __restrict__ expert_idx,
                                                int32_t* __restrict__ slot_idx, float* __restrict__ gate_w,
@@ -129,26 +166,43 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
 #pragma unroll
         for (int m = 0; m < MA; ++m)
             a_src[m] = x + (size_t)min(t0 + 16 * m + (lane & 15), T - 1) * d + (lane >> 4) * 8;
-        const uint16_t* b_src = frags + (size_t)et0 * 3 * kFragElems + lane * 8;
+        const uint16_t* b_src = PLAIN ? nullptr : frags + (size_t)et0 * 3 * kFragElems + lane * 8;
         const size_t b_kb_stride = (size_t)ET * 3 * kFragElems;
+        const int n0 = et0 * 16 + (lane & 15);                    // PLAIN: this lane's column of the first expert tile
 
         // Operands of one k-block: A fragments straight from the token rows, B fragments as stored.
         // Plain loads: the compiler tracks their completion.  (Loads issued from inline asm with
         // hand-placed waits are NOT an option here: the compiler regards an asm output as valid at once
         // and, under register pressure, copies it elsewhere before the data has arrived.)
         struct Stage {
-            u32x4_t r[PER];                                       // MA token fragments, then 3*NE weight fragments
+            u32x4_t r[PLAIN ? MA : PER];                          // MA token fragments, then 3*NE weight fragments
+            float wv[PLAIN ? NE : 1][8];                          // or the weights
         };
         auto load = [&](Stage& st, int step) {
             const int kb = wk + min(step, nkb - 1) * WK;          // past the end: harmless re-read, dropped
 #pragma unroll
             for (int m = 0; m < MA; ++m) st.r[m] = *reinterpret_cast<const u32x4_t*>(a_src[m] + kb * kKB);
-            const uint16_t* bp = b_src + (size_t)kb * b_kb_stride;
+            if constexpr (PLAIN) {
 #pragma unroll
-            for (int i = 0; i < 3 * NE; ++i) st.r[MA + i] = *reinterpret_cast<const u32x4_t*>(bp + i * kFragElems);
+                for (int e = 0; e < NE; ++e) load_weights(Wg, kb, lane >> 4, n0 + 16 * e, E, st.wv[e]);
+            } else {
+                const uint16_t* bp = b_src + (size_t)kb * b_kb_stride;
+#pragma unroll
+                for (int i = 0; i < 3 * NE; ++i) st.r[MA + i] = *reinterpret_cast<const u32x4_t*>(bp + i * kFragElems);
+            }
         };
-        auto mma = [&](const Stage& st) {
-            bf16x8_t af[MA];
+        auto mma = [&](Stage& st) {
+            bf16x8_t af[MA], bf[NE][3];
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                if constexpr (PLAIN) {
+                    zero_past(n0 + 16 * e, E, st.wv[e]);
+                    split_weights(st.wv[e], bf[e]);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) bf[e][q] = __builtin_bit_cast(bf16x8_t, st.r[MA + e * 3 + q]);
+                }
+            }
 #pragma unroll
             for (int m = 0; m < MA; ++m) af[m] = __builtin_bit_cast(bf16x8_t, st.r[m]);
 #pragma unroll
@@ -157,8 +211,7 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
                 for (int q = 0; q < 3; ++q)
 #pragma unroll
                     for (int m = 0; m < MA; ++m)
-                        acc[m][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], __builtin_bit_cast(bf16x8_t, st.r[MA + e * 3 + q]),
-                                                                            acc[m][e], 0, 0, 0);
+                        acc[m][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[m], bf[e][q], acc[m][e], 0, 0, 0);
         };
 
         Stage st[D];
@@ -292,14 +345,14 @@ __device__ __forceinline__ void gate_bf16_body(char* lds, const uint16_t* __rest
     }
 }
 
-template <int MA, int NE, int K>
-__global__ __launch_bounds__(256) void gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags,
+template <int MA, int NE, int K, bool PLAIN>
+__global__ __launch_bounds__(256) void gate_bf16_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ Wg,
                                                         const float* __restrict__ bg, float* __restrict__ logits, int T, int d,
                                                         int E, int ET, int32_t* __restrict__ expert_idx,
                                                         int32_t* __restrict__ slot_idx, float* __restrict__ gate_w,
                                                         int32_t* __restrict__ hist) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    gate_bf16_body<MA, NE, K>(lds, x, frags, bg, logits, T, d, E, ET, expert_idx, slot_idx, gate_w, hist);
+    gate_bf16_body<MA, NE, K, PLAIN>(lds, x, frags, Wg, bg, logits, T, d, E, ET, expert_idx, slot_idx, gate_w, hist);
 }
 
 // The whole gate of a decode step (at most 256 tokens) in ONE launch.  Bound by latencies: the gate weights' round trip,
@@ -318,9 +371,9 @@ __global__ __launch_bounds__(256) void gate_bf16_kernel(const uint16_t* __restri
 // the same, and gives up (leaving wrong tables, never a hung GPU) after about 10^6 polls.
 // One token, d = 1024, 128 experts: 12.4 us with four waves and a routing by 256 threads; 64 tokens, d = 2048: 23.2.
 constexpr int kDecodeWaves = 16, kDecodeBlocks = 4;      // waves; k-blocks in flight per wave
-template <int MA, int RK, int NV>
+template <int MA, int RK, int NV, bool PLAIN>
 __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
-    const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ bg, float* __restrict__ logits,
+    const uint16_t* __restrict__ x, const uint16_t* __restrict__ frags, const float* __restrict__ Wg, const float* __restrict__ bg, float* __restrict__ logits,
     int T, int d, int E, int ET, int C, int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
     float* __restrict__ gate_w, int32_t* __restrict__ expert_rows, int32_t* __restrict__ slot_token,
     int32_t* __restrict__ expert_order, uint64_t* __restrict__ flags, uint64_t tag) {
@@ -339,23 +392,32 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
     const uint16_t* a_src[MA];                                   // token rows, clamped: results past T are never stored
 #pragma unroll
     for (int m = 0; m < MA; ++m) a_src[m] = x + (size_t)min(t0 + 16 * m + c, T - 1) * d + kg * 8;
-    const uint16_t* b_src = frags + (size_t)et * 3 * kFragElems + lane * 8;
+    const uint16_t* b_src = PLAIN ? nullptr : frags + (size_t)et * 3 * kFragElems + lane * 8;
     for (int i0 = 0; i0 < nkb; i0 += kDecodeBlocks) {
         bf16x8_t a[kDecodeBlocks][MA], b[kDecodeBlocks][3];
+        float wv[PLAIN ? kDecodeBlocks : 1][8];
 #pragma unroll
         for (int i = 0; i < kDecodeBlocks; ++i) {
             if (i0 + i >= nkb) break;
             const int kb = w + (i0 + i) * kDecodeWaves;
 #pragma unroll
             for (int m = 0; m < MA; ++m) a[i][m] = *reinterpret_cast<const bf16x8_t*>(a_src[m] + kb * kKB);
+            if constexpr (PLAIN) {
+                load_weights(Wg, kb, kg, et * 16 + c, E, wv[i]);
+            } else {
 #pragma unroll
-            for (int q = 0; q < 3; ++q)
-                b[i][q] = *reinterpret_cast<const bf16x8_t*>(b_src + ((size_t)kb * ET * 3 + q) * kFragElems);
+                for (int q = 0; q < 3; ++q)
+                    b[i][q] = *reinterpret_cast<const bf16x8_t*>(b_src + ((size_t)kb * ET * 3 + q) * kFragElems);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);                       // all loads go out before the first use
 #pragma unroll
         for (int i = 0; i < kDecodeBlocks; ++i) {
             if (i0 + i >= nkb) break;
+            if constexpr (PLAIN) {
+                zero_past(et * 16 + c, E, wv[i]);
+                split_weights(wv[i], b[i]);
+            }
 #pragma unroll
             for (int q = 0; q < 3; ++q)
 #pragma unroll
@@ -394,19 +456,19 @@ __global__ __launch_bounds__(kDecodeWaves * 64) void gate_decode_kernel(
                               slot_token, expert_order);
 }
 
-template <int MA, int NE, int K>
-int launch_cfg(const uint16_t* x, const uint16_t* frags, const float* bg, float* logits, int T, int d, int E, int ET,
+template <int MA, int NE, int K, bool PLAIN>
+int launch_cfg(const uint16_t* x, const uint16_t* frags, const float* Wg, const float* bg, float* logits, int T, int d, int E, int ET,
                int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* hist, hipStream_t s) {
     constexpr int smem = GateLds<MA, NE, K>::BYTES;
     static bool attr_set = false;             // one flag per instantiation
     if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_bf16_kernel<MA, NE, K>),
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_bf16_kernel<MA, NE, K, PLAIN>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
             return MOE_ERR_HIP;
         attr_set = true;
     }
     const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET / NE);
-    hipLaunchKernelGGL((gate_bf16_kernel<MA, NE, K>), grid, dim3(256), smem, s, x, frags, bg, logits, T, d, E, ET, expert_idx,
+    hipLaunchKernelGGL((gate_bf16_kernel<MA, NE, K, PLAIN>), grid, dim3(256), smem, s, x, frags, Wg, bg, logits, T, d, E, ET, expert_idx,
                        slot_idx, gate_w, hist);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
@@ -437,17 +499,12 @@ int launch_pack_gate(const float* Wg, void* packed, int d, int E, hipStream_t s)
     return launch_prepare(Wg, static_cast<uint16_t*>(packed), d, E, d / kKB, padded_expert_tiles(E), s);
 }
 
-// Wg_packed != nullptr: the gate weights as launch_pack_gate wrote them (Wg and frag_ws are then not used)
+// Wg_packed != nullptr: the gate weights as launch_pack_gate wrote them (Wg is then not used)
 int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T,
-                            int d, int E, void* frag_ws, hipStream_t s) {
-    if (!gate_bf16_supported(d, E) || (!frag_ws && !Wg_packed)) return MOE_ERR_INVALID_ARG;
-    const int KB = d / kKB, ET = padded_expert_tiles(E);
+                            int d, int E, hipStream_t s) {
+    if (!gate_bf16_supported(d, E) || (!Wg && !Wg_packed)) return MOE_ERR_INVALID_ARG;
+    const int ET = padded_expert_tiles(E);
     const uint16_t* frags = static_cast<const uint16_t*>(Wg_packed);
-    if (!frags) {
-        const int rc = launch_prepare(Wg, static_cast<uint16_t*>(frag_ws), d, E, KB, ET, s);
-        if (rc != MOE_OK) return rc;
-        frags = static_cast<const uint16_t*>(frag_ws);
-    }
     const uint16_t* xb = static_cast<const uint16_t*>(x);
     // Largest tile (fewest operand bytes per output) that still gives every CU a work-group; when even
     // the smallest tile cannot (few tokens), the smallest one: most work-groups, least time per CU.
@@ -458,7 +515,8 @@ int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packe
             if ((long long)((T + 16 * ma - 1) / (16 * ma)) * (ET / ne) >= 256) { MA = ma; NE = ne; found = true; }
 #define MOE_GATE_CASE(ma, ne) \
     if (MA == ma && NE == ne)   \
-    return launch_cfg<ma, ne, 0>(xb, frags, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s)
+    return frags ? launch_cfg<ma, ne, 0, false>(xb, frags, nullptr, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s) \
+                 : launch_cfg<ma, ne, 0, true>(xb, nullptr, Wg, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s)
     MOE_GATE_CASE(4, 4); MOE_GATE_CASE(4, 2); MOE_GATE_CASE(4, 1);
     MOE_GATE_CASE(2, 4); MOE_GATE_CASE(2, 2); MOE_GATE_CASE(2, 1);
 #undef MOE_GATE_CASE
@@ -469,35 +527,39 @@ int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packe
 // tag: next_call_tag().
 bool gate_decode_supported(int T, int d, int E) { return gate_bf16_supported(d, E) && T <= kRouteTokens; }
 
-template <int MA, int RK, int NV>
-static int launch_decode_cfg(const uint16_t* x, const uint16_t* frags, const float* bg, float* logits, int T, int d, int E,
+template <int MA, int RK, int NV, bool PLAIN>
+static int launch_decode_p(const uint16_t* x, const uint16_t* frags, const float* Wg, const float* bg, float* logits, int T, int d, int E,
                              int ET, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
                              int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s) {
     const size_t route = route_single_lds_ints(E, RK) * sizeof(int32_t), sums = (size_t)kDecodeWaves * 16 * MA * 16 * 4;
     const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET);              // smallest tiles: most work-groups (at most 8 x 8)
     if (grid.x * grid.y > kGateFlags) return MOE_ERR_INVALID_ARG;
-    hipLaunchKernelGGL((gate_decode_kernel<MA, RK, NV>), grid, dim3(kDecodeWaves * 64), route > sums ? route : sums, s, x, frags,
+    hipLaunchKernelGGL((gate_decode_kernel<MA, RK, NV, PLAIN>), grid, dim3(kDecodeWaves * 64), route > sums ? route : sums, s, x, frags, Wg,
                        bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows, slot_token, expert_order, flags, tag);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+template <int MA, int RK, int NV>
+static int launch_decode_cfg(const uint16_t* x, const uint16_t* frags, const float* Wg, const float* bg, float* logits, int T, int d, int E,
+                             int ET, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
+                             int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s) {
+    return frags ? launch_decode_p<MA, RK, NV, false>(x, frags, nullptr, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows,
+                                                      slot_token, expert_order, flags, tag, s)
+                 : launch_decode_p<MA, RK, NV, true>(x, nullptr, Wg, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, expert_rows,
+                                                     slot_token, expert_order, flags, tag, s);
+}
+
 int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T, int d,
                        int E, int k, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
-                       int32_t* slot_token, int32_t* expert_order, void* frag_ws, uint64_t* flags, uint64_t tag,
-                       hipStream_t s) {
-    if (!gate_decode_supported(T, d, E) || (!frag_ws && !Wg_packed) || !flags || k < 1 || k > 2) return MOE_ERR_INVALID_ARG;
-    const int KB = d / kKB, ET = padded_expert_tiles(E);
+                       int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s) {
+    if (!gate_decode_supported(T, d, E) || (!Wg && !Wg_packed) || !flags || k < 1 || k > 2) return MOE_ERR_INVALID_ARG;
+    const int ET = padded_expert_tiles(E);
     const uint16_t* frags = static_cast<const uint16_t*>(Wg_packed);
-    if (!frags) {
-        const int rc = launch_prepare(Wg, static_cast<uint16_t*>(frag_ws), d, E, KB, ET, s);
-        if (rc != MOE_OK) return rc;
-        frags = static_cast<const uint16_t*>(frag_ws);
-    }
     const uint16_t* xb = static_cast<const uint16_t*>(x);
 #define MOE_DECODE_CASE(kk, nv) \
-    return T <= 128 ? launch_decode_cfg<1, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
+    return T <= 128 ? launch_decode_cfg<1, kk, nv>(xb, frags, Wg, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
                                                    expert_rows, slot_token, expert_order, flags, tag, s)              \
-                    : launch_decode_cfg<2, kk, nv>(xb, frags, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
+                    : launch_decode_cfg<2, kk, nv>(xb, frags, Wg, bg, logits, T, d, E, ET, C, expert_idx, slot_idx, gate_w, \
                                                    expert_rows, slot_token, expert_order, flags, tag, s)
     if (k == 1) {
         if (E <= 16) MOE_DECODE_CASE(1, 1);
@@ -537,7 +599,7 @@ int launch_gate_bf16_fused(const void* x, const float* Wg, const void* Wg_packed
     rc = MOE_ERR_INVALID_ARG;
 #define MOE_GATE_CASE(ma, ne, kk) \
     if (MA == ma && ET == ne && k == kk) \
-    rc = launch_cfg<ma, ne, kk>(xb, frags, bg, logits, T, d, E, ET, expert_idx, slot_idx, gate_w, hist, s)
+    rc = launch_cfg<ma, ne, kk, false>(xb, frags, nullptr, bg, logits, T, d, E, ET, expert_idx, slot_idx, gate_w, hist, s)
     MOE_GATE_CASE(4, 8, 1); MOE_GATE_CASE(4, 4, 1); MOE_GATE_CASE(4, 2, 1); MOE_GATE_CASE(4, 1, 1);
     MOE_GATE_CASE(2, 8, 1); MOE_GATE_CASE(2, 4, 1); MOE_GATE_CASE(2, 2, 1); MOE_GATE_CASE(2, 1, 1);
     MOE_GATE_CASE(4, 8, 2); MOE_GATE_CASE(4, 4, 2); MOE_GATE_CASE(4, 2, 2); MOE_GATE_CASE(4, 1, 2);

@@ -67,17 +67,18 @@ __device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int 
 int launch_gate_logits(const void* x, int dtype, const float* Wg, const float* bg, float* logits,
                        int T, int d, int E, hipStream_t s);
 
-// the same for bf16 tokens on the bf16 matrix cores (fp32 weights split into three bf16 pieces, exact);
-// frag_ws: gate_bf16_ws_bytes(d, E) bytes of scratch for the split weights, rewritten by every call
+// the same for bf16 tokens on the bf16 matrix cores (fp32 weights split into three bf16 pieces, exact); Wg_packed: the pieces as
+// launch_pack_gate wrote them, or nullptr: Wg
 bool gate_bf16_supported(int d, int E);
 size_t gate_bf16_ws_bytes(int d, int E);
 int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T,
-                            int d, int E, void* frag_ws, hipStream_t s);
+                            int d, int E, hipStream_t s);
 // the split weights written once into a caller-owned buffer of gate_bf16_ws_bytes(d, E) bytes (Wg_packed above)
 int launch_pack_gate(const float* Wg, void* packed, int d, int E, hipStream_t s);
 
 // logits, top-k, gate weights, tile-local ranks (parked in slot_idx) and per-tile histograms for bf16 tokens;
 // launch_route_finalize(..., *tokens_per_hist, ..., *hist_out) completes the routing.
+// frag_ws: gate_bf16_ws_bytes(d, E) bytes of scratch for the split weights, rewritten by every call without Wg_packed;
 // scratch as for launch_route; logits is always written
 bool gate_bf16_fused_supported(int T, int d, int E);
 int launch_gate_bf16_fused(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T,
@@ -90,8 +91,7 @@ constexpr int kGateFlags = 64;
 bool gate_decode_supported(int T, int d, int E);
 int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, const float* bg, float* logits, int T, int d,
                        int E, int k, int C, int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* expert_rows,
-                       int32_t* slot_token, int32_t* expert_order, void* frag_ws, uint64_t* flags, uint64_t tag,
-                       hipStream_t s);
+                       int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s);
 
 // number of int32 the routing kernels need as scratch
 size_t route_scratch_ints(int T, int E, int k);
