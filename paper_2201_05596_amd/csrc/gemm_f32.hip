@@ -10,7 +10,7 @@
 // every operand is a 16-byte access, no value is moved between lanes, and a lane ends with four consecutive columns
 // of four rows (16-byte stores).
 //
-// Four kernels:
+// Five kernels:
 //   * f32_split_kernel, groups of more than 32 rows and K beyond 128: bound by the bf16 matrix cores and the vector ALUs beside them.  An
 //     fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, so six of the nine products of pieces (the
 //     other three are below 2^-26 of it) give an fp32 product at 2.6 times the fp32 matrix rate.  64 x 128 tiles; pairs of
@@ -35,6 +35,7 @@
 //     185 / 160; 1000 tokens, 1024/4096, 16 experts, skewed 202 / 188).  Many full tiles would be a little faster with two (8192
 //     tokens, 512/2048, 8 experts 294 / 303).
 //   * f32_ffn_kernel, d_model up to 64: both products in one launch;
+//   * f32_rows_split_kernel, f32_rows_kernel's products of 17 rows and more with K beyond 128, on split operands;
 //   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products with few tiles and those of 2^24 columns or
 //     more, whose 32-row chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
@@ -557,16 +558,11 @@ template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, 
 constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
 
+// sums and epilogue of MS * 16 rows x 64 columns from (m0, n0); part: [kFWaves][MS * 16][16] in LDS
 template <int MS, int EPI>
-__global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
-    __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves][MS * 16][16];
+__device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const part, int g, int rows, int m0, int n0) {
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
-    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
-    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * MS * 16, n0 = nt * 64;
-    if (m0 >= rows) return;
-
     const float* a_src[MS];
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms) a_src[ms] = f32_arow(a, g, min(m0 + ms * 16 + c, rows - 1));
@@ -625,14 +621,132 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
     for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
+            part[(w * MS * 16 + ms * 16 + kg * 4 + r) * 16 + c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
     __syncthreads();
     const int row = tid / 16, n = n0 + (tid & 15) * 4;
     if (m0 + row >= rows || row >= MS * 16 || n >= a.N) return;
-    f32x4_t v = part[0][row][tid & 15];
+    f32x4_t v = part[row * 16 + (tid & 15)];
 #pragma unroll
-    for (int s = 1; s < kFWaves; ++s) v += part[s][row][tid & 15];
+    for (int s = 1; s < kFWaves; ++s) v += part[(s * MS * 16 + row) * 16 + (tid & 15)];
     f32_finish<EPI>(a, g, m0 + row, n, v);
+}
+
+
+template <int MS, int EPI>
+__global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
+    __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves * MS * 16 * 16];
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, threadIdx.x, kFWaves * 64);
+    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
+    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * MS * 16;
+    if (m0 < rows) f32_rows_tile<MS, EPI>(a, part, g, rows, m0, nt * 64);
+}
+
+// The same with 32 rows and K beyond 128 on the bf16 matrix instructions, operands split as in f32_split_kernel: every wave splits what
+// it loads, nothing is shared.  WGS work-groups per compute unit (the register limit of one keeps a second away, so that few tiles
+// spread over the chip).  Products, us, fp32 / split with one / with two: 4 x 75 rows, 2048 x 512 25.9 / 20.3 / 20.6, 512 x 2048 18.2 /
+// 14.6 / 13.7; 8 x 256, 2048 x 512 56.0 / 42.5 / 41.6, half of the tiles empty 55.3 / 26.2 / 37.2; 31 x 24, 512 x 2048 33.8 / 30.9 / 26.2;
+// 1 x 60, 2048 x 512 23.7 / 18.2 / 18.6; K = 128 no faster (4 x 64, 128 x 512 5.2 / 5.0 / 5.5; 31 x 130, 128 x 128 8.4 / 8.4 / 9.9).
+constexpr int kRowsSplitLds = kFWaves * 32 * 64 * 4 + 16;        // partial sums and a flag
+template <int WGS, int EPI>
+__global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(const GemmArgs a, const int n_tiles) {
+    constexpr int AHEAD = 2;                                     // 16-deep blocks in flight per wave
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float* const part = reinterpret_cast<float*>(lds);           // [kFWaves][32][64]
+    int* const flag = reinterpret_cast<int*>(lds + kRowsSplitLds - 16);
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, half = lane >> 5;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
+    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
+    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * 32, n0 = nt * 64;
+    if (m0 >= rows) return;
+    if (tid == 0) *flag = 0;
+    const float* const a_src = f32_arow(a, g, min(m0 + c, rows - 1));              // rows past the end repeat the last one
+    const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
+    const int b_off = (half * 8 * a.N + min(n0 + c * 2, a.N - 2)) * 4;             // columns past the end: never stored
+    const float sign = w % 2 ? -1.f : 1.f;                       // every other wave's sums negated: the matrix instruction rounds down
+    float largest = 0.f;
+    struct Block {
+        f32x4_t av[2];
+        float bv[8][2];
+    };
+    const int blocks = (a.K + 15) / 16;
+    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + kFWaves - 1) / kFWaves : 0);   // blocks w, w + 8, ...
+    auto load = [&](Block& b, int i) {                           // past K: weights zero (also past the wave's last block), activations any
+        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+        const int k_in = __builtin_amdgcn_readfirstlane(min((w + i * kFWaves) * 16, a.K));
+        const int left = __builtin_amdgcn_readfirstlane(min(a.K - k_in, 16));
+        const __amdgpu_buffer_rsrc_t rs =
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B + (size_t)k_in * a.N), 0, left * a.N * 4, 0x00027000);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) b.av[h] = *reinterpret_cast<const f32x4_t*>(a_src + min(k_in + half * 8 + h * 4, a.K - 4));
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, b_off + j * a.N * 4, 0, 0));
+            b.bv[j][0] = __uint_as_float(v[0]);
+            b.bv[j][1] = __uint_as_float(v[1]);
+        }
+    };
+    f32x16_t acc[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
+    auto frag = [](const uint32_t (&u)[4]) { return __builtin_bit_cast(bf16x8_t, make_uint4(u[0], u[1], u[2], u[3])); };
+    auto multiply = [&](const Block& b) {
+        constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
+        uint32_t ua[3][4], ub[2][3][4];
+        float x[4][2];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = sign * b.av[j / 4][j % 4];
+        split_pairs(x, ua, largest);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = b.bv[j][i];
+            split_pairs(x, ub[i], largest);
+        }
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(ua[PA[t]]), frag(ub[i][PB[t]]), acc[i], 0, 0, 0);
+    };
+    Block st[AHEAD];
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s) load(st[s], s);
+    int i = 0;
+    for (; i + AHEAD < mine; i += AHEAD) {                       // the last round fetches nothing
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) {
+            multiply(st[s]);
+            __builtin_amdgcn_sched_barrier(0);
+            load(st[s], i + s + AHEAD);
+            __builtin_amdgcn_sched_barrier(0);                   // the refill stays here, AHEAD blocks ahead of its use
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < AHEAD; ++s)
+        if (i + s < mine) multiply(st[s]);
+#pragma unroll
+    for (int j = 0; j < 16; ++j)                                 // D: rows 8 (j / 4) + 4 half + j % 4, column lane % 32
+        *reinterpret_cast<float2*>(part + (w * 32 + 8 * (j / 4) + 4 * half + j % 4) * 64 + c * 2) = make_float2(acc[0][j], acc[1][j]);
+    lds_barrier();
+    const int row = tid / 16, n = (tid & 15) * 4;
+    f32x4_t v = *reinterpret_cast<const f32x4_t*>(part + row * 64 + n);
+#pragma unroll
+    for (int s = 1; s < kFWaves; ++s) {
+        const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + (s * 32 + row) * 64 + n);
+        v = s % 2 ? v - u : v + u;
+    }
+    bool bad = !(largest <= kSplitLargest);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[j]) <= 3.4028234e38f) || (fabsf(v[j]) < kSplitSmallest && v[j] != 0.f);
+    if (__ballot(bad)) *flag = 1;
+    lds_barrier();
+    if (*flag) {                                                 // uniform over the work-group: unsplit, as above
+        f32_rows_tile<2, EPI>(a, reinterpret_cast<f32x4_t*>(lds), g, rows, m0, n0);
+        return;
+    }
+    if (m0 + row < rows && n0 + n < a.N) f32_finish<EPI>(a, g, m0 + row, n0 + n, v);
 }
 
 // ---- both products of a narrow FFN -------------------------------------------------------------------------
@@ -758,12 +872,23 @@ template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipS
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
+template <int WGS, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
+    static bool attr_set = false;            // one flag per instantiation
+    if (!attr_set) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_rows_split_kernel<WGS, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kRowsSplitLds) != hipSuccess)
+            return MOE_ERR_HIP;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((f32_rows_split_kernel<WGS, EPI>), grid, dim3(kFWaves * 64), kRowsSplitLds, s, a, n_tiles);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
 template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
     // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
-    // flop, so the line is where two of them on every unit hold all (products, us, 32 x 64 / 64 x 128 split: 2048 x 512, 256 small
-    // tiles 27 / 35, 512 tiles 58 / 39 full, but 27 / 36 where skewed routing leaves half of them empty, 640 tiles 84 / 44; 512 x
-    // 2048, 256 tiles 9.5 / 13.7, 512 tiles 18.2 / 14.9, 640 24.4 / 15.3; 256 x 1024, 512 tiles 10.3 / 10.8, 640 13.5 / 11.0).
+    // flop, so the line is where two of them on every unit hold all (products, us, 32 x 64 / 64 x 128, both split: 2048 x 512, 256
+    // small tiles 23 / 38, 512 tiles 42 / 43, with half of them empty 26 / 38; 512 x 2048, 384 tiles 13.7 / 15.8; 256 x 1024, 512
+    // tiles 9.0 / 11.3; 200 x 800, 520 tiles 11.4 / 11.7).
     const long long small_tiles = ((long long)a.max_rows + 31) / 32 * (((long long)a.N + 63) / 64) * a.G;
     const bool few = a.max_rows <= 32 || small_tiles <= 512 || a.N >= 1 << 24;
     const bool narrow = a.N <= 64;                               // one 64-column tile: all four pairs along the rows
@@ -783,7 +908,10 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     static_assert(kFWaves * 64 == 512, "all kernels have the same work-group");
     static_assert(kSRows == 64 && kSCols == 128, "the same tile");
     if (few && tm == 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
+    else if (few && a.K > 128 && a.N < 1 << 24) {
+        const long long live32 = (long long)a.G * ((expect + 31) / 32) * n_tiles;
+        return live32 > 256 ? launch_rows_split<2, EPI>(a, grid, n_tiles, s) : launch_rows_split<1, EPI>(a, grid, n_tiles, s);
+    } else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
     else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
     else if (a.K <= (live > 256 ? 128 : 255)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
     else return live > 256 ? launch_split<2, EPI>(a, grid, n_tiles, s) : launch_split<4, EPI>(a, grid, n_tiles, s);

@@ -68,3 +68,36 @@ def test_far_from_one(scale):
     print(f"case {scale}", flush=True)
     ye, ref = _ffn(4, 640, 256, 1024, [640] * 4, scale=scale)
     assert (ye.double() - ref).abs().max() <= 2 * 1024 ** 0.5 * 2 * EPS * ref.abs().max()
+
+
+# few tiles (32 x 64, every wave splits what it loads): rows around 16 and 32, K and N off the blocks, one and two work-groups per unit
+@pytest.mark.parametrize("E,C,d,f,rows", [
+    (2, 17, 132, 260, [17, 1]), (3, 32, 196, 148, [32, 31, 0]), (4, 33, 516, 132, [33, 32, 16, 1]), (16, 32, 260, 2052, [32] * 15 + [5]),
+    (1, 300, 132, 1028, [300]), (8, 256, 2052, 516, [256, 255, 1, 0, 97, 96, 64, 33]),
+])
+def test_few_tiles(E, C, d, f, rows):
+    test_edges(E, C, d, f, rows)
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 3.4e38])
+def test_values_beyond_the_split_few_tiles(value):
+    print(f"case {value}", flush=True)
+
+    def edit(xe, W1, W2):
+        W2[1, 200, 130] = value
+        xe[0, 33, 7] = value
+    clean, _ = _ffn(2, 40, 256, 300, [40, 40])
+    ye, ref = _ffn(2, 40, 256, 300, [40, 40], edit)
+    hit = torch.zeros_like(ye, dtype=torch.bool)
+    hit[1, :, 130], hit[0, 33] = True, True
+    bad = ~torch.isfinite(ref) | (ref.abs() > 3.4e38)
+    assert bool((torch.isfinite(ye) == ~bad)[hit].all())
+    assert torch.equal(torch.isnan(ye), torch.isnan(ref)) or value == 3.4e38
+    assert (ye - clean)[~hit].abs().max() <= 4 * 300 ** 0.5 * EPS * clean.abs().max()
+
+
+@pytest.mark.parametrize("scale", [2.0 ** -118, 2.0 ** -100, 2.0 ** 100])
+def test_far_from_one_few_tiles(scale):
+    print(f"case {scale}", flush=True)
+    ye, ref = _ffn(2, 40, 256, 300, [40, 40], scale=scale)
+    assert (ye.double() - ref).abs().max() <= 2 * 300 ** 0.5 * 2 * EPS * ref.abs().max()
