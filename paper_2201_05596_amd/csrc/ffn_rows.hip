@@ -258,11 +258,19 @@ static int rows_columns(long long groups, int max_rows, int N, bool packed) {
 // 8 experts 44 / 52; 64, 16: 86 / 88).  K = 1024 loses (64 tokens, 128 experts layer 166 -> 171: two rounds of loads per wave
 // do not pay for a work-group).  with_dense: the dense branch's first product comes along in the launch, which pays for it
 // (block of 10 tokens, top-2 of 8 experts, 2048 / 8192: 122 / 138).
+//
+// K below 2048, where a work-group's waves have four blocks each, and up to 256 rows: as long as few experts have more than one (layers,
+// even routing and with gate bias 1.5 ln(1 / (e + 1)), streaming / this kernel: 16 tokens, 1024 / 4096, 64 experts 57.6 / 53.4 and
+// 38.8 / 22.7; 64 tokens, 128 experts 141 / 139 and 42.6 / 28.5; 180 tokens, 128 experts -4 % and -10 %; 64 tokens of 32 87.9 / 89.0, 34.2 /
+// 24.6; 20 tokens, top-2 of 32 +2 % and -19 %). 
 int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool with_dense) {
     if (max_rows > 16) return 0;
     if (touched * N > 48 * 1024) {
-        if (!packed || K < 2048 || kept > 128) return 0;
-        if (!with_dense && kept > 2 * touched && (touched % 8 == 0 || touched < 8)) return 0;
+        if (!packed) return 0;
+        const bool spread = 2 * kept < 3 * touched;                // few experts have more than one row
+        if (K < 1024 || kept > (spread ? 256 : 128)) return 0;
+        if (K < 2048 && (kept >= 2 * touched || (touched < 64 && 4 * kept >= 5 * touched))) return 0;
+        if (K >= 2048 && !with_dense && kept > 2 * touched && (touched % 8 == 0 || touched < 8)) return 0;
     }
     const int nf = rows_columns(touched, max_rows, N, packed);
     return packed ? nf : 4;                                    // plain rows of 64 bytes: 4 tokens, d = 2048, 110 against 91
@@ -281,12 +289,22 @@ int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int 
 // 1 of 64 82 / 50; K = 4096, N = 1024, 1 of 64 26.5 / 22.5.
 // Plain weights (rows of 64 bytes, so twice the lines are touched): one or two experts only, and with a long K only out of at
 // least eight (fewer are spread over the XCDs by columns: K = 8192, 2 experts of 16 rows 31 / 27, K = 16384, 1 of 16 54 / 40; 2
-// tokens out of 8 experts, 2048 / 8192: layer 44 / 59).
+// tokens out of 8 experts, 2048 / 8192: layer 44 / 59)).
+// At most 16 rows per expert, packed, against the streaming kernel without a split as well: that one's waves are then enough for the
+// chip only if all experts have rows, and with skewed routing most have none.  With few rows per expert (whatever few_waves says) or, K
+// below 8192, up to 256 rows (layers, us, even routing and with gate bias 1.5 ln(1 / (e + 1)), streaming / this kernel: 2048 / 8192, 64
+// tokens of 64 experts 453 / 423 and 136 / 70, 96 of 128 729 / 664 and 203 / 85, 180 of 128 974 / 959 and 224 / 112, 40 tokens, top-2 of
+// 64 484 / 484 and 156 / 106, but 90 of 64 522 / 525; 1024 / 4096, 180 of 128 280 / 261 and 88 / 44, 100 tokens, top-2 of 64 180 / 174 and 50 / 43; with 32 columns
+// 180 of 128 962 / 980).  Not with fewer tokens than three quarters of the experts, where even routing loses what it gains elsewhere (64
+// of 128 498 / 507, skewed 196 / 76), nor with two rows per expert and more (+1 .. +4 %, skewed -17 .. -38 %).
 int rows_pick_gemm2(int E, long long touched, int max_rows, long long kept, int K, int N, bool packed, bool few_waves) {
-    if (!few_waves || kept > (K >= 8192 ? 256 : 96)) return 0;
-    if (!packed) return (K < 8192 || E >= 8) && max_rows <= 16 && touched * N <= 4096 ? 2 : 0;
+    const bool few_rows = max_rows <= 16;
+    const bool spread = touched >= 96 ? 2 * kept < 3 * touched : 4 * kept <= 5 * touched;      // few experts have more than one row
+    if (packed && few_rows && !few_waves && kept <= 256 && spread && 4 * kept >= 3ll * E) return 1;
+    if (!few_waves || kept > (K >= 8192 || (packed && few_rows) ? 256 : 96)) return 0;
+    if (!packed) return (K < 8192 || E >= 8) && few_rows && touched * N <= 4096 ? 2 : 0;
     int nf = rows_columns(touched, max_rows, N, packed);
-    if (max_rows <= 16) return K < 8192 ? 1 : nf > 2 && (K < 16384 || kept < 8 * touched) ? 2 : nf;
+    if (few_rows) return K < 8192 ? 1 : nf > 2 && (K < 16384 || kept < 8 * touched) ? 2 : nf;
     if (K < 8192) return K >= 4096 && kept > 48 * touched ? 0 : nf;
     if (kept > 16 * touched && (max_rows > 32 || nf == 2)) return 0;
     return kept > 24 * touched && nf < 4 ? 0 : nf;

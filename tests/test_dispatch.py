@@ -79,3 +79,23 @@ def test_ragged_inner_dimension(T, d, f, E, C, packed, kernel):
 ])
 def test_few_rows(T, d, f, E, C, packed, which, kernel):
     assert plan(T, d, f, E, 1, C, False, packed)[0][which] == kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,k,C,packed,which,kernel", [
+    # few rows per expert, beyond 48 K columns of a first product with K = 1024: the few-weights kernel (us, streaming / here, even and skewed)
+    (16, 1024, 4096, 64, 1, 1, True, 0, 4),              # layer 57.6 / 53.4, 38.8 / 22.7
+    (64, 1024, 4096, 128, 1, 1, True, 0, 4),             # 141 / 139, 42.6 / 28.5
+    (180, 1024, 4096, 128, 1, 2, True, 0, 4),            # 280 / 261, 88 / 44, with the second product
+    # ... the streaming kernel where the tokens reach most of few experts, or with plain weights
+    (64, 1024, 4096, 32, 1, 4, True, 0, 116), (20, 1024, 4096, 64, 1, 1, False, 0, 116),
+    # second product, waves enough for the streaming kernel without a split
+    (64, 2048, 8192, 64, 1, 2, True, 1, 1),              # 453 / 423, 136 / 70
+    (96, 2048, 8192, 128, 1, 2, True, 1, 1),             # 729 / 664, 203 / 85
+    (180, 1024, 4096, 128, 1, 2, True, 1, 1),
+    # ... not with few of the experts, nor with more rows per expert
+    (64, 2048, 8192, 128, 1, 1, True, 1, 116), (90, 2048, 8192, 64, 1, 3, True, 1, 116),
+    # K below 8192: up to 256 rows
+    (100, 1024, 4096, 64, 2, 7, True, 1, 1),             # 180 / 174, 50 / 43
+])
+def test_few_rows_per_expert(T, d, f, E, k, C, packed, which, kernel):
+    assert plan(T, d, f, E, k, C, False, packed)[0][which] == kernel
