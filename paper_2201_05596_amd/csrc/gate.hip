@@ -8,8 +8,6 @@
 // scan on its hardware; here the count is done with 64-wide wavefront ballots
 // (rank inside a wave), a per-tile histogram and a prefix over tiles, which
 // is deterministic (no atomics) and needs two small launches.
-#include <type_traits>
-
 #include "route_device.h"
 
 namespace moe {
@@ -121,17 +119,15 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
             }
         };
         // one step: tile of chunk c to LDS, refill the register slot kGPD steps ahead, multiply
-        auto step = [&](bword_t (&bslot)[NB], XRaw<XT>& aslot, int c, auto refill) {
+        auto step = [&](bword_t (&bslot)[NB], XRaw<XT>& aslot, int c) {
             lds_barrier();                            // the previous step has finished reading the tile
             b_store(bslot, c);
             float av[8];
             const int ka = (wk * cper + c) * kGK + 8 * g;
             aslot.widen(FULL ? 0 : (c < cper ? ka : d), d, av);
             lds_barrier();
-            if constexpr (decltype(refill)::value) {
-                b_load(bslot, c + kGPD);
-                aslot.load(xrow, (wk * cper + c + kGPD) * kGK + 8 * g, d);
-            }
+            b_load(bslot, c + kGPD);
+            aslot.load(xrow, (wk * cper + c + kGPD) * kGK + 8 * g, d);
             __builtin_amdgcn_sched_barrier(0);
             float bv[8][4];
 #pragma unroll
@@ -152,13 +148,12 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
             areg[s].load(xrow, (wk * cper + s) * kGK + 8 * g, d);
         }
         int c0 = 0;
-        for (; c0 + kGPD < cper; c0 += kGPD) {            // the last round fetches nothing
+        for (; c0 + kGPD <= cper; c0 += kGPD) {
 #pragma unroll
-            for (int s = 0; s < kGPD; ++s) step(breg[s], areg[s], c0 + s, std::true_type());
+            for (int s = 0; s < kGPD; ++s) step(breg[s], areg[s], c0 + s);
         }
-#pragma unroll
-        for (int s = 0; s < kGPD; ++s)
-            if (c0 + s < cper) step(breg[s], areg[s], c0 + s, std::false_type());
+        if (c0 < cper) step(breg[0], areg[0], c0);
+        if (c0 + 1 < cper) step(breg[1], areg[1], c0 + 1);
 
         if (WK > 1) {
             __syncthreads();

@@ -636,9 +636,10 @@ template <int MS, int EPI>
 __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
     __shared__ __attribute__((aligned(16))) f32x4_t part[kFWaves * MS * 16 * 16];
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, threadIdx.x, kFWaves * 64);
-    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
-    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * MS * 16;
-    if (m0 < rows) f32_rows_tile<MS, EPI>(a, part, g, rows, m0, nt * 64);
+    const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * MS * 16), g = blockIdx.y;
+    const int rows = f32_rows_of(a, g);
+    if (m0 >= rows) return;
+    f32_rows_tile<MS, EPI>(a, part, g, rows, m0, nt * 64);
 }
 
 // The same with 32 rows and K beyond 128 on the bf16 matrix instructions, operands split as in f32_split_kernel: every wave splits what
@@ -656,8 +657,8 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
-    const int nt = blockIdx.x % n_tiles, g = blockIdx.y;
-    const int rows = f32_rows_of(a, g), m0 = blockIdx.x / n_tiles * 32, n0 = nt * 64;
+    const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * 32), g = blockIdx.y;
+    const int rows = f32_rows_of(a, g), n0 = nt * 64;
     if (m0 >= rows) return;
     if (tid == 0) *flag = 0;
     const float* const a_src = f32_arow(a, g, min(m0 + c, rows - 1));              // rows past the end repeat the last one
