@@ -255,14 +255,13 @@ static int rows_columns(long long groups, int max_rows, int N, bool packed) {
 // (up to two choices per expert) this kernel wins (2048 x 8192: 64 tokens, 32 experts 158 / 150; 64, 64: 204 / 194; 16, 16:
 // 65 / 53; 64 tokens, 128 experts, of which about 51 are reached: layer 519 / 506; where they happen to be 48: 242 / 246 for the
 // product); with all of a multiple of eight experts reached, or fewer than eight of them, the streaming one does (128 tokens,
-// 8 experts 44 / 52; 64, 16: 86 / 88).  K = 1024 loses (64 tokens, 128 experts layer 166 -> 171: two rounds of loads per wave
-// do not pay for a work-group).  with_dense: the dense branch's first product comes along in the launch, which pays for it
+// 8 experts 44 / 52; 64, 16: 86 / 88).  with_dense: the dense branch's first product comes along in the launch, which pays for it
 // (block of 10 tokens, top-2 of 8 experts, 2048 / 8192: 122 / 138).
 //
 // K below 2048, where a work-group's waves have four blocks each, and up to 256 rows: as long as few experts have more than one (layers,
 // even routing and with gate bias 1.5 ln(1 / (e + 1)), streaming / this kernel: 16 tokens, 1024 / 4096, 64 experts 57.6 / 53.4 and
 // 38.8 / 22.7; 64 tokens, 128 experts 141 / 139 and 42.6 / 28.5; 180 tokens, 128 experts -4 % and -10 %; 64 tokens of 32 87.9 / 89.0, 34.2 /
-// 24.6; 20 tokens, top-2 of 32 +2 % and -19 %). 
+// 24.6; 20 tokens, top-2 of 32 +2 % and -19 %).
 int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int N, bool packed, bool with_dense) {
     if (max_rows > 16) return 0;
     if (touched * N > 48 * 1024) {

@@ -1,10 +1,10 @@
-// Grouped GEMM of the fp32 layer on the fp32 matrix cores (paper Sec. 3.1: each expert is an FFN; this is one of its
+// Grouped GEMM of the fp32 layer on the matrix cores (paper Sec. 3.1: each expert is an FFN; this is one of its
 // two products), with the layout transforms of Sec. 5.4 fused in as in the bf16 kernels:
 //   out[g, r, n] = epi( sum_k A[row(g, r), k] B[g, k, n] + bias[g, n] ),  r < rows(g)
 // where row() may go through the slot->token table (dispatch) and epi may scale by the gate probability and write the
 // token's row, or add the expert outputs to the dense branch (combine).
 //
-// v_mfma_f32_16x16x4_f32, fp32 all the way.  A lane (c = lane % 16, kg = lane / 16) holds four consecutive k
+// v_mfma_f32_16x16x4_f32 (all but the split kernels): a lane (c = lane % 16, kg = lane / 16) holds four consecutive k
 // (4 kg .. 4 kg + 3 of a 16-deep block) of one activation row, and four consecutive columns 4c .. 4c + 3 of the weight
 // rows with the same k: matrix instruction (j, i) multiplies element j of the first with element i of the second, so
 // every operand is a 16-byte access, no value is moved between lanes, and a lane ends with four consecutive columns
@@ -41,6 +41,7 @@
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
 //     memory into registers, three blocks ahead, and add up through LDS in wave order.
 //     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before, 5.5 + 7.4 here.
+#include <atomic>
 #include <type_traits>
 
 #include "moe_internal.h"
@@ -543,13 +544,21 @@ __global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a,
     else run(std::integral_constant<int, 1>());
 }
 
+// LDS beyond 64 KB is asked for on every device that a kernel runs on (asked: a bit per device; past 64 of them at every launch).
+int ask_lds(const void* kernel, int bytes, std::atomic<unsigned long long>& asked) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return MOE_ERR_HIP;
+    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
+    if (asked.load(std::memory_order_relaxed) & bit) return MOE_OK;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return MOE_ERR_HIP;
+    asked.fetch_or(bit, std::memory_order_relaxed);
+    return MOE_OK;
+}
+
 template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
-    static bool attr_set = false;            // one flag per instantiation
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_split_kernel<P, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, split_lds<P>()) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_set = true;
-    }
+    static std::atomic<unsigned long long> asked{0};             // one per instantiation
+    const int rc = ask_lds(reinterpret_cast<const void*>(&f32_split_kernel<P, EPI>), split_lds<P>(), asked);
+    if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((f32_split_kernel<P, EPI>), grid, dim3(P * 128), split_lds<P>(), s, a, n_tiles);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
@@ -874,12 +883,9 @@ template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipS
 }
 
 template <int WGS, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
-    static bool attr_set = false;            // one flag per instantiation
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&f32_rows_split_kernel<WGS, EPI>), hipFuncAttributeMaxDynamicSharedMemorySize, kRowsSplitLds) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_set = true;
-    }
+    static std::atomic<unsigned long long> asked{0};             // one per instantiation
+    const int rc = ask_lds(reinterpret_cast<const void*>(&f32_rows_split_kernel<WGS, EPI>), kRowsSplitLds, asked);
+    if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((f32_rows_split_kernel<WGS, EPI>), grid, dim3(kFWaves * 64), kRowsSplitLds, s, a, n_tiles);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
