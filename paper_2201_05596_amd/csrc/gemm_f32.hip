@@ -760,10 +760,12 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
 }
 
 // ---- both products of a narrow FFN -------------------------------------------------------------------------
-// d_model up to 64: a work-group owns 16 MS rows and does both products; the intermediate never leaves its wave.  Wave w computes
-// columns 32 w .. + 31 of every 256 of the first product, two per lane, and they are just the K that it multiplies in the second: the
+// d_model up to 64, d_ffn up to 256: a work-group owns 16 MS rows and does both products; the intermediate never leaves its wave.  Wave w
+// computes columns 32 w .. + 31 of the first product, two per lane, and they are just the K that it multiplies in the second: the
 // rows turn from one operand order into the other through a piece of LDS of its own, no barrier until the waves' sums meet.  All
-// weights of a round are asked for before the first is used.  Bound by latency with few rows, by the fp32 matrix cores with many.
+// weights are asked for before the first is used.  Bound by latency with few rows, by the fp32 matrix cores with many.  Sums are of 16 products,
+// added afterwards: with chains of 32 in the second product the error against 64 bits is 1.05 .. 1.38 times that of two launches (64/64, one-sided
+// operands 5.7e-8 / 7.5e-8), so 0.80 .. 1.00 (5.5e-8); the time is the same.
 template <int MS, int EPI>
 __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs a, const GemmArgs b) {
     constexpr int HS = 36;                                       // floats per row of a wave's piece: 16 rows, 16 different units
@@ -792,12 +794,13 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
     const float* W2 = static_cast<const float*>(b.B) + (size_t)g * f * d + min(c * 4, d - 4);
     const float* bias1 = static_cast<const float*>(a.bias);
     float* const hs = reinterpret_cast<float*>(&part[w][0][0]);
-    f32x4_t acc[MS][4];
+    f32x4_t acc[2][MS][4];                                       // every 16 k of the second product on their own, too
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc[ms][i] = zero;
-    for (int n0 = w * 32; n0 < f; n0 += kFWaves * 32) {
+        for (int i = 0; i < 4; ++i) acc[0][ms][i] = acc[1][ms][i] = zero;
+    const int n0 = w * 32;                                       // ffn_f32_fused: f is at most 8 x 32
+    if (n0 < f) {
         const int n = n0 + c * 2, nc = min(n, f - 2);            // f is a multiple of 4: both columns inside or both outside
         f32x2_t w1[4][4], bv = {0.f, 0.f};
         f32x4_t w2[2][4];
@@ -854,15 +857,18 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
 #pragma unroll
-                    for (int ms = 0; ms < MS; ++ms) acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(hv[ms][j], w2[q][j][i], acc[ms][i], 0, 0, 0);
+                    for (int ms = 0; ms < MS; ++ms) acc[q][ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(hv[ms][j], w2[q][j][i], acc[q][ms][i], 0, 0, 0);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_wave_barrier();                         // the piece is read before the sums are written over it
     }
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
+    for (int ms = 0; ms < MS; ++ms) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
+        for (int i = 0; i < 4; ++i) acc[0][ms][i] += acc[1][ms][i];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[w][ms * 16 + kg * 4 + r][c] = f32x4_t{acc[0][ms][0][r], acc[0][ms][1][r], acc[0][ms][2][r], acc[0][ms][3][r]};
+    }
     __syncthreads();
     const int row = tid / 16, n = (tid & 15) * 4;
     if (m0 + row >= rows || row >= MS * 16 || n >= d) return;
@@ -931,7 +937,7 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
 // 24.2, 20000 52.5 / 46.1; 31 experts, top-2, 2048 tokens 38.5 / 31.8; 20/64 beside a dense branch, 1000 tokens 36.5 / 28.2.  Beyond
 // 1024 row tiles the products on their own are as fast (65536 tokens 96.1 / 97.2), and with a longer d_ffn one work-group's rounds
 // are the longer chain (256 tokens, 512: 25.0 / 26.0, 1024: 30.2 / 36.1).
-bool ffn_f32_fused(const GemmArgs& a) { return a.K <= 64 && a.N <= 256 && (long long)a.G * ((a.max_rows + 31) / 32) <= 1024; }
+bool ffn_f32_fused(const GemmArgs& a) { return a.K <= 64 && a.N <= kFWaves * 32 && (long long)a.G * ((a.max_rows + 31) / 32) <= 1024; }
 int launch_ffn_f32(const GemmArgs& a, const GemmArgs& b, int epi, hipStream_t s) {
     if (a.max_rows <= 0 || a.G <= 0) return MOE_OK;
     if (a.K % 4 || a.N % 4 || !ffn_f32_fused(a) || b.K != a.N || b.N != a.K) return MOE_ERR_INVALID_ARG;
