@@ -11,13 +11,19 @@
 // of four rows (16-byte stores).
 //
 // Five kernels:
-//   * f32_split_kernel, groups of more than 32 rows and K beyond 128: bound by the bf16 matrix cores and the vector ALUs beside them.  An
-//     fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, so six of the nine products of pieces (the
-//     other three are below 2^-26 of it) give an fp32 product at 2.6 times the fp32 matrix rate.  64 x 128 tiles; pairs of
-//     waves of 64 x 64 split K, v_mfma_f32_32x32x16_bf16 (a matrix instruction keeps the vector ALU from issuing for 8 clocks, so
-//     that six others fit beside one of 32 clocks, two beside one of 16 x 16 x 32).  Activations are split once per tile and go
-//     through LDS, weights straight into the registers of the wave that multiplies them.  Errors against 64 bits, of the FFN:
-//     512/2048, 8 experts x 480 rows 6.6e-7 -> 3.9e-7, x 256 4.3e-7 -> 3.5e-7, 256/1024, 16 x 256 3.1e-7 -> 2.5e-7.
+//   * f32_split_kernel, groups of more than 32 rows and K beyond 128 (255 where its tiles are few): bound by the bf16 matrix cores and the
+//     vector ALUs beside them.  An fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, and six of the nine
+//     products of pieces give an fp32 product at 2.6 times the fp32 matrix rate: the other three are 2^-27.5 of it (root mean square; 2^-24
+//     at most).  64 x 128 tiles; sets of four waves of 64 x 32 split K, v_mfma_f32_32x32x16_bf16 (a matrix instruction keeps the vector
+//     ALU from issuing for 8 clocks, so that six others fit beside one of 32 clocks, two beside one of 16 x 16 x 32).  Activations are
+//     split once per tile and go through LDS, weights straight into the registers of the wave that multiplies them.
+//     The instruction takes its 16 products in two groups of eight, one after the other: a group is cut to 2^-24 of its largest product,
+//     its sum rounded into the accumulator.  So the product of two first pieces has accumulators of its own, which are rounded twice in 16 k
+//     (the fp32 instructions round at every k), and the five small products theirs, whose roundings do not show.  In one accumulator, rounded
+//     12 times in 16 k, sums of rectified values (zero products cost an fp32 chain no rounding) were up to 1.13 times as far from 64 bits as
+//     fp32 ones.  Errors against 64 bits, fp32 / here with one set / with two: K = 512 3.3e-7 / 2.1e-7 / 1.8e-7, K = 2048 6.4e-7 / 3.5e-7 /
+//     2.6e-7, operands of one sign 9.5e-8 / 9.2e-8 / 8.9e-8, rectified 4.2e-7 / 2.5e-7 / 1.9e-7, one column 1000 times the others 4.0e-7 / 2.8e-7
+//     / 1.9e-7.
 //     1536 tokens, 512/2048, 8 experts, top-2 (12.9 GFLOP): 81 + 75 us on f32_tile_kernel, 58 + 50 here; with both operands' pieces
 //     through LDS 76 + 59 (every piece is written and read at half the rate it is used at).
 //   * f32_tile_kernel, the same with shorter K or at most 64 columns: bound by the fp32 matrix cores (157 TFLOP/s).  64 x 128 or
@@ -260,27 +266,27 @@ __global__ __launch_bounds__(512, 2) void f32_tile_kernel(const GemmArgs a, cons
 // ---- more than 32 rows per group, long K: on the bf16 matrix instructions --------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
-constexpr int kSRows = 64, kSCols = 128;      // of a tile: two waves of 64 columns
+constexpr int kSRows = 64, kSCols = 128;      // of a tile: four waves of 32 columns
 
 // The matrix instruction takes pieces below 2^-126 for zero.  That cannot show in a sum of at least 2^-70 over operands of at most 2^20
 // (2^11 products, each off by less than 2^-105: 2^-24 of it); tiles with other sums or operands are multiplied unsplit.
 constexpr float kSplitSmallest = 0x1p-70f, kSplitLargest = 0x1p20f;
 
-// Four pairs of fp32 values as three times four pairs of bf16: a value is piece 0 + piece 1 + piece 2 exactly (3 x 8 significant
+// M pairs of fp32 values as three times M pairs of bf16: a value is piece 0 + piece 1 + piece 2 exactly (3 x 8 significant
 // bits, each piece the nearest bf16 of what is left).  Infinities, NaN and values that round to infinity leave NaN in the later pieces.
-__device__ __forceinline__ void split_pairs(float (&x)[4][2], uint32_t (&piece)[3][4], float& largest) {
+template <int M> __device__ __forceinline__ void split_pairs(float (&x)[M][2], uint32_t (&piece)[3][M], float& largest) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) largest = fmaxf(fmaxf(largest, fabsf(x[i][0])), fabsf(x[i][1]));
+    for (int i = 0; i < M; ++i) largest = fmaxf(fmaxf(largest, fabsf(x[i][0])), fabsf(x[i][1]));
 #pragma unroll
     for (int q = 0; q < 3; ++q) {                            // piece by piece, so that no instruction waits for the one before it
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < M; ++i) {
             piece[q][i] = pack_bf16x2(x[i][0], x[i][1]);
             asm("" : "+v"(piece[q][i]));                     // one conversion for both values, not one more for the first alone
         }
         if (q == 2) break;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < M; ++i) {
             x[i][0] -= __uint_as_float(piece[q][i] << 16);
             x[i][1] -= __uint_as_float(piece[q][i] & 0xffff0000u);
         }
@@ -322,16 +328,16 @@ template <int EPI> __device__ void f32_unsplit(const GemmArgs& a, int g, int row
 
 template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + 16; }   // partial sums and a flag; less before
 
-// P pairs of waves split K between them, 32 deep in turn; wave 2 q + wn has columns 64 wn .. + 63 of the tile and pair q's K.
+// P sets of four waves split K between them, 32 deep in turn; wave 4 q + wn has columns 32 wn .. + 31 of the tile and set q's K.
 template <int P, int EPI>
-__global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a, const int n_tiles) {
-    constexpr int FRAG = 1024, PAIR = 2 * 2 * 3 * FRAG, BUF = P * PAIR, STEP = P * 32;      // STEP: k per step of the loop
+__global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a, const int n_tiles) {
+    constexpr int FRAG = 1024, PART = 2 * 2 * 3 * FRAG, BUF = P * PART, STEP = P * 32;      // STEP: k per step of the loop
     extern __shared__ __attribute__((aligned(16))) char lds[];
     static_assert(2 * BUF <= split_lds<P>() - 16, "two buffers of activation pieces");
     int* const flag = reinterpret_cast<int*>(lds + split_lds<P>() - 16);
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, half = lane >> 5;
-    const int q = w >> 1, wn = w & 1;
-    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, P * 128);
+    const int q = w >> 2, wn = w & 3;
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, P * 256);
     // column tiles innermost: with a multiple of 8 of them all row tiles of a column tile run on one XCD and share its
     // weights in that L2, and every XCD has the same work however unevenly the rows fall on the groups
     const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles, g = blockIdx.y;
@@ -343,126 +349,124 @@ __global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a,
     // v_mfma_f32_32x32x16_bf16.  Row r's 16 bytes of k-octet o stand at (o % 2) * 32 + (r ^ x(o)): x sends the lanes of one LDS
     // write to different banks.
     auto swizzle = [](int o) { return (o & 1) * 10 + (o >> 1) * 4; };
-    const int oct = tid & 3, a_r = (tid & 127) >> 2;
-    const float* a_src[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) a_src[i] = f32_arow(a, g, min(m0 + a_r + i * 32, rows - 1));      // rows past the end repeat the last one
-    char* const a_dst = lds + q * PAIR + (oct >> 1) * 3 * FRAG + ((oct & 1) * 32 + (a_r ^ swizzle(oct))) * 16;
-    auto load_a = [&](f32x4_t (&r)[2], int i, int t) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) r[h] = *reinterpret_cast<const f32x4_t*>(a_src[i] + min(t * STEP + q * 32 + oct * 8 + h * 4, a.K - 4));
-    };
+    const int oct = tid & 3, a_r = (tid & 255) >> 2;
+    const float* const a_src = f32_arow(a, g, min(m0 + a_r, rows - 1));            // rows past the end repeat the last one
+    char* const a_dst = lds + q * PART + ((a_r >> 5) * 6 + (oct >> 1) * 3) * FRAG + ((oct & 1) * 32 + ((a_r & 31) ^ swizzle(oct))) * 16;
+    // values 4 h .. 4 h + 3 of a thread's eight of step t
+    auto load_a = [&](f32x4_t& r, int h, int t) { r = *reinterpret_cast<const f32x4_t*>(a_src + min(t * STEP + q * 32 + oct * 8 + h * 4, a.K - 4)); };
     float largest = 0.f;                                     // of the operands that this thread splits
-    // The matrix instruction rounds its sums down, not to nearest: every other pair of waves sums the products negated.
+    // Every other set of waves sums the products negated: where a sum is cut to the grid of a larger product, the cut is not to nearest.
     const float sign = q % 2 ? -1.f : 1.f;
+    uint32_t ua[3][4];                                       // pieces of a thread's eight values
     // Past K the weights are zeros, the activations any of the row's (an infinity there makes NaN, and those sums are taken again).
-    auto store_a = [&](const f32x4_t (&r)[2], int i, int t) {
-        float x[4][2];
+    auto split_a = [&](const f32x4_t& r, int h) {
+        float x[2][2];
+        uint32_t u[3][2];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = sign * r[j / 4][j % 4];
-        uint32_t u[3][4];
+        for (int j = 0; j < 4; ++j) x[j / 2][j % 2] = sign * r[j];
         split_pairs(x, u, largest);
 #pragma unroll
-        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(a_dst + (t & 1) * BUF + (i * 6 + p) * FRAG) = make_uint4(u[p][0], u[p][1], u[p][2], u[p][3]);
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) ua[p][2 * h + i] = u[p][i];
     };
-    // Weights go straight into the registers of the wave that multiplies them: eight rows of two neighbouring columns per lane, which
-    // are its column of two fragments, through a buffer descriptor that starts at the 16 rows of a half step (rows past K come
-    // back as zeros).
+    auto write_a = [&](int t) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(a_dst + (t & 1) * BUF + p * FRAG) = make_uint4(ua[p][0], ua[p][1], ua[p][2], ua[p][3]);
+    };
+    // Weights go straight into the registers of the wave that multiplies them: eight rows of a lane's column, through a buffer descriptor
+    // that starts at the 16 rows of a half step (rows past K come back as zeros).
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
-    const int b_off = (half * 8 * a.N + min(n0 + wn * 64 + c * 2, a.N - 2)) * 4;        // columns past the end: never stored
-    // rows 4 h .. 4 h + 3 of a lane's eight in half step s of step t; a half step's pieces of two columns
-    typedef uint32_t Pieces[2][3][4];
-    auto load_b = [&](float (&r)[8][2], int h, int t, int s) {
-        typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    const int b_off = (half * 8 * a.N + min(n0 + wn * 32 + c, a.N - 1)) * 4;            // columns past the end: never stored
+    // rows 4 h .. 4 h + 3 of a lane's eight in half step s of step t
+    typedef uint32_t Pieces[3][4];
+    auto load_b = [&](float (&r)[8], int h, int t, int s) {
         const int k_in = __builtin_amdgcn_readfirstlane(min(t * STEP + q * 32 + s * 16, a.K));
         const int left = __builtin_amdgcn_readfirstlane(min(a.K - k_in, 16));
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B + (size_t)k_in * a.N), 0, left * a.N * 4, 0x00027000);
 #pragma unroll
-        for (int j = 4 * h; j < 4 * h + 4; ++j) {
-            const u32x2_t v = __builtin_bit_cast(u32x2_t, __builtin_amdgcn_raw_buffer_load_b64(rs, b_off + j * a.N * 4, 0, 0));
-            r[j][0] = __uint_as_float(v[0]);
-            r[j][1] = __uint_as_float(v[1]);
-        }
+        for (int j = 4 * h; j < 4 * h + 4; ++j) r[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, b_off + j * a.N * 4, 0, 0));
     };
-    auto split_b = [&](const float (&r)[8][2], int h, Pieces& f) {
-        float x[4][2];
-        uint32_t u[3][4];
+    auto split_b = [&](const float (&r)[8], int h, Pieces& f) {
+        float x[2][2];
+        uint32_t u[3][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {                        // pairs 0, 1: rows of the first column, 2, 3: of the second
-            x[i][0] = r[4 * h + i % 2 * 2][i / 2];
-            x[i][1] = r[4 * h + i % 2 * 2 + 1][i / 2];
-        }
+        for (int j = 0; j < 4; ++j) x[j / 2][j % 2] = r[4 * h + j];
         split_pairs(x, u, largest);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int p = 0; p < 3; ++p)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) f[i / 2][p][2 * h + i % 2] = u[p][i];
+            for (int i = 0; i < 2; ++i) f[p][2 * h + i] = u[p][i];
     };
 
     const int steps = (a.K + STEP - 1) / STEP;
     // The loop exists once per number MS of row blocks that hold rows.
     auto run = [&](auto ms_count) {
         constexpr int MS = decltype(ms_count)::value;
-        f32x16_t acc[MS][2];
+        f32x16_t hi[MS], lo[MS];                             // sums of the products of two first pieces, and of the others
 #pragma unroll
-        for (int i = 0; i < MS * 2; ++i)
+        for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
-            for (int j = 0; j < 16; ++j) acc[i / 2][i % 2][j] = 0.f;
+            for (int j = 0; j < 16; ++j) hi[ms][j] = lo[ms][j] = 0.f;
         auto read_a = [&](bf16x8_t (&f)[MS][3], int t, int s) {
-            const char* p0 = lds + (t & 1) * BUF + q * PAIR + s * 3 * FRAG + (half * 32 + (c ^ swizzle(2 * s + half))) * 16;
+            const char* p0 = lds + (t & 1) * BUF + q * PART + s * 3 * FRAG + (half * 32 + (c ^ swizzle(2 * s + half))) * 16;
 #pragma unroll
             for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
                 for (int p = 0; p < 3; ++p) f[ms][p] = *reinterpret_cast<const bf16x8_t*>(p0 + (ms * 6 + p) * FRAG);
         };
-        // the six products of pieces that reach into the 24 bits of the sum, the smallest first
+        // the six products of pieces that reach into the 24 bits of the sum
         auto multiply = [&](const bf16x8_t (&fa)[MS][3], const Pieces& fb, int from, int to) {
             constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
 #pragma unroll
             for (int t = from; t < to; ++t)
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int ms = 0; ms < MS; ++ms) {
-                        const uint32_t* f = fb[i][PB[t]];
-                        acc[ms][i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ms][PA[t]], __builtin_bit_cast(bf16x8_t, make_uint4(f[0], f[1], f[2], f[3])), acc[ms][i], 0, 0, 0);
-                    }
+                for (int ms = 0; ms < MS; ++ms) {
+                    const uint32_t* f = fb[PB[t]];
+                    f32x16_t& acc = t == 5 ? hi[ms] : lo[ms];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ms][PA[t]], __builtin_bit_cast(bf16x8_t, make_uint4(f[0], f[1], f[2], f[3])), acc, 0, 0, 0);
+                }
         };
         // Everything else goes into the shadow of the matrix instructions (32 clocks each, 24 of them free for six others), evenly: the
-        // waves of a SIMD go through a step together.  A third of a half step each time.  Loads come when what they overwrite has been
+        // waves of a SIMD go through a step together.  A third TH of half step S each time.  Loads come when what they overwrite has been
         // split: any earlier they would get registers of their own, and copies.
-        auto place = [&](auto third) {
-            constexpr int TH = decltype(third)::value;
+        auto place = [&](auto s, auto third) {
+            constexpr int S = decltype(s)::value, TH = decltype(third)::value;
             if (MS == 2) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
+                for (int i = 0; i < 4; ++i) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                   // matrix
-                    if (TH == 0 && i < 6) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);             // LDS read
-                    if (TH == 0 ? i < 4 : TH == 1 ? i >= 2 && i < 4 : i >= 2 && i < 6) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // global load
+                    if (TH == 0) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);                      // LDS read
+                    if (TH == 0 && i < 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    if (TH != 1 || i == 1) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);            // global load
                     __builtin_amdgcn_sched_group_barrier(0x002, 7, 0);                                   // vector ALU
-                    if (TH == 0 && i >= 5) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);            // LDS write
+                    if (S == 0 && TH == 0 && i > 0) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);   // LDS write
                 }
             }
             __builtin_amdgcn_sched_barrier(0);
         };
-        // Step t enters with its first half's fragments in registers, t's activations and the first block of t + 1's in LDS; what is
-        // fetched is used a step later.
-        float b0[8][2], b1[8][2];
-        f32x4_t ra[2][2], first[2][2];
+        constexpr std::integral_constant<int, 0> c0;
+        constexpr std::integral_constant<int, 1> c1;
+        constexpr std::integral_constant<int, 2> c2;
+        // Step t enters with its first half's fragments in registers, t's activations in LDS and half of t + 1's pieces in registers; what
+        // is fetched is used a step later.
+        float b0[8], b1[8];
+        f32x4_t ra[2], first[2];
         bf16x8_t fa0[MS][3], fa1[MS][3];
         Pieces fb0, fb1;
         // (issued in the loop's order: the loop waits for all but so many)
-#pragma unroll
-        for (int i = 0; i < 2; ++i) load_a(first[i], i, 0);
+        load_a(first[0], 0, 0);
+        load_a(first[1], 1, 0);
         load_b(b0, 0, 0, 0);
         load_b(b0, 1, 0, 0);
         load_a(ra[0], 0, 1);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) store_a(first[i], i, 0);
+        split_a(first[0], 0);
+        split_a(first[1], 1);
+        write_a(0);
         split_b(b0, 0, fb0);
         split_b(b0, 1, fb0);
-        store_a(ra[0], 0, 1);
+        split_a(ra[0], 0);
         __builtin_amdgcn_sched_barrier(0);
         load_a(ra[1], 1, 1);
         load_b(b1, 0, 0, 1);
@@ -476,33 +480,34 @@ __global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a,
             multiply(fa0, fb0, 0, 2);
             read_a(fa1, t, 1);
             load_b(b0, 1, t + 1, 0);
-            store_a(ra[1], 1, t + 1);
-            place(std::integral_constant<int, 0>());
+            split_a(ra[1], 1);
+            write_a(t + 1);
+            place(c0, c0);
             multiply(fa0, fb0, 2, 4);
             load_a(ra[1], 1, t + 2);
             split_b(b1, 0, fb1);
-            place(std::integral_constant<int, 1>());
+            place(c0, c1);
             multiply(fa0, fb0, 4, 6);
             load_b(b1, 0, t + 1, 1);
             split_b(b1, 1, fb1);
-            place(std::integral_constant<int, 2>());
+            place(c0, c2);
             lds_barrier();                               // t + 1 is in LDS, and everybody has the fragments of t
             multiply(fa1, fb1, 0, 2);
             read_a(fa0, t + 1, 0);
             load_b(b1, 1, t + 1, 1);
-            store_a(ra[0], 0, t + 2);
-            place(std::integral_constant<int, 0>());
+            split_a(ra[0], 0);
+            place(c1, c0);
             multiply(fa1, fb1, 2, 4);
             load_a(ra[0], 0, t + 3);
             split_b(b0, 0, fb0);
-            place(std::integral_constant<int, 1>());
+            place(c1, c1);
             multiply(fa1, fb1, 4, 6);
             load_b(b0, 0, t + 2, 0);
             split_b(b0, 1, fb0);
-            place(std::integral_constant<int, 2>());
+            place(c1, c2);
         }
 
-        // the pairs' sums meet in LDS, in the order of the pairs
+        // the sets' sums meet in LDS, in the order of the sets
         lds_barrier();
         float* const part = reinterpret_cast<float*>(lds);
 #pragma unroll
@@ -510,15 +515,15 @@ __global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a,
 #pragma unroll
             for (int j = 0; j < 16; ++j) {
                 const int r = ms * 32 + 8 * (j / 4) + 4 * half + j % 4;                  // D: that row, column lane % 32
-                *reinterpret_cast<float2*>(part + ((size_t)q * kSRows + r) * kSCols + wn * 64 + c * 2) = make_float2(acc[ms][0][j], acc[ms][1][j]);
+                part[((size_t)q * kSRows + r) * kSCols + wn * 32 + c] = hi[ms][j] + lo[ms][j];
             }
         lds_barrier();
-        constexpr int NV = MS * 32 * kSCols / 4 / (P * 128);
+        constexpr int NV = MS * 32 * kSCols / 4 / (P * 256);
         f32x4_t v[NV];
         bool bad = !(largest <= kSplitLargest);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int r = (tid + i * P * 128) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
+            const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
             v[i] = *reinterpret_cast<const f32x4_t*>(part + (size_t)r * kSCols + n);
 #pragma unroll
             for (int p = 1; p < P; ++p) {
@@ -531,12 +536,12 @@ __global__ __launch_bounds__(P * 128, 2) void f32_split_kernel(const GemmArgs a,
         if (__ballot(bad)) *flag = 1;
         lds_barrier();
         if (*flag) {
-            for (int i = q; i < 4; i += P) f32_unsplit<EPI>(a, g, rows, m0 + i * 16, n0 + wn * 64, lane);
+            for (int i = w; i < 8; i += P * 4) f32_unsplit<EPI>(a, g, rows, m0 + (i >> 1) * 16, n0 + (i & 1) * 64, lane);
             return;
         }
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int r = (tid + i * P * 128) / (kSCols / 4), n = n0 + tid % (kSCols / 4) * 4;
+            const int r = (tid + i * P * 256) / (kSCols / 4), n = n0 + tid % (kSCols / 4) * 4;
             if (m0 + r < rows && n < a.N) f32_finish<EPI>(a, g, m0 + r, n, v[i]);
         }
     };
@@ -559,7 +564,7 @@ template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, 
     static std::atomic<unsigned long long> asked{0};             // one per instantiation
     const int rc = ask_lds(reinterpret_cast<const void*>(&f32_split_kernel<P, EPI>), split_lds<P>(), asked);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL((f32_split_kernel<P, EPI>), grid, dim3(P * 128), split_lds<P>(), s, a, n_tiles);
+    hipLaunchKernelGGL((f32_split_kernel<P, EPI>), grid, dim3(P * 256), split_lds<P>(), s, a, n_tiles);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -909,12 +914,13 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
     const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;
     if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
-    // Split pieces or fp32 products, two small or one large work-group per compute unit (products, us, fp32 / split with four pairs / with
-    // two): the split kernel's set-up and epilogue want a long K (8 groups x 2000 rows 64 x 256 12.7 / 19.5 / 13.6; 31 x 265, 128 x 512
-    // 23.4 / 27.6 / 24.2; 4 x 2000, 200 x 800 43.6 / 47.9 / 38.3; 8 x 2000, 200 x 100 12.4 / 12.8 / 13.2, 256 x 128 14.1 / 13.3 / 13.6) and
-    // more than half a tile of columns (8 x 8192, 256 x 64 29 / 47 / 35).  Two pairs leave room for a second work-group, whose products run
-    // under the first one's set-up and epilogue, but two of few tiles may meet on a unit while another has none (8 x 384, 512 x 2048,
-    // 768 tiles 60 / 50 / 44; 4 x 480 with room for 720, 2048 x 1024, 256 tiles 69 / 50 / 75; 31 x 132, 2048 x 512, 372 tiles 130 / 84 / 83).
+    // Split pieces or fp32 products, two small or one large work-group per compute unit (products, us, fp32 / split with two sets of waves /
+    // with one): the split kernel's set-up and epilogue want a long K (4 x 2000, 200 x 800 45.6 / 44.7 / 37.8; 31 x 265, 128 x 512 25.2 / 24.8 /
+    // 22.7; 8 x 2000, 100 x 200 20.0 / 18.2 / 17.1; 8 x 300, 192 x 256, 80 tiles 12.6 / 11.2 / 12.8: the line was drawn with waves of 64 columns,
+    // which were the slower ones below it) and more than half a tile of columns (8 x 8192, 256 x 64 29 / 49 / 38).  One set leaves
+    // room for a second work-group, whose products run under the first one's set-up and epilogue, but two of few tiles may meet on a
+    // unit while another has none (8 x 384, 512 x 2048, 768 tiles 64 / 53 / 48; 4 x 480 with room for 720, 2048 x 1024, 256 tiles 75 / 53 / 80;
+    // 31 x 132, 2048 x 512, 372 tiles 135 / 93 / 91).
     const int expect = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
     const long long live = (long long)a.G * ((expect + 63) / 64) * n_tiles;      // tiles if the rows fall evenly on the groups
     const dim3 grid((unsigned)tiles, (unsigned)a.G), block(512);
@@ -927,7 +933,7 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     } else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
     else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
     else if (a.K <= (live > 256 ? 128 : 255)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
-    else return live > 256 ? launch_split<2, EPI>(a, grid, n_tiles, s) : launch_split<4, EPI>(a, grid, n_tiles, s);
+    else return live > 256 ? launch_split<1, EPI>(a, grid, n_tiles, s) : launch_split<2, EPI>(a, grid, n_tiles, s);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
