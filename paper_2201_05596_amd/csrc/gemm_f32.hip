@@ -11,7 +11,7 @@
 // of four rows (16-byte stores).
 //
 // Five kernels:
-//   * f32_split_kernel, groups of more than 32 rows and K beyond 128 (255 where its tiles are few): bound by the bf16 matrix cores and the
+//   * f32_split_kernel, groups of more than 32 rows and K from 160 on (256 where its tiles are few): bound by the bf16 matrix cores and the
 //     vector ALUs beside them.  An fp32 value is the exact sum of three bf16 ones, products of bf16 are exact in fp32, and six of the nine
 //     products of pieces give an fp32 product at 2.6 times the fp32 matrix rate: the other three are 2^-27.5 of it (root mean square; 2^-24
 //     at most).  64 x 128 tiles; sets of four waves of 64 x 32 split K, v_mfma_f32_32x32x16_bf16 (a matrix instruction keeps the vector
@@ -41,7 +41,7 @@
 //     185 / 160; 1000 tokens, 1024/4096, 16 experts, skewed 202 / 188).  Many full tiles would be a little faster with two (8192
 //     tokens, 512/2048, 8 experts 294 / 303).
 //   * f32_ffn_kernel, d_model up to 64: both products in one launch;
-//   * f32_rows_split_kernel, f32_rows_kernel's products of 17 rows and more with K beyond 128, on split operands;
+//   * f32_rows_split_kernel, f32_rows_kernel's products of 17 rows and more with K from 512 on, on split operands;
 //   * f32_rows_kernel, groups of at most 32 rows (and, 32 rows at a time, products with few tiles and those of 2^24 columns or
 //     more, whose 32-row chunks of weights are beyond the offsets of a buffer descriptor): a read of the weights, bound by latency
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
@@ -572,9 +572,11 @@ template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, 
 constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
 
-// sums and epilogue of MS * 16 rows x 64 columns from (m0, n0); part: [kFWaves][MS * 16][16] in LDS
-template <int MS, int EPI>
+// sums and epilogue of MS * 16 rows x 64 columns from (m0, n0) by W waves; part: [W][MS * 16][16] in LDS.
+// Eight sums whatever W is, each in a chain over every eighth block.
+template <int MS, int W, int EPI>
 __device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const part, int g, int rows, int m0, int n0) {
+    constexpr int CHAINS = kFWaves / W, AHEAD = W == kFWaves ? kFAhead : CHAINS;
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const float* a_src[MS];
@@ -591,14 +593,10 @@ __device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const 
 #pragma unroll
         for (int j = 0; j < 4; ++j) b.bv[j] = *reinterpret_cast<const f32x4_t*>(B + (size_t)min(k + j, a.K - 1) * a.N);
     };
-    f32x4_t acc[MS][4];
-#pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) acc[ms][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    f32x4_t acc[CHAINS][MS][4] = {};
     const int blocks = (a.K + 15) / 16;
-    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + kFWaves - 1) / kFWaves : 0);   // blocks w, w + 8, ...
-    auto multiply = [&](Block& b, int kb) {
+    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + W - 1) / W : 0);   // blocks w, w + 8, ...
+    auto multiply = [&](Block& b, int kb, int chain) {
         if (kb * 16 + 16 > a.K) {                            // K ends inside: zeros on both sides (0 times infinity is NaN)
             const bool in = kb * 16 + kg * 4 < a.K;
 #pragma unroll
@@ -614,37 +612,45 @@ __device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const 
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int ms = 0; ms < MS; ++ms)
-                    acc[ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.av[ms][j], b.bv[j][i], acc[ms][i], 0, 0, 0);
+                    acc[chain][ms][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(b.av[ms][j], b.bv[j][i], acc[chain][ms][i], 0, 0, 0);
     };
-    Block st[kFAhead];
+    Block st[AHEAD];
 #pragma unroll
-    for (int s = 0; s < kFAhead; ++s) load(st[s], w + s * kFWaves);        // past the end: in bounds (clamped), never multiplied
+    for (int s = 0; s < AHEAD; ++s) load(st[s], w + s * W);        // past the end: in bounds (clamped), never multiplied
     int q = 0;
-    for (; q + kFAhead < mine; q += kFAhead) {               // the last round fetches nothing
+    for (; q + AHEAD < mine; q += AHEAD) {               // the last round fetches nothing
 #pragma unroll
-        for (int s = 0; s < kFAhead; ++s) {
-            multiply(st[s], w + (q + s) * kFWaves);
-            load(st[s], w + (q + s + kFAhead) * kFWaves);
-            __builtin_amdgcn_sched_barrier(0);               // the refill stays here, kFAhead blocks ahead of its use
+        for (int s = 0; s < AHEAD; ++s) {
+            multiply(st[s], w + (q + s) * W, s % CHAINS);
+            load(st[s], w + (q + s + AHEAD) * W);
+            __builtin_amdgcn_sched_barrier(0);               // the refill stays here, AHEAD blocks ahead of its use
         }
     }
 #pragma unroll
-    for (int s = 0; s < kFAhead; ++s)
-        if (q + s < mine) multiply(st[s], w + (q + s) * kFWaves);
+    for (int s = 0; s < AHEAD; ++s)
+        if (q + s < mine) multiply(st[s], w + (q + s) * W, s % CHAINS);
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms)
+    for (int ms = 0; ms < MS; ++ms) {
+#pragma unroll
+        for (int h = 1; h < CHAINS; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[0][ms][i] += acc[h][ms][i];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            part[(w * MS * 16 + ms * 16 + kg * 4 + r) * 16 + c] = f32x4_t{acc[ms][0][r], acc[ms][1][r], acc[ms][2][r], acc[ms][3][r]};
+            part[(w * MS * 16 + ms * 16 + kg * 4 + r) * 16 + c] = f32x4_t{acc[0][ms][0][r], acc[0][ms][1][r], acc[0][ms][2][r], acc[0][ms][3][r]};
+    }
     __syncthreads();
-    const int row = tid / 16, n = n0 + (tid & 15) * 4;
-    if (m0 + row >= rows || row >= MS * 16 || n >= a.N) return;
-    f32x4_t v = part[row * 16 + (tid & 15)];
+    const int n = n0 + (tid & 15) * 4;
+    if (n >= a.N) return;
 #pragma unroll
-    for (int s = 1; s < kFWaves; ++s) v += part[(s * MS * 16 + row) * 16 + (tid & 15)];
-    f32_finish<EPI>(a, g, m0 + row, n, v);
+    for (int row = tid / 16; row < MS * 16; row += W * 4) {
+        if (m0 + row >= rows) return;
+        f32x4_t v = part[row * 16 + (tid & 15)];
+#pragma unroll
+        for (int s = 1; s < W; ++s) v += part[(s * MS * 16 + row) * 16 + (tid & 15)];
+        f32_finish<EPI>(a, g, m0 + row, n, v);
+    }
 }
-
 
 template <int MS, int EPI>
 __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArgs a, const int n_tiles) {
@@ -653,24 +659,27 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
     const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * MS * 16), g = blockIdx.y;
     const int rows = f32_rows_of(a, g);
     if (m0 >= rows) return;
-    f32_rows_tile<MS, EPI>(a, part, g, rows, m0, nt * 64);
+    f32_rows_tile<MS, kFWaves, EPI>(a, part, g, rows, m0, nt * 64);
 }
 
-// The same with 32 rows and K beyond 128 on the bf16 matrix instructions, operands split as in f32_split_kernel: every wave splits what
-// it loads, nothing is shared.  WGS work-groups per compute unit (the register limit of one keeps a second away, so that few tiles
-// spread over the chip).  Products, us, fp32 / split with one / with two: 4 x 75 rows, 2048 x 512 25.9 / 20.3 / 20.6, 512 x 2048 18.2 /
-// 14.6 / 13.7; 8 x 256, 2048 x 512 56.0 / 42.5 / 41.6, half of the tiles empty 55.3 / 26.2 / 37.2; 31 x 24, 512 x 2048 33.8 / 30.9 / 26.2;
-// 1 x 60, 2048 x 512 23.7 / 18.2 / 18.6; K = 128 no faster (4 x 64, 128 x 512 5.2 / 5.0 / 5.5; 31 x 130, 128 x 128 8.4 / 8.4 / 9.9).
-constexpr int kRowsSplitLds = kFWaves * 32 * 64 * 4 + 16;        // partial sums and a flag
-template <int WGS, int EPI>
-__global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(const GemmArgs a, const int n_tiles) {
+// The same with 32 rows and K from 512 on on the bf16 matrix instructions, operands split as in f32_split_kernel: every wave splits what
+// it loads, nothing is shared.  W waves share K: eight, which have a compute unit to themselves (few tiles then spread over the chip),
+// or four, of which two or three work-groups share a unit.  Products, us, fp32 / eight waves / four: 4 x 75 rows, 2048 x 512 24.4 / 19.1
+// / 19.3, 512 x 2048 17.9 / 15.2 / 13.9; 8 x 256, 2048 x 512 51.9 / 38.4 / 37.2, half of the tiles empty 50.2 / 20.8 / 33.7; 31 x 24, 512 x 2048 31.8 /
+// 31.1 / 25.2; 1 x 60, 2048 x 512 24.0 / 18.6 / 19.4; 8 x 130, 800 x 200 12.4 / 10.2 / 10.4; 16 x 100, 256 x 1024 17.9 / 18.7 / 15.8.
+// Errors against 64 bits 0.5 to 1.0 of the fp32 ones on every class of operands named at f32_split_kernel.  Not with a shorter K: there one
+// large column among values of one sign, whose group's products are cut to its grid, is 1.02 .. 1.4 times as far off (K = 320 / 256 / 132: the
+// fp32 sums are eight chains of few roundings), and there is little to gain.
+template <int W> constexpr int rows_split_lds() { return W * 32 * 64 * 4 + 16; }     // partial sums and a flag
+template <int W, int EPI>
+__global__ __launch_bounds__(W * 64, 2) void f32_rows_split_kernel(const GemmArgs a, const int n_tiles) {
     constexpr int AHEAD = 2;                                     // 16-deep blocks in flight per wave
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    float* const part = reinterpret_cast<float*>(lds);           // [kFWaves][32][64]
-    int* const flag = reinterpret_cast<int*>(lds + kRowsSplitLds - 16);
+    float* const part = reinterpret_cast<float*>(lds);           // [W][32][64]
+    int* const flag = reinterpret_cast<int*>(lds + rows_split_lds<W>() - 16);
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, kFWaves * 64);
+    if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, W * 64);
     const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * 32), g = blockIdx.y;
     const int rows = f32_rows_of(a, g), n0 = nt * 64;
     if (m0 >= rows) return;
@@ -678,17 +687,17 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
     const float* const a_src = f32_arow(a, g, min(m0 + c, rows - 1));              // rows past the end repeat the last one
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
     const int b_off = (half * 8 * a.N + min(n0 + c * 2, a.N - 2)) * 4;             // columns past the end: never stored
-    const float sign = w % 2 ? -1.f : 1.f;                       // every other wave's sums negated: the matrix instruction rounds down
+    const float sign = w % 2 ? -1.f : 1.f;                       // every other wave's sums negated, as in f32_split_kernel
     float largest = 0.f;
     struct Block {
         f32x4_t av[2];
         float bv[8][2];
     };
     const int blocks = (a.K + 15) / 16;
-    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + kFWaves - 1) / kFWaves : 0);   // blocks w, w + 8, ...
+    const int mine = __builtin_amdgcn_readfirstlane(w < blocks ? (blocks - w + W - 1) / W : 0);   // blocks w, w + W, ...
     auto load = [&](Block& b, int i) {                           // past K: weights zero (also past the wave's last block), activations any
         typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
-        const int k_in = __builtin_amdgcn_readfirstlane(min((w + i * kFWaves) * 16, a.K));
+        const int k_in = __builtin_amdgcn_readfirstlane(min((w + i * W) * 16, a.K));
         const int left = __builtin_amdgcn_readfirstlane(min(a.K - k_in, 16));
         const __amdgpu_buffer_rsrc_t rs =
             __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(B + (size_t)k_in * a.N), 0, left * a.N * 4, 0x00027000);
@@ -701,11 +710,11 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
             b.bv[j][1] = __uint_as_float(v[1]);
         }
     };
-    f32x16_t acc[2];
+    f32x16_t hi[2], lo[2];                                       // sums of the products of two first pieces, and of the others
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 16; ++j) acc[i][j] = 0.f;
+        for (int j = 0; j < 16; ++j) hi[i][j] = lo[i][j] = 0.f;
     auto frag = [](const uint32_t (&u)[4]) { return __builtin_bit_cast(bf16x8_t, make_uint4(u[0], u[1], u[2], u[3])); };
     auto multiply = [&](const Block& b) {
         constexpr int PA[6] = {0, 1, 2, 0, 1, 0}, PB[6] = {2, 1, 0, 1, 0, 0};
@@ -723,7 +732,10 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
 #pragma unroll
         for (int t = 0; t < 6; ++t)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(ua[PA[t]]), frag(ub[i][PB[t]]), acc[i], 0, 0, 0);
+            for (int i = 0; i < 2; ++i) {
+                f32x16_t& acc = t == 5 ? hi[i] : lo[i];
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag(ua[PA[t]]), frag(ub[i][PB[t]]), acc, 0, 0, 0);
+            }
     };
     Block st[AHEAD];
 #pragma unroll
@@ -743,25 +755,35 @@ __global__ __launch_bounds__(kFWaves * 64, 2 * WGS) void f32_rows_split_kernel(c
         if (i + s < mine) multiply(st[s]);
 #pragma unroll
     for (int j = 0; j < 16; ++j)                                 // D: rows 8 (j / 4) + 4 half + j % 4, column lane % 32
-        *reinterpret_cast<float2*>(part + (w * 32 + 8 * (j / 4) + 4 * half + j % 4) * 64 + c * 2) = make_float2(acc[0][j], acc[1][j]);
+        *reinterpret_cast<float2*>(part + (w * 32 + 8 * (j / 4) + 4 * half + j % 4) * 64 + c * 2) = make_float2(hi[0][j] + lo[0][j], hi[1][j] + lo[1][j]);
     lds_barrier();
-    const int row = tid / 16, n = (tid & 15) * 4;
-    f32x4_t v = *reinterpret_cast<const f32x4_t*>(part + row * 64 + n);
-#pragma unroll
-    for (int s = 1; s < kFWaves; ++s) {
-        const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + (s * 32 + row) * 64 + n);
-        v = s % 2 ? v - u : v + u;
-    }
+    constexpr int NV = 32 * 16 / (W * 64);
+    const int n = (tid & 15) * 4;
+    f32x4_t v[NV];
     bool bad = !(largest <= kSplitLargest);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[j]) <= 3.4028234e38f) || (fabsf(v[j]) < kSplitSmallest && v[j] != 0.f);
+    for (int i = 0; i < NV; ++i) {
+        const int row = tid / 16 + i * W * 4;
+        v[i] = *reinterpret_cast<const f32x4_t*>(part + row * 64 + n);
+#pragma unroll
+        for (int s = 1; s < W; ++s) {
+            const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + (s * 32 + row) * 64 + n);
+            v[i] = s % 2 ? v[i] - u : v[i] + u;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[i][j]) <= 3.4028234e38f) || (fabsf(v[i][j]) < kSplitSmallest && v[i][j] != 0.f);
+    }
     if (__ballot(bad)) *flag = 1;
     lds_barrier();
     if (*flag) {                                                 // uniform over the work-group: unsplit, as above
-        f32_rows_tile<2, EPI>(a, reinterpret_cast<f32x4_t*>(lds), g, rows, m0, n0);
+        f32_rows_tile<2, W, EPI>(a, reinterpret_cast<f32x4_t*>(lds), g, rows, m0, n0);
         return;
     }
-    if (m0 + row < rows && n0 + n < a.N) f32_finish<EPI>(a, g, m0 + row, n0 + n, v);
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+        const int row = tid / 16 + i * W * 4;
+        if (m0 + row < rows && n0 + n < a.N) f32_finish<EPI>(a, g, m0 + row, n0 + n, v[i]);
+    }
 }
 
 // ---- both products of a narrow FFN -------------------------------------------------------------------------
@@ -893,11 +915,11 @@ template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipS
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-template <int WGS, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
+template <int W, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
     static std::atomic<unsigned long long> asked{0};             // one per instantiation
-    const int rc = ask_lds(reinterpret_cast<const void*>(&f32_rows_split_kernel<WGS, EPI>), kRowsSplitLds, asked);
+    const int rc = ask_lds(reinterpret_cast<const void*>(&f32_rows_split_kernel<W, EPI>), rows_split_lds<W>(), asked);
     if (rc != MOE_OK) return rc;
-    hipLaunchKernelGGL((f32_rows_split_kernel<WGS, EPI>), grid, dim3(kFWaves * 64), kRowsSplitLds, s, a, n_tiles);
+    hipLaunchKernelGGL((f32_rows_split_kernel<W, EPI>), grid, dim3(W * 64), rows_split_lds<W>(), s, a, n_tiles);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -917,7 +939,7 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // Split pieces or fp32 products, two small or one large work-group per compute unit (products, us, fp32 / split with two sets of waves /
     // with one): the split kernel's set-up and epilogue want a long K (4 x 2000, 200 x 800 45.6 / 44.7 / 37.8; 31 x 265, 128 x 512 25.2 / 24.8 /
     // 22.7; 8 x 2000, 100 x 200 20.0 / 18.2 / 17.1; 8 x 300, 192 x 256, 80 tiles 12.6 / 11.2 / 12.8: the line was drawn with waves of 64 columns,
-    // which were the slower ones below it) and more than half a tile of columns (8 x 8192, 256 x 64 29 / 49 / 38).  One set leaves
+    // which were the slower ones below it, and below 160 one large column among values of one sign is 1.1 times as far off 64 bits) and more than half a tile of columns (8 x 8192, 256 x 64 29 / 49 / 38).  One set leaves
     // room for a second work-group, whose products run under the first one's set-up and epilogue, but two of few tiles may meet on a
     // unit while another has none (8 x 384, 512 x 2048, 768 tiles 64 / 53 / 48; 4 x 480 with room for 720, 2048 x 1024, 256 tiles 75 / 53 / 80;
     // 31 x 132, 2048 x 512, 372 tiles 135 / 93 / 91).
@@ -927,12 +949,12 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     static_assert(kFWaves * 64 == 512, "all kernels have the same work-group");
     static_assert(kSRows == 64 && kSCols == 128, "the same tile");
     if (few && tm == 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (few && a.K > 128 && a.N < 1 << 24) {
+    else if (few && a.K >= 512 && a.N < 1 << 24) {
         const long long live32 = (long long)a.G * ((expect + 31) / 32) * n_tiles;
-        return live32 > 256 ? launch_rows_split<2, EPI>(a, grid, n_tiles, s) : launch_rows_split<1, EPI>(a, grid, n_tiles, s);
+        return live32 > 256 ? launch_rows_split<4, EPI>(a, grid, n_tiles, s) : launch_rows_split<8, EPI>(a, grid, n_tiles, s);
     } else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
     else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (a.K <= (live > 256 ? 128 : 255)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
+    else if (a.K < (live > 256 ? 160 : 256)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
     else return live > 256 ? launch_split<1, EPI>(a, grid, n_tiles, s) : launch_split<2, EPI>(a, grid, n_tiles, s);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
