@@ -50,6 +50,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "gate_common.h"
 #include "moe_internal.h"
 
 namespace moe {
@@ -268,9 +269,32 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 constexpr int kSRows = 64, kSCols = 128;      // of a tile: four waves of 32 columns
 
-// The matrix instruction takes pieces below 2^-126 for zero.  That cannot show in a sum of at least 2^-70 over operands of at most 2^20
-// (2^11 products, each off by less than 2^-105: 2^-24 of it); tiles with other sums or operands are multiplied unsplit.
-constexpr float kSplitSmallest = 0x1p-70f, kSplitLargest = 0x1p20f;
+// Which elements of a vector of four sums the split does not hold (a bit each); they are taken again on the fp32 instructions.  bf16 ends
+// at 2^-133, so up to 2^-134 of an operand is left out of its pieces.  With row and column the largest magnitudes in an element's row of
+// activations and column of weights, K products lose less than K 2^-133 (row + column): 2^-25 of a sum of at least K 2^-108 (row + column).
+// Smaller ones, zero included, are not held, unless the row or the column is all zeros.  Nor are sums that are not finite: pieces of
+// infinities do not add up.
+__device__ __forceinline__ int split_misses(const f32x4_t& v, int K, float row, const f32x4_t& column) {
+    const float k = (float)K * 0x1p-108f;
+    int bits = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool small = fabsf(v[j]) < fmaf(k, column[j], k * row) && row != 0.f && column[j] != 0.f;
+        bits |= (!(fabsf(v[j]) <= 3.4028234e38f) || small) << j;
+    }
+    return bits;
+}
+
+// the largest of a wave's values
+__device__ __forceinline__ float wave_largest(float v) {
+    v = fmaxf(v, dpp_f<kDppSwap1>(v));
+    v = fmaxf(v, dpp_f<kDppSwap2>(v));
+    v = fmaxf(v, dpp_f<kDppHalfMirror>(v));
+    v = fmaxf(v, dpp_f<kDppMirror>(v));                      // of 16 lanes
+    const int b = __float_as_int(v);
+    auto lane = [b](int l) { return __int_as_float(__builtin_amdgcn_readlane(b, l)); };
+    return fmaxf(fmaxf(lane(0), lane(16)), fmaxf(lane(32), lane(48)));
+}
 
 // M pairs of fp32 values as three times M pairs of bf16: a value is piece 0 + piece 1 + piece 2 exactly (3 x 8 significant
 // bits, each piece the nearest bf16 of what is left).  Infinities, NaN and values that round to infinity leave NaN in the later pieces.
@@ -293,10 +317,16 @@ template <int M> __device__ __forceinline__ void split_pairs(float (&x)[M][2], u
     }
 }
 
-// 16 rows x 64 columns from (m0, n0) on the fp32 matrix instructions, straight from memory, finished: for the tiles that hold an
-// infinity, a NaN or an overflow, whose pieces do not add up.
-template <int EPI> __device__ void f32_unsplit(const GemmArgs& a, int g, int rows, int m0, int n0, int lane) {
+// 16 rows x 64 columns from (m0, n0) on the fp32 matrix instructions, straight from memory: finishes the vectors of four sums that have bits in
+// misses, taking the marked elements from here and the others from sums (both start at the rows and columns of this part of the tile).  So an
+// element is the same whatever the other rows and columns hold.
+template <int EPI>
+__device__ void f32_unsplit(const GemmArgs& a, int g, int rows, int m0, int n0, int lane, const uint8_t* misses, const float* sums) {
     const int c = lane & 15, kg = lane >> 4, n = n0 + c * 4;
+    uint32_t bits = 0;                                       // of the lane's four rows, a byte each
+#pragma unroll
+    for (int r = 0; r < 4; ++r) bits |= (uint32_t)misses[(kg * 4 + r) * (kSCols / 4) + c] << (8 * r);
+    if (!__ballot(bits)) return;
     const float* A = f32_arow(a, g, min(m0 + c, rows - 1));
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N + min(n, a.N - 4);
     f32x4_t acc[2][4] = {};                                  // every other 16 k: half as many steps that round a sum
@@ -318,23 +348,32 @@ template <int EPI> __device__ void f32_unsplit(const GemmArgs& a, int g, int row
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) acc[0][i] += acc[1][i];
-    if (n >= a.N) return;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int row = m0 + kg * 4 + r;
-        if (row < rows) f32_finish<EPI>(a, g, row, n, f32x4_t{acc[0][0][r], acc[0][1][r], acc[0][2][r], acc[0][3][r]});
+        const int b = bits >> (8 * r) & 15;
+        if (!b) continue;
+        f32x4_t v = *reinterpret_cast<const f32x4_t*>(sums + (kg * 4 + r) * kSCols + c * 4);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (b >> i & 1) v[i] = acc[0][i][r];
+        f32_finish<EPI>(a, g, m0 + kg * 4 + r, n, v);
     }
 }
 
-template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + 16; }   // partial sums and a flag; less before
+// partial sums (less before), the largest values of rows and columns, a flag, bits of split_misses
+constexpr int kSplitMisses = kSRows * kSCols / 4, kSplitLargest = (kSRows + kSCols) * 4;
+template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + kSplitLargest + 16 + kSplitMisses; }
 
 // P sets of four waves split K between them, 32 deep in turn; wave 4 q + wn has columns 32 wn .. + 31 of the tile and set q's K.
 template <int P, int EPI>
 __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a, const int n_tiles) {
     constexpr int FRAG = 1024, PART = 2 * 2 * 3 * FRAG, BUF = P * PART, STEP = P * 32;      // STEP: k per step of the loop
     extern __shared__ __attribute__((aligned(16))) char lds[];
-    static_assert(2 * BUF <= split_lds<P>() - 16, "two buffers of activation pieces");
-    int* const flag = reinterpret_cast<int*>(lds + split_lds<P>() - 16);
+    static_assert(2 * BUF <= P * kSRows * kSCols * 4, "two buffers of activation pieces");
+    float* const part = reinterpret_cast<float*>(lds);
+    uint32_t* const largest = reinterpret_cast<uint32_t*>(lds + P * kSRows * kSCols * 4);        // [kSRows + kSCols], magnitudes as integers
+    int* const flag = reinterpret_cast<int*>(largest + kSRows + kSCols);
+    uint8_t* const misses = reinterpret_cast<uint8_t*>(flag + 4);                                // [kSRows][kSCols / 4]
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, half = lane >> 5;
     const int q = w >> 2, wn = w & 3;
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, P * 256);
@@ -343,7 +382,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
     const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles, g = blockIdx.y;
     const int rows = f32_rows_of(a, g), m0 = mt * kSRows, n0 = nt * kSCols;
     if (m0 >= rows) return;
-    if (tid == 0) *flag = 0;
+    if (tid <= kSRows + kSCols) largest[tid] = 0;                // and the flag
 
     // Activations: four threads take 32 k of a row, eight each, and put the pieces into LDS as fragments [row block][16 k][piece] of
     // v_mfma_f32_32x32x16_bf16.  Row r's 16 bytes of k-octet o stand at (o % 2) * 32 + (r ^ x(o)): x sends the lanes of one LDS
@@ -354,7 +393,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
     char* const a_dst = lds + q * PART + ((a_r >> 5) * 6 + (oct >> 1) * 3) * FRAG + ((oct & 1) * 32 + ((a_r & 31) ^ swizzle(oct))) * 16;
     // values 4 h .. 4 h + 3 of a thread's eight of step t
     auto load_a = [&](f32x4_t& r, int h, int t) { r = *reinterpret_cast<const f32x4_t*>(a_src + min(t * STEP + q * 32 + oct * 8 + h * 4, a.K - 4)); };
-    float largest = 0.f;                                     // of the operands that this thread splits
+    float row_max = 0.f, col_max = 0.f;                      // largest magnitudes that this thread splits
     // Every other set of waves sums the products negated: where a sum is cut to the grid of a larger product, the cut is not to nearest.
     const float sign = q % 2 ? -1.f : 1.f;
     uint32_t ua[3][4];                                       // pieces of a thread's eight values
@@ -364,7 +403,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
         uint32_t u[3][2];
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[j / 2][j % 2] = sign * r[j];
-        split_pairs(x, u, largest);
+        split_pairs(x, u, row_max);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
 #pragma unroll
@@ -393,7 +432,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
         uint32_t u[3][2];
 #pragma unroll
         for (int j = 0; j < 4; ++j) x[j / 2][j % 2] = r[4 * h + j];
-        split_pairs(x, u, largest);
+        split_pairs(x, u, col_max);
 #pragma unroll
         for (int p = 0; p < 3; ++p)
 #pragma unroll
@@ -509,7 +548,8 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
 
         // the sets' sums meet in LDS, in the order of the sets
         lds_barrier();
-        float* const part = reinterpret_cast<float*>(lds);
+        atomicMax(&largest[a_r], __float_as_uint(row_max));
+        atomicMax(&largest[kSRows + wn * 32 + c], __float_as_uint(col_max));
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
@@ -520,7 +560,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
         lds_barrier();
         constexpr int NV = MS * 32 * kSCols / 4 / (P * 256);
         f32x4_t v[NV];
-        bool bad = !(largest <= kSplitLargest);
+        int bits[NV], any = 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
@@ -530,19 +570,27 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
                 const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + ((size_t)p * kSRows + r) * kSCols + n);
                 v[i] = p % 2 ? v[i] - u : v[i] + u;
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[i][j]) <= 3.4028234e38f) || (fabsf(v[i][j]) < kSplitSmallest && v[i][j] != 0.f);
+            const bool in = m0 + r < rows && n0 + n < a.N;
+            bits[i] = in ? split_misses(v[i], a.K, __uint_as_float(largest[r]), *reinterpret_cast<const f32x4_t*>(largest + kSRows + n)) : 0;
+            any |= bits[i];
         }
-        if (__ballot(bad)) *flag = 1;
+        if (__ballot(any)) *flag = 1;
         lds_barrier();
-        if (*flag) {
-            for (int i = w; i < 8; i += P * 4) f32_unsplit<EPI>(a, g, rows, m0 + (i >> 1) * 16, n0 + (i & 1) * 64, lane);
-            return;
-        }
+        const bool again = *flag;                            // uniform over the work-group
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            const int r = (tid + i * P * 256) / (kSCols / 4), n = n0 + tid % (kSCols / 4) * 4;
-            if (m0 + r < rows && n < a.N) f32_finish<EPI>(a, g, m0 + r, n, v[i]);
+            const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
+            if (again) {
+                misses[r * (kSCols / 4) + n / 4] = bits[i];
+                if (bits[i]) *reinterpret_cast<f32x4_t*>(part + (size_t)r * kSCols + n) = v[i];  // where this thread alone read before
+            }
+            if (m0 + r < rows && n0 + n < a.N && !bits[i]) f32_finish<EPI>(a, g, m0 + r, n0 + n, v[i]);
+        }
+        if (!again) return;
+        lds_barrier();
+        for (int i = w; i < 4 * MS; i += P * 4) {            // 16 rows x 64 columns at a time
+            const int r = (i >> 1) * 16, n = (i & 1) * 64;
+            f32_unsplit<EPI>(a, g, rows, m0 + r, n0 + n, lane, misses + r * (kSCols / 4) + n / 4, part + (size_t)r * kSCols + n);
         }
     };
     if (rows - m0 > 32) run(std::integral_constant<int, 2>());
@@ -572,10 +620,10 @@ template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, 
 constexpr int kFWaves = 8;                    // waves of a work-group = ways K is split
 constexpr int kFAhead = 3;                    // 16-deep blocks in flight per wave
 
-// sums and epilogue of MS * 16 rows x 64 columns from (m0, n0) by W waves; part: [W][MS * 16][16] in LDS.
+// sums of MS * 16 rows x 64 columns from (m0, n0) by W waves, a part by each: part is [W][MS * 16][16] in LDS.
 // Eight sums whatever W is, each in a chain over every eighth block.
-template <int MS, int W, int EPI>
-__device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const part, int g, int rows, int m0, int n0) {
+template <int MS, int W>
+__device__ __forceinline__ void f32_rows_parts(const GemmArgs& a, f32x4_t* const part, int g, int rows, int m0, int n0) {
     constexpr int CHAINS = kFWaves / W, AHEAD = W == kFWaves ? kFAhead : CHAINS;
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -640,16 +688,13 @@ __device__ __forceinline__ void f32_rows_tile(const GemmArgs& a, f32x4_t* const 
             part[(w * MS * 16 + ms * 16 + kg * 4 + r) * 16 + c] = f32x4_t{acc[0][ms][0][r], acc[0][ms][1][r], acc[0][ms][2][r], acc[0][ms][3][r]};
     }
     __syncthreads();
-    const int n = n0 + (tid & 15) * 4;
-    if (n >= a.N) return;
+}
+// columns 4 n .. 4 n + 3 of a row of the tile
+template <int MS, int W> __device__ __forceinline__ f32x4_t f32_rows_sum(const f32x4_t* part, int row, int n) {
+    f32x4_t v = part[row * 16 + n];
 #pragma unroll
-    for (int row = tid / 16; row < MS * 16; row += W * 4) {
-        if (m0 + row >= rows) return;
-        f32x4_t v = part[row * 16 + (tid & 15)];
-#pragma unroll
-        for (int s = 1; s < W; ++s) v += part[(s * MS * 16 + row) * 16 + (tid & 15)];
-        f32_finish<EPI>(a, g, m0 + row, n, v);
-    }
+    for (int s = 1; s < W; ++s) v += part[(s * MS * 16 + row) * 16 + n];
+    return v;
 }
 
 template <int MS, int EPI>
@@ -659,7 +704,10 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
     const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * MS * 16), g = blockIdx.y;
     const int rows = f32_rows_of(a, g);
     if (m0 >= rows) return;
-    f32_rows_tile<MS, kFWaves, EPI>(a, part, g, rows, m0, nt * 64);
+    f32_rows_parts<MS, kFWaves>(a, part, g, rows, m0, nt * 64);
+    const int row = threadIdx.x / 16, n = nt * 64 + (threadIdx.x & 15) * 4;
+    if (m0 + row >= rows || row >= MS * 16 || n >= a.N) return;
+    f32_finish<EPI>(a, g, m0 + row, n, f32_rows_sum<MS, kFWaves>(part, row, threadIdx.x & 15));
 }
 
 // The same with 32 rows and K from 512 on on the bf16 matrix instructions, operands split as in f32_split_kernel: every wave splits what
@@ -670,25 +718,27 @@ __global__ __launch_bounds__(kFWaves * 64, 4) void f32_rows_kernel(const GemmArg
 // Errors against 64 bits 0.5 to 1.0 of the fp32 ones on every class of operands named at f32_split_kernel.  Not with a shorter K: there one
 // large column among values of one sign, whose group's products are cut to its grid, is 1.02 .. 1.4 times as far off (K = 320 / 256 / 132: the
 // fp32 sums are eight chains of few roundings), and there is little to gain.
-template <int W> constexpr int rows_split_lds() { return W * 32 * 64 * 4 + 16; }     // partial sums and a flag
+template <int W> constexpr int rows_split_lds() { return W * 32 * 64 * 4 + (32 + 64 + 4 + W) * 4; }     // partial sums, largest values, flags
 template <int W, int EPI>
 __global__ __launch_bounds__(W * 64, 2) void f32_rows_split_kernel(const GemmArgs a, const int n_tiles) {
     constexpr int AHEAD = 2;                                     // 16-deep blocks in flight per wave
     extern __shared__ __attribute__((aligned(16))) char lds[];
     float* const part = reinterpret_cast<float*>(lds);           // [W][32][64]
-    int* const flag = reinterpret_cast<int*>(lds + rows_split_lds<W>() - 16);
+    uint32_t* const largest = reinterpret_cast<uint32_t*>(lds + W * 32 * 64 * 4);  // [32 rows + 64 columns], magnitudes as integers
+    int* const flags = reinterpret_cast<int*>(largest + 32 + 64);                  // [2]
+    float* const wave_max = reinterpret_cast<float*>(flags + 4);                   // [W]
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, half = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, W * 64);
     const int nt = blockIdx.x % n_tiles, m0 = __builtin_amdgcn_readfirstlane(blockIdx.x / n_tiles * 32), g = blockIdx.y;
     const int rows = f32_rows_of(a, g), n0 = nt * 64;
     if (m0 >= rows) return;
-    if (tid == 0) *flag = 0;
+    if (tid < 32 + 64 + 2) largest[tid] = 0;                     // and the flags
     const float* const a_src = f32_arow(a, g, min(m0 + c, rows - 1));              // rows past the end repeat the last one
     const float* B = static_cast<const float*>(a.B) + (size_t)g * a.K * a.N;
     const int b_off = (half * 8 * a.N + min(n0 + c * 2, a.N - 2)) * 4;             // columns past the end: never stored
     const float sign = w % 2 ? -1.f : 1.f;                       // every other wave's sums negated, as in f32_split_kernel
-    float largest = 0.f;
+    float row_max = 0.f, col_max[2] = {0.f, 0.f};
     struct Block {
         f32x4_t av[2];
         float bv[8][2];
@@ -722,12 +772,12 @@ __global__ __launch_bounds__(W * 64, 2) void f32_rows_split_kernel(const GemmArg
         float x[4][2];
 #pragma unroll
         for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = sign * b.av[j / 4][j % 4];
-        split_pairs(x, ua, largest);
+        split_pairs(x, ua, row_max);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = b.bv[j][i];
-            split_pairs(x, ub[i], largest);
+            split_pairs(x, ub[i], col_max[i]);
         }
 #pragma unroll
         for (int t = 0; t < 6; ++t)
@@ -756,11 +806,16 @@ __global__ __launch_bounds__(W * 64, 2) void f32_rows_split_kernel(const GemmArg
 #pragma unroll
     for (int j = 0; j < 16; ++j)                                 // D: rows 8 (j / 4) + 4 half + j % 4, column lane % 32
         *reinterpret_cast<float2*>(part + (w * 32 + 8 * (j / 4) + 4 * half + j % 4) * 64 + c * 2) = make_float2(hi[0][j] + lo[0][j], hi[1][j] + lo[1][j]);
+    const float lane_max = fmaxf(row_max, fmaxf(col_max[0], col_max[1])), in_wave = wave_largest(lane_max);
+    if (lane == 0) wave_max[w] = in_wave;
     lds_barrier();
     constexpr int NV = 32 * 16 / (W * 64);
     const int n = (tid & 15) * 4;
     f32x4_t v[NV];
-    bool bad = !(largest <= kSplitLargest);
+    float tile_max = wave_max[0];
+#pragma unroll
+    for (int s = 1; s < W; ++s) tile_max = fmaxf(tile_max, wave_max[s]);
+    int any = 0;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
         const int row = tid / 16 + i * W * 4;
@@ -770,14 +825,37 @@ __global__ __launch_bounds__(W * 64, 2) void f32_rows_split_kernel(const GemmArg
             const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + (s * 32 + row) * 64 + n);
             v[i] = s % 2 ? v[i] - u : v[i] + u;
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bad |= !(fabsf(v[i][j]) <= 3.4028234e38f) || (fabsf(v[i][j]) < kSplitSmallest && v[i][j] != 0.f);
+        if (m0 + row < rows && n0 + n < a.N) any |= split_misses(v[i], a.K, tile_max, f32x4_t{tile_max, tile_max, tile_max, tile_max});
     }
-    if (__ballot(bad)) *flag = 1;
+    // Sums that are too small under the largest values of the whole tile are looked at again under those of their row and column.
+    if (__ballot(any)) flags[0] = 1;
     lds_barrier();
-    if (*flag) {                                                 // uniform over the work-group: unsplit, as above
-        f32_rows_tile<2, W, EPI>(a, reinterpret_cast<f32x4_t*>(lds), g, rows, m0, n0);
-        return;
+    if (flags[0]) {                                              // uniform over the work-group
+        atomicMax(&largest[c], __float_as_uint(row_max));
+#pragma unroll
+        for (int i = 0; i < 2; ++i) atomicMax(&largest[32 + c * 2 + i], __float_as_uint(col_max[i]));
+        lds_barrier();
+        int bits[NV];
+        any = 0;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int row = tid / 16 + i * W * 4;
+            const bool in = m0 + row < rows && n0 + n < a.N;
+            bits[i] = in ? split_misses(v[i], a.K, __uint_as_float(largest[row]), *reinterpret_cast<const f32x4_t*>(largest + 32 + n)) : 0;
+            any |= bits[i];
+        }
+        if (__ballot(any)) flags[1] = 1;
+        lds_barrier();
+        if (flags[1]) {                                          // marked elements from the fp32 instructions
+            f32_rows_parts<2, W>(a, reinterpret_cast<f32x4_t*>(lds), g, rows, m0, n0);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const f32x4_t u = f32_rows_sum<2, W>(reinterpret_cast<f32x4_t*>(lds), tid / 16 + i * W * 4, tid & 15);
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (bits[i] >> j & 1) v[i][j] = u[j];
+            }
+        }
     }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {

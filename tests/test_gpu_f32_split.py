@@ -157,3 +157,58 @@ def test_no_further_from_64_bits_than_fp32(E, C, d, f, chains, operands):
     error, allowed = (ye.double() - ref).norm().item(), (fp32.double() - ref).norm().item()
     print(f"  {error / allowed:.3f}", flush=True)
     assert error <= 1.01 * allowed                           # the fp32 kernels themselves: 0.78 to 1.001 (their order of 16 k)
+
+
+# one and two sets of waves per tile; eight and four waves per tile of 32 rows
+SHAPES = [(32, 640, 512, 128), (8, 1200, 512, 128), (32, 64, 512, 128), (64, 96, 512, 128)]
+
+
+def _expert_ffn(xe, W1, W2):
+    m, (E, C, d), f = U.amd(), xe.shape, W1.shape[2]
+    shape = m.make_shape(E * C, d, f, E, 1, C, "f32")
+    ye, zero = torch.empty_like(xe), torch.zeros(E, max(d, f), device="cuda")
+    m.moe_expert_ffn(shape, xe, torch.full((E,), C, dtype=torch.int32, device="cuda"), W1, zero[:, :f].contiguous(), W2, zero[:, :d].contiguous(), ye,
+                     m.alloc_workspace(shape, "cuda"))
+    torch.cuda.synchronize()
+    return ye
+
+
+@pytest.mark.parametrize("x,w", [(-130, 0), (-130, 20), (-140, 19), (-140, 30), (-110, 10), (-100, 0), (-60, -50), (-60, 0), (100, -100), (60, -60), (0, 0)])
+@pytest.mark.parametrize("E,C,d,f", SHAPES + [(2, 300, 4096, 128)])
+def test_magnitudes(E, C, d, f, x, w):
+    """Activations around 2^x (below -126 subnormal, below -134 without a bf16 piece) under weights around 2^w, no bias: sums as small as fp32 holds."""
+    print(f"case E={E} C={C} d={d} f={f} 2^{x} 2^{w}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(d + f)
+    n = lambda *s, std: torch.empty(s, device="cuda").normal_(0.0, std, generator=g)
+    xe, W1, W2 = n(E, C, d, std=2.0 ** x), n(E, d, f, std=2.0 ** (w - 5)), n(E, f, d, std=2.0 ** -min(x + w, 0) if x + w > -120 else 2.0 ** 100)
+    ye = _expert_ffn(xe, W1, W2)
+    ref = torch.nn.functional.gelu(xe.double() @ W1.double(), approximate="tanh") @ W2.double()
+    # subnormal intermediate values: K units of 2^-149 times the second weights
+    floor = f * 2.0 ** -149 * W2.abs().max().item() * 4
+    assert (ye.double() - ref).abs().max() <= 2 * f ** 0.5 * 2 * EPS * ref.abs().max() + floor
+    assert ye.abs().max() > 0
+
+
+@pytest.mark.parametrize("value", [float("inf"), float("nan"), 1e38, 3.0 * 2 ** 40, 2.0 ** -135])
+@pytest.mark.parametrize("E,C,d,f", SHAPES)
+def test_rows_and_columns_do_not_see_each_other(E, C, d, f, value):
+    """A row of activations or a column of weights beyond the split changes its own results only: the others stay the same bit by bit."""
+    print(f"case E={E} C={C} d={d} f={f} {value}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(d + f)
+    n = lambda *s, std: torch.empty(s, device="cuda").normal_(0.0, std, generator=g)
+    xe, W1, W2 = n(E, C, d, std=1.0), n(E, d, f, std=0.05), n(E, f, d, std=0.05)
+    clean = _expert_ffn(xe, W1, W2)
+    rows, columns = [0, 5, C // 2, C - 1], [3, 64, d - 1]
+    for r in rows:
+        xe[1, r] = value if abs(value) < 1 else xe[1, r].clone().index_fill_(0, torch.tensor([7], device="cuda"), value)
+    ye = _expert_ffn(xe, W1, W2)
+    keep = torch.ones(E, C, d, dtype=torch.bool, device="cuda")
+    keep[1, rows] = False
+    assert torch.equal(ye[keep], clean[keep])
+    xe[1, rows] = 1.0
+    clean = _expert_ffn(xe, W1, W2)
+    W2[1, f // 2, columns] = value
+    ye = _expert_ffn(xe, W1, W2)
+    keep[1, rows] = True
+    keep[1, :, columns] = False
+    assert torch.equal(ye[keep], clean[keep])
