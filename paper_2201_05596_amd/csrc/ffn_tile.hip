@@ -378,13 +378,9 @@ static int launch_tp(const WsGemmArgs& a, const WsGemmArgs* b, hipStream_t s) {
     static_assert(TileCfg<WM, NWM, NSX, WN>::LDS_BYTES <= 160 * 1024, "a work-group's ring must fit one CU's LDS");
     static_assert(TileCfg<WM, NWM, NSX, WN>::WGS_PER_CU * TileCfg<WM, NWM, NSX, WN>::LDS_BYTES <= 160 * 1024,
                   "the promised work-groups per CU must fit its LDS together");
-    static bool attr_set = false;            // one flag per instantiation
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED, RAGGED>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_set = true;
-    }
+    static OncePerDevice asked;
+    const int rc = ask_lds(reinterpret_cast<const void*>(&tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED, RAGGED>), (int)smem, asked);
+    if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((tgemm_kernel<WM, NWM, NSX, EPI, WN, PACKED, RAGGED>), dim3((unsigned)blocks), dim3(NWM * 128), smem, s, a,
                        b ? *b : a, (int)blocks_a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;

@@ -335,13 +335,9 @@ template <int BM, int EPI, bool RAGGED, int POLICY> static int launch_wide_p(con
     const long long blocks_b = b ? tile_grid_blocks(*b, n_tiles, (b->max_rows + BM - 1) / BM) : 0;
     const long long blocks = blocks_a + blocks_b;                // both multiples of the XCD count
     if (blocks > (1ll << 30)) return MOE_ERR_UNSUPPORTED;        // block indices are ints in the kernel
-    static bool attr_set = false;            // one flag per instantiation
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&wide_kernel<BM, EPI, RAGGED, POLICY>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                kWideLds) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_set = true;
-    }
+    static OncePerDevice asked;
+    const int rc = ask_lds(reinterpret_cast<const void*>(&wide_kernel<BM, EPI, RAGGED, POLICY>), kWideLds, asked);
+    if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((wide_kernel<BM, EPI, RAGGED, POLICY>), dim3((unsigned)blocks), dim3(kWideThreads), kWideLds, s, a, b ? *b : a, (int)blocks_a);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

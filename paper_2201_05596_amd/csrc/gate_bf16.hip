@@ -460,13 +460,9 @@ template <int MA, int NE, int K, bool PLAIN>
 int launch_cfg(const uint16_t* x, const uint16_t* frags, const float* Wg, const float* bg, float* logits, int T, int d, int E, int ET,
                int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* hist, hipStream_t s) {
     constexpr int smem = GateLds<MA, NE, K>::BYTES;
-    static bool attr_set = false;             // one flag per instantiation
-    if (!attr_set) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gate_bf16_kernel<MA, NE, K, PLAIN>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, smem) != hipSuccess)
-            return MOE_ERR_HIP;
-        attr_set = true;
-    }
+    static OncePerDevice asked;
+    const int rc = ask_lds(reinterpret_cast<const void*>(&gate_bf16_kernel<MA, NE, K, PLAIN>), smem, asked);
+    if (rc != MOE_OK) return rc;
     const dim3 grid((T + 16 * MA - 1) / (16 * MA), ET / NE);
     hipLaunchKernelGGL((gate_bf16_kernel<MA, NE, K, PLAIN>), grid, dim3(256), smem, s, x, frags, Wg, bg, logits, T, d, E, ET, expert_idx,
                        slot_idx, gate_w, hist);

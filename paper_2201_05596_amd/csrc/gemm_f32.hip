@@ -47,7 +47,6 @@
 //     when they are few.  A work-group of eight waves owns 64 columns, the waves take 16-deep blocks of K in turn straight from
 //     memory into registers, three blocks ahead, and add up through LDS in wave order.
 //     256 tokens, 64/256, 8 experts: both products 48 us on the vector-ALU kernel before, 5.5 + 7.4 here.
-#include <atomic>
 #include <type_traits>
 
 #include "gate_common.h"
@@ -597,19 +596,8 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
     else run(std::integral_constant<int, 1>());
 }
 
-// LDS beyond 64 KB is asked for on every device that a kernel runs on (asked: a bit per device; past 64 of them at every launch).
-int ask_lds(const void* kernel, int bytes, std::atomic<unsigned long long>& asked) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return MOE_ERR_HIP;
-    const unsigned long long bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;
-    if (asked.load(std::memory_order_relaxed) & bit) return MOE_OK;
-    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) return MOE_ERR_HIP;
-    asked.fetch_or(bit, std::memory_order_relaxed);
-    return MOE_OK;
-}
-
 template <int P, int EPI> int launch_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
-    static std::atomic<unsigned long long> asked{0};             // one per instantiation
+    static OncePerDevice asked;
     const int rc = ask_lds(reinterpret_cast<const void*>(&f32_split_kernel<P, EPI>), split_lds<P>(), asked);
     if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((f32_split_kernel<P, EPI>), grid, dim3(P * 256), split_lds<P>(), s, a, n_tiles);
@@ -994,7 +982,7 @@ template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipS
 }
 
 template <int W, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& grid, int n_tiles, hipStream_t s) {
-    static std::atomic<unsigned long long> asked{0};             // one per instantiation
+    static OncePerDevice asked;
     const int rc = ask_lds(reinterpret_cast<const void*>(&f32_rows_split_kernel<W, EPI>), rows_split_lds<W>(), asked);
     if (rc != MOE_OK) return rc;
     hipLaunchKernelGGL((f32_rows_split_kernel<W, EPI>), grid, dim3(W * 64), rows_split_lds<W>(), s, a, n_tiles);

@@ -5,11 +5,21 @@
 #include <stdint.h>
 
 #include "moe.h"
+#include "once_per_device.h"
 
 namespace moe {
 
 constexpr int kWave = 64;            // CDNA wavefront width
 constexpr int kRouteTokens = 256;    // tokens per block in the routing kernels
+
+// Leave for a kernel to be launched with so much dynamic LDS, which takes a call per device beyond 64 KB; asked: one per kernel.
+inline int ask_lds(const void* kernel, int bytes, OncePerDevice& asked) {
+    if (bytes <= 64 * 1024) return MOE_OK;
+    int device = 0;
+    if (hipGetDevice(&device) != hipSuccess) return MOE_ERR_HIP;
+    auto ask = [=] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess; };
+    return asked(device, ask) ? MOE_OK : MOE_ERR_HIP;
+}
 
 // Work-group barrier that orders LDS traffic only.  __syncthreads() also drains every outstanding
 // global load (on gfx9 loads and stores share one counter), which would empty the register prefetch
