@@ -79,6 +79,20 @@ def algorithmic_work(cfg, rows):
             "touched_experts": touched, "kept_rows": kept}
 
 
+def place_work(cfg, alg, stage_ms):
+    """Moves a product's work to the stage whose launch held it: bf16 layers may run the dense branch's product in the experts' launch, fp32
+    ones both products of a narrow FFN in the first one's.  Returns what else is in a stage's launch."""
+    pairs = ([("expert_gemm1", "expert_gemm2", "both products")] + [("dense_gemm1", "dense_gemm2", "both products")] * cfg.residual if cfg.dtype == "f32"
+             else [(f"expert_gemm{i}", f"dense_gemm{i}", "experts + dense branch") for i in (1, 2)] * cfg.residual)
+    shared = {}
+    for stage, other, what in pairs:
+        if stage in stage_ms and other not in stage_ms:
+            for work in ("stage_bytes", "stage_flops"):
+                alg[work][stage] += alg[work][other]
+            shared[stage] = what
+    return shared
+
+
 def describe(cfg):
     return (f"{cfg.name}: T={cfg.T} d_model={cfg.d_model} d_ffn={cfg.d_ffn} E={cfg.E} top_k={cfg.top_k} "
             f"capacity={cfg.capacity} residual={int(cfg.residual)} seed={cfg.seed}")
@@ -124,12 +138,7 @@ def time_config(cfg, steps, warmup, pack):
 
     rows = layer.routing["expert_rows"].cpu().numpy()
     alg = algorithmic_work(cfg, rows)
-    paired = []    # stages in which the dense branch's product ran inside the experts' launch: its work belongs there
-    for e, dn in (("expert_gemm1", "dense_gemm1"), ("expert_gemm2", "dense_gemm2")):
-        if cfg.residual and dn not in stage_ms and e in stage_ms:
-            alg["stage_flops"][e] += alg["stage_flops"][dn]
-            alg["stage_bytes"][e] += alg["stage_bytes"][dn]
-            paired.append(e)
+    shared = place_work(cfg, alg, stage_ms)
     t_hbm = alg["layer_bytes"] / (HBM_PEAK_GBS * 1e9)
     t_mfma = alg["layer_flops"] / (MFMA_BF16_PEAK_TFLOPS * 1e12) if cfg.dtype == "bf16" else 0.0
     bound = "mfma" if t_mfma > t_hbm else "hbm"
@@ -142,7 +151,7 @@ def time_config(cfg, steps, warmup, pack):
         work, peak, unit = alg["stage_flops"].get(dom, 0), MFMA_BF16_PEAK_TFLOPS, "TFLOP/s"
         achieved = work / (dom_ms * 1e-3) / 1e12 if dom_ms > 0 else 0.0
     traffic = PROFILED_TRAFFIC.get((cfg.name, dom))
-    roofline = {"bound": bound, "kernel": dom + (" (experts + dense branch in one launch)" if dom in paired else "") if dom else dom, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
+    roofline = {"bound": bound, "kernel": dom + (f" ({shared[dom]} in one launch)" if dom in shared else "") if dom else dom, "achieved": achieved, "peak": peak, "unit": unit, "frac": achieved / peak,
                 "traffic": traffic, "traffic_source": "rocprofv3 --pmc FETCH_SIZE + WRITE_SIZE, separate runs on packed weights "
                                   "(profiles/hbm_traffic_all_configs.md); not measured in this process" if traffic else None,
                 "algorithmic_work_per_launch": work, "avg_ms": dom_ms, "timed_launches": ncalls,
