@@ -502,21 +502,15 @@ int launch_gate_logits_bf16(const void* x, const float* Wg, const void* Wg_packe
     const int ET = padded_expert_tiles(E);
     const uint16_t* frags = static_cast<const uint16_t*>(Wg_packed);
     const uint16_t* xb = static_cast<const uint16_t*>(x);
-    // Largest tile (fewest operand bytes per output) that still gives every CU a work-group; when even
-    // the smallest tile cannot (few tokens), the smallest one: most work-groups, least time per CU.
-    int MA = 2, NE = 1;
-    bool found = false;
-    for (int ma = 4; ma >= 2 && !found; ma -= 2)
-        for (int ne = ET < 4 ? ET : 4; ne >= 1 && !found; ne /= 2)
-            if ((long long)((T + 16 * ma - 1) / (16 * ma)) * (ET / ne) >= 256) { MA = ma; NE = ne; found = true; }
-#define MOE_GATE_CASE(ma, ne) \
-    if (MA == ma && NE == ne)   \
-    return frags ? launch_cfg<ma, ne, 0, false>(xb, frags, nullptr, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s) \
-                 : launch_cfg<ma, ne, 0, true>(xb, nullptr, Wg, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s)
-    MOE_GATE_CASE(4, 4); MOE_GATE_CASE(4, 2); MOE_GATE_CASE(4, 1);
-    MOE_GATE_CASE(2, 4); MOE_GATE_CASE(2, 2); MOE_GATE_CASE(2, 1);
+    // One expert tile: most work-groups, least time per CU.  64 tokens instead of 32 (fewer operand bytes per output) where that still
+    // gives every CU a work-group; with the fewer than 2048 tokens that come here larger tiles never would.
+    const int tokens = (long long)((T + 63) / 64) * ET >= 256 ? 64 : 32;
+#define MOE_GATE_CASE(ma) \
+    return frags ? launch_cfg<ma, 1, 0, false>(xb, frags, nullptr, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s) \
+                 : launch_cfg<ma, 1, 0, true>(xb, nullptr, Wg, bg, logits, T, d, E, ET, nullptr, nullptr, nullptr, nullptr, s)
+    if (tokens == 64) MOE_GATE_CASE(4);
+    MOE_GATE_CASE(2);
 #undef MOE_GATE_CASE
-    return MOE_ERR_INVALID_ARG;
 }
 
 // The decode gate in one launch: bf16 tokens, at most 256 of them.  flags: kGateFlags words of scratch, whatever they hold;
