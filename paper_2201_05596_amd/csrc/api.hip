@@ -279,17 +279,32 @@ int run_gate(const moe_shape_t* s, const void* x, const float* Wg, const float* 
     return rc;
 }
 
+// First product of an fp32 FFN: h = gelu_tanh(rows of x W1 + b1), and the second one on its result
+GemmArgs f32_expert_args(const moe_shape_t* s) {
+    GemmArgs a{};
+    a.max_rows = s->capacity; a.expect_rows = (int)(((long long)s->T * s->top_k + s->E - 1) / s->E); a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
+    a.a_group_stride = s->capacity; a.o_group_stride = s->capacity;
+    return a;
+}
+GemmArgs f32_dense_args(const moe_shape_t* s) {
+    GemmArgs a{};
+    a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1; a.K = s->d_model; a.N = s->d_ffn;
+    return a;
+}
+GemmArgs f32_second_args(const GemmArgs& a, const void* W2, const void* b2, void* out) {
+    GemmArgs b = a;
+    b.A = a.out; b.B = W2; b.bias = b2; b.out = out; b.row_map = nullptr; b.K = a.N; b.N = a.K;
+    return b;
+}
+
 // The two GEMMs of the expert FFNs in fp32.  row_map == nullptr: rows are xin[e*C + r], else xin[row_map[e*C + r]]
 // (dispatch fused in).  scatter_map == nullptr: rows of `out` are e*C + r, else the tokens' (top-1 combine fused in).
 int run_expert_ffn_f32(const moe_shape_t* s, const void* xin, const int32_t* row_map, const int32_t* rows, const void* W1,
                        const void* b1, const void* W2, const void* b2, void* h, const int32_t* scatter_map,
                        const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
-    GemmArgs a{};
+    GemmArgs a = f32_expert_args(s);
     a.A = xin; a.B = W1; a.bias = b1; a.out = h; a.rows = rows; a.row_map = row_map;
-    a.max_rows = s->capacity; a.expect_rows = (int)(((long long)s->T * s->top_k + s->E - 1) / s->E); a.G = s->E; a.K = s->d_model; a.N = s->d_ffn;
-    a.a_group_stride = s->capacity; a.o_group_stride = s->capacity;
-    GemmArgs b = a;
-    b.A = h; b.B = W2; b.bias = b2; b.out = out; b.row_map = nullptr; b.K = s->d_ffn; b.N = s->d_model;
+    GemmArgs b = f32_second_args(a, W2, b2, out);
     b.scatter_map = scatter_map; b.T = s->T; b.gate_w = gate_w; b.slot_idx = slot_idx; b.top_k = s->top_k;
     const int epi = scatter_map ? EPI_SCATTER : EPI_STORE;
     prof_pre(ST_GEMM1, st);
@@ -311,11 +326,9 @@ int run_expert_ffn_f32(const moe_shape_t* s, const void* xin, const int32_t* row
 int run_dense_f32(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, const void* Wd2, const void* bd2,
                   void* hd, const void* ye, const int32_t* expert_idx, const int32_t* slot_idx, const float* gate_w, void* out,
                   hipStream_t st) {
-    GemmArgs a{};
-    a.A = x; a.B = Wd1; a.bias = bd1; a.out = hd; a.fixed_rows = s->T; a.max_rows = s->T; a.G = 1;
-    a.K = s->d_model; a.N = s->d_ffn;
-    GemmArgs b = a;
-    b.A = hd; b.B = Wd2; b.bias = bd2; b.out = out; b.K = s->d_ffn; b.N = s->d_model;
+    GemmArgs a = f32_dense_args(s);
+    a.A = x; a.B = Wd1; a.bias = bd1; a.out = hd;
+    GemmArgs b = f32_second_args(a, Wd2, bd2, out);
     b.ye = ye; b.expert_idx = expert_idx; b.slot_idx = slot_idx; b.gate_w = gate_w; b.top_k = s->top_k; b.C = s->capacity;
     prof_pre(ST_DENSE1, st);
     if (ffn_f32_fused(a)) {                   // counted under ST_DENSE1
@@ -795,18 +808,27 @@ int moe_layer_forward(const moe_shape_t* shape, const void* x, const float* Wg, 
     return rc;
 }
 
-// Which kernel each product of a bf16 moe_layer_forward call takes, from the shape alone; for the tests of the dispatch, not
+// Which kernel each product of a moe_layer_forward call takes, from the shape alone; for the tests of the dispatch, not
 // part of the interface (moe.h does not declare it).  kernels: expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2, each
-// 0 = none, 1..4 = few-weights kernel with that many 16-column fragments, 100 S + rows = streaming kernel with tiles of that
+// 0 = none; fp32: F32Kernel; bf16: 1..4 = few-weights kernel with that many 16-column fragments, 100 S + rows = streaming kernel with tiles of that
 // many rows and K split S ways, beyond that a tiled kernel (tgemm_code).
 // shared: do the experts' and the dense product of the first / second half run in one launch?
 int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2]) {
     const int rc = check_shape(shape);
     if (rc != MOE_OK) return rc;
     const FfnPlan p = plan_ffn(shape);
-    if (!p.mfma) return MOE_ERR_UNSUPPORTED;
+    if (!p.mfma && shape->dtype != MOE_F32) return MOE_ERR_UNSUPPORTED;
     for (int i = 0; i < 4; ++i) kernels[i] = 0;
     shared[0] = shared[1] = 0;
+    if (!p.mfma) {
+        for (int i = 0; i < (shape->residual ? 4 : 2); i += 2) {
+            const GemmArgs a = i ? f32_dense_args(shape) : f32_expert_args(shape);
+            const bool fused = ffn_f32_fused(a);
+            kernels[i] = fused ? F32_FFN : f32_kernel(a);
+            kernels[i + 1] = fused ? F32_FFN : f32_kernel(f32_second_args(a, nullptr, nullptr, nullptr));
+        }
+        return MOE_OK;
+    }
     const WsGemmArgs e1 = expert_gemm1_args(shape, p, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
     const WsGemmArgs d1 = dense_gemm1_args(shape, nullptr, nullptr, nullptr, nullptr);
     const WsGemmArgs e2 = second_half(e1, nullptr, nullptr, nullptr, nullptr), d2 = second_half(d1, nullptr, nullptr, nullptr, nullptr);

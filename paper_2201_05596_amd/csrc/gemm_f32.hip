@@ -989,19 +989,25 @@ template <int W, int EPI> int launch_rows_split(const GemmArgs& a, const dim3& g
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
-    // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
+// The kernel of a product and its tile.
+struct F32Choice {
+    F32Kernel kernel;
+    int rows, cols;
+};
+F32Choice pick_f32(const GemmArgs& a) {
     // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
     // flop, so the line is where two of them on every unit hold all (products, us, 32 x 64 / 64 x 128, both split: 2048 x 512, 256
     // small tiles 23 / 38, 512 tiles 42 / 43, with half of them empty 26 / 38; 512 x 2048, 384 tiles 13.7 / 15.8; 256 x 1024, 512
     // tiles 9.0 / 11.3; 200 x 800, 520 tiles 11.4 / 11.7).
     const long long small_tiles = ((long long)a.max_rows + 31) / 32 * (((long long)a.N + 63) / 64) * a.G;
-    const bool few = a.max_rows <= 32 || small_tiles <= 512 || a.N >= 1 << 24;
-    const bool narrow = a.N <= 64;                               // one 64-column tile: all four pairs along the rows
-    const int tm = few ? (a.max_rows <= 16 ? 16 : 32) : narrow ? 128 : 64, tn = few || narrow ? 64 : 128;
-    const int n_tiles = (int)(((long long)a.N + tn - 1) / tn);
-    const long long tiles = ((long long)a.max_rows + tm - 1) / tm * n_tiles;
-    if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
+    const int expect = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
+    // tiles if the rows fall evenly on the groups
+    auto live = [&](int rows, int cols) { return (long long)a.G * ((expect + rows - 1) / rows) * (((long long)a.N + cols - 1) / cols); };
+    if (a.max_rows <= 32 || small_tiles <= 512 || a.N >= 1 << 24) {
+        if (a.max_rows <= 16) return {F32_ROWS16, 16, 64};
+        if (a.K < 512 || a.N >= 1 << 24) return {F32_ROWS32, 32, 64};
+        return {live(32, 64) > 256 ? F32_ROWS_SPLIT4 : F32_ROWS_SPLIT8, 32, 64};
+    }
     // Split pieces or fp32 products, two small or one large work-group per compute unit (products, us, fp32 / split with two sets of waves /
     // with one): the split kernel's set-up and epilogue want a long K (4 x 2000, 200 x 800 45.6 / 44.7 / 37.8; 31 x 265, 128 x 512 25.2 / 24.8 /
     // 22.7; 8 x 2000, 100 x 200 20.0 / 18.2 / 17.1; 8 x 300, 192 x 256, 80 tiles 12.6 / 11.2 / 12.8: the line was drawn with waves of 64 columns,
@@ -1009,19 +1015,30 @@ template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
     // room for a second work-group, whose products run under the first one's set-up and epilogue, but two of few tiles may meet on a
     // unit while another has none (8 x 384, 512 x 2048, 768 tiles 64 / 53 / 48; 4 x 480 with room for 720, 2048 x 1024, 256 tiles 75 / 53 / 80;
     // 31 x 132, 2048 x 512, 372 tiles 135 / 93 / 91).
-    const int expect = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
-    const long long live = (long long)a.G * ((expect + 63) / 64) * n_tiles;      // tiles if the rows fall evenly on the groups
-    const dim3 grid((unsigned)tiles, (unsigned)a.G), block(512);
-    static_assert(kFWaves * 64 == 512, "all kernels have the same work-group");
+    if (a.N <= 64) return {F32_TILE_NARROW, 128, 64};            // one 64-column tile: all four pairs of waves along the rows
     static_assert(kSRows == 64 && kSCols == 128, "the same tile");
-    if (few && tm == 16) hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (few && a.K >= 512 && a.N < 1 << 24) {
-        const long long live32 = (long long)a.G * ((expect + 31) / 32) * n_tiles;
-        return live32 > 256 ? launch_rows_split<4, EPI>(a, grid, n_tiles, s) : launch_rows_split<8, EPI>(a, grid, n_tiles, s);
-    } else if (few) hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (narrow) hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles);
-    else if (a.K < (live > 256 ? 160 : 256)) hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles);
-    else return live > 256 ? launch_split<1, EPI>(a, grid, n_tiles, s) : launch_split<2, EPI>(a, grid, n_tiles, s);
+    if (live(64, 128) > 256) return {a.K < 160 ? F32_TILE : F32_SPLIT1, 64, 128};
+    return {a.K < 256 ? F32_TILE : F32_SPLIT2, 64, 128};
+}
+
+template <int EPI> int launch_epi(const GemmArgs& a, hipStream_t s) {
+    const F32Choice c = pick_f32(a);
+    const int n_tiles = (int)(((long long)a.N + c.cols - 1) / c.cols);
+    const long long tiles = ((long long)a.max_rows + c.rows - 1) / c.rows * n_tiles;
+    if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)tiles, (unsigned)a.G), block(512);     // groups along y: x alone is limited to 2^32 threads, which E * capacity reaches
+    static_assert(kFWaves * 64 == 512, "all unsplit kernels have the same work-group");
+    switch (c.kernel) {
+        case F32_ROWS16: hipLaunchKernelGGL((f32_rows_kernel<1, EPI>), grid, block, 0, s, a, n_tiles); break;
+        case F32_ROWS32: hipLaunchKernelGGL((f32_rows_kernel<2, EPI>), grid, block, 0, s, a, n_tiles); break;
+        case F32_ROWS_SPLIT8: return launch_rows_split<8, EPI>(a, grid, n_tiles, s);
+        case F32_ROWS_SPLIT4: return launch_rows_split<4, EPI>(a, grid, n_tiles, s);
+        case F32_TILE_NARROW: hipLaunchKernelGGL((f32_tile_kernel<4, 1, EPI>), grid, block, 0, s, a, n_tiles); break;
+        case F32_TILE: hipLaunchKernelGGL((f32_tile_kernel<2, 2, EPI>), grid, block, 0, s, a, n_tiles); break;
+        case F32_SPLIT1: return launch_split<1, EPI>(a, grid, n_tiles, s);
+        case F32_SPLIT2: return launch_split<2, EPI>(a, grid, n_tiles, s);
+        default: return MOE_ERR_INVALID_ARG;
+    }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -1042,6 +1059,8 @@ int launch_ffn_f32(const GemmArgs& a, const GemmArgs& b, int epi, hipStream_t s)
         default: return MOE_ERR_INVALID_ARG;
     }
 }
+
+F32Kernel f32_kernel(const GemmArgs& a) { return pick_f32(a).kernel; }
 
 int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s) {
     if (a.max_rows <= 0 || a.G <= 0) return MOE_OK;

@@ -163,6 +163,15 @@ struct GemmArgs {
     int32_t C;
 };
 int launch_gemm_f32(const GemmArgs& a, int epi, hipStream_t s);
+// which kernel that is (gemm_f32.hip), for the dispatch report
+enum F32Kernel {
+    F32_ROWS16 = 1, F32_ROWS32 = 2,              // f32_rows_kernel, tiles of 16 and 32 rows
+    F32_ROWS_SPLIT8 = 3, F32_ROWS_SPLIT4 = 4,    // f32_rows_split_kernel, eight and four waves
+    F32_TILE_NARROW = 5, F32_TILE = 6,           // f32_tile_kernel, 128 x 64 and 64 x 128
+    F32_SPLIT1 = 7, F32_SPLIT2 = 8,              // f32_split_kernel, one and two sets of waves
+    F32_FFN = 9                                  // f32_ffn_kernel: both products
+};
+F32Kernel f32_kernel(const GemmArgs& a);
 // both products of an FFN in one launch: a is the first, b the second on its output (a.out and b.A are not used); epi: the second's
 bool ffn_f32_fused(const GemmArgs& a);
 int launch_ffn_f32(const GemmArgs& a, const GemmArgs& b, int epi, hipStream_t s);

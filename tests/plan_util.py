@@ -1,7 +1,9 @@
-"""Which kernel each product of a bf16 layer call takes, by the library's own dispatch (moe_test_plan, host only)."""
+"""Which kernel each product of a layer call takes, by the library's own dispatch (moe_test_plan, host only)."""
 import ctypes
 
 from paper_2201_05596_amd import binding as B
+
+F32_KERNELS = ["none", "rows16", "rows32", "rows_split8", "rows_split4", "tile_narrow", "tile", "split1", "split2", "ffn"]
 
 
 def plan(T, d, f, E, k, C, residual=False, packed=False):
@@ -11,3 +13,10 @@ def plan(T, d, f, E, k, C, residual=False, packed=False):
     kernels, shared = (ctypes.c_int32 * 4)(), (ctypes.c_int32 * 2)()
     assert B.load_library().moe_test_plan(ctypes.byref(shape), kernels, shared) == 0
     return list(kernels), list(shared)
+
+
+def plan_f32(T, d, f, E, k, C, residual=False):
+    """Names (F32Kernel in csrc/moe_internal.h) for the experts' products and, with a dense branch, for its."""
+    shape, kernels = B.make_shape(T, d, f, E, k, C, "f32", residual), (ctypes.c_int32 * 4)()
+    assert B.load_library().moe_test_plan(ctypes.byref(shape), kernels, (ctypes.c_int32 * 2)()) == 0
+    return [F32_KERNELS[n] for n in kernels][:4 if residual else 2]

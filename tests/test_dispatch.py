@@ -2,7 +2,7 @@
 tile shapes: of the product, on packed weights)."""
 import pytest
 
-from tests.plan_util import plan
+from tests.plan_util import plan, plan_f32
 
 T256, T256N, T128, T128X2, T128N = 256256, 256128, 128256, 128257, 128128
 W256, W256H, W256G, W128, W128H = 256258, 256259, 256260, 128258, 128259     # four-wave kernel: cached, with the hint, by group
@@ -99,3 +99,20 @@ def test_few_rows(T, d, f, E, C, packed, which, kernel):
 ])
 def test_few_rows_per_expert(T, d, f, E, k, C, packed, which, kernel):
     assert plan(T, d, f, E, k, C, False, packed)[0][which] == kernel
+
+
+@pytest.mark.parametrize("T,d,f,E,k,C,residual,kernels", [
+    # fp32: both products of a narrow FFN; the next ones beyond
+    (256, 64, 256, 8, 1, 32, True, ["ffn"] * 4), (2500, 64, 228, 32, 1, 1024, False, ["ffn", "ffn"]),
+    (2500, 64, 228, 32, 1, 1025, False, ["tile", "tile_narrow"]), (100, 68, 256, 3, 1, 40, False, ["rows32", "rows32"]), (100, 64, 260, 3, 1, 16, False, ["rows16", "rows16"]),
+    # at most 512 tiles of 32 x 64: split from K = 512 on, four waves beyond 256 tiles that have rows
+    (1024, 512, 2048, 8, 1, 128, False, ["split2", "rows_split8"]), (300, 512, 2048, 4, 1, 75, True, ["rows_split4", "rows_split8", "rows_split4", "rows_split8"]),
+    (300, 508, 508, 4, 1, 75, False, ["rows32", "rows32"]), (300, 516, 508, 4, 1, 16, False, ["rows16", "rows16"]),
+    (2048, 512, 2048, 8, 1, 256, False, ["split1", "rows_split4"]), (1024, 512, 2048, 8, 1, 256, False, ["split2", "rows_split8"]),
+    # more of them: split from K = 160 (more than 256 tiles of 64 x 128 that have rows) and 256 on, more than 64 columns
+    (1536, 512, 2048, 8, 2, 480, False, ["split1", "split2"]), (16000, 156, 1024, 8, 1, 2000, False, ["tile", "split1"]), (16000, 160, 1024, 8, 1, 2000, False, ["split1", "split1"]),
+    (4000, 192, 256, 8, 1, 600, False, ["tile", "rows32"]), (4096, 64, 1024, 8, 1, 2100, False, ["tile", "tile_narrow"]),
+    (1000, 16777216, 512, 1, 1, 1000, False, ["rows_split8", "rows32"]),      # columns beyond a buffer descriptor's offsets
+])
+def test_f32_kernels(T, d, f, E, k, C, residual, kernels):
+    assert plan_f32(T, d, f, E, k, C, residual) == kernels
