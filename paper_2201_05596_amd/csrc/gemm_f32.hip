@@ -359,9 +359,8 @@ __device__ void f32_unsplit(const GemmArgs& a, int g, int rows, int m0, int n0, 
     }
 }
 
-// partial sums (less before), the largest values of rows and columns, a flag, bits of split_misses
-constexpr int kSplitMisses = kSRows * kSCols / 4, kSplitLargest = (kSRows + kSCols) * 4;
-template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + kSplitLargest + 16 + kSplitMisses; }
+// partial sums (less before), the largest values of rows and columns, flags, the largest values of waves, bits of split_misses
+template <int P> constexpr int split_lds() { return P * kSRows * kSCols * 4 + (kSRows + kSCols + 4 + 8) * 4 + kSRows * kSCols / 4; }
 
 // P sets of four waves split K between them, 32 deep in turn; wave 4 q + wn has columns 32 wn .. + 31 of the tile and set q's K.
 template <int P, int EPI>
@@ -371,8 +370,9 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
     static_assert(2 * BUF <= P * kSRows * kSCols * 4, "two buffers of activation pieces");
     float* const part = reinterpret_cast<float*>(lds);
     uint32_t* const largest = reinterpret_cast<uint32_t*>(lds + P * kSRows * kSCols * 4);        // [kSRows + kSCols], magnitudes as integers
-    int* const flag = reinterpret_cast<int*>(largest + kSRows + kSCols);
-    uint8_t* const misses = reinterpret_cast<uint8_t*>(flag + 4);                                // [kSRows][kSCols / 4]
+    int* const flags = reinterpret_cast<int*>(largest + kSRows + kSCols);                        // [2]
+    float* const wave_max = reinterpret_cast<float*>(flags + 4);                                 // [4 P]
+    uint8_t* const misses = reinterpret_cast<uint8_t*>(wave_max + 8);                            // [kSRows][kSCols / 4]
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), c = lane & 31, half = lane >> 5;
     const int q = w >> 2, wn = w & 3;
     if (EPI == EPI_SCATTER) f32_zero_dropped(a, tid, P * 256);
@@ -381,7 +381,7 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
     const int nt = blockIdx.x % n_tiles, mt = blockIdx.x / n_tiles, g = blockIdx.y;
     const int rows = f32_rows_of(a, g), m0 = mt * kSRows, n0 = nt * kSCols;
     if (m0 >= rows) return;
-    if (tid <= kSRows + kSCols) largest[tid] = 0;                // and the flag
+    if (tid < kSRows + kSCols + 2) largest[tid] = 0;             // and the flags
 
     // Activations: four threads take 32 k of a row, eight each, and put the pieces into LDS as fragments [row block][16 k][piece] of
     // v_mfma_f32_32x32x16_bf16.  Row r's 16 bytes of k-octet o stand at (o % 2) * 32 + (r ^ x(o)): x sends the lanes of one LDS
@@ -547,8 +547,8 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
 
         // the sets' sums meet in LDS, in the order of the sets
         lds_barrier();
-        atomicMax(&largest[a_r], __float_as_uint(row_max));
-        atomicMax(&largest[kSRows + wn * 32 + c], __float_as_uint(col_max));
+        const float in_wave = wave_largest(fmaxf(row_max, col_max));
+        if (lane == 0) wave_max[w] = in_wave;
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
 #pragma unroll
@@ -559,7 +559,11 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
         lds_barrier();
         constexpr int NV = MS * 32 * kSCols / 4 / (P * 256);
         f32x4_t v[NV];
-        int bits[NV], any = 0;
+        float tile_max = wave_max[0];
+#pragma unroll
+        for (int s = 1; s < 4 * P; ++s) tile_max = fmaxf(tile_max, wave_max[s]);
+        const f32x4_t columns_max = {tile_max, tile_max, tile_max, tile_max};
+        int any = 0;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
@@ -569,21 +573,30 @@ __global__ __launch_bounds__(P * 256, 2) void f32_split_kernel(const GemmArgs a,
                 const f32x4_t u = *reinterpret_cast<const f32x4_t*>(part + ((size_t)p * kSRows + r) * kSCols + n);
                 v[i] = p % 2 ? v[i] - u : v[i] + u;
             }
-            const bool in = m0 + r < rows && n0 + n < a.N;
-            bits[i] = in ? split_misses(v[i], a.K, __uint_as_float(largest[r]), *reinterpret_cast<const f32x4_t*>(largest + kSRows + n)) : 0;
-            any |= bits[i];
+            if (m0 + r < rows && n0 + n < a.N) any |= split_misses(v[i], a.K, tile_max, columns_max);
         }
-        if (__ballot(any)) *flag = 1;
+        // Sums that are too small under the largest values of the whole tile are looked at again under those of their row and column.
+        if (__ballot(any)) flags[0] = 1;
         lds_barrier();
-        const bool again = *flag;                            // uniform over the work-group
+        const bool again = flags[0];                         // uniform over the work-group
+        int bits[NV] = {};
+        if (again) {
+            atomicMax(&largest[a_r], __float_as_uint(row_max));
+            atomicMax(&largest[kSRows + wn * 32 + c], __float_as_uint(col_max));
+            lds_barrier();
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
-            if (again) {
+            for (int i = 0; i < NV; ++i) {
+                const int r = (tid + i * P * 256) / (kSCols / 4), n = tid % (kSCols / 4) * 4;
+                if (m0 + r < rows && n0 + n < a.N)
+                    bits[i] = split_misses(v[i], a.K, __uint_as_float(largest[r]), *reinterpret_cast<const f32x4_t*>(largest + kSRows + n));
                 misses[r * (kSCols / 4) + n / 4] = bits[i];
                 if (bits[i]) *reinterpret_cast<f32x4_t*>(part + (size_t)r * kSCols + n) = v[i];  // where this thread alone read before
             }
-            if (m0 + r < rows && n0 + n < a.N && !bits[i]) f32_finish<EPI>(a, g, m0 + r, n0 + n, v[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int r = (tid + i * P * 256) / (kSCols / 4), n = n0 + tid % (kSCols / 4) * 4;
+            if (m0 + r < rows && n < a.N && !bits[i]) f32_finish<EPI>(a, g, m0 + r, n, v[i]);
         }
         if (!again) return;
         lds_barrier();
