@@ -108,9 +108,9 @@ int moe_pack_weights(int32_t G, int32_t K, int32_t N, const void* W, void* packe
 
 /* moe_pack_gate -- optional one-time preparation of the gate weights for bf16
  * layers: every fp32 weight as the exact sum of three bf16 numbers, laid out as
- * matrix-instruction operands (the gate kernel otherwise does this split into
- * its workspace at every call, one kernel launch more; Sec. 5.4 counts kernel
- * launches among the gate's costs).  `packed` receives moe_packed_gate_bytes(d,E)
+ * matrix-instruction operands (the gate kernels otherwise do this split at
+ * every call, from 2048 tokens on into the workspace with one kernel launch
+ * more; Sec. 5.4 counts kernel launches among the gate's costs).  `packed` receives moe_packed_gate_bytes(d,E)
  * bytes (0 = shape not covered: d_model not a multiple of 32, or E > 128); pass it
  * as Wg (cast to const float*) with MOE_FLAG_PACKED_GATE.  Logits are bit-identical
  * to those from the plain weights. */

@@ -288,7 +288,7 @@ int rows_pick_gemm1(long long touched, int max_rows, long long kept, int K, int 
 // 1 of 64 82 / 50; K = 4096, N = 1024, 1 of 64 26.5 / 22.5.
 // Plain weights (rows of 64 bytes, so twice the lines are touched): one or two experts only, and with a long K only out of at
 // least eight (fewer are spread over the XCDs by columns: K = 8192, 2 experts of 16 rows 31 / 27, K = 16384, 1 of 16 54 / 40; 2
-// tokens out of 8 experts, 2048 / 8192: layer 44 / 59)).
+// tokens out of 8 experts, 2048 / 8192: layer 44 / 59).
 // At most 16 rows per expert, packed, against the streaming kernel without a split as well: that one's waves are then enough for the
 // chip only if all experts have rows, and with skewed routing most have none.  With few rows per expert (whatever few_waves says) or, K
 // below 8192, up to 256 rows (layers, us, even routing and with gate bias 1.5 ln(1 / (e + 1)), streaming / this kernel: 2048 / 8192, 64

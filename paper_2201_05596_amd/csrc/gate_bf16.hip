@@ -74,24 +74,13 @@ __global__ __launch_bounds__(256) void gate_prepare_kernel(const float* __restri
 // call of few tokens reads each weight so seldom that a launch for the split costs more than splitting as it goes (layers on plain
 // weights, us: one token, 1024/4096, 128 experts 34.6 -> 27.8; 200 tokens of 32 112.6 -> 107.9; 2000 of 128 370 -> 362).
 __device__ __forceinline__ void split_weights(const float (&v)[8], bf16x8_t (&piece)[3]) {
-    float x[8];
+    float x[4][2];
     uint32_t u[3][4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = v[j];
+    for (int j = 0; j < 8; ++j) x[j / 2][j % 2] = v[j];
+    split_bf16x3(x, u);
 #pragma unroll
-    for (int q = 0; q < 3; ++q) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            u[q][i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
-            asm("" : "+v"(u[q][i]));                              // one conversion for both values
-        }
-#pragma unroll
-        for (int i = 0; i < 4 && q < 2; ++i) {
-            x[2 * i] -= __uint_as_float(u[q][i] << 16);           // exact
-            x[2 * i + 1] -= __uint_as_float(u[q][i] & 0xffff0000u);
-        }
-        piece[q] = __builtin_bit_cast(bf16x8_t, make_uint4(u[q][0], u[q][1], u[q][2], u[q][3]));
-    }
+    for (int q = 0; q < 3; ++q) piece[q] = __builtin_bit_cast(bf16x8_t, make_uint4(u[q][0], u[q][1], u[q][2], u[q][3]));
 }
 // the weights themselves: column n of k-block kb, zero past E; Wg is [d, E]
 __device__ __forceinline__ void load_weights(const float* __restrict__ Wg, int kb, int kg, int n, int E, float (&v)[8]) {

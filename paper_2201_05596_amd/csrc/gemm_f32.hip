@@ -295,25 +295,11 @@ __device__ __forceinline__ float wave_largest(float v) {
     return fmaxf(fmaxf(lane(0), lane(16)), fmaxf(lane(32), lane(48)));
 }
 
-// M pairs of fp32 values as three times M pairs of bf16: a value is piece 0 + piece 1 + piece 2 exactly (3 x 8 significant
-// bits, each piece the nearest bf16 of what is left).  Infinities, NaN and values that round to infinity leave NaN in the later pieces.
+// split_bf16x3 with the largest magnitude so far.  Infinities, NaN and values that round to infinity leave NaN in the later pieces.
 template <int M> __device__ __forceinline__ void split_pairs(float (&x)[M][2], uint32_t (&piece)[3][M], float& largest) {
 #pragma unroll
     for (int i = 0; i < M; ++i) largest = fmaxf(fmaxf(largest, fabsf(x[i][0])), fabsf(x[i][1]));
-#pragma unroll
-    for (int q = 0; q < 3; ++q) {                            // piece by piece, so that no instruction waits for the one before it
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            piece[q][i] = pack_bf16x2(x[i][0], x[i][1]);
-            asm("" : "+v"(piece[q][i]));                     // one conversion for both values, not one more for the first alone
-        }
-        if (q == 2) break;
-#pragma unroll
-        for (int i = 0; i < M; ++i) {
-            x[i][0] -= __uint_as_float(piece[q][i] << 16);
-            x[i][1] -= __uint_as_float(piece[q][i] & 0xffff0000u);
-        }
-    }
+    split_bf16x3(x, piece);
 }
 
 // 16 rows x 64 columns from (m0, n0) on the fp32 matrix instructions, straight from memory: finishes the vectors of four sums that have bits in

@@ -47,6 +47,24 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     const bf16x2_t v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
     return __builtin_bit_cast(uint32_t, v);
 }
+// M pairs of fp32 values as three times M pairs of bf16: a value is piece 0 + piece 1 + piece 2 (3 x 8 significant bits, each piece the
+// nearest bf16 of what is left), exactly as long as the pieces are not below bf16's 2^-133.  x holds what is left before the last piece.
+template <int M> __device__ __forceinline__ void split_bf16x3(float (&x)[M][2], uint32_t (&piece)[3][M]) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {                            // piece by piece, so that no instruction waits for the one before it
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            piece[q][i] = pack_bf16x2(x[i][0], x[i][1]);
+            asm("" : "+v"(piece[q][i]));                     // one conversion for both values, not one more for the first alone
+        }
+        if (q == 2) break;
+#pragma unroll
+        for (int i = 0; i < M; ++i) {
+            x[i][0] -= __uint_as_float(piece[q][i] << 16);
+            x[i][1] -= __uint_as_float(piece[q][i] & 0xffff0000u);
+        }
+    }
+}
 
 // gelu_tanh(z) = 0.5 z (1 + tanh(u)), u = sqrt(2/pi) (z + 0.044715 z^3).  Since tanh(u) = 2 sigmoid(2u) - 1 this is
 // z sigmoid(2u) = z / (1 + exp(-2u)): one exp2 and one rcp on the hardware units, five multiply-adds.
