@@ -994,10 +994,9 @@ struct F32Choice {
     int rows, cols;
 };
 F32Choice pick_f32(const GemmArgs& a) {
-    // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernel are four times as many.  They cost more per
+    // Few tiles leave compute units idle, and the 32 x 64 ones of the rows kernels are four times as many.  They cost more per
     // flop, so the line is where two of them on every unit hold all (products, us, 32 x 64 / 64 x 128, both split: 2048 x 512, 256
-    // small tiles 23 / 38, 512 tiles 42 / 43, with half of them empty 26 / 38; 512 x 2048, 384 tiles 13.7 / 15.8; 256 x 1024, 512
-    // tiles 9.0 / 11.3; 200 x 800, 520 tiles 11.4 / 11.7).
+    // small tiles 22 / 38, 512 tiles 38 / 38, with half of them empty 34 / 37; 512 x 2048, 384 tiles 12.4 / 15.0).
     const long long small_tiles = ((long long)a.max_rows + 31) / 32 * (((long long)a.N + 63) / 64) * a.G;
     const int expect = a.expect_rows > 0 && a.expect_rows < a.max_rows ? a.expect_rows : a.max_rows;
     // tiles if the rows fall evenly on the groups
