@@ -287,16 +287,16 @@ __global__ __launch_bounds__(TB == kRouteTokens ? 1024 : 256) void route_tile_ke
 //   second choices: row = total_1[e] + base_2[e] + rank      (all first choices rank first)
 // row >= C -> dropped (-1).  Rows >= expert_rows[e] of slot_token are set to -1.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void expert_order_kernel(const int32_t* __restrict__ expert_rows, int E, int C,
-                                                           int32_t* __restrict__ order) {
-    extern __shared__ int32_t smem[];                 // rows [E], sorted [E + 2]
-    for (int e = threadIdx.x; e < E; e += 256) smem[e] = min(expert_rows[e], C);
+__global__ __launch_bounds__(1024) void expert_order_kernel(const int32_t* __restrict__ expert_rows, int E, int C,
+                                                            int32_t* __restrict__ order) {
+    extern __shared__ int32_t smem[];                 // rows, sorted and active experts: [E] each
+    if (threadIdx.x < E) smem[threadIdx.x] = min(expert_rows[threadIdx.x], C);
     __syncthreads();
-    write_expert_order(smem, E, order, smem + E, threadIdx.x, 256);
+    write_expert_order(smem, E, order, smem + E, smem + 2 * E, threadIdx.x, blockDim.x);
 }
 
 int launch_expert_order(const int32_t* expert_rows, int E, int C, int32_t* order, hipStream_t s) {
-    hipLaunchKernelGGL(expert_order_kernel, dim3(1), dim3(256), sizeof(int32_t) * (2 * E + 2), s, expert_rows, E, C, order);
+    hipLaunchKernelGGL(expert_order_kernel, dim3(1), dim3(E <= 256 ? 256 : 1024), sizeof(int32_t) * 3 * E, s, expert_rows, E, C, order);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -313,7 +313,7 @@ __host__ __device__ inline int finalize_row_groups(int ncol, int nthreads) {
 // tokens.  Every work-group sums the histograms of all blocks before its own: the reads grow with the square of the
 // number of blocks (T = 16384, E = 64, top-2: 8 MB in all, served by L2), a stated limit of this kernel.
 template <int K>
-__device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E, int C, int nblocks, int TB,
+__device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E, int C, int nblocks, int chunk, int TB,
                                                     const int32_t* __restrict__ expert_idx, int32_t* __restrict__ slot_idx,
                                                     int32_t* __restrict__ expert_rows, int32_t* __restrict__ slot_token,
                                                     int32_t* __restrict__ expert_order, const int32_t* __restrict__ hist) {
@@ -329,7 +329,7 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
     // partial sums meet in LDS
     const int nt = blockDim.x, nfine = (T + TB - 1) / TB, R = finalize_row_groups(ncol, nt);
     for (int idx = tid; idx < R * ncol; idx += nt) {
-        const int col = idx % ncol, rg = idx / ncol;
+        const int rg = (int)(((float)idx + 0.5f) * __builtin_amdgcn_rcpf((float)ncol)), col = idx - rg * ncol;   // idx < 2^12: exact
         int pre = 0, tot = 0;
         // every TB-token block's histogram once; those of 256-token blocks before this one also count as "before me"
         const int first_own = b * q;
@@ -384,7 +384,7 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
 
     const int t = b * kRouteTokens + tid;
     if (tid < kRouteTokens && t < T) {
-        const int f = tid / TB;
+        const int f = tid >> ceil_log2(TB);
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int e = expert_idx[(size_t)t * K + j];
@@ -398,10 +398,8 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
         }
     }
 
-    const long long total_slots = (long long)E * C;
-    const long long chunk = (total_slots + nblocks - 1) / nblocks;
-    const long long lo = (long long)b * chunk;
-    const long long hi = min(lo + chunk, total_slots);
+    const long long lo = (long long)b * chunk;                   // chunk: a block's share of the E C entries
+    const long long hi = min(lo + chunk, (long long)E * C);
     for (uint32_t i = (uint32_t)lo + tid; i < hi; i += nt)        // E * C < 2^31
         if ((int)(i % (uint32_t)C) >= rows_sh[i / (uint32_t)C]) slot_token[i] = -1;
     // The rows per expert and the launch order are the work of one block: with an order to write, of an extra block
@@ -409,12 +407,12 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
     // lengthen a block that also has tokens to place.
     if (b == (expert_order ? nblocks : 0)) {
         for (int e = tid; e < E; e += nt) expert_rows[e] = rows_sh[e];
-        if (expert_order) write_expert_order(rows_sh, E, expert_order, part, tid, nt);   // part: free by now
+        if (expert_order) write_expert_order(rows_sh, E, expert_order, part, part + E, tid, nt);   // part: free by now
     }
 }
 
 template <int K>
-__global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(int T, int E, int C, int nblocks, int TB,
+__global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(int T, int E, int C, int nblocks, int chunk, int TB,
                                                                       const int32_t* __restrict__ expert_idx,
                                                                       int32_t* __restrict__ slot_idx,
                                                                       int32_t* __restrict__ expert_rows,
@@ -422,7 +420,7 @@ __global__ __launch_bounds__(kFinThreads) void route_finalize_kernel(int T, int 
                                                                       int32_t* __restrict__ expert_order,
                                                                       const int32_t* __restrict__ hist) {
     extern __shared__ int32_t smem[];
-    route_finalize_body<K>(smem, T, E, C, nblocks, TB, expert_idx, slot_idx, expert_rows, slot_token, expert_order, hist);
+    route_finalize_body<K>(smem, T, E, C, nblocks, chunk, TB, expert_idx, slot_idx, expert_rows, slot_token, expert_order, hist);
 }
 
 // At most 256 tokens (decode): one block, whose local ranks are already global ones -- the whole routing in one
@@ -456,12 +454,13 @@ int launch_route_finalize(int T, int E, int k, int C, int TB, const int32_t* exp
     // 128 experts, 65536 21.7 / 24.6).
     const int nt = T >= kSmallRouteTiles && k * E <= 64 ? 256 : kFinThreads;
     const size_t sm = route_finalize_lds_bytes(E, k, TB, nt);
+    const int chunk = (int)(((long long)E * C + nb - 1) / nb);
     const int grid = nb + (expert_order ? 1 : 0);               // + the block that ranks the experts
     if (k == 1)
-        hipLaunchKernelGGL((route_finalize_kernel<1>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, TB, expert_idx,
+        hipLaunchKernelGGL((route_finalize_kernel<1>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, chunk, TB, expert_idx,
                            slot_idx, expert_rows, slot_token, expert_order, hist);
     else
-        hipLaunchKernelGGL((route_finalize_kernel<2>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, TB, expert_idx,
+        hipLaunchKernelGGL((route_finalize_kernel<2>), dim3(grid), dim3(nt), sm, s, T, E, C, nb, chunk, TB, expert_idx,
                            slot_idx, expert_rows, slot_token, expert_order, hist);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

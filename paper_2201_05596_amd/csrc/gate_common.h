@@ -126,10 +126,13 @@ __device__ __forceinline__ int wave_rank_by_expert(int e, int lane, int E, int32
     const unsigned long long lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const int bits = 32 - __clz(E);                       // E >= 1; covers 0 .. E - 1
     unsigned long long same = __ballot(e >= 0);
-    for (int i = 0; i < bits; ++i) {
-        const bool one = e >> i & 1;
-        const unsigned long long ones = __ballot(one);
-        same &= one ? ones : ~ones;
+    for (int b = 0; b < bits; b += 4) {                   // four ballots at a time; bits past the last are 0 in every e
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool one = e >> (b + i) & 1;
+            const unsigned long long ones = __ballot(one);
+            same &= one ? ones : ~ones;
+        }
     }
     const int rank = __popcll(same & lt_mask);
     if (e >= 0 && rank == 0) count[e] = __popcll(same);
