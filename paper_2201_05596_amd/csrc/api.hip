@@ -163,6 +163,9 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
     return p;
 }
 
+// do the bf16 matrix cores compute the gate logits?
+bool gate_on_bf16(const moe_shape_t* s) { return s->dtype == MOE_BF16 && gate_bf16_supported(s->d_model, s->E); }
+
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
     size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, h, ye, hd, dense, partial, total;
@@ -177,7 +180,7 @@ WsLayout ws_layout(const moe_shape_t* s) {
     auto take = [&](size_t bytes) { const size_t o = off; off += align_up(bytes); return o; };
     L.logits = take(T * E * 4);
     L.wg_frags = take(s->dtype == MOE_BF16 ? gate_bf16_ws_bytes(s->d_model, s->E) : 0);
-    L.hist = take(route_scratch_ints(s->T, s->E, s->top_k) * 4);
+    L.hist = take(route_scratch_ints(s->T, s->E, s->top_k, !gate_on_bf16(s)) * 4);
     // hand-over flags of the one-launch decode gate: it leaves no histograms, so they reach back into that region
     static_assert(kGateFlags * 8 <= 2 * kAlign, "at least one unit of histograms before the extra one");
     take(kAlign);
@@ -231,7 +234,7 @@ int static_scratch(void** out) {
 // With MOE_FLAG_PACKED_GATE, Wg is the buffer moe_pack_gate wrote and no weight is split at call time.
 int run_gate_logits(const moe_shape_t* s, const void* x, const float* Wg, const float* bg, float* logits, hipStream_t st) {
     const bool packed = s->flags & MOE_FLAG_PACKED_GATE;
-    if (s->dtype == MOE_BF16 && gate_bf16_supported(s->d_model, s->E))
+    if (gate_on_bf16(s))
         return launch_gate_logits_bf16(x, packed ? nullptr : Wg, packed ? Wg : nullptr, bg, logits, s->T, s->d_model, s->E, st);
     return launch_gate_logits(x, s->dtype, Wg, bg, logits, s->T, s->d_model, s->E, st);
 }
@@ -269,6 +272,16 @@ int run_gate(const moe_shape_t* s, const void* x, const float* Wg, const float* 
         return rc;
     }
     if (profile) prof_pre(ST_LOGITS, st);
+    if (!gate_on_bf16(s) && gate_logits_routes(s->T, s->E)) {
+        int tb = 0;
+        rc = launch_gate_logits_route(x, s->dtype, Wg, bg, logits, s->T, s->d_model, s->E, s->top_k, expert_idx, slot_idx, gate_w, scratch, &tb, st);
+        if (profile) prof_mark(ST_LOGITS, st);
+        if (rc != MOE_OK) return rc;
+        if (profile) prof_pre(ST_ROUTE, st);
+        rc = launch_route_finalize(s->T, s->E, s->top_k, s->capacity, tb, expert_idx, slot_idx, rows, slot_token, order, scratch, st);
+        if (profile) prof_mark(ST_ROUTE, st);
+        return rc;
+    }
     rc = run_gate_logits(s, x, Wg, bg, logits, st);
     if (profile) prof_mark(ST_LOGITS, st);
     if (rc != MOE_OK) return rc;

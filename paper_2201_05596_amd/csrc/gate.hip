@@ -27,6 +27,7 @@ namespace moe {
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 constexpr int kGK = 32;      // k-rows per step
 constexpr int kGPD = 3;      // steps of operands kept in flight in registers
+constexpr int kLogitsTokens = 16;   // tokens of a work-group that also routes them
 
 // 8 consecutive k of a token row as raw 16-byte words (bf16: one word; fp32: two), widened later
 template <typename XT> struct XRaw;
@@ -60,11 +61,17 @@ template <> struct XRaw<float> {
 // VEC = 4: E is a multiple of 4 and Wg rows are read as float4; VEC = 1: any E, scalar reads.
 // FULL: d is a multiple of 32*WK and E of the work-group's expert width, so no operand is ever out
 // of range and the selects that zero them disappear from the loop.
-template <typename XT, int WT, int WE, int WK, int VEC, bool FULL>
+// K > 0 (four k-splits, at most 64 experts): the kernel goes on to what route_tile_kernel does for its 16 tokens.  The logits of
+// a token lie in 16 adjacent lanes as the top-k wants them, a wave finishes four tokens: about 1 us more than the logits alone
+// where that kernel is a launch of 4.8.  1536 tokens, d = 512, 8 experts, top-2: gate and routing 18.7 -> 16.5 us.
+template <typename XT, int WT, int WE, int WK, int VEC, bool FULL, int K = 0>
 __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__ x, const float* __restrict__ Wg,
                                                           const float* __restrict__ bg, float* __restrict__ logits,
-                                                          int T, int d, int E) {
+                                                          int T, int d, int E, int32_t* __restrict__ expert_idx = nullptr,
+                                                          int32_t* __restrict__ slot_idx = nullptr, float* __restrict__ gate_w = nullptr,
+                                                          int32_t* __restrict__ hist = nullptr) {
     static_assert(WT * WE * WK == 4, "four waves");
+    static_assert(K == 0 || WK == 4, "a wave finishes a row of each group of four");
     constexpr int EN = WE * 64;                       // experts per pass of the work-group
     constexpr int TM = WT * 16;                       // tokens per work-group
     constexpr int NB = WK * kGK * EN / 256 / VEC;     // Wg words staged per thread and step
@@ -155,6 +162,62 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
         if (c0 < cper) step(breg[0], areg[0], c0);
         if (c0 + 1 < cper) step(breg[1], areg[1], c0 + 1);
 
+        if constexpr (K > 0) {                       // one pass: E <= 64
+            __shared__ int32_t e_sh[K * kLogitsTokens], h_sh[K * 64];
+            __syncthreads();
+            // partial sums of the rows that other waves finish: wave r finishes rows 4 g + r
+            float own[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int nt = 0; nt < 4; ++nt) {
+                    if (r != wk) red[((wk * 3 + (r < wk ? r : r - 1)) * 4 + nt) * 64 + lane] = acc[nt][r];
+                    else own[nt] = acc[nt][r];
+                }
+            for (int i = tid; i < K * E; i += 256) h_sh[i] = 0;
+            __syncthreads();
+            const int tl = 4 * g + wk, t = t0 + tl;
+            float v[4];
+#pragma unroll
+            for (int nt = 0; nt < 4; ++nt) {
+                const int e = nt * 16 + n;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {        // in the order of the splits
+                    const float p = s == wk ? own[nt] : red[((s * 3 + (wk < s ? wk : wk - 1)) * 4 + nt) * 64 + lane];
+                    v[nt] = s == 0 ? p : v[nt] + p;
+                }
+                v[nt] += bg ? bg[min(e, E - 1)] : 0.f;
+                if (t < T && e < E) logits[(size_t)t * E + e] = v[nt];
+                v[nt] = e < E ? v[nt] : -INFINITY;
+            }
+            Best g1, g2;
+            float w1, w2;
+            token_gate_regs<K, 4>(v, E, n, g1, g2, w1, w2);
+            if (n == 0) {
+                e_sh[tl] = t < T ? g1.i : -1;
+                if (K == 2) e_sh[kLogitsTokens + tl] = t < T ? g2.i : -1;
+                if (t < T) {
+                    expert_idx[(size_t)t * K] = g1.i;
+                    gate_w[(size_t)t * K] = w1;
+                    if (K == 2) {
+                        expert_idx[(size_t)t * K + 1] = g2.i;
+                        gate_w[(size_t)t * K + 1] = w2;
+                    }
+                }
+            }
+            __syncthreads();
+            if (w == 0) {                            // one lane per token: rank among the tile's tokens with the same expert
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const int e = lane < kLogitsTokens ? e_sh[j * kLogitsTokens + lane] : -1;
+                    const int rank = wave_rank_by_expert(e, lane, E, h_sh + j * E);
+                    if (e >= 0) slot_idx[(size_t)(t0 + lane) * K + j] = rank;
+                }
+            }
+            __syncthreads();
+            for (int i = tid; i < K * E; i += 256) hist[(size_t)blockIdx.x * K * E + i] = h_sh[i];
+            return;
+        }
         if (WK > 1) {
             __syncthreads();
             float* mine = red + ((size_t)((wk - 1) * WT * WE + wt * WE + we) * 16) * 64;
@@ -192,6 +255,7 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
     }
 }
 
+constexpr int kFewTokens = 4096;
 template <typename XT>
 static int launch_logits_t(const XT* x, const float* Wg, const float* bg, float* logits, int T, int d, int E,
                            hipStream_t s) {
@@ -210,7 +274,7 @@ static int launch_logits_t(const XT* x, const float* Wg, const float* bg, float*
                                logits, T, d, E);                                                             \
     } while (0)
     const bool wide = E > 64;          // 128 experts per pass, else 64
-    const bool few = T <= 4096;        // few tokens: waves go to k-splits, not token tiles (1536 tokens, d = 512: 14.6 us without)
+    const bool few = T <= kFewTokens;  // few tokens: waves go to k-splits, not token tiles (1536 tokens, d = 512: 14.6 us without)
     if (wide) {
         if (few) MOE_LOGITS_CASE(1, 2, 2);
         else MOE_LOGITS_CASE(2, 2, 1);
@@ -220,6 +284,38 @@ static int launch_logits_t(const XT* x, const float* Wg, const float* bg, float*
     }
 #undef MOE_LOGITS_CASE
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+
+// Logits, top-k, tile-local ranks and histograms of 16 tokens each in one launch: few enough tokens that the waves go to k-splits,
+// one pass of experts.  Fewer than 257 tokens have the whole routing in one work-group.
+bool gate_logits_routes(int T, int E) { return T > kRouteTokens && T <= kFewTokens && E <= 64; }
+
+template <typename XT>
+static int launch_logits_route_t(const XT* x, const float* Wg, const float* bg, float* logits, int T, int d, int E, int k, int32_t* expert_idx,
+                                 int32_t* slot_idx, float* gate_w, int32_t* hist, hipStream_t s) {
+    const dim3 grid((T + kLogitsTokens - 1) / kLogitsTokens);
+    const bool full = d % (kGK * 4) == 0 && E == 64;
+#define MOE_LOGITS_CASE(vec, is_full, kk) \
+    hipLaunchKernelGGL((gate_logits_kernel<XT, 1, 1, 4, vec, is_full, kk>), grid, dim3(256), 0, s, x, Wg, bg, logits, T, d, E, expert_idx, \
+                       slot_idx, gate_w, hist)
+    if (k == 1) {
+        if (full) MOE_LOGITS_CASE(4, true, 1);
+        else if (E % 4 == 0) MOE_LOGITS_CASE(4, false, 1);
+        else MOE_LOGITS_CASE(1, false, 1);
+    } else {
+        if (full) MOE_LOGITS_CASE(4, true, 2);
+        else if (E % 4 == 0) MOE_LOGITS_CASE(4, false, 2);
+        else MOE_LOGITS_CASE(1, false, 2);
+    }
+#undef MOE_LOGITS_CASE
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
+}
+int launch_gate_logits_route(const void* x, int dtype, const float* Wg, const float* bg, float* logits, int T, int d, int E, int k,
+                             int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* scratch, int* tokens_per_hist, hipStream_t s) {
+    if (!gate_logits_routes(T, E) || k < 1 || k > 2) return MOE_ERR_INVALID_ARG;
+    *tokens_per_hist = kLogitsTokens;
+    if (dtype == MOE_F32) return launch_logits_route_t(static_cast<const float*>(x), Wg, bg, logits, T, d, E, k, expert_idx, slot_idx, gate_w, scratch, s);
+    return launch_logits_route_t(static_cast<const uint16_t*>(x), Wg, bg, logits, T, d, E, k, expert_idx, slot_idx, gate_w, scratch, s);
 }
 
 int launch_gate_logits(const void* x, int dtype, const float* Wg, const float* bg, float* logits, int T, int d,
@@ -300,7 +396,6 @@ int launch_expert_order(const int32_t* expert_rows, int E, int C, int32_t* order
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-constexpr int kMaxFine = 8;      // fine blocks per 256 tokens at most (32-token tiles)
 constexpr int kFinThreads = 1024;   // at most; four times the tokens of a block: the sums over all tiles are most of its work
 
 // row groups that share a column's sum: all threads, but few enough that adding up their results stays short
@@ -309,7 +404,7 @@ __host__ __device__ inline int finalize_row_groups(int ncol, int nthreads) {
     return r < 16 ? r : 16;
 }
 
-// hist holds one histogram [K][E] per block of TB tokens (TB divides 256, TB >= 32).  A work-group finalises 256
+// hist holds one histogram [K][E] per block of TB tokens (TB divides 256, TB >= 16).  A work-group finalises 256
 // tokens.  Every work-group sums the histograms of all blocks before its own: the reads grow with the square of the
 // number of blocks (T = 16384, E = 64, top-2: 8 MB in all, served by L2), a stated limit of this kernel.
 template <int K>
@@ -342,43 +437,34 @@ __device__ __forceinline__ void route_finalize_body(int32_t* smem, int T, int E,
         part[rg * ncol + col] = pre;
         part[(R + rg) * ncol + col] = tot;
     }
+    // the histograms of this block's own tiles on the same memory round trip, turned into bases below
+    for (int idx = tid; idx < q * ncol; idx += nt) {
+        const long long at = (long long)b * q * ncol + idx;
+        base[idx] = at < (long long)nfine * ncol ? hist[at] : 0;
+    }
     __syncthreads();
-    for (int e = tid; e < E; e += nt) {
-        int pre[K], tot[K];
+    for (int col = tid; col < ncol; col += nt) {
+        const int j = K == 2 && col >= E ? 1 : 0, e = col - j * E;
+        int pre = 0, tot[K] = {};
+#pragma unroll 8
+        for (int rg = 0; rg < R; ++rg) {
+            pre += part[rg * ncol + col];
 #pragma unroll
-        for (int j = 0; j < K; ++j) {
-            pre[j] = tot[j] = 0;
-            for (int rg = 0; rg < R; ++rg) {
-                pre[j] += part[rg * ncol + j * E + e];
-                tot[j] += part[(R + rg) * ncol + j * E + e];
-            }
+            for (int i = 0; i < K; ++i) tot[i] += part[(R + rg) * ncol + i * E + e];
         }
         // first choices: rows before = first choices of earlier tokens; second choices rank behind ALL first ones
-        int run[K];
-        run[0] = pre[0];
-        int total = tot[0];
-        if (K == 2) {
-            run[1] = tot[0] + pre[1];
-            total += tot[1];
-        }
-        // the fine histograms of this block, fetched together (one memory round trip, not one per fine block)
-        int fine[kMaxFine - 1][K];
+        int run = pre + (j == 1 ? tot[0] : 0);
+        for (int f0 = 0; f0 < q; f0 += 4) {                     // four LDS reads at a time
+            int v[4];
 #pragma unroll
-        for (int f = 0; f < kMaxFine - 1; ++f)
+            for (int i = 0; i < 4; ++i) v[i] = f0 + i < q ? base[(f0 + i) * ncol + col] : 0;
 #pragma unroll
-            for (int j = 0; j < K; ++j)
-                fine[f][j] = (f + 1 < q && (b * q + f) * TB < T) ? hist[((size_t)(b * q + f) * K + j) * E + e] : 0;
-#pragma unroll
-        for (int f = 0; f < kMaxFine; ++f) {
-            if (f < q) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    base[(f * K + j) * E + e] = run[j];
-                    if (f < kMaxFine - 1) run[j] += fine[f < kMaxFine - 1 ? f : 0][j];
-                }
+            for (int i = 0; i < 4; ++i) {
+                if (f0 + i < q) base[(f0 + i) * ncol + col] = run;
+                run += v[i];
             }
         }
-        rows_sh[e] = min(total, C);
+        if (j == 0) rows_sh[e] = min(tot[0] + (K == 2 ? tot[K - 1] : 0), C);
     }
     __syncthreads();
 
@@ -465,9 +551,9 @@ int launch_route_finalize(int T, int E, int k, int C, int TB, const int32_t* exp
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// histograms for blocks of 32 tokens at the finest
-size_t route_scratch_ints(int T, int E, int k) {
-    const size_t fine = ((size_t)T + 31) / 32;
+// histograms for blocks of 32 tokens at the finest, of 16 where gate_logits_kernel writes them
+size_t route_scratch_ints(int T, int E, int k, bool by_logits) {
+    const size_t fine = by_logits && gate_logits_routes(T, E) ? ((size_t)T + kLogitsTokens - 1) / kLogitsTokens : ((size_t)T + 31) / 32;
     return fine * (size_t)k * (size_t)E;
 }
 

@@ -95,6 +95,12 @@ __device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int 
 int launch_gate_logits(const void* x, int dtype, const float* Wg, const float* bg, float* logits,
                        int T, int d, int E, hipStream_t s);
 
+// the same and, for few tokens and experts, the top-k, tile-local ranks (parked in slot_idx) and histograms in the same launch;
+// launch_route_finalize(..., *tokens_per_hist, ..., scratch) completes the routing
+bool gate_logits_routes(int T, int E);
+int launch_gate_logits_route(const void* x, int dtype, const float* Wg, const float* bg, float* logits, int T, int d, int E, int k,
+                             int32_t* expert_idx, int32_t* slot_idx, float* gate_w, int32_t* scratch, int* tokens_per_hist, hipStream_t s);
+
 // the same for bf16 tokens on the bf16 matrix cores (fp32 weights split into three bf16 pieces, exact); Wg_packed: the pieces as
 // launch_pack_gate wrote them, or nullptr: Wg
 bool gate_bf16_supported(int d, int E);
@@ -122,7 +128,7 @@ int launch_gate_decode(const void* x, const float* Wg, const void* Wg_packed, co
                        int32_t* slot_token, int32_t* expert_order, uint64_t* flags, uint64_t tag, hipStream_t s);
 
 // number of int32 the routing kernels need as scratch
-size_t route_scratch_ints(int T, int E, int k);
+size_t route_scratch_ints(int T, int E, int k, bool by_logits /* tokens or shapes that the bf16 gate kernels do not take */);
 
 // softmax + top-k + capacity slots from fp32 logits
 int launch_route(const float* logits, int T, int E, int k, int C,
