@@ -865,9 +865,12 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
     static_assert(HS * 4 <= 16 * 16, "a wave's rows of 32 columns fit where its sums go");
     const int tid = threadIdx.x, lane = tid & 63, c = lane & 15, kg = lane >> 4;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if (EPI == EPI_SCATTER) f32_zero_dropped(b, tid, kFWaves * 64);
+    auto zero_dropped = [&]() {                                  // a memory round trip: behind the operands' loads, not before them
+        __builtin_amdgcn_sched_barrier(0);
+        if (EPI == EPI_SCATTER) f32_zero_dropped(b, tid, kFWaves * 64);
+    };
     const int g = blockIdx.y, rows = f32_rows_of(a, g), m0 = blockIdx.x * MS * 16;
-    if (m0 >= rows) return;
+    if (m0 >= rows) return zero_dropped();
     const int d = a.K, f = a.N;
     const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
     typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -913,6 +916,7 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
                 w2[q][j] = k < f ? v : zero;
             }
         if (bias1) bv = *reinterpret_cast<const f32x2_t*>(bias1 + (size_t)g * f + nc);
+        zero_dropped();
         f32x4_t h[4][MS][2];                                     // every 16 k on their own: as few steps that round a sum as in the split products
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -953,6 +957,8 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();                         // the piece is read before the sums are written over it
+    } else {
+        zero_dropped();
     }
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms) {
@@ -971,7 +977,9 @@ __global__ __launch_bounds__(kFWaves * 64, 2) void f32_ffn_kernel(const GemmArgs
 }
 
 template <int EPI> int launch_ffn_epi(const GemmArgs& a, const GemmArgs& b, hipStream_t s) {
-    const int tm = a.max_rows <= 16 ? 16 : 32;
+    // A full 32-row tile keeps its compute unit's matrix cores busy for 4 us; 16-row ones as long as there are units for them
+    // (256 tokens, 64/256, 8 experts x 32 rows 10.2 -> 8.3 us; 1500 tokens, top-2 of 16, dense branch 10.8 + 10.8 -> 8.0 + 8.0)
+    const int tm = a.max_rows <= 16 || (long long)a.G * ((a.max_rows + 15) / 16) <= 256 ? 16 : 32;
     const long long tiles = ((long long)a.max_rows + tm - 1) / tm;
     if (tiles * 512 > 0xffffffffll) return MOE_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)tiles, (unsigned)a.G), block(kFWaves * 64);
