@@ -10,6 +10,7 @@ a call returns a non-zero status, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -170,12 +171,13 @@ def _w(shape, G: int, K: int, N: int) -> int:
 def _wg(shape) -> int:
     """float32 elements of the gate weights: plain [d,E], or the buffer moe_pack_gate returns."""
     if shape.flags & MOE_FLAG_PACKED_GATE:
-        return (moe_packed_gate_bytes(shape.d_model, shape.E) + 3) // 4
+        return (_packed_gate_bytes(shape.d_model, shape.E) + 3) // 4
     return shape.d_model * shape.E
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # torch.cuda.current_stream().cuda_stream without the Stream object, whose making is 1 us of a call of 20
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _check(fn: str, status: int) -> None:
@@ -189,6 +191,22 @@ def _elem(shape: MoeShape) -> torch.dtype:
 
 def moe_workspace_bytes(shape: MoeShape) -> int:
     return int(load_library().moe_workspace_bytes(ctypes.byref(shape)))
+
+
+# Byte counts that every call asks for, by the values they depend on (not by the object that holds them)
+@functools.lru_cache(maxsize=256)
+def _workspace_need(shape: bytes) -> int:
+    return moe_workspace_bytes(MoeShape.from_buffer_copy(shape))
+
+
+@functools.lru_cache(maxsize=256)
+def _block_workspace_need(shape: bytes, block: bytes) -> int:
+    return moe_decode_block_workspace_bytes(MoeShape.from_buffer_copy(shape), MoeBlockShape.from_buffer_copy(block))
+
+
+@functools.lru_cache(maxsize=256)
+def _packed_gate_bytes(d_model: int, E: int) -> int:
+    return moe_packed_gate_bytes(d_model, E)
 
 
 def moe_version() -> str:
@@ -245,7 +263,7 @@ def _gate_args(shape, x, Wg, bg, logits, expert_idx, slot_idx, gate_w, expert_ro
 
 
 def moe_gate(shape, x, Wg, bg, logits, expert_idx, slot_idx, gate_w, expert_rows, slot_token, ws) -> None:
-    wsp, wsn = _ws(shape, ws, moe_workspace_bytes(shape))
+    wsp, wsn = _ws(shape, ws, _workspace_need(bytes(shape)))
     rc = load_library().moe_gate(ctypes.byref(shape), *_gate_args(shape, x, Wg, bg, logits, expert_idx, slot_idx, gate_w,
                                                                  expert_rows, slot_token), wsp, wsn, _stream())
     _check("moe_gate", rc)
@@ -277,7 +295,7 @@ def moe_dispatch(shape, x, slot_token, expert_rows, xe) -> None:
 def moe_expert_ffn(shape, xe, expert_rows, W1, b1, W2, b2, ye, ws) -> None:
     el = _elem(shape)
     d, f, E, C = shape.d_model, shape.d_ffn, shape.E, shape.capacity
-    wsp, wsn = _ws(shape, ws, moe_workspace_bytes(shape))
+    wsp, wsn = _ws(shape, ws, _workspace_need(bytes(shape)))
     rc = load_library().moe_expert_ffn(
         ctypes.byref(shape), _ptr(xe, el, E * C * d, "xe"), _ptr(expert_rows, torch.int32, E, "expert_rows"),
         _ptr(W1, el, _w(shape, E, d, f), "W1"), _ptr(b1, el, E * f, "b1"), _ptr(W2, el, _w(shape, E, f, d), "W2"),
@@ -288,7 +306,7 @@ def moe_expert_ffn(shape, xe, expert_rows, W1, b1, W2, b2, ye, ws) -> None:
 def moe_expert_ffn_slice(shape, xe, expert_rows, W1s, b1s, W2s, ye_partial, ws) -> None:
     el = _elem(shape)
     d, f, E, C = shape.d_model, shape.d_ffn, shape.E, shape.capacity
-    wsp, wsn = _ws(shape, ws, moe_workspace_bytes(shape))
+    wsp, wsn = _ws(shape, ws, _workspace_need(bytes(shape)))
     rc = load_library().moe_expert_ffn_slice(
         ctypes.byref(shape), _ptr(xe, el, E * C * d, "xe"), _ptr(expert_rows, torch.int32, E, "expert_rows"),
         _ptr(W1s, el, _w(shape, E, d, f), "W1s"), _ptr(b1s, el, E * f, "b1s"), _ptr(W2s, el, _w(shape, E, f, d), "W2s"),
@@ -327,7 +345,7 @@ def moe_layer_forward(shape, x, Wg, bg, W1, b1, W2, b2, Wd1, bd1, Wd2, bd2, out,
                       logits_out, expert_idx_out, slot_idx_out, gate_w_out, expert_rows_out, slot_token_out, ws) -> None:
     el, i32, f32 = _elem(shape), torch.int32, torch.float32
     T, d, E, k, C = shape.T, shape.d_model, shape.E, shape.top_k, shape.capacity
-    wsp, wsn = _ws(shape, ws, moe_workspace_bytes(shape))
+    wsp, wsn = _ws(shape, ws, _workspace_need(bytes(shape)))
     rc = load_library().moe_layer_forward(
         ctypes.byref(shape), _ptr(x, el, T * d, "x"), _ptr(Wg, f32, _wg(shape), "Wg"), _ptr(bg, f32, E, "bg"),
         *_ffn_weight_args(shape, W1, b1, W2, b2, Wd1, bd1, Wd2, bd2), _ptr(out, el, T * d, "out"),
@@ -354,7 +372,7 @@ def moe_decode_block_forward(shape, block, weights: dict, x, k_cache, v_cache, p
              "W2": (el, _w(shape, E, f, d)), "b2": (el, E * d), "Wd1": (el, _w(shape, 1, d, f)), "bd1": (el, f),
              "Wd2": (el, _w(shape, 1, f, d)), "bd2": (el, d)}
     w = MoeBlockWeights(**{n: _ptr(weights.get(n), sizes[n][0], sizes[n][1], n) for n in BLOCK_WEIGHT_FIELDS})
-    wsp, wsn = _ws(shape, ws, moe_decode_block_workspace_bytes(shape, block))
+    wsp, wsn = _ws(shape, ws, _block_workspace_need(bytes(shape), bytes(block)))
     rc = load_library().moe_decode_block_forward(
         ctypes.byref(shape), ctypes.byref(block), ctypes.byref(w), _ptr(x, el, T * d, "x"),
         _ptr(k_cache, el, cache, "k_cache"), _ptr(v_cache, el, cache, "v_cache"), _ptr(pos, torch.int32, T, "pos"),
