@@ -394,10 +394,11 @@ int run_expert_gemm1(const moe_shape_t* s, const FfnPlan& p, const void* xin, co
 }
 
 // Expert GEMM-2 on the MFMA kernel.  scatter == false: ye[e, r, :] = h[e, r, :] W2[e] + b2[e].
-// scatter == true (top-1): out[token(e, r), :] = gate_w[token] * (...), rows of dropped tokens zeroed.
+// scatter == true (top-1): out[token(e, r), :] = gate_w[token] * (...), rows of dropped tokens zeroed; with `add` (a decoder
+// block) its rows are added.
 int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, const int32_t* rows,
                      const int32_t* order, const void* W2, const void* b2, bool scatter, const int32_t* slot_token, const int32_t* slot_idx,
-                     const float* gate_w, void* dst, float* partial, hipStream_t st) {
+                     const float* gate_w, const uint16_t* add, void* dst, float* partial, hipStream_t st) {
     WsGemmArgs a{};
     a.A = u16(h); a.B = u16(W2); a.bias = u16(b2); a.rows = rows; a.row_map = nullptr;
     // The tiled kernel's tiles of this product are long (K = d_ffn) and few per CU: the busiest experts go first, so
@@ -408,7 +409,7 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     a.max_rows = s->capacity; a.expect_rows = p.expect; a.G = s->E; a.K = s->d_ffn; a.N = s->d_model;
     a.a_group_stride = s->capacity; a.out = u16(dst); a.o_group_stride = s->capacity; a.ksplit = p.ksplit2;
     a.scatter_map = slot_token; a.scatter_stride = s->capacity; a.zero_slot_idx = slot_idx; a.T = s->T;
-    a.gate_w = gate_w; a.top_k = s->top_k;
+    a.gate_w = gate_w; a.top_k = s->top_k; a.add = add;
     prof_pre(ST_GEMM2, st);
     if (p.ksplit2 == 1) {
         const int epi = scatter ? EPI_SCATTER : EPI_STORE;
@@ -426,7 +427,7 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     SplitKReduceArgs r{};
     r.partial = partial; r.ksplit = p.ksplit2; r.G = s->E; r.N = s->d_model; r.group_stride = s->capacity;
     r.rows = rows; r.max_rows = s->capacity; r.bias = u16(b2); r.out = u16(dst);
-    r.scatter_map = scatter ? slot_token : nullptr; r.gate_w = gate_w; r.top_k = s->top_k;
+    r.scatter_map = scatter ? slot_token : nullptr; r.gate_w = gate_w; r.top_k = s->top_k; r.add = add;
     r.zero_slot_idx = scatter ? slot_idx : nullptr; r.T = s->T;
     prof_pre(ST_REDUCE, st);
     rc = launch_splitk_reduce(r, st);
@@ -444,11 +445,11 @@ bool dense1_shared(const moe_shape_t* s, const FfnPlan& p) {
 }
 
 // Dense branch of Residual-MoE on the MFMA kernels, with the combine fused into its second GEMM:
-// out[t, :] = gelu_tanh(x[t] Wd1 + bd1) Wd2 + bd2 + sum_j keep_j g_j ye[e_j, slot_j, :].
+// out[t, :] = gelu_tanh(x[t] Wd1 + bd1) Wd2 + bd2 + sum_j keep_j g_j ye[e_j, slot_j, :] (+ add[t, :]).
 // first_done: hd is there already (the first product shared a launch with the experts').
 int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, const void* Wd2,
                      const void* bd2, void* hd, bool first_done, const void* ye, const int32_t* expert_idx,
-                     const int32_t* slot_idx, const float* gate_w, void* out, hipStream_t st) {
+                     const int32_t* slot_idx, const float* gate_w, const uint16_t* add, void* out, hipStream_t st) {
     int MT, NW, rc = MOE_OK;
     WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
     const bool tiled = dense_tiled(s);
@@ -464,7 +465,7 @@ int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const
     }
     a.A = u16(hd); a.B = u16(Wd2); a.bias = u16(bd2); a.K = s->d_ffn; a.N = s->d_model; a.out = u16(out);
     a.ye = u16(ye); a.expert_idx = expert_idx; a.slot_idx = slot_idx; a.gate_w = gate_w; a.top_k = s->top_k;
-    a.C = s->capacity;
+    a.C = s->capacity; a.add = add;
     const int nf = rows_pick_dense(s->T, s->d_model, a.packed);
     wsgemm_pick_tile(s->T, 1, s->d_model, &MT, &NW);
     prof_pre(ST_DENSE2, st);
@@ -662,7 +663,7 @@ int moe_expert_ffn(const moe_shape_t* shape, const void* xe, const int32_t* expe
     if (rc != MOE_OK) return rc;
     rc = run_expert_gemm1(shape, plan, xe, nullptr, expert_rows, order, W1, b1, at<void>(ws, L.h), st);
     if (rc != MOE_OK) return rc;
-    return run_expert_gemm2(shape, plan, at<void>(ws, L.h), expert_rows, order, W2, b2, false, nullptr, nullptr, nullptr, ye,
+    return run_expert_gemm2(shape, plan, at<void>(ws, L.h), expert_rows, order, W2, b2, false, nullptr, nullptr, nullptr, nullptr, ye,
                             at<float>(ws, L.partial), st);
 }
 
@@ -726,7 +727,7 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
                       const void* b1, const void* W2, const void* b2, const void* Wd1, const void* bd1, const void* Wd2,
                       const void* bd2, void* out, float* logits_out, int32_t* expert_idx_out, int32_t* slot_idx_out,
                       float* gate_w_out, int32_t* expert_rows_out, int32_t* slot_token_out, void* ws, size_t ws_bytes,
-                      void* stream) {
+                      const uint16_t* add, void* stream) {
     int rc = check_shape(shape);
     if (rc != MOE_OK) return rc;
     if (!x || !Wg || !W1 || !W2 || !out) return MOE_ERR_INVALID_ARG;
@@ -795,16 +796,16 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
     if (rc != MOE_OK) return rc;
     // ... and, for top-1 Standard-MoE, combine into GEMM-2 (scale by the gate weight, write the token's row)
     if (k == 1 && !shape->residual)
-        return run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, true, slot_token, slot_idx, gate_w, out,
+        return run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, true, slot_token, slot_idx, gate_w, add, out,
                                 at<float>(ws, L.partial), st);
-    rc = run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, false, nullptr, nullptr, nullptr,
+    rc = run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, false, nullptr, nullptr, nullptr, nullptr,
                           at<void>(ws, L.ye), at<float>(ws, L.partial), st);
     if (rc != MOE_OK) return rc;
     if (shape->residual)
         return run_dense_branch(shape, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd), dense1_done, at<void>(ws, L.ye),
-                                expert_idx, slot_idx, gate_w, out, st);
+                                expert_idx, slot_idx, gate_w, add, out, st);
     prof_pre(ST_COMBINE, st);
-    rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, nullptr, out, T, k, C, d, st);
+    rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st);
     prof_mark(ST_COMBINE, st);
     return rc;
 }
@@ -816,7 +817,7 @@ int moe_layer_forward(const moe_shape_t* shape, const void* x, const float* Wg, 
                       void* stream) {
     const int rc = layer_forward_checked(shape, x, Wg, bg, W1, b1, W2, b2, Wd1, bd1, Wd2, bd2, out, logits_out,
                                          expert_idx_out, slot_idx_out, gate_w_out, expert_rows_out, slot_token_out, ws,
-                                         ws_bytes, stream);
+                                         ws_bytes, nullptr, stream);
     g_prof.cur = -1;       // stage events belong to this call only: a later moe_expert_ffn must not add to them
     return rc;
 }
@@ -873,7 +874,6 @@ namespace {
 struct BlockLayout {
     size_t qkv, attn, proj, x1, xn, moe_out, attn_partial, lin_partial, moe_ws, total;
 };
-constexpr int kLinearMaxSplit = 8;
 
 BlockLayout block_layout(const moe_shape_t* s, const moe_block_shape_t* b) {
     BlockLayout L{};
@@ -904,9 +904,11 @@ int check_block_shape(const moe_shape_t* s, const moe_block_shape_t* b) {
 }
 
 // out[T, N] = x[T, K] W[K, N] + bias on the weight-streaming kernel (a decode step has few rows: the product is a
-// read of W); with few output columns the inner dimension is split over more waves and summed in a fixed order
+// read of W); with few output columns the inner dimension is split over more waves and summed in a fixed order: here, or
+// (split_out given and more than 1) by whoever reads `partial` next
 int run_linear(const uint16_t* x, const uint16_t* W, const uint16_t* bias, uint16_t* out, int T, int K, int N,
-               float* partial, hipStream_t st) {
+               float* partial, int* split_out, hipStream_t st) {
+    if (split_out) *split_out = 1;
     WsGemmArgs a{};
     a.A = x; a.B = W; a.bias = bias; a.fixed_rows = T; a.max_rows = T; a.G = 1; a.K = K; a.N = N; a.out = out;
     a.o_group_stride = T; a.a_group_stride = T; a.ksplit = 1;
@@ -922,6 +924,10 @@ int run_linear(const uint16_t* x, const uint16_t* W, const uint16_t* bias, uint1
     a.ksplit = (int)ks; a.partial = partial; a.partial_rows = T;
     int rc = launch_wsgemm(a, EPI_PARTIAL, MT, NW, 2, st);
     if (rc != MOE_OK) return rc;
+    if (split_out) {
+        *split_out = (int)ks;
+        return MOE_OK;
+    }
     SplitKReduceArgs r{};
     r.partial = partial; r.ksplit = (int)ks; r.G = 1; r.N = N; r.group_stride = T; r.rows = nullptr; r.max_rows = T;
     r.bias = bias; r.out = out; r.top_k = 1; r.T = T;
@@ -966,25 +972,36 @@ int moe_decode_block_forward(const moe_shape_t* shape, const moe_block_shape_t* 
     float* lin_partial = at<float>(ws, L.lin_partial);
 
     // a = LayerNorm(x); qkv = a Wqkv + bqkv
-    rc = launch_add_layernorm(u16(x), nullptr, w->ln1_gamma, w->ln1_beta, nullptr, xn, T, d, eps, st);
+    rc = launch_add_layernorm(u16(x), AddedRows{}, w->ln1_gamma, w->ln1_beta, nullptr, xn, T, d, eps, st);
     if (rc != MOE_OK) return rc;
-    rc = run_linear(xn, u16(w->Wqkv), u16(w->bqkv), qkv, T, d, 3 * d, lin_partial, st);
+    rc = run_linear(xn, u16(w->Wqkv), u16(w->bqkv), qkv, T, d, 3 * d, lin_partial, nullptr, st);
     if (rc != MOE_OK) return rc;
     // the new token over its sequence's cache (its own key/value rows join the cache)
     rc = launch_attn_decode(qkv, u16(k_cache), u16(v_cache), pos, at<float>(ws, L.attn_partial), attn, T, H, dh,
                             block->max_len, st);
     if (rc != MOE_OK) return rc;
-    rc = run_linear(attn, u16(w->Wo), u16(w->bo), proj, T, d, d, lin_partial, st);
+    int split = 1;
+    rc = run_linear(attn, u16(w->Wo), u16(w->bo), proj, T, d, d, lin_partial, add_layernorm_sums(d) ? &split : nullptr, st);
     if (rc != MOE_OK) return rc;
     // x1 = x + attention; the MoE layer sees LayerNorm(x1)
-    rc = launch_add_layernorm(u16(x), proj, w->ln2_gamma, w->ln2_beta, x1, moe_in, T, d, eps, st);
+    const AddedRows projected = split > 1 ? AddedRows{nullptr, lin_partial, u16(w->bo), split} : AddedRows{proj, nullptr, nullptr, 0};
+    rc = launch_add_layernorm(u16(x), projected, w->ln2_gamma, w->ln2_beta, x1, moe_in, T, d, eps, st);
     if (rc != MOE_OK) return rc;
+    // out = x1 + MoE: in the layer's last kernel, or (experts and dense branch in one launch) behind it
+    FfnPlan plan = plan_ffn(shape);
+    if (!plan.mfma || (shape->residual && residual_pairs(shape, plan))) {
+        rc = layer_forward_checked(shape, moe_in, w->Wg, w->bg, w->W1, w->b1, w->W2, w->b2, w->Wd1, w->bd1, w->Wd2, w->bd2,
+                                   moe_out, logits_out, nullptr, nullptr, nullptr, nullptr, nullptr,
+                                   at<void>(ws, L.moe_ws), ws_layout(shape).total, nullptr, stream);
+        g_prof.cur = -1;
+        if (rc != MOE_OK) return rc;
+        return launch_add_rows(x1, moe_out, u16(out), (long long)T * d, st);
+    }
     rc = layer_forward_checked(shape, moe_in, w->Wg, w->bg, w->W1, w->b1, w->W2, w->b2, w->Wd1, w->bd1, w->Wd2, w->bd2,
-                               moe_out, logits_out, nullptr, nullptr, nullptr, nullptr, nullptr,
-                               at<void>(ws, L.moe_ws), ws_layout(shape).total, stream);
+                               out, logits_out, nullptr, nullptr, nullptr, nullptr, nullptr,
+                               at<void>(ws, L.moe_ws), ws_layout(shape).total, x1, stream);
     g_prof.cur = -1;
-    if (rc != MOE_OK) return rc;
-    return launch_add_rows(x1, moe_out, u16(out), (long long)T * d, st);
+    return rc;
 }
 
 int moe_profile_enable(int max_calls) {

@@ -30,12 +30,15 @@ __device__ __forceinline__ float wave_sum(float v) {
 // A row by one work-group, its pieces of 8 elements held in registers from the sum to the result (NP per thread): one
 // memory round trip and the two sums across the waves.  A wave per row with three passes over it, below, left 64 rows to 16
 // work-groups: 10.7 us for 64 rows of 2048 with the residual add, 6.6 without.
-template <int NP>
-__global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ r,
+// SUMS: the added rows are a projection's partial sums, added up here in their order, biased and rounded as the launch that did
+// nothing else left them (4.7 us of a step).
+template <int NP, bool SUMS>
+__global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* __restrict__ x, const AddedRows added,
                                                                 const float* __restrict__ gamma, const float* __restrict__ beta,
                                                                 uint16_t* __restrict__ sum_out, uint16_t* __restrict__ y, int d,
                                                                 float eps) {
     __shared__ float part[2][4];
+    const uint16_t* r = added.rows;
     const int tid = threadIdx.x, pieces = d / 8;
     const size_t row = (size_t)blockIdx.x * d;
     float f[NP][8], gm[NP][8], bt[NP][8];
@@ -44,7 +47,32 @@ __global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* 
     for (int p = 0; p < NP; ++p) {                      // all loads first; past the end: the last piece, not counted
         const int i = min(tid + p * 256, pieces - 1);
         xv[p] = reinterpret_cast<const uint4*>(x + row)[i];
-        if (r) rv[p] = reinterpret_cast<const uint4*>(r + row)[i];
+        if constexpr (SUMS) {
+            float4 part4[kLinearMaxSplit][2];
+#pragma unroll
+            for (int s = 0; s < kLinearMaxSplit; ++s)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    part4[s][q] = s < added.ksplit ? reinterpret_cast<const float4*>(added.partial + (size_t)s * gridDim.x * d + row)[2 * i + q]
+                                                   : make_float4(0.f, 0.f, 0.f, 0.f);
+            const uint4 bias = added.bias ? reinterpret_cast<const uint4*>(added.bias)[i] : make_uint4(0, 0, 0, 0);
+            float v[8], bf[8];
+            unpack8(bias, bf);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = 0.f;
+#pragma unroll
+            for (int s = 0; s < kLinearMaxSplit; ++s) {
+                if (s >= added.ksplit) break;
+                const float a8[8] = {part4[s][0].x, part4[s][0].y, part4[s][0].z, part4[s][0].w, part4[s][1].x, part4[s][1].y, part4[s][1].z, part4[s][1].w};
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] += a8[q];
+            }
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += bf[q];
+            rv[p] = pack8(v);
+        } else if (r) {
+            rv[p] = reinterpret_cast<const uint4*>(r + row)[i];
+        }
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             *reinterpret_cast<float4*>(&gm[p][4 * q]) = reinterpret_cast<const float4*>(gamma)[2 * i + q];
@@ -62,7 +90,7 @@ __global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* 
     for (int p = 0; p < NP; ++p) {
         const int i = tid + p * 256;
         unpack8(xv[p], f[p]);
-        if (r) {
+        if (SUMS || r) {
             float g[8];
             unpack8(rv[p], g);
 #pragma unroll
@@ -146,13 +174,22 @@ __global__ __launch_bounds__(256) void add_layernorm_kernel(const uint16_t* __re
     }
 }
 
-int launch_add_layernorm(const uint16_t* x, const uint16_t* r, const float* gamma, const float* beta, uint16_t* sum_out,
+bool add_layernorm_sums(int d) { return d <= 4096; }
+int launch_add_layernorm(const uint16_t* x, const AddedRows& r, const float* gamma, const float* beta, uint16_t* sum_out,
                          uint16_t* y, int T, int d, float eps, hipStream_t s) {
-    if (d <= 2048)
-        hipLaunchKernelGGL(add_layernorm_row_kernel<1>, dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps);
-    else if (d <= 4096)
-        hipLaunchKernelGGL(add_layernorm_row_kernel<2>, dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps);
-    else hipLaunchKernelGGL(add_layernorm_kernel, dim3((T + 3) / 4), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, T, d, eps);
+    if (r.partial && (!add_layernorm_sums(d) || r.ksplit < 1 || r.ksplit > kLinearMaxSplit)) return MOE_ERR_INVALID_ARG;
+#define MOE_LN_ROW(NP, SUMS) \
+    hipLaunchKernelGGL((add_layernorm_row_kernel<NP, SUMS>), dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps)
+    if (d <= 2048) {
+        if (r.partial) MOE_LN_ROW(1, true);
+        else MOE_LN_ROW(1, false);
+    } else if (d <= 4096) {
+        if (r.partial) MOE_LN_ROW(2, true);
+        else MOE_LN_ROW(2, false);
+    } else {
+        hipLaunchKernelGGL(add_layernorm_kernel, dim3((T + 3) / 4), dim3(256), 0, s, x, r.rows, gamma, beta, sum_out, y, T, d, eps);
+    }
+#undef MOE_LN_ROW
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
@@ -183,7 +220,11 @@ int launch_add_rows(const uint16_t* a, const uint16_t* b, uint16_t* out, long lo
 // A work-group takes kAttnChunk consecutive positions of one (sequence, head); LPP = DH/8 lanes share a position
 // (16 bytes of its key and value each), a wave step covers 64/LPP consecutive positions = 1 KB of contiguous cache.
 // Every lane group keeps a running softmax (maximum, sum, weighted values); the groups of a work-group meet in LDS
-// and leave one partial (m, l, o[DH]) per chunk, merged by attn_merge_kernel.  The chunk that holds position pos[b]
+// and leave one partial (m, l, o[DH]) per chunk.
+// attn_merge_kernel merges them; a sequence's only chunk is the result, and with room for one chunk there is no merge.
+// (Merged by the work-group of a sequence and head that comes last, every work-group pays for the hand-over across the XCDs' L2s:
+// 64 sequences of 16 heads, 8 chunks 92.9 + 4.6 -> 99.8 us; 107 of 8, 4 chunks 35 + 4.8 -> 46.6; 10 of 8, 3 chunks 8.1 + 3.9 -> 11.2.)
+// The chunk that holds position pos[b]
 // takes the new key/value from qkv, never from the cache, so the write of the new rows into the cache (by chunk 0)
 // races with nobody.
 // Bound by the read of the cache: kAttnAhead steps are loaded together and meet in one rescaling of the running softmax
@@ -191,10 +232,45 @@ int launch_add_rows(const uint16_t* a, const uint16_t* b, uint16_t* out, long lo
 constexpr int kAttnChunk = 256;
 constexpr int kAttnAhead = 4;
 
+// cached positions (clamped into the cache: no access can leave it), and chunks with a position: the new token is position npast
+__device__ __forceinline__ int past_positions(int pos, int Lmax) { return min(max(pos, 0), Lmax - 1); }
+__device__ __forceinline__ int live_chunks(int pos, int Lmax) { return past_positions(pos, Lmax) / kAttnChunk + 1; }
+
+// Element t of a (sequence, head)'s result from its chunks' partials
+template <int DH> __device__ __forceinline__ uint16_t merge_chunks(const float* p, int nlive, int t) {
+    // sum_split o exp(m - M) / sum_split l exp(m - M), eight chunks' partials in flight; a chunk whose scores are all NaN holds
+    // m = -inf and NaN
+    float M = -INFINITY, L = 0.f, O = 0.f;
+    for (int s0 = 0; s0 < nlive; s0 += 8) {
+        float mu[8], lu[8], ou[8], mn = M;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float* ps = p + min(s0 + u, nlive - 1) * (DH + 2);
+            mu[u] = s0 + u < nlive ? ps[0] : -INFINITY;
+            lu[u] = s0 + u < nlive ? ps[1] : 0.f;
+            ou[u] = s0 + u < nlive ? ps[2 + t] : 0.f;              // not the last chunk's once more: 0 times infinity is NaN
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) mn = fmaxf(mn, mu[u]);
+        const float c = M == mn ? 1.f : __expf(M - mn);
+        L *= c;
+        O *= c;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const float e = s0 + u >= nlive ? 0.f : mu[u] == mn ? 1.f : __expf(mu[u] - mn);
+            L = fmaf(lu[u], e, L);
+            O = fmaf(ou[u], e, O);
+        }
+        M = mn;
+    }
+    return f32_to_bf16(O / L);
+}
+
 template <int DH, bool STREAM>
 __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __restrict__ qkv, uint16_t* __restrict__ cache_k,
                                                           uint16_t* __restrict__ cache_v, const int32_t* __restrict__ pos,
-                                                          float* __restrict__ partial, int H, int Lmax, int nsplit) {
+                                                          float* __restrict__ partial, uint16_t* __restrict__ attn,
+                                                          int H, int Lmax, int nsplit) {
     constexpr int LPP = DH / 8, PPW = 64 / LPP, NG = 4 * PPW;       // lanes per position, positions per wave step, groups
     __shared__ float m_sh[NG], l_sh[NG];
     __shared__ float o_sh[NG][DH];
@@ -202,8 +278,9 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
     const int d = H * DH;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int sub = lane % LPP, grp = lane / LPP;
-    const int npast = min(max(pos[b], 0), Lmax - 1);                 // cached positions (clamped into the cache: no
-                                                                     // access can leave it); the new token is position npast
+    const int npast = past_positions(pos[b], Lmax);
+    const int nlive = live_chunks(npast, Lmax);
+    if (split >= nlive) return;
     const uint16_t* qrow = qkv + (size_t)b * 3 * d + h * DH;
     float q[8];
     unpack8(*reinterpret_cast<const uint4*>(qrow + sub * 8), q);
@@ -283,44 +360,21 @@ __global__ __launch_bounds__(256) void attn_decode_kernel(const uint16_t* __rest
             L = fmaf(l_sh[j], c, L);
             O = fmaf(o_sh[j][tid], c, O);
         }
-        float* dst = partial + ((size_t)bh * nsplit + split) * (DH + 2);
-        dst[2 + tid] = O;
-        if (tid == 0) { dst[0] = M; dst[1] = L; }
+        if (nlive == 1) {
+            attn[(size_t)bh * DH + tid] = f32_to_bf16(O / L);
+        } else {
+            float* dst = partial + ((size_t)bh * nsplit + split) * (DH + 2);
+            dst[2 + tid] = O;
+            if (tid == 0) { dst[0] = M; dst[1] = L; }
+        }
     }
 }
 
-// attn[b, h*DH + t] = sum_split o * exp(m - M) / sum_split l * exp(m - M)
 template <int DH>
-__global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict__ partial, uint16_t* __restrict__ attn, int H,
-                                                        int nsplit) {
-    const int bh = blockIdx.x, b = bh / H, h = bh % H, t = threadIdx.x;
-    const float* p = partial + (size_t)bh * nsplit * (DH + 2);
-    // eight chunks' partials in flight; a chunk without positions holds m = -inf and zeros, one whose scores are all NaN
-    // m = -inf and NaN
-    float M = -INFINITY, L = 0.f, O = 0.f;
-    for (int s0 = 0; s0 < nsplit; s0 += 8) {
-        float m[8], l[8], o[8], mn = M;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float* ps = p + min(s0 + u, nsplit - 1) * (DH + 2);
-            m[u] = s0 + u < nsplit ? ps[0] : -INFINITY;
-            l[u] = s0 + u < nsplit ? ps[1] : 0.f;
-            o[u] = s0 + u < nsplit ? ps[2 + t] : 0.f;            // not the last chunk's once more: 0 times infinity is NaN
-        }
-#pragma unroll
-        for (int u = 0; u < 8; ++u) mn = fmaxf(mn, m[u]);
-        const float c = M == mn ? 1.f : __expf(M - mn);
-        L *= c;
-        O *= c;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const float e = s0 + u >= nsplit ? 0.f : m[u] == mn ? 1.f : __expf(m[u] - mn);
-            L = fmaf(l[u], e, L);
-            O = fmaf(o[u], e, O);
-        }
-        M = mn;
-    }
-    attn[(size_t)b * H * DH + h * DH + t] = f32_to_bf16(O / L);
+__global__ __launch_bounds__(DH) void attn_merge_kernel(const float* __restrict__ partial, const int32_t* __restrict__ pos, uint16_t* __restrict__ attn,
+                                                        int H, int Lmax, int nsplit) {
+    const int bh = blockIdx.x, nlive = live_chunks(pos[bh / H], Lmax);
+    if (nlive > 1) attn[(size_t)bh * DH + threadIdx.x] = merge_chunks<DH>(partial + (size_t)bh * nsplit * (DH + 2), nlive, threadIdx.x);
 }
 
 int attn_nsplit(int Lmax) { return (Lmax + kAttnChunk - 1) / kAttnChunk; }
@@ -337,16 +391,19 @@ int launch_attn_decode(const uint16_t* qkv, uint16_t* cache_k, uint16_t* cache_v
     // without much of a feed-forward part: 108.6 -> 112.5; all 2048: 202 -> 184).
     const bool stream = (long long)T * H * Lmax * dh * 4 > 256ll << 20;
 #define MOE_ATTN(DH, STREAM) \
-    hipLaunchKernelGGL((attn_decode_kernel<DH, STREAM>), grid, dim3(256), 0, s, qkv, cache_k, cache_v, pos, partial, H, Lmax, nsplit)
+    hipLaunchKernelGGL((attn_decode_kernel<DH, STREAM>), grid, dim3(256), 0, s, qkv, cache_k, cache_v, pos, partial, attn, H, Lmax, nsplit)
+#define MOE_ATTN_MERGE(DH) \
+    if (nsplit > 1) hipLaunchKernelGGL((attn_merge_kernel<DH>), dim3((unsigned)(T * H)), dim3(DH), 0, s, partial, pos, attn, H, Lmax, nsplit)
     if (dh == 128) {
         if (stream) MOE_ATTN(128, true);
         else MOE_ATTN(128, false);
-        hipLaunchKernelGGL((attn_merge_kernel<128>), dim3((unsigned)(T * H)), dim3(128), 0, s, partial, attn, H, nsplit);
+        MOE_ATTN_MERGE(128);
     } else {
         if (stream) MOE_ATTN(64, true);
         else MOE_ATTN(64, false);
-        hipLaunchKernelGGL((attn_merge_kernel<64>), dim3((unsigned)(T * H)), dim3(64), 0, s, partial, attn, H, nsplit);
+        MOE_ATTN_MERGE(64);
     }
+#undef MOE_ATTN_MERGE
 #undef MOE_ATTN
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

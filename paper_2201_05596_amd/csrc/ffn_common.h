@@ -103,14 +103,15 @@ inline long long tile_grid_blocks(const WsGemmArgs& a, int n_tiles, int inner_n)
     return ((long long)a.G * n_tiles + kXcd - 1) / kXcd * kXcd * inner_n;
 }
 
-// Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them, spread over the waves of all
+// Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them (or copy what is added to), spread over the waves of all
 // work-groups (a dropped token has no other writer).  A wave looks at 16 tokens at once: one token after the other, a
 // work-group of a small grid waited for up to 16 memory round trips before its first tile (8192 tokens, 512 work-groups).
 __device__ __forceinline__ void zero_dropped_rows(const WsGemmArgs& a, int tid, int nthreads) {
     if (!a.zero_slot_idx) return;
     for_dropped_tokens(a.zero_slot_idx, 1, a.T, tid, nthreads, [&](int t, int lane) {
         uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
-        for (int i = lane; i < a.N / 8; i += kWave) o[i] = make_uint4(0, 0, 0, 0);
+        for (int i = lane; i < a.N / 8; i += kWave)
+            o[i] = a.add ? reinterpret_cast<const uint4*>(a.add + (size_t)t * a.N)[i] : make_uint4(0, 0, 0, 0);
     });
 }
 
@@ -202,6 +203,13 @@ __device__ __forceinline__ void finish_row(const WsGemmArgs& a, int g, int row, 
             const Vec y = *reinterpret_cast<const Vec*>(yp);
 #pragma unroll
             for (int i = 0; i < NC; ++i) v[i] = fmaf(gw, bf16_of(y, i), v[i]);
+        }
+    }
+    if constexpr (EPI == EPI_SCATTER || EPI == EPI_COMBINE) {
+        if (a.add) {
+            const Vec y = *reinterpret_cast<const Vec*>(a.add + orow * a.N + n_lane);
+#pragma unroll
+            for (int i = 0; i < NC; ++i) v[i] += bf16_of(y, i);
         }
     }
     uint32_t o[(NC + 1) / 2];

@@ -318,7 +318,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitKReduceAr
         for (long long t = wave; t < a.T; t += nwaves) {
             if (a.zero_slot_idx[t] < 0) {
                 uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
-                for (int i = lane; i < a.N / 8; i += 64) o[i] = make_uint4(0, 0, 0, 0);
+                for (int i = lane; i < a.N / 8; i += 64)
+                    o[i] = a.add ? reinterpret_cast<const uint4*>(a.add + (size_t)t * a.N)[i] : make_uint4(0, 0, 0, 0);
             }
         }
     }
@@ -369,9 +370,17 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitKReduceAr
             v[4] += __uint_as_float(bv.z << 16); v[5] += __uint_as_float(bv.z & 0xffff0000u);
             v[6] += __uint_as_float(bv.w << 16); v[7] += __uint_as_float(bv.w & 0xffff0000u);
         }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] *= gw;
+        if (a.add) {
+            float y[8];
+            unpack_bias8(*reinterpret_cast<const uint4*>(a.add + orow * a.N + (size_t)i * 8), y);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] += y[q];
+        }
         uint4 o;
-        o.x = pack_bf16x2(gw * v[0], gw * v[1]); o.y = pack_bf16x2(gw * v[2], gw * v[3]);
-        o.z = pack_bf16x2(gw * v[4], gw * v[5]); o.w = pack_bf16x2(gw * v[6], gw * v[7]);
+        o.x = pack_bf16x2(v[0], v[1]); o.y = pack_bf16x2(v[2], v[3]);
+        o.z = pack_bf16x2(v[4], v[5]); o.w = pack_bf16x2(v[6], v[7]);
         *reinterpret_cast<uint4*>(a.out + orow * a.N + (size_t)i * 8) = o;
     }
 }

@@ -196,7 +196,8 @@ __global__ __launch_bounds__(kRWaves * 64) void rows_kernel(const WsGemmArgs a0,
         for (int t = blockIdx.x; t < a.T; t += gridDim.x) {
             if (t != (int)blockIdx.x ? a.zero_slot_idx[t] < 0 : zero_first) {
                 uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
-                for (int i = tid; i < a.N / 8; i += kRWaves * 64) o[i] = make_uint4(0, 0, 0, 0);
+                for (int i = tid; i < a.N / 8; i += kRWaves * 64)
+                    o[i] = a.add ? reinterpret_cast<const uint4*>(a.add + (size_t)t * a.N)[i] : make_uint4(0, 0, 0, 0);
             }
         }
     }

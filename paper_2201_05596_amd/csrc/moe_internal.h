@@ -227,6 +227,7 @@ struct WsGemmArgs {
     const int32_t* zero_slot_idx;  // [T*top_k]: rows t with zero_slot_idx[t*top_k] < 0 are zero-filled (top_k == 1)
     int32_t T;
     // EPI_SCATTER / EPI_COMBINE
+    const uint16_t* add;           // [T, N] rows that the results are added to, or nullptr
     const float* gate_w;           // [T, top_k]
     int32_t top_k;
     const uint16_t* ye;            // [E, C, N]
@@ -282,6 +283,7 @@ struct SplitKReduceArgs {
     const uint16_t* bias;      // [G, N] or nullptr
     uint16_t* out;
     const int32_t* scatter_map;
+    const uint16_t* add;       // with scatter_map: [T, N] rows that the results are added to, or nullptr
     const float* gate_w;
     int32_t top_k;
     const int32_t* zero_slot_idx;
@@ -290,7 +292,15 @@ struct SplitKReduceArgs {
 int launch_splitk_reduce(const SplitKReduceArgs& a, hipStream_t s);
 
 // ---- the non-expert half of a decoder block, one decode step (block.hip) --------------------------------------
-int launch_add_layernorm(const uint16_t* x, const uint16_t* r /* or nullptr */, const float* gamma, const float* beta,
+struct AddedRows {             // what a LayerNorm adds to its rows first: nothing, [T, d] rows, or a product's split-K partial sums
+    const uint16_t* rows;
+    const float* partial;      // [ksplit, T, d]: only where add_layernorm_sums(d)
+    const uint16_t* bias;      // of that product, or nullptr
+    int32_t ksplit;
+};
+constexpr int kLinearMaxSplit = 8;
+bool add_layernorm_sums(int d);
+int launch_add_layernorm(const uint16_t* x, const AddedRows& r, const float* gamma, const float* beta,
                          uint16_t* sum_out /* x + r, or nullptr */, uint16_t* y, int T, int d, float eps, hipStream_t s);
 int launch_add_rows(const uint16_t* a, const uint16_t* b, uint16_t* out, long long n, hipStream_t s);
 bool attn_supported(int d, int H);
