@@ -166,6 +166,16 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
 // do the bf16 matrix cores compute the gate logits?
 bool gate_on_bf16(const moe_shape_t* s) { return s->dtype == MOE_BF16 && gate_bf16_supported(s->d_model, s->E); }
 
+// Does the dense branch's second product share the launch of the experts' in the few-weights kernel?  Wherever both take that
+// kernel: alone the dense one is a chain through all of K on few work-groups (16 tokens, 2048/8192 16 us, 96 tokens 42, for 34 MB of
+// weights).  Its sums stay unrounded in 32 bits for the combine, which then is a launch of its own (4.7).  Layers, us, apart /
+// shared: one token, 1024/4096, 64 experts 26.9 / 23.8; 16 tokens, 2048/8192, 64 experts 174.2 / 169.6, two tokens, plain weights
+// 101.8 / 77.7; 40 tokens, 1024/4096, 128 experts 126 / 113; 96, top-2 of 32, skewed 196 / 169; 150 of 128 270 / 258.
+constexpr int kSharedTokens = 256;             // the few-weights kernel takes no second products of more rows
+bool dense2_shared(const moe_shape_t* s, const FfnPlan& p) {
+    return s->residual && s->T <= kSharedTokens && p.mfma && p.nf2 && p.ksplit2 == 1 && rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS);
+}
+
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
     size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, h, ye, hd, dense, partial, total;
@@ -194,7 +204,9 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.h = take(E * C * f * es);
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
-    L.dense = take(s->residual && plan.mfma ? T * d * es : 0);   // the dense branch's output where it is not combined in place
+    // the dense branch's output where it is not combined in place: rounded, or sums in 32 bits (dense2_shared, with either layout
+    // of the weights: no size depends on that)
+    L.dense = take(s->residual && plan.mfma ? T * d * (T <= kSharedTokens ? 4 : es) : 0);
     L.partial = take(plan.ksplit_room > 1 ? (size_t)plan.ksplit_room * E * C * d * 4 : 0);
     L.total = off;
     return L;
@@ -444,6 +456,20 @@ bool dense1_shared(const moe_shape_t* s, const FfnPlan& p) {
     return s->residual && p.nf1 && s->T <= 16 && rows_pick_dense(s->T, s->d_ffn, s->flags & MOE_FLAG_PACKED_WEIGHTS);
 }
 
+// First product of the dense branch: hd = gelu_tanh(x Wd1 + bd1)
+int run_dense_first(const moe_shape_t* s, const void* x, const void* Wd1, const void* bd1, void* hd, hipStream_t st) {
+    int MT, NW;
+    const WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
+    const int nf = rows_pick_dense(s->T, s->d_ffn, a.packed);
+    wsgemm_pick_tile(s->T, 1, s->d_ffn, &MT, &NW);
+    prof_pre(ST_DENSE1, st);
+    const int rc = nf               ? launch_rows(a, nullptr, EPI_GELU, nf, st)
+                   : dense_tiled(s) ? launch_tgemm(a, EPI_GELU, st)
+                                    : launch_wsgemm(a, EPI_GELU, MT, NW, 2, st);
+    prof_mark(ST_DENSE1, st);
+    return rc;
+}
+
 // Dense branch of Residual-MoE on the MFMA kernels, with the combine fused into its second GEMM:
 // out[t, :] = gelu_tanh(x[t] Wd1 + bd1) Wd2 + bd2 + sum_j keep_j g_j ye[e_j, slot_j, :] (+ add[t, :]).
 // first_done: hd is there already (the first product shared a launch with the experts').
@@ -451,27 +477,20 @@ int run_dense_branch(const moe_shape_t* s, const void* x, const void* Wd1, const
                      const void* bd2, void* hd, bool first_done, const void* ye, const int32_t* expert_idx,
                      const int32_t* slot_idx, const float* gate_w, const uint16_t* add, void* out, hipStream_t st) {
     int MT, NW, rc = MOE_OK;
-    WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
-    const bool tiled = dense_tiled(s);
     if (!first_done) {
-        const int nf = rows_pick_dense(s->T, s->d_ffn, a.packed);
-        wsgemm_pick_tile(s->T, 1, s->d_ffn, &MT, &NW);
-        prof_pre(ST_DENSE1, st);
-        rc = nf      ? launch_rows(a, nullptr, EPI_GELU, nf, st)
-             : tiled ? launch_tgemm(a, EPI_GELU, st)
-                     : launch_wsgemm(a, EPI_GELU, MT, NW, 2, st);
-        prof_mark(ST_DENSE1, st);
+        rc = run_dense_first(s, x, Wd1, bd1, hd, st);
         if (rc != MOE_OK) return rc;
     }
+    WsGemmArgs a = dense_gemm1_args(s, x, Wd1, bd1, hd);
     a.A = u16(hd); a.B = u16(Wd2); a.bias = u16(bd2); a.K = s->d_ffn; a.N = s->d_model; a.out = u16(out);
     a.ye = u16(ye); a.expert_idx = expert_idx; a.slot_idx = slot_idx; a.gate_w = gate_w; a.top_k = s->top_k;
     a.C = s->capacity; a.add = add;
     const int nf = rows_pick_dense(s->T, s->d_model, a.packed);
     wsgemm_pick_tile(s->T, 1, s->d_model, &MT, &NW);
     prof_pre(ST_DENSE2, st);
-    rc = nf      ? launch_rows(a, nullptr, EPI_COMBINE, nf, st)
-         : tiled ? launch_tgemm(a, EPI_COMBINE, st)
-                 : launch_wsgemm(a, EPI_COMBINE, MT, NW, 2, st);
+    rc = nf               ? launch_rows(a, nullptr, EPI_COMBINE, nf, st)
+         : dense_tiled(s) ? launch_tgemm(a, EPI_COMBINE, st)
+                          : launch_wsgemm(a, EPI_COMBINE, MT, NW, 2, st);
     prof_mark(ST_DENSE2, st);
     return rc;
 }
@@ -798,6 +817,24 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
     if (k == 1 && !shape->residual)
         return run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, true, slot_token, slot_idx, gate_w, add, out,
                                 at<float>(ws, L.partial), st);
+    if (dense2_shared(shape, plan)) {
+        if (!dense1_done) {
+            rc = run_dense_first(shape, x, Wd1, bd1, at<void>(ws, L.hd), st);
+            if (rc != MOE_OK) return rc;
+        }
+        WsGemmArgs d2 = second_half(dense_gemm1_args(shape, nullptr, nullptr, nullptr, nullptr), at<void>(ws, L.hd), Wd2, bd2, nullptr);
+        d2.partial = at<float>(ws, L.dense);
+        const WsGemmArgs e2 = second_half(expert_gemm1_args(shape, plan, nullptr, nullptr, rows, order, nullptr, nullptr, nullptr),
+                                          at<void>(ws, L.h), W2, b2, at<void>(ws, L.ye));
+        prof_pre(ST_GEMM2, st);
+        rc = launch_rows(d2, &e2, EPI_STORE, plan.nf2, st);      // the dense branch's work-groups, with more rows, first
+        prof_mark(ST_GEMM2, st);
+        if (rc != MOE_OK) return rc;
+        prof_pre(ST_COMBINE, st);
+        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, at<float>(ws, L.dense));
+        prof_mark(ST_COMBINE, st);
+        return rc;
+    }
     rc = run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, false, nullptr, nullptr, nullptr, nullptr,
                           at<void>(ws, L.ye), at<float>(ws, L.partial), st);
     if (rc != MOE_OK) return rc;
@@ -858,12 +895,13 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
     kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_code(e2, nullptr, shape->top_k == 1 && !shape->residual ? EPI_SCATTER : EPI_STORE) : 100 * p.ksplit2 + p.MT;
     if (!shape->residual) return MOE_OK;
     shared[0] = dense1_shared(shape, p);
+    shared[1] = dense2_shared(shape, p);
     for (int i = 0; i < 2; ++i) {
         const WsGemmArgs& a = i ? d2 : d1;
         const int nf = rows_pick_dense(shape->T, a.N, a.packed);
         int MT, NW;
         wsgemm_pick_tile(shape->T, 1, a.N, &MT, &NW);
-        kernels[2 + i] = i == 0 && shared[0] ? p.nf1 : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
+        kernels[2 + i] = shared[i] ? (i ? p.nf2 : p.nf1) : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
     }
     return MOE_OK;
 }

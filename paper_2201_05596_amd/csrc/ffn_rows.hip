@@ -183,7 +183,13 @@ __global__ __launch_bounds__(kRWaves * 64) void rows_kernel(const WsGemmArgs a0,
                     for (int f = 0; f < NF; ++f) v[f] += part[s][fr][fc * NF + f];
 #pragma unroll
                 for (int f = 0; f < NF; ++f) v[f] += bias[f];
-                finish_row<EPI, NF>(a, g, m0 + rl, 0, n_fin, v, tok[p], gw[p]);
+                if (EPI == EPI_STORE && a.partial) {             // the dense branch's sums, unrounded, for the combine
+                    float* o = a.partial + (size_t)(m0 + rl) * a.N + n_fin;
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) o[f] = v[f];
+                } else {
+                    finish_row<EPI, NF>(a, g, m0 + rl, 0, n_fin, v, tok[p], gw[p]);
+                }
             }
         }
     };

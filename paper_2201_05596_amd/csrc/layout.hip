@@ -74,11 +74,12 @@ __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
     f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
 }
 
-template <int K>
+// DENSE: sums begin with the dense branch's, unrounded, and addend comes last
+template <int K, bool DENSE>
 __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restrict__ ye, const int32_t* __restrict__ expert_idx,
                                                            const int32_t* __restrict__ slot_idx, const float* __restrict__ gate_w,
-                                                           const uint4* __restrict__ addend, uint4* __restrict__ out, int T,
-                                                           int C, int row_vecs) {
+                                                           const float4* __restrict__ dense, const uint4* __restrict__ addend,
+                                                           uint4* __restrict__ out, int T, int C, int row_vecs) {
     const int lane = threadIdx.x % kWave;
     const int t = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
     if (t >= T) return;
@@ -93,7 +94,10 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
     }
     for (int i = lane; i < row_vecs; i += kWave) {
         float acc[8];
-        if (addend) {
+        if constexpr (DENSE) {
+            *reinterpret_cast<float4*>(acc) = dense[((size_t)t * row_vecs + i) * 2];
+            *reinterpret_cast<float4*>(acc + 4) = dense[((size_t)t * row_vecs + i) * 2 + 1];
+        } else if (addend) {
             unpack8(addend[(size_t)t * row_vecs + i], acc);
         } else {
 #pragma unroll
@@ -108,6 +112,12 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
                 for (int q = 0; q < 8; ++q) acc[q] = fmaf(g[j], v[q], acc[q]);
             }
         }
+        if (DENSE && addend) {
+            float v[8];
+            unpack8(addend[(size_t)t * row_vecs + i], v);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) acc[q] += v[q];
+        }
         uint4 o;
         o.x = pack_bf16x2(acc[0], acc[1]);
         o.y = pack_bf16x2(acc[2], acc[3]);
@@ -118,7 +128,8 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
 }
 
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx, const float* gate_w,
-                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s) {
+                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s, const float* dense) {
+    if (dense && dtype != MOE_BF16) return MOE_ERR_INVALID_ARG;
     const int rpb = 256 / kWave;
     const dim3 grid((T + rpb - 1) / rpb), block(256);
     if (dtype == MOE_F32) {
@@ -131,12 +142,17 @@ int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const i
                                slot_idx, gate_w, static_cast<const float4*>(addend), static_cast<float4*>(out), T, C, rv);
     } else {
         const int rv = d / 8;
-        if (k == 1)
-            hipLaunchKernelGGL((combine_bf16_kernel<1>), grid, block, 0, s, static_cast<const uint4*>(ye), expert_idx,
-                               slot_idx, gate_w, static_cast<const uint4*>(addend), static_cast<uint4*>(out), T, C, rv);
-        else
-            hipLaunchKernelGGL((combine_bf16_kernel<2>), grid, block, 0, s, static_cast<const uint4*>(ye), expert_idx,
-                               slot_idx, gate_w, static_cast<const uint4*>(addend), static_cast<uint4*>(out), T, C, rv);
+#define MOE_COMBINE(K, DENSE)                                                                                                        \
+    hipLaunchKernelGGL((combine_bf16_kernel<K, DENSE>), grid, block, 0, s, static_cast<const uint4*>(ye), expert_idx, slot_idx, gate_w, \
+                       reinterpret_cast<const float4*>(dense), static_cast<const uint4*>(addend), static_cast<uint4*>(out), T, C, rv)
+        if (k == 1) {
+            if (dense) MOE_COMBINE(1, true);
+            else MOE_COMBINE(1, false);
+        } else {
+            if (dense) MOE_COMBINE(2, true);
+            else MOE_COMBINE(2, false);
+        }
+#undef MOE_COMBINE
     }
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }

@@ -150,7 +150,8 @@ int launch_dispatch(const void* x, int dtype, const int32_t* slot_token, const i
 
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx,
                    const float* gate_w, const void* addend, void* out,
-                   int T, int k, int C, int d, hipStream_t s);
+                   int T, int k, int C, int d, hipStream_t s,
+                   const float* dense = nullptr /* bf16: [T, d] sums that come first */);
 
 // What a grouped GEMM does with a finished row.
 enum WsEpilogue {
