@@ -176,6 +176,22 @@ bool dense2_shared(const moe_shape_t* s, const FfnPlan& p) {
     return s->residual && s->T <= kSharedTokens && p.mfma && p.nf2 && p.ksplit2 == 1 && rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS);
 }
 
+// Where it does not: K split on the streaming kernel, whose sums the combine adds up (1: not that way).  For 33 to 192 tokens and a long K,
+// where the few-weights kernel would take the product, every work-group of it reading 64 rows through all of K: layers, us, that
+// kernel with the combine in it / split: 120 tokens, 2048/8192, top-2 of 64, skewed 225 / 215, 140 of 64, skewed 204 / 190;
+// 180 tokens, 1024/4096, top-2 of 64 226 / 219; plain weights, 50 tokens, 2048/8192, top-2 of 32 401 / 392; but 256 tokens, 1024/4096,
+// 137.8 / 138.7.
+constexpr int kSplitTokens = 192;
+int dense2_split(const moe_shape_t* s) {
+    if (s->T <= 32 || s->T > kSplitTokens || s->d_ffn < 4096 || !rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS)) return 1;
+    int MT, NW;
+    wsgemm_pick_tile(s->T, 1, s->d_model, &MT, &NW);
+    const long long waves = (long long)((s->d_model + 127) / 128) * ((s->T + MT - 1) / MT);
+    const int chunks = (s->d_ffn + wsgemm_chunk_k(MT) - 1) / wsgemm_chunk_k(MT);
+    const long long ks = (2048 + waves - 1) / waves < kLinearMaxSplit ? (2048 + waves - 1) / waves : kLinearMaxSplit;
+    return (int)(ks > chunks ? chunks : ks);
+}
+
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
     size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, h, ye, hd, dense, partial, total;
@@ -204,9 +220,9 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.h = take(E * C * f * es);
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
-    // the dense branch's output where it is not combined in place: rounded, or sums in 32 bits (dense2_shared, with either layout
-    // of the weights: no size depends on that)
-    L.dense = take(s->residual && plan.mfma ? T * d * (T <= kSharedTokens ? 4 : es) : 0);
+    // the dense branch's output where it is not combined in place: rounded, or sums in 32 bits (dense2_shared, dense2_split, with
+    // either layout of the weights: no size depends on that)
+    L.dense = take(s->residual && plan.mfma ? T * d * (T <= kSharedTokens ? (T > 32 && T <= kSplitTokens ? 4 * kLinearMaxSplit : 4) : es) : 0);
     L.partial = take(plan.ksplit_room > 1 ? (size_t)plan.ksplit_room * E * C * d * 4 : 0);
     L.total = off;
     return L;
@@ -831,13 +847,31 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
         prof_mark(ST_GEMM2, st);
         if (rc != MOE_OK) return rc;
         prof_pre(ST_COMBINE, st);
-        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, at<float>(ws, L.dense));
+        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, DenseSums{at<float>(ws, L.dense), 1, nullptr});
         prof_mark(ST_COMBINE, st);
         return rc;
     }
     rc = run_expert_gemm2(shape, plan, at<void>(ws, L.h), rows, order, W2, b2, false, nullptr, nullptr, nullptr, nullptr,
                           at<void>(ws, L.ye), at<float>(ws, L.partial), st);
     if (rc != MOE_OK) return rc;
+    if (shape->residual && dense2_split(shape) > 1) {
+        if (!dense1_done) {
+            rc = run_dense_first(shape, x, Wd1, bd1, at<void>(ws, L.hd), st);
+            if (rc != MOE_OK) return rc;
+        }
+        WsGemmArgs d2 = second_half(dense_gemm1_args(shape, nullptr, nullptr, nullptr, nullptr), at<void>(ws, L.hd), Wd2, nullptr, nullptr);
+        d2.ksplit = dense2_split(shape); d2.partial = at<float>(ws, L.dense); d2.partial_rows = T; d2.o_group_stride = T;
+        int MT, NW;
+        wsgemm_pick_tile(T, 1, d, &MT, &NW);
+        prof_pre(ST_DENSE2, st);
+        rc = launch_wsgemm(d2, EPI_PARTIAL, MT, NW, 2, st);
+        prof_mark(ST_DENSE2, st);
+        if (rc != MOE_OK) return rc;
+        prof_pre(ST_COMBINE, st);
+        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, DenseSums{d2.partial, d2.ksplit, u16(bd2)});
+        prof_mark(ST_COMBINE, st);
+        return rc;
+    }
     if (shape->residual)
         return run_dense_branch(shape, x, Wd1, bd1, Wd2, bd2, at<void>(ws, L.hd), dense1_done, at<void>(ws, L.ye),
                                 expert_idx, slot_idx, gate_w, add, out, st);
@@ -901,7 +935,8 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
         const int nf = rows_pick_dense(shape->T, a.N, a.packed);
         int MT, NW;
         wsgemm_pick_tile(shape->T, 1, a.N, &MT, &NW);
-        kernels[2 + i] = shared[i] ? (i ? p.nf2 : p.nf1) : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
+        const int ks = i ? dense2_split(shape) : 1;
+        kernels[2 + i] = shared[i] ? (i ? p.nf2 : p.nf1) : ks > 1 ? 100 * ks + MT : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
     }
     return MOE_OK;
 }

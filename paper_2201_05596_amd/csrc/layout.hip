@@ -74,11 +74,11 @@ __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
     f[6] = __uint_as_float(v.w << 16); f[7] = __uint_as_float(v.w & 0xffff0000u);
 }
 
-// DENSE: sums begin with the dense branch's, unrounded, and addend comes last
+// DENSE: sums begin with the dense branch's, unrounded (split-K sums are added up here), and addend comes last
 template <int K, bool DENSE>
 __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restrict__ ye, const int32_t* __restrict__ expert_idx,
                                                            const int32_t* __restrict__ slot_idx, const float* __restrict__ gate_w,
-                                                           const float4* __restrict__ dense, const uint4* __restrict__ addend,
+                                                           const DenseSums dense, const uint4* __restrict__ addend,
                                                            uint4* __restrict__ out, int T, int C, int row_vecs) {
     const int lane = threadIdx.x % kWave;
     const int t = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
@@ -95,8 +95,28 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
     for (int i = lane; i < row_vecs; i += kWave) {
         float acc[8];
         if constexpr (DENSE) {
-            *reinterpret_cast<float4*>(acc) = dense[((size_t)t * row_vecs + i) * 2];
-            *reinterpret_cast<float4*>(acc + 4) = dense[((size_t)t * row_vecs + i) * 2 + 1];
+            const float4* p = reinterpret_cast<const float4*>(dense.partial) + ((size_t)t * row_vecs + i) * 2;
+            float4 v[kLinearMaxSplit][2];
+#pragma unroll
+            for (int s = 0; s < kLinearMaxSplit; ++s)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    v[s][q] = s < dense.ksplit ? p[(size_t)s * T * row_vecs * 2 + q] : make_float4(0.f, 0.f, 0.f, 0.f);
+            const uint4 bias = dense.bias ? reinterpret_cast<const uint4*>(dense.bias)[i] : make_uint4(0, 0, 0, 0);
+            *reinterpret_cast<float4*>(acc) = v[0][0];
+            *reinterpret_cast<float4*>(acc + 4) = v[0][1];
+#pragma unroll
+            for (int s = 1; s < kLinearMaxSplit; ++s) {
+                if (s >= dense.ksplit) break;
+                acc[0] += v[s][0].x; acc[1] += v[s][0].y; acc[2] += v[s][0].z; acc[3] += v[s][0].w;
+                acc[4] += v[s][1].x; acc[5] += v[s][1].y; acc[6] += v[s][1].z; acc[7] += v[s][1].w;
+            }
+            if (dense.bias) {
+                float b[8];
+                unpack8(bias, b);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[q] += b[q];
+            }
         } else if (addend) {
             unpack8(addend[(size_t)t * row_vecs + i], acc);
         } else {
@@ -128,8 +148,8 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
 }
 
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx, const float* gate_w,
-                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s, const float* dense) {
-    if (dense && dtype != MOE_BF16) return MOE_ERR_INVALID_ARG;
+                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s, const DenseSums& dense) {
+    if (dense.partial && (dtype != MOE_BF16 || dense.ksplit < 1 || dense.ksplit > kLinearMaxSplit)) return MOE_ERR_INVALID_ARG;
     const int rpb = 256 / kWave;
     const dim3 grid((T + rpb - 1) / rpb), block(256);
     if (dtype == MOE_F32) {
@@ -144,12 +164,12 @@ int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const i
         const int rv = d / 8;
 #define MOE_COMBINE(K, DENSE)                                                                                                        \
     hipLaunchKernelGGL((combine_bf16_kernel<K, DENSE>), grid, block, 0, s, static_cast<const uint4*>(ye), expert_idx, slot_idx, gate_w, \
-                       reinterpret_cast<const float4*>(dense), static_cast<const uint4*>(addend), static_cast<uint4*>(out), T, C, rv)
+                       dense, static_cast<const uint4*>(addend), static_cast<uint4*>(out), T, C, rv)
         if (k == 1) {
-            if (dense) MOE_COMBINE(1, true);
+            if (dense.partial) MOE_COMBINE(1, true);
             else MOE_COMBINE(1, false);
         } else {
-            if (dense) MOE_COMBINE(2, true);
+            if (dense.partial) MOE_COMBINE(2, true);
             else MOE_COMBINE(2, false);
         }
 #undef MOE_COMBINE

@@ -148,10 +148,16 @@ int launch_expert_order(const int32_t* expert_rows, int E, int C, int32_t* order
 int launch_dispatch(const void* x, int dtype, const int32_t* slot_token, const int32_t* expert_rows,
                     void* xe, int E, int C, int d, hipStream_t s);
 
+constexpr int kLinearMaxSplit = 8;   // split-K factors whose sums another kernel adds up
+struct DenseSums {             // bf16: fp32 sums that come first in every row, or none
+    const float* partial;      // [ksplit, T, d], added up in order
+    int32_t ksplit;
+    const uint16_t* bias;      // added behind them, or nullptr
+};
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx,
                    const float* gate_w, const void* addend, void* out,
                    int T, int k, int C, int d, hipStream_t s,
-                   const float* dense = nullptr /* bf16: [T, d] sums that come first */);
+                   const DenseSums& dense = DenseSums{});
 
 // What a grouped GEMM does with a finished row.
 enum WsEpilogue {
@@ -299,7 +305,6 @@ struct AddedRows {             // what a LayerNorm adds to its rows first: nothi
     const uint16_t* bias;      // of that product, or nullptr
     int32_t ksplit;
 };
-constexpr int kLinearMaxSplit = 8;
 bool add_layernorm_sums(int d);
 int launch_add_layernorm(const uint16_t* x, const AddedRows& r, const float* gamma, const float* beta,
                          uint16_t* sum_out /* x + r, or nullptr */, uint16_t* y, int T, int d, float eps, hipStream_t s);
