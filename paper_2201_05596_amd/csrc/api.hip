@@ -527,6 +527,14 @@ bool residual_pairs(const moe_shape_t* s, const FfnPlan& p) {
                               second_half(dense_gemm1_args(s, nullptr, nullptr, nullptr, nullptr), nullptr, nullptr, nullptr, nullptr));
 }
 
+// Can the layer's last kernel add rows to its results?  All can but the tiled ones.
+bool layer_adds(const moe_shape_t* s, const FfnPlan& p) {
+    if (!p.mfma) return false;
+    if (!s->residual) return s->top_k == 2 || p.nf2 || !p.tiled;
+    if (residual_pairs(s, p)) return false;
+    return dense2_shared(s, p) || dense2_split(s) > 1 || rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS) || !dense_tiled(s);
+}
+
 // Residual-MoE with experts and dense branch both on the tiled kernel: the experts' and the dense branch's products of
 // each FFN half share one launch (same inner and outer sizes), so that the second half, with only d_model columns,
 // has more tiles and can use a larger one; the combine then is a kernel of its own on the two outputs.
@@ -1060,9 +1068,8 @@ int moe_decode_block_forward(const moe_shape_t* shape, const moe_block_shape_t* 
     const AddedRows projected = split > 1 ? AddedRows{nullptr, lin_partial, u16(w->bo), split} : AddedRows{proj, nullptr, nullptr, 0};
     rc = launch_add_layernorm(u16(x), projected, w->ln2_gamma, w->ln2_beta, x1, moe_in, T, d, eps, st);
     if (rc != MOE_OK) return rc;
-    // out = x1 + MoE: in the layer's last kernel, or (experts and dense branch in one launch) behind it
-    FfnPlan plan = plan_ffn(shape);
-    if (!plan.mfma || (shape->residual && residual_pairs(shape, plan))) {
+    // out = x1 + MoE: in the layer's last kernel or behind it
+    if (!layer_adds(shape, plan_ffn(shape))) {
         rc = layer_forward_checked(shape, moe_in, w->Wg, w->bg, w->W1, w->b1, w->W2, w->b2, w->Wd1, w->bd1, w->Wd2, w->bd2,
                                    moe_out, logits_out, nullptr, nullptr, nullptr, nullptr, nullptr,
                                    at<void>(ws, L.moe_ws), ws_layout(shape).total, nullptr, stream);

@@ -106,12 +106,12 @@ inline long long tile_grid_blocks(const WsGemmArgs& a, int n_tiles, int inner_n)
 // Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them (or copy what is added to), spread over the waves of all
 // work-groups (a dropped token has no other writer).  A wave looks at 16 tokens at once: one token after the other, a
 // work-group of a small grid waited for up to 16 memory round trips before its first tile (8192 tokens, 512 work-groups).
-__device__ __forceinline__ void zero_dropped_rows(const WsGemmArgs& a, int tid, int nthreads) {
+template <bool ADD = false> __device__ __forceinline__ void zero_dropped_rows(const WsGemmArgs& a, int tid, int nthreads) {
     if (!a.zero_slot_idx) return;
     for_dropped_tokens(a.zero_slot_idx, 1, a.T, tid, nthreads, [&](int t, int lane) {
         uint4* o = reinterpret_cast<uint4*>(a.out + (size_t)t * a.N);
         for (int i = lane; i < a.N / 8; i += kWave)
-            o[i] = a.add ? reinterpret_cast<const uint4*>(a.add + (size_t)t * a.N)[i] : make_uint4(0, 0, 0, 0);
+            o[i] = ADD && a.add ? reinterpret_cast<const uint4*>(a.add + (size_t)t * a.N)[i] : make_uint4(0, 0, 0, 0);
     });
 }
 
@@ -170,8 +170,9 @@ __device__ __forceinline__ void scatter_lookup(const WsGemmArgs& a, int g, int r
 }
 
 // Finishes NC (8, 4, 2 or 1) consecutive columns n_lane.. of row `row` (index inside group g): v = acc + bias on entry.
-// EPI_SCATTER: (t, gw) = scatter_lookup of the row, fetched by the caller.
-template <int EPI, int NC = 8>
+// EPI_SCATTER: (t, gw) = scatter_lookup of the row, fetched by the caller.  ADD: a.add is looked at (the kernels of a decode step; in
+// the tiled ones its test alone cost 16384-wide products on plain weights 0.6 %).
+template <int EPI, int NC = 8, bool ADD = false>
 __device__ __forceinline__ void finish_row(const WsGemmArgs& a, int g, int row, int ks, int n_lane, float (&v)[NC],
                                            int t = 0, float gw = 1.f) {
     typedef typename Bf16Vec<NC>::type Vec;
@@ -205,7 +206,7 @@ __device__ __forceinline__ void finish_row(const WsGemmArgs& a, int g, int row, 
             for (int i = 0; i < NC; ++i) v[i] = fmaf(gw, bf16_of(y, i), v[i]);
         }
     }
-    if constexpr (EPI == EPI_SCATTER || EPI == EPI_COMBINE) {
+    if constexpr (ADD && (EPI == EPI_SCATTER || EPI == EPI_COMBINE)) {
         if (a.add) {
             const Vec y = *reinterpret_cast<const Vec*>(a.add + orow * a.N + n_lane);
 #pragma unroll

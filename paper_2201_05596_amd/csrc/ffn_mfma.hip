@@ -274,7 +274,7 @@ __device__ __forceinline__ void ws_tile(const WsGemmArgs& a, const WsGeo& geo, c
                 float v[8];
 #pragma unroll
                 for (int i = 0; i < 8; ++i) v[i] = acc[ms][i][r] + bias[i];
-                finish_row<EPI>(a, g, m0 + rl, ks, n_lane, v, EPI == EPI_SCATTER ? tok_sh[rl] : 0,
+                finish_row<EPI, 8, true>(a, g, m0 + rl, ks, n_lane, v, EPI == EPI_SCATTER ? tok_sh[rl] : 0,
                                 EPI == EPI_SCATTER ? gw_sh[rl] : 1.f);
             }
         }
@@ -290,7 +290,7 @@ __global__ __launch_bounds__(NW * 64) void wsgemm_kernel(const WsGemmArgs a, con
     __shared__ float gw_sh[MT];
 
     const WsGeo geo = ws_geo<MT, NW>(a);
-    if (EPI == EPI_SCATTER) zero_dropped_rows(a, threadIdx.x, TC::NT);
+    if (EPI == EPI_SCATTER) zero_dropped_rows<true>(a, threadIdx.x, TC::NT);
 
     // The grid holds as many work-groups as fit on the chip at once; work-group b takes the virtual
     // blocks b, b + gridDim.x, ... that have work (the XCD of a virtual block is that of b: the grid

@@ -188,7 +188,7 @@ __global__ __launch_bounds__(kRWaves * 64) void rows_kernel(const WsGemmArgs a0,
 #pragma unroll
                     for (int f = 0; f < NF; ++f) o[f] = v[f];
                 } else {
-                    finish_row<EPI, NF>(a, g, m0 + rl, 0, n_fin, v, tok[p], gw[p]);
+                    finish_row<EPI, NF, true>(a, g, m0 + rl, 0, n_fin, v, tok[p], gw[p]);
                 }
             }
         }

@@ -234,7 +234,7 @@ struct WsGemmArgs {
     const int32_t* zero_slot_idx;  // [T*top_k]: rows t with zero_slot_idx[t*top_k] < 0 are zero-filled (top_k == 1)
     int32_t T;
     // EPI_SCATTER / EPI_COMBINE
-    const uint16_t* add;           // [T, N] rows that the results are added to, or nullptr
+    const uint16_t* add;           // streaming and few-weights kernels: [T, N] rows that the results are added to, or nullptr
     const float* gate_w;           // [T, top_k]
     int32_t top_k;
     const uint16_t* ye;            // [E, C, N]
