@@ -905,7 +905,8 @@ int moe_layer_forward(const moe_shape_t* shape, const void* x, const float* Wg, 
 // part of the interface (moe.h does not declare it).  kernels: expert GEMM-1, expert GEMM-2, dense GEMM-1, dense GEMM-2, each
 // 0 = none; fp32: F32Kernel; bf16: 1..4 = few-weights kernel with that many 16-column fragments, 100 S + rows = streaming kernel with tiles of that
 // many rows and K split S ways, beyond that a tiled kernel (tgemm_code).
-// shared: do the experts' and the dense product of the first / second half run in one launch?
+// shared: do the experts' and the dense product of the first / second half run in one launch, the second one's dense results rounded
+// for the combine?  Dense GEMM-2 < 0: in the experts' launch of the few-weights kernel, its sums unrounded.
 int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2]) {
     const int rc = check_shape(shape);
     if (rc != MOE_OK) return rc;
@@ -937,14 +938,14 @@ int moe_test_plan(const moe_shape_t* shape, int32_t kernels[4], int32_t shared[2
     kernels[1] = p.nf2 ? p.nf2 : p.tiled ? tgemm_code(e2, nullptr, shape->top_k == 1 && !shape->residual ? EPI_SCATTER : EPI_STORE) : 100 * p.ksplit2 + p.MT;
     if (!shape->residual) return MOE_OK;
     shared[0] = dense1_shared(shape, p);
-    shared[1] = dense2_shared(shape, p);
+    const bool sums = dense2_shared(shape, p);
     for (int i = 0; i < 2; ++i) {
         const WsGemmArgs& a = i ? d2 : d1;
         const int nf = rows_pick_dense(shape->T, a.N, a.packed);
         int MT, NW;
         wsgemm_pick_tile(shape->T, 1, a.N, &MT, &NW);
         const int ks = i ? dense2_split(shape) : 1;
-        kernels[2 + i] = shared[i] ? (i ? p.nf2 : p.nf1) : ks > 1 ? 100 * ks + MT : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
+        kernels[2 + i] = i && sums ? -p.nf2 : shared[i] ? p.nf1 : ks > 1 ? 100 * ks + MT : nf ? nf : dense_tiled(shape) ? tgemm_code(a, nullptr, i ? EPI_COMBINE : EPI_GELU) : 100 + MT;
     }
     return MOE_OK;
 }

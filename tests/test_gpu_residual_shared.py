@@ -18,6 +18,6 @@ CASES = [(1, 128, 256, 2, 1, 1, True, True), (2, 256, 512, 8, 2, 1, True, True),
 @pytest.mark.parametrize("T,d,f,E,k,C,plain,packed", CASES)
 def test_shared_second_products(T, d, f, E, k, C, plain, packed):
     print(f"case T={T} d={d} f={f} E={E} k={k} C={C}", flush=True)
-    assert [bool(plan(T, d, f, E, k, C, True, p)[1][1]) for p in (False, True)] == [plain, packed]
+    assert [plan(T, d, f, E, k, C, True, p)[0][3] < 0 for p in (False, True)] == [plain, packed]
     cfg = CONFIGS["c3a"].scaled(name="shared", T=T, d_model=d, d_ffn=f, E=E, top_k=k, residual=True, seed=13)
     U.check_layer(make_inputs(cfg, "cuda", bias_std=0.05), capacity=C)
