@@ -192,6 +192,17 @@ int dense2_split(const moe_shape_t* s) {
     return (int)(ks > chunks ? chunks : ks);
 }
 
+// The waves' tiles of an expert GEMM-2 whose K is split on the streaming kernel: as many as two of its work-groups of two waves for
+// most compute units.  The factor in the plan is for few experts with rows (2048 tiles, eight ways at most, of those that the
+// tokens can reach at most); where all have some, it wrote and read more partial sums than the product gains.  Layers, us, the
+// plan's factor / at least 600 tiles / at least 400, even routing: 1000/4000, plain, 40 experts x 64 rows 237 / 212 / 212; 32 x 20
+// 123 / 121 / 112; 1024/4096, packed, 32 x 60 142 / 133 / 124; plain, 64 x 30 213 / 204 / 195; 4096/16384, 16 x 30 741 / 685 / 662; 16
+// tokens of 64 experts 86 / 90 / 84.
+// Experts of very different sizes (skewed routing) keep the plan's factor: with at least 400 423 tokens, 4096/16384, 16 experts beside a
+// dense branch took 885 -> 899, with at least 300 100 tokens, 1000/4000, top-2 of 32 84 -> 87.  The host, which knows no routing,
+// cannot choose: its own factor for 400 tiles took skewed 40 x 48 79 -> 87, 40 x 60 74 -> 93.
+constexpr int kSplitTiles = 400;
+
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
     size_t logits, wg_frags, hist, flags, expert_idx, slot_idx, gate_w, rows, order, slot_token, h, ye, hd, dense, partial, total;
@@ -449,12 +460,13 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     }
     a.partial = partial;
     a.partial_rows = (long long)s->E * s->capacity;
+    a.split_tiles = order && s->capacity <= p.MT ? kSplitTiles : 0;       // one row tile per expert
     int rc = launch_wsgemm(a, EPI_PARTIAL, p.MT, p.NW2, p.NBUF, st);
     prof_mark(ST_GEMM2, st);
     if (rc != MOE_OK) return rc;
     SplitKReduceArgs r{};
     r.partial = partial; r.ksplit = p.ksplit2; r.G = s->E; r.N = s->d_model; r.group_stride = s->capacity;
-    r.rows = rows; r.max_rows = s->capacity; r.bias = u16(b2); r.out = u16(dst);
+    r.rows = rows; r.max_rows = s->capacity; r.bias = u16(b2); r.out = u16(dst); r.order = order; r.split_tiles = a.split_tiles;
     r.scatter_map = scatter ? slot_token : nullptr; r.gate_w = gate_w; r.top_k = s->top_k; r.add = add;
     r.zero_slot_idx = scatter ? slot_idx : nullptr; r.T = s->T;
     prof_pre(ST_REDUCE, st);

@@ -77,13 +77,13 @@ __device__ __forceinline__ TileId tile_of_block(const WsGemmArgs& a, int n_tiles
 // still enters exactly one L2 (its row tiles run back to back there); only the groups' activation rows are read by
 // all eight.  Because the launch order alternates busy and light groups, the CUs of an XCD run matrix-bound and
 // weight-streaming tiles at the same time, instead of one phase after the other.
-// Which mapping applies is decided on the device, by the flag behind the launch order (only the device knows the row
+// Which mapping applies is decided on the device, by the flag (bit 0) behind the launch order (only the device knows the row
 // counts); the host sizes the grid for either.
 __host__ __device__ __forceinline__ bool tile_spread_possible(const WsGemmArgs& a, int n_tiles) {
     return a.order != nullptr && a.spread != 2 && a.ksplit == 1 && a.G >= kXcd && n_tiles % kXcd == 0;
 }
 __device__ __forceinline__ bool tile_spread(const WsGemmArgs& a, int n_tiles) {
-    return tile_spread_possible(a, n_tiles) && (a.spread == 1 || a.order[a.G] != 0);
+    return tile_spread_possible(a, n_tiles) && (a.spread == 1 || (a.order[a.G] & 1));
 }
 __device__ __forceinline__ TileId tile_of_block_spread(const WsGemmArgs& a, int n_tiles, int inner_n, int block) {
     TileId t;

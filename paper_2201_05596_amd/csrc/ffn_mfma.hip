@@ -52,6 +52,15 @@ template <int MT, int NW> struct WsTile {
     static_assert(PIECES % NT == 0 && SFC >= 1, "tile configuration");
 };
 
+// Parts that K is split into: as many as fill the chip with the tiles of the groups that have rows.  Only the device knows those
+// (behind the launch order); `most` is what the workspace has room for, and what groups of very different sizes take: the XCD of
+// the busy ones ends last.  The product and the kernel that adds up must agree.
+__device__ __forceinline__ int live_split(const int32_t* order, int split_tiles, int G, int N, int most) {
+    if (!split_tiles || (order[G] & 1)) return most;
+    const int waves = (order[G] >> 1) * ((N + kWaveCols - 1) / kWaveCols);
+    return max(1, min(most, (split_tiles + waves - 1) / max(1, waves)));
+}
+
 // Tile counts of one GEMM (uniform over the grid)
 struct WsGeo {
     int n_tiles, m_tiles, inner_n, chunks_total, chunks_per;
@@ -60,9 +69,10 @@ template <int MT, int NW> __device__ __forceinline__ WsGeo ws_geo(const WsGemmAr
     WsGeo g;
     g.n_tiles = (a.N + NW * kWaveCols - 1) / (NW * kWaveCols);
     g.m_tiles = (a.max_rows + MT - 1) / MT;
-    g.inner_n = g.m_tiles * a.ksplit;
+    const int ksplit = live_split(a.order, a.split_tiles, a.G, a.N, a.ksplit);
+    g.inner_n = g.m_tiles * ksplit;
     g.chunks_total = (a.K + WsTile<MT, NW>::KC - 1) / WsTile<MT, NW>::KC;
-    g.chunks_per = (g.chunks_total + a.ksplit - 1) / a.ksplit;     // whole chunks per k-split
+    g.chunks_per = (g.chunks_total + ksplit - 1) / ksplit;     // whole chunks per k-split
     return g;
 }
 
@@ -282,7 +292,7 @@ __device__ __forceinline__ void ws_tile(const WsGemmArgs& a, const WsGeo& geo, c
 }
 
 template <int MT, int NW, int EPI, int NBUF, bool PACKED>
-__global__ __launch_bounds__(NW * 64) void wsgemm_kernel(const WsGemmArgs a, const int total_blocks) {
+__global__ __launch_bounds__(NW * 64) void wsgemm_kernel(const WsGemmArgs a, const int most_blocks) {
     typedef WsTile<MT, NW> TC;
     __shared__ __attribute__((aligned(16))) char lds[TC::LDS_A];
     __shared__ long long arow_sh[MT];
@@ -290,6 +300,7 @@ __global__ __launch_bounds__(NW * 64) void wsgemm_kernel(const WsGemmArgs a, con
     __shared__ float gw_sh[MT];
 
     const WsGeo geo = ws_geo<MT, NW>(a);
+    const int total_blocks = EPI == EPI_PARTIAL ? most_blocks / (geo.m_tiles * a.ksplit) * geo.inner_n : most_blocks;
     if (EPI == EPI_SCATTER) zero_dropped_rows<true>(a, threadIdx.x, TC::NT);
 
     // The grid holds as many work-groups as fit on the chip at once; work-group b takes the virtual
@@ -324,7 +335,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitKReduceAr
         }
     }
     // one wave per (row, 512-column piece): few rows (a decode step) still spread over the chip
-    const int pieces = (a.N / 8 + 63) / 64;
+    const int pieces = (a.N / 8 + 63) / 64, ksplit = live_split(a.order, a.split_tiles, a.G, a.N, a.ksplit);
     for (long long item = wave; item < total_rows * pieces; item += nwaves) {
         const long long row = item / pieces;
         const int i = (int)(item % pieces) * 64 + lane;
@@ -343,7 +354,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitKReduceAr
         const float* p0 = a.partial + (size_t)row * a.N + (size_t)i * 8;
         const size_t sstride = (size_t)total_rows * a.N;
         int s = 0;
-        for (; s + 4 <= a.ksplit; s += 4) {                     // four splits' loads in flight, summed in split order
+        for (; s + 4 <= ksplit; s += 4) {                       // four splits' loads in flight, summed in split order
             float4 x0[4], x1[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -357,7 +368,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const SplitKReduceAr
                 v[4] += x1[u].x; v[5] += x1[u].y; v[6] += x1[u].z; v[7] += x1[u].w;
             }
         }
-        for (; s < a.ksplit; ++s) {
+        for (; s < ksplit; ++s) {
             const float* p = p0 + (size_t)s * sstride;
             const float4 x0 = *reinterpret_cast<const float4*>(p), x1 = *reinterpret_cast<const float4*>(p + 4);
             v[0] += x0.x; v[1] += x0.y; v[2] += x0.z; v[3] += x0.w;

@@ -215,7 +215,7 @@ struct WsGemmArgs {
     int32_t packed;            // B is [G, ceil(K/32), ceil(N/128), 8, 64, 8] as written by launch_pack_weights
     const uint16_t* bias;      // [G, N] or nullptr
     const int32_t* rows;       // [G] device row counts or nullptr -> fixed_rows
-    const int32_t* order;      // [G + 1] groups in launch order (busiest first), then the tile-dealing flag; or nullptr -> identity
+    const int32_t* order;      // [G + 1] groups in launch order (busiest first), then 2 * (groups that have rows) + the tile-dealing flag; or nullptr -> identity
     const int32_t* row_map;    // [G, map_stride]: A-row of (g, r), or nullptr -> g*a_group_stride + r
     int32_t fixed_rows, max_rows, map_stride;
     int32_t expect_rows;       // tiled kernel: rows of a group if the tokens fall evenly on them; 0: max_rows
@@ -225,6 +225,7 @@ struct WsGemmArgs {
     uint16_t* out;             // leading dimension N
     long long o_group_stride;
     int32_t ksplit;            // >= 1; > 1 only with EPI_PARTIAL
+    int32_t split_tiles;       // with `order`: so many waves' tiles are enough, ksplit is the most (live_split); 0: always ksplit
     int32_t spread;            // tiled kernel, tile dealing: 0 = as order[G] says, 1 = always spread, 2 = never
     float* partial;            // [ksplit, partial_rows, N]
     long long partial_rows;
@@ -284,6 +285,8 @@ int launch_pack_weights(const uint16_t* W, uint16_t* packed, int G, int K, int N
 struct SplitKReduceArgs {
     const float* partial;      // [ksplit, G*group_stride, N]
     int32_t ksplit, G, N;
+    const int32_t* order;      // with split_tiles: as the product that wrote the partials had them
+    int32_t split_tiles;
     long long group_stride;
     const int32_t* rows;       // [G], or nullptr: max_rows for every group
     int32_t max_rows;

@@ -74,10 +74,11 @@ __device__ __forceinline__ void choose_experts(int32_t* e_sh, const float* __res
 // x) takes the next busiest remaining expert when j + x is even, the next lightest when odd.  All
 // XCDs get the same number of active experts, and while half of them multiply the others stream
 // weights.  Experts without rows follow at the end.  O(active^2) compares, E <= 1024.
-// order[E] (one entry past the list) tells the tiled GEMM how to deal its tiles to the XCDs: 1 when the active
+// order[E] (one entry past the list) holds twice the number of active experts plus a flag that
+// tells the tiled GEMM how to deal its tiles to the XCDs: 1 when the active
 // experts are of very different sizes (at least a quarter of them hold at most a quarter of the largest one's
 // rows), so that dealing whole experts would leave the XCDs with unequal work; 0 otherwise.
-// A second list follows at order[E + 1 ..]: the experts plainly by rows, busiest first, and the same flag at
+// A second list follows at order[E + 1 ..]: the experts plainly by rows, busiest first, and the same entry at
 // order[2E + 1] (for products whose tiles are long and few per compute unit: longest first, short ones fill the end).
 // `order` holds 2E + 2 ints.  `sorted`, `active`: LDS scratch of E ints each; every thread of the block must call, at least E of
 // them and a power of two; `rows` is visible to all.
@@ -142,7 +143,7 @@ __device__ __forceinline__ void write_expert_order(const int32_t* rows /* LDS */
     // (a thread of the last wave, beside the first ones' look-ups) a quarter of the active experts hold at most a quarter of the
     // largest one's rows if the first of the last quarter does
     if (tid == nthreads - 1)
-        order[E] = order[2 * E + 1] = na > 0 && (long long)rows[sorted[na - (na + 3) / 4]] * 4 <= rows[sorted[0]] ? 1 : 0;
+        order[E] = order[2 * E + 1] = 2 * na + (na > 0 && (long long)rows[sorted[na - (na + 3) / 4]] * 4 <= rows[sorted[0]] ? 1 : 0);
     if (tid < E) {
         const int p = tid, j = p >> 3, x = p & 7;
         // busy takes among positions 8j .. 8j+x-1: those x' with (j + x') even
