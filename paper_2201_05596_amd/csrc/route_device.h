@@ -67,6 +67,17 @@ __device__ __forceinline__ void choose_experts(int32_t* e_sh, const float* __res
     }
 }
 
+__host__ __device__ __forceinline__ int ceil_log2(int n) { return n > 1 ? 32 - __builtin_clz(n - 1) : 0; }
+
+// f(expert, row) for the rows rows[e] .. C - 1 of every expert, each by one of the nthreads (a power of two, 64 at least): 2^sh
+// adjacent threads per expert, so that no entry's number is divided by C.
+template <typename F>
+__host__ __device__ __forceinline__ void for_unused_rows(const int32_t* rows, int E, int C, int tid, int nthreads, F f) {
+    const int all = ceil_log2(nthreads) - ceil_log2(E), sh = all > 0 ? all : 0;
+    for (int e = tid >> sh; e < E; e += nthreads >> sh)
+        for (uint32_t i = rows[e] + (tid & ((1 << sh) - 1)); i < (uint32_t)C; i += 1u << sh) f(e, i);     // C may be 2^31 - 1
+}
+
 // Launch order of the experts for the grouped GEMMs, which deal consecutive entries round-robin to
 // the 8 XCDs.  Experts are ranked by kept rows (most first, ties by index); active ones are then
 // handed out so that every XCD alternates between a busy expert (matrix-core bound) and a light one
@@ -86,7 +97,6 @@ __device__ __forceinline__ void choose_experts(int32_t* e_sh, const float* __res
 // instructions: only active experts are ranked (one token has one or two), rows and index compared as one key, no scalar
 // loops (an iteration is as long as an LDS round trip), no sums in LDS atomics, no exchanges between lanes through LDS.
 // Decode gate of one token of 128 experts: 2.1 us of 9.0 before, 0.9 of 7.2 (16 tokens of 64: 1.5 of 10.3, 0.9 of 9.2).
-__device__ __forceinline__ int ceil_log2(int n) { return n > 1 ? 32 - __clz(n - 1) : 0; }
 __device__ __forceinline__ void write_expert_order(const int32_t* rows /* LDS */, int E, int32_t* __restrict__ order,
                                                    int32_t* sorted /* LDS */, int32_t* active /* LDS */, int tid, int nthreads) {
     // every wave counts the active experts by itself, and those before its own
@@ -213,10 +223,7 @@ __device__ __forceinline__ void route_single_body(int32_t* smem, const float* __
         }
     }
     __syncthreads();
-    // entries past an expert's rows: 2^sh adjacent threads per expert (no division of an entry's number by C)
-    const int sh = max(0, ceil_log2(NT) - ceil_log2(E));
-    for (int e = tid >> sh; e < E; e += NT >> sh)
-        for (int i = rows_sh[e] + (tid & ((1 << sh) - 1)); i < C; i += 1 << sh) slot_token[(size_t)e * C + i] = -1;
+    for_unused_rows(rows_sh, E, C, tid, NT, [&](int e, uint32_t i) { slot_token[(size_t)e * C + i] = -1; });
     if (expert_order) write_expert_order(rows_sh, E, expert_order, sorted, tot_sh, tid, NT);   // tot_sh: free by now
 }
 // LDS ints of route_single_body: chosen experts, per-wave histograms, totals, rows, order scratch
