@@ -41,7 +41,7 @@ struct TileId {
     int g, nt, inner;
     bool live;
 };
-__device__ __forceinline__ TileId tile_of_block(const WsGemmArgs& a, int n_tiles, int inner_n, int block) {
+__host__ __device__ __forceinline__ TileId tile_of_block(const WsGemmArgs& a, int n_tiles, int inner_n, int block) {
     TileId t;
     const int xcd = block % kXcd;
     const int q = block / kXcd;
@@ -101,6 +101,12 @@ inline long long tile_grid_blocks(const WsGemmArgs& a, int n_tiles, int inner_n)
     if (a.G >= kXcd) return (long long)(a.G + kXcd - 1) / kXcd * kXcd * n_tiles * inner_n;
     if (a.ksplit == 1 && inner_n >= kXcd) return (long long)a.G * ((inner_n + kXcd - 1) / kXcd) * n_tiles * kXcd;
     return ((long long)a.G * n_tiles + kXcd - 1) / kXcd * kXcd * inner_n;
+}
+
+// Of a grid sized for `most` inner tiles per (group, column tile): the virtual blocks that deal inner_n of them.  Exact where the K of a
+// product is split (the grid then is a multiple of `most`); elsewhere the two are the same and so are the blocks.
+__host__ __device__ __forceinline__ int blocks_dealt(int most_blocks, int most, int inner_n) {
+    return inner_n == most ? most_blocks : most_blocks / most * inner_n;
 }
 
 // Top-1 combine fused into GEMM-2 leaves rows of dropped tokens unwritten: zero them (or copy what is added to), spread over the waves of all

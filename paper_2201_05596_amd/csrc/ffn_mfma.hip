@@ -300,7 +300,7 @@ __global__ __launch_bounds__(NW * 64) void wsgemm_kernel(const WsGemmArgs a, con
     __shared__ float gw_sh[MT];
 
     const WsGeo geo = ws_geo<MT, NW>(a);
-    const int total_blocks = EPI == EPI_PARTIAL ? most_blocks / (geo.m_tiles * a.ksplit) * geo.inner_n : most_blocks;
+    const int total_blocks = EPI == EPI_PARTIAL ? blocks_dealt(most_blocks, geo.m_tiles * a.ksplit, geo.inner_n) : most_blocks;
     if (EPI == EPI_SCATTER) zero_dropped_rows<true>(a, threadIdx.x, TC::NT);
 
     // The grid holds as many work-groups as fit on the chip at once; work-group b takes the virtual
