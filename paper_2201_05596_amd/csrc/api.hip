@@ -1,5 +1,6 @@
 // C ABI of the library: argument checks, workspace carving and launch sequencing.
 // Every check happens on the host before the first HIP call.
+#include <algorithm>
 #include <vector>
 
 #include "call_tag.h"
@@ -232,8 +233,11 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
     // the dense branch's output where it is not combined in place: rounded, or sums in 32 bits (dense2_shared, dense2_split, with
-    // either layout of the weights: no size depends on that)
-    L.dense = take(s->residual && plan.mfma ? T * d * (T <= kSharedTokens ? (T > 32 && T <= kSplitTokens ? 4 * kLinearMaxSplit : 4) : es) : 0);
+    // either layout of the weights: no size depends on that); as much as any smaller number of tokens takes, so that a program's
+    // workspace for its most tokens serves the others
+    size_t dense = std::max(T * es, 4 * std::min(T, (size_t)kSharedTokens));
+    if (T > 32) dense = std::max(dense, 4 * kLinearMaxSplit * std::min(T, (size_t)kSplitTokens));
+    L.dense = take(s->residual && plan.mfma ? dense * d : 0);
     L.partial = take(plan.ksplit_room > 1 ? (size_t)plan.ksplit_room * E * C * d * 4 : 0);
     L.total = off;
     return L;
