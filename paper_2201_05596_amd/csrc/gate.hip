@@ -551,9 +551,14 @@ int launch_route_finalize(int T, int E, int k, int C, int TB, const int32_t* exp
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_ERR_HIP;
 }
 
-// histograms for blocks of 32 tokens at the finest, of 16 where gate_logits_kernel writes them
+// histograms for blocks of 32 tokens at the finest, of 16 where gate_logits_kernel writes them; no less than for fewer tokens
 size_t route_scratch_ints(int T, int E, int k, bool by_logits) {
-    const size_t fine = by_logits && gate_logits_routes(T, E) ? ((size_t)T + kLogitsTokens - 1) / kLogitsTokens : ((size_t)T + 31) / 32;
+    size_t fine = ((size_t)T + 31) / 32;
+    const int few = T < kFewTokens ? T : kFewTokens;
+    if (by_logits && gate_logits_routes(few, E)) {
+        const size_t tiles = (few + kLogitsTokens - 1) / kLogitsTokens;
+        fine = fine < tiles ? tiles : fine;
+    }
     return fine * (size_t)k * (size_t)E;
 }
 

@@ -29,3 +29,13 @@ def test_dense_branch_takes_no_less_for_more_tokens(d, f):
             with_dense, without = (B.moe_workspace_bytes(B.make_shape(T, d, f, E, k, max(1, T * k // E), "bf16", residual)) for residual in (True, False))
             assert with_dense - without >= last, f"T={T} E={E}"
             last = with_dense - without
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 64), ("f32", 512), ("bf16", 1000), ("bf16", 1024)])
+def test_gate_takes_no_less_for_more_tokens(dtype, d):
+    for E, k in ((1, 1), (8, 2), (40, 1), (64, 2), (65, 2), (128, 1)):
+        last = 0
+        for T in [*range(1, 700), *range(700, 4000, 33), *range(4000, 4400)]:
+            size = B.moe_gate_noalloc_bytes(B.make_shape(T, d, 64, E, k, 4, dtype))
+            assert size >= last, f"T={T} E={E}"
+            last = size
