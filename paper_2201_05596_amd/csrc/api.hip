@@ -233,11 +233,12 @@ WsLayout ws_layout(const moe_shape_t* s) {
     L.ye = take(E * C * d * es);
     L.hd = take(s->residual ? T * f * es : 0);
     // the dense branch's output where it is not combined in place: rounded, or sums in 32 bits (dense2_shared, dense2_split, with
-    // either layout of the weights: no size depends on that); as much as any smaller number of tokens takes, so that a program's
-    // workspace for its most tokens serves the others
-    size_t dense = std::max(T * es, 4 * std::min(T, (size_t)kSharedTokens));
-    if (T > 32) dense = std::max(dense, 4 * kLinearMaxSplit * std::min(T, (size_t)kSplitTokens));
-    L.dense = take(s->residual && plan.mfma ? dense * d : 0);
+    // either layout of the weights: no size depends on that).  What the sums take beyond the rounded output is room of its own, as much as
+    // any smaller number of tokens wants: a workspace for a program's most tokens serves the others wherever one without the sums did
+    size_t sums = (4 - es) * std::min(T, (size_t)kSharedTokens);
+    if (T > 32) sums = std::max(sums, (4 * kLinearMaxSplit - es) * std::min(T, (size_t)kSplitTokens));
+    L.dense = take(s->residual && plan.mfma ? T * d * es : 0);
+    take(s->residual && plan.mfma ? sums * d : 0);
     L.partial = take(plan.ksplit_room > 1 ? (size_t)plan.ksplit_room * E * C * d * 4 : 0);
     L.total = off;
     return L;
