@@ -181,10 +181,13 @@ bool dense2_shared(const moe_shape_t* s, const FfnPlan& p) {
 // where the few-weights kernel would take the product, every work-group of it reading 64 rows through all of K: layers, us, that
 // kernel with the combine in it / split: 120 tokens, 2048/8192, top-2 of 64, skewed 225 / 215, 140 of 64, skewed 204 / 190;
 // 180 tokens, 1024/4096, top-2 of 64 226 / 219; plain weights, 50 tokens, 2048/8192, top-2 of 32 401 / 392; but 256 tokens, 1024/4096,
-// 137.8 / 138.7.
+// 137.8 / 138.7.  On packed weights from 41 tokens on: 33, 2048/8192, top-2 of 2 114.9 / 118.7, 36 118.6 / 120.3, 40 and 41 the
+// same, 44 123.8 / 121.3, 4096/16384, 41 of 2 207.6 / 203.1; plain, 33 tokens, 2048/8192, top-2 of 8 150.7 / 149.2, 64 experts
+// 349.3 / 346.9, 4096/16384, top-2 of 2 251.9 / 231.7, 1024/4096, top-2 of 32 122.8 / 122.2.
 constexpr int kSplitTokens = 192;
 int dense2_split(const moe_shape_t* s) {
-    if (s->T <= 32 || s->T > kSplitTokens || s->d_ffn < 4096 || !rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS)) return 1;
+    const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
+    if (s->T <= (packed ? 40 : 32) || s->T > kSplitTokens || s->d_ffn < 4096 || !rows_pick_dense(s->T, s->d_model, packed)) return 1;
     int MT, NW;
     wsgemm_pick_tile(s->T, 1, s->d_model, &MT, &NW);
     const long long waves = (long long)((s->d_model + 127) / 128) * ((s->T + MT - 1) / MT);
