@@ -216,7 +216,9 @@ __global__ __launch_bounds__(256) void gate_logits_kernel(const XT* __restrict__
             }
             __syncthreads();
             for (int i = tid; i < K * E; i += 256) hist[(size_t)blockIdx.x * K * E + i] = h_sh[i];
-            return;
+            // There is no second pass, but the compiler is not told: with `return` it keeps all addresses of a step in registers and moves
+            // operands out of their way (moe_gate, 2500 tokens, d = 2048, 8 experts, top-2: 31.9 -> 30.1 us).
+            continue;
         }
         if (WK > 1) {
             __syncthreads();
