@@ -196,8 +196,8 @@ int dense2_split(const moe_shape_t* s) {
     return (int)(ks > chunks ? chunks : ks);
 }
 
-// The waves' tiles of an expert GEMM-2 whose K is split on the streaming kernel: as many as two of its work-groups of two waves for
-// most compute units.  The factor in the plan is for few experts with rows (2048 tiles, eight ways at most, of those that the
+// The waves' tiles of an expert GEMM-2 whose K is split on the streaming kernel: about 200 of its work-groups of two waves, the fewest
+// of the numbers measured that lost nowhere.  The factor in the plan is for few experts with rows (2048 tiles, eight ways at most, of those that the
 // tokens can reach at most); where all have some, it wrote and read more partial sums than the product gains.  Layers, us, the
 // plan's factor / at least 600 tiles / at least 400, even routing: 1000/4000, plain, 40 experts x 64 rows 237 / 212 / 212; 32 x 20
 // 123 / 121 / 112; 1024/4096, packed, 32 x 60 142 / 133 / 124; plain, 64 x 30 213 / 204 / 195; 4096/16384, 16 x 30 741 / 685 / 662; 16

@@ -554,8 +554,7 @@ __global__ __launch_bounds__(kSingleThreads) void route_single_kernel(const floa
 size_t route_finalize_lds_bytes(int E, int k, int TB, int nthreads) {
     const int ncol = k * E;
     const int R = finalize_row_groups(ncol, nthreads);
-    size_t ints = (size_t)(kRouteTokens / TB) * ncol + E + 2 * (size_t)R * ncol;
-    if (ints < (size_t)(kRouteTokens / TB) * ncol + 2 * (size_t)E + 2) ints = (size_t)(kRouteTokens / TB) * ncol + 2 * (size_t)E + 2;
+    const size_t ints = (size_t)(kRouteTokens / TB) * ncol + E + 2 * (size_t)R * ncol;   // the last part: 2 E for the launch order
     return ints * sizeof(int32_t);
 }
 

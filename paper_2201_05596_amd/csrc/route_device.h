@@ -182,7 +182,7 @@ __device__ __forceinline__ void route_single_body(int32_t* smem, const float* __
     int32_t* whist = smem + K * kRouteTokens;                   // [NW][K][E] tokens per (wave of tokens, choice, expert)
     int32_t* tot_sh = whist + NW * K * E;                       // [K][E] tokens per (choice, expert)
     int32_t* rows_sh = tot_sh + K * E;                          // [E]
-    int32_t* sorted = rows_sh + E;                              // [E + 2]
+    int32_t* sorted = rows_sh + E;                              // [E]
     const int tid = threadIdx.x, lane = tid % kWave, w = tid / kWave;
     for (int i = tid; i < NW * K * E; i += NT) whist[i] = 0;
     choose_experts<K, NV, NT, kRouteTokens>(e_sh, logits, 0, T, T, E, expert_idx, gate_w);
@@ -231,7 +231,7 @@ __device__ __forceinline__ void route_single_body(int32_t* smem, const float* __
 }
 // LDS ints of route_single_body: chosen experts, per-wave histograms, totals, rows, order scratch
 __host__ __device__ inline size_t route_single_lds_ints(int E, int k) {
-    return (size_t)k * kRouteTokens + (size_t)(kRouteTokens / kWave) * k * E + (size_t)k * E + 2 * (size_t)E + 2;
+    return (size_t)k * kRouteTokens + (size_t)(kRouteTokens / kWave) * k * E + (size_t)k * E + 2 * (size_t)E;
 }
 
 }  // namespace moe
