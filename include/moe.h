@@ -175,7 +175,10 @@ int moe_dispatch(const moe_shape_t* shape, const void* x, const int32_t* slot_to
  *   ye[e,c,:] = gelu_tanh(xe[e,c,:] W1[e] + b1[e]) W2[e] + b2[e].
  *   W1 [E,d,f], b1 [E,f] or NULL, W2 [E,f,d], b2 [E,d] or NULL.
  * Rows c >= expert_rows[e] of ye are left untouched; weights of experts with
- * no rows are not read. */
+ * no rows are not read.  A call with the same arguments gives the same bits;
+ * the last bits of an expert's rows (bf16) may depend on how many other experts
+ * have rows and how even their numbers are, which decide how many partial sums
+ * in 32 bits the second product is added up from (moe_layer_forward likewise). */
 int moe_expert_ffn(const moe_shape_t* shape, const void* xe, const int32_t* expert_rows,
                    const void* W1, const void* b1, const void* W2, const void* b2,
                    void* ye /* [E,C,d] */, void* ws, size_t ws_bytes, void* stream);
