@@ -875,7 +875,7 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
         prof_mark(ST_GEMM2, st);
         if (rc != MOE_OK) return rc;
         prof_pre(ST_COMBINE, st);
-        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, DenseSums{at<float>(ws, L.dense), 1, nullptr});
+        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, PartSums{at<float>(ws, L.dense), 1, nullptr});
         prof_mark(ST_COMBINE, st);
         return rc;
     }
@@ -896,7 +896,7 @@ static int layer_forward_checked(const moe_shape_t* shape, const void* x, const 
         prof_mark(ST_DENSE2, st);
         if (rc != MOE_OK) return rc;
         prof_pre(ST_COMBINE, st);
-        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, DenseSums{d2.partial, d2.ksplit, u16(bd2)});
+        rc = launch_combine(at<void>(ws, L.ye), dt, expert_idx, slot_idx, gate_w, add, out, T, k, C, d, st, PartSums{d2.partial, d2.ksplit, u16(bd2)});
         prof_mark(ST_COMBINE, st);
         return rc;
     }
@@ -1086,7 +1086,7 @@ int moe_decode_block_forward(const moe_shape_t* shape, const moe_block_shape_t* 
     rc = run_linear(attn, u16(w->Wo), u16(w->bo), proj, T, d, d, lin_partial, add_layernorm_sums(d) ? &split : nullptr, st);
     if (rc != MOE_OK) return rc;
     // x1 = x + attention; the MoE layer sees LayerNorm(x1)
-    const AddedRows projected = split > 1 ? AddedRows{nullptr, lin_partial, u16(w->bo), split} : AddedRows{proj, nullptr, nullptr, 0};
+    const AddedRows projected = split > 1 ? AddedRows{nullptr, PartSums{lin_partial, split, u16(w->bo)}} : AddedRows{proj, PartSums{}};
     rc = launch_add_layernorm(u16(x), projected, w->ln2_gamma, w->ln2_beta, x1, moe_in, T, d, eps, st);
     if (rc != MOE_OK) return rc;
     // out = x1 + MoE: in the layer's last kernel or behind it

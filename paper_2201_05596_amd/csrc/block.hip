@@ -48,27 +48,8 @@ __global__ __launch_bounds__(256) void add_layernorm_row_kernel(const uint16_t* 
         const int i = min(tid + p * 256, pieces - 1);
         xv[p] = reinterpret_cast<const uint4*>(x + row)[i];
         if constexpr (SUMS) {
-            float4 part4[kLinearMaxSplit][2];
-#pragma unroll
-            for (int s = 0; s < kLinearMaxSplit; ++s)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    part4[s][q] = s < added.ksplit ? reinterpret_cast<const float4*>(added.partial + (size_t)s * gridDim.x * d + row)[2 * i + q]
-                                                   : make_float4(0.f, 0.f, 0.f, 0.f);
-            const uint4 bias = added.bias ? reinterpret_cast<const uint4*>(added.bias)[i] : make_uint4(0, 0, 0, 0);
-            float v[8], bf[8];
-            unpack8(bias, bf);
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] = 0.f;
-#pragma unroll
-            for (int s = 0; s < kLinearMaxSplit; ++s) {
-                if (s >= added.ksplit) break;
-                const float a8[8] = {part4[s][0].x, part4[s][0].y, part4[s][0].z, part4[s][0].w, part4[s][1].x, part4[s][1].y, part4[s][1].z, part4[s][1].w};
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] += a8[q];
-            }
-#pragma unroll
-            for (int q = 0; q < 8; ++q) v[q] += bf[q];
+            float v[8];
+            add_parts8(added.sums, (size_t)gridDim.x * d, row, i, v);
             rv[p] = pack8(v);
         } else if (r) {
             rv[p] = reinterpret_cast<const uint4*>(r + row)[i];
@@ -177,14 +158,14 @@ __global__ __launch_bounds__(256) void add_layernorm_kernel(const uint16_t* __re
 bool add_layernorm_sums(int d) { return d <= 4096; }
 int launch_add_layernorm(const uint16_t* x, const AddedRows& r, const float* gamma, const float* beta, uint16_t* sum_out,
                          uint16_t* y, int T, int d, float eps, hipStream_t s) {
-    if (r.partial && (!add_layernorm_sums(d) || r.ksplit < 1 || r.ksplit > kLinearMaxSplit)) return MOE_ERR_INVALID_ARG;
+    if (r.sums.partial && (!add_layernorm_sums(d) || r.sums.ksplit < 1 || r.sums.ksplit > kLinearMaxSplit)) return MOE_ERR_INVALID_ARG;
 #define MOE_LN_ROW(NP, SUMS) \
     hipLaunchKernelGGL((add_layernorm_row_kernel<NP, SUMS>), dim3(T), dim3(256), 0, s, x, r, gamma, beta, sum_out, y, d, eps)
     if (d <= 2048) {
-        if (r.partial) MOE_LN_ROW(1, true);
+        if (r.sums.partial) MOE_LN_ROW(1, true);
         else MOE_LN_ROW(1, false);
     } else if (d <= 4096) {
-        if (r.partial) MOE_LN_ROW(2, true);
+        if (r.sums.partial) MOE_LN_ROW(2, true);
         else MOE_LN_ROW(2, false);
     } else {
         hipLaunchKernelGGL(add_layernorm_kernel, dim3((T + 3) / 4), dim3(256), 0, s, x, r.rows, gamma, beta, sum_out, y, T, d, eps);

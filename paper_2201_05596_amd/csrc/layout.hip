@@ -78,7 +78,7 @@ __device__ __forceinline__ void unpack8(const uint4& v, float* f) {
 template <int K, bool DENSE>
 __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restrict__ ye, const int32_t* __restrict__ expert_idx,
                                                            const int32_t* __restrict__ slot_idx, const float* __restrict__ gate_w,
-                                                           const DenseSums dense, const uint4* __restrict__ addend,
+                                                           const PartSums dense, const uint4* __restrict__ addend,
                                                            uint4* __restrict__ out, int T, int C, int row_vecs) {
     const int lane = threadIdx.x % kWave;
     const int t = blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
@@ -95,28 +95,7 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
     for (int i = lane; i < row_vecs; i += kWave) {
         float acc[8];
         if constexpr (DENSE) {
-            const float4* p = reinterpret_cast<const float4*>(dense.partial) + ((size_t)t * row_vecs + i) * 2;
-            float4 v[kLinearMaxSplit][2];
-#pragma unroll
-            for (int s = 0; s < kLinearMaxSplit; ++s)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-                    v[s][q] = s < dense.ksplit ? p[(size_t)s * T * row_vecs * 2 + q] : make_float4(0.f, 0.f, 0.f, 0.f);
-            const uint4 bias = dense.bias ? reinterpret_cast<const uint4*>(dense.bias)[i] : make_uint4(0, 0, 0, 0);
-            *reinterpret_cast<float4*>(acc) = v[0][0];
-            *reinterpret_cast<float4*>(acc + 4) = v[0][1];
-#pragma unroll
-            for (int s = 1; s < kLinearMaxSplit; ++s) {
-                if (s >= dense.ksplit) break;
-                acc[0] += v[s][0].x; acc[1] += v[s][0].y; acc[2] += v[s][0].z; acc[3] += v[s][0].w;
-                acc[4] += v[s][1].x; acc[5] += v[s][1].y; acc[6] += v[s][1].z; acc[7] += v[s][1].w;
-            }
-            if (dense.bias) {
-                float b[8];
-                unpack8(bias, b);
-#pragma unroll
-                for (int q = 0; q < 8; ++q) acc[q] += b[q];
-            }
+            add_parts8(dense, (size_t)T * row_vecs * 8, (size_t)t * row_vecs * 8, i, acc);
         } else if (addend) {
             unpack8(addend[(size_t)t * row_vecs + i], acc);
         } else {
@@ -148,7 +127,7 @@ __global__ __launch_bounds__(256) void combine_bf16_kernel(const uint4* __restri
 }
 
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx, const float* gate_w,
-                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s, const DenseSums& dense) {
+                   const void* addend, void* out, int T, int k, int C, int d, hipStream_t s, const PartSums& dense) {
     if (dense.partial && (dtype != MOE_BF16 || dense.ksplit < 1 || dense.ksplit > kLinearMaxSplit)) return MOE_ERR_INVALID_ARG;
     const int rpb = 256 / kWave;
     const dim3 grid((T + rpb - 1) / rpb), block(256);

@@ -89,6 +89,38 @@ __device__ __forceinline__ void for_dropped_tokens(const int32_t* slot_idx, int 
     }
 }
 
+// ---- sums of a product whose K was split, added up by the kernel that reads them next -------
+constexpr int kLinearMaxSplit = 8;   // parts at most
+struct PartSums {
+    const float* partial;      // [ksplit, T, d], or nullptr: none
+    int32_t ksplit;
+    const uint16_t* bias;      // [d] in bf16, or nullptr
+};
+
+// v = elements 8 i .. 8 i + 7 of the row at `row` (T d elements per part): the parts in order, then the bias; all loads first
+__device__ __forceinline__ void add_parts8(const PartSums& s, size_t part, size_t row, int i, float (&v)[8]) {
+    float4 p[kLinearMaxSplit][2];
+#pragma unroll
+    for (int n = 0; n < kLinearMaxSplit; ++n)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            p[n][q] = n < s.ksplit ? reinterpret_cast<const float4*>(s.partial + n * part + row)[2 * i + q] : make_float4(0.f, 0.f, 0.f, 0.f);
+    const uint4 bias = s.bias ? reinterpret_cast<const uint4*>(s.bias)[i] : make_uint4(0, 0, 0, 0);
+    // from the first part on: a sum that starts at 0 waits for it before the others' loads
+    *reinterpret_cast<float4*>(v) = p[0][0];
+    *reinterpret_cast<float4*>(v + 4) = p[0][1];
+#pragma unroll
+    for (int n = 1; n < kLinearMaxSplit; ++n) {
+        if (n >= s.ksplit) break;
+        v[0] += p[n][0].x; v[1] += p[n][0].y; v[2] += p[n][0].z; v[3] += p[n][0].w;
+        v[4] += p[n][1].x; v[5] += p[n][1].y; v[6] += p[n][1].z; v[7] += p[n][1].w;
+    }
+    v[0] += __uint_as_float(bias.x << 16); v[1] += __uint_as_float(bias.x & 0xffff0000u);
+    v[2] += __uint_as_float(bias.y << 16); v[3] += __uint_as_float(bias.y & 0xffff0000u);
+    v[4] += __uint_as_float(bias.z << 16); v[5] += __uint_as_float(bias.z & 0xffff0000u);
+    v[6] += __uint_as_float(bias.w << 16); v[7] += __uint_as_float(bias.w & 0xffff0000u);
+}
+
 // ---- launchers (each returns MOE_OK or MOE_ERR_HIP) ---------------------------------------
 
 // logits[t,e] = bg[e] + sum_i x[t,i] Wg[i,e]
@@ -148,16 +180,10 @@ int launch_expert_order(const int32_t* expert_rows, int E, int C, int32_t* order
 int launch_dispatch(const void* x, int dtype, const int32_t* slot_token, const int32_t* expert_rows,
                     void* xe, int E, int C, int d, hipStream_t s);
 
-constexpr int kLinearMaxSplit = 8;   // split-K factors whose sums another kernel adds up
-struct DenseSums {             // bf16: fp32 sums that come first in every row, or none
-    const float* partial;      // [ksplit, T, d], added up in order
-    int32_t ksplit;
-    const uint16_t* bias;      // added behind them, or nullptr
-};
 int launch_combine(const void* ye, int dtype, const int32_t* expert_idx, const int32_t* slot_idx,
                    const float* gate_w, const void* addend, void* out,
                    int T, int k, int C, int d, hipStream_t s,
-                   const DenseSums& dense = DenseSums{});
+                   const PartSums& dense = PartSums{});
 
 // What a grouped GEMM does with a finished row.
 enum WsEpilogue {
@@ -302,11 +328,9 @@ struct SplitKReduceArgs {
 int launch_splitk_reduce(const SplitKReduceArgs& a, hipStream_t s);
 
 // ---- the non-expert half of a decoder block, one decode step (block.hip) --------------------------------------
-struct AddedRows {             // what a LayerNorm adds to its rows first: nothing, [T, d] rows, or a product's split-K partial sums
+struct AddedRows {             // what a LayerNorm adds to its rows first: nothing, [T, d] rows, or a product's sums
     const uint16_t* rows;
-    const float* partial;      // [ksplit, T, d]: only where add_layernorm_sums(d)
-    const uint16_t* bias;      // of that product, or nullptr
-    int32_t ksplit;
+    PartSums sums;             // only where add_layernorm_sums(d)
 };
 bool add_layernorm_sums(int d);
 int launch_add_layernorm(const uint16_t* x, const AddedRows& r, const float* gamma, const float* beta,
