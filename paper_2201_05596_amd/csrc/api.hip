@@ -205,7 +205,18 @@ int dense2_split(const moe_shape_t* s) {
 // Experts of very different sizes (skewed routing) keep the plan's factor: with at least 400 423 tokens, 4096/16384, 16 experts beside a
 // dense branch took 885 -> 899, with at least 300 100 tokens, 1000/4000, top-2 of 32 84 -> 87.  The host, which knows no routing,
 // cannot choose: its own factor for 400 tiles took skewed 40 x 48 79 -> 87, 40 x 60 74 -> 93.
+// Nor with few rows per expert, whose sums are few: below 3 on average (4096 columns and more: 3/2) the plan's factor is the faster one
+// with even and slightly skewed routing.  Layers, us, the plan's factor / at least 400 tiles: 1024/4096, plain, 32 experts, 16
+// tokens 55.9 / 58.0, 32 78.3 / 85.3, 48 89.6 / 91.6, but 96 102.6 / 100.4; 1000/4000, 30 of 40 96.3 / 107.2; 2048/8192, 8 of 16 96.1 / 103.1, 24
+// 167.6 / 170.3, 48 189.0 / 179.0; 4096/16384, 2 of 16 173.9 / 182.4, 24 637 / 613.  And not where all experts together have too few tiles
+// for another factor: looking for the count costs both kernels a round trip (512/2048, 32 experts, 192 tokens 42.5 / 43.4).
 constexpr int kSplitTiles = 400;
+int split_tiles(const moe_shape_t* s, const FfnPlan& p) {
+    const long long kept = (long long)s->T * s->top_k, touched = s->E < kept ? s->E : kept;
+    const long long waves = touched * ((s->d_model + 127) / 128);
+    const bool one_row_tile = s->capacity <= p.MT, many_rows = s->d_model < 4096 ? kept >= 3ll * s->E : 2 * kept >= 3ll * s->E;
+    return one_row_tile && many_rows && (kSplitTiles + waves - 1) / waves < p.ksplit2 ? kSplitTiles : 0;
+}
 
 // Carving of the caller's workspace.  Offsets in bytes; every region 256-byte aligned.
 struct WsLayout {
@@ -468,7 +479,7 @@ int run_expert_gemm2(const moe_shape_t* s, const FfnPlan& p, const void* h, cons
     }
     a.partial = partial;
     a.partial_rows = (long long)s->E * s->capacity;
-    a.split_tiles = order && s->capacity <= p.MT ? kSplitTiles : 0;       // one row tile per expert
+    a.split_tiles = order ? split_tiles(s, p) : 0;
     int rc = launch_wsgemm(a, EPI_PARTIAL, p.MT, p.NW2, p.NBUF, st);
     prof_mark(ST_GEMM2, st);
     if (rc != MOE_OK) return rc;

@@ -88,6 +88,15 @@ def test_fewer_parts_than_planned(T, d, f, E, C, live, parts, even, packed):
     assert parts < planned and took == (parts if even else planned)
 
 
+# T, d, f, E, capacity, experts with rows: too few rows per expert on average, too few tiles of all experts for another factor
+@pytest.mark.parametrize("T,d,f,E,C,live", [(119, 1000, 2000, 40, 17, 40), (23, 4096, 1040, 16, 2, 16), (100, 128, 2048, 4, 40, 4)])
+def test_parts_as_planned(T, d, f, E, C, live):
+    print(f"case T={T} d={d} f={f} E={E} C={C} live={live}", flush=True)
+    gen = torch.Generator().manual_seed(E + live)
+    took, planned = check_ffn(T, d, f, E, C, torch.full((E,), C, dtype=torch.int32), False, gen)
+    assert took == planned
+
+
 @pytest.mark.parametrize("packed", [False, True])
 @pytest.mark.parametrize("T,d,f,E,C,dead,parts", [(1000, 1000, 1400, 40, 20, 0, 2), (1000, 1000, 1400, 40, 20, 20, 3), (300, 2048, 1040, 7, 33, 2, 5)])
 def test_scattered_sums(T, d, f, E, C, dead, parts, packed):
