@@ -167,14 +167,32 @@ FfnPlan plan_ffn(const moe_shape_t* s) {
 // do the bf16 matrix cores compute the gate logits?
 bool gate_on_bf16(const moe_shape_t* s) { return s->dtype == MOE_BF16 && gate_bf16_supported(s->d_model, s->E); }
 
-// Does the dense branch's second product share the launch of the experts' in the few-weights kernel?  Wherever both take that
-// kernel: alone the dense one is a chain through all of K on few work-groups (16 tokens, 2048/8192 16 us, 96 tokens 42, for 34 MB of
+// Does the dense branch's second product share the launch of the experts' in the few-weights kernel?  Both have to take that kernel:
+// alone the dense one is a chain through all of K on few work-groups (16 tokens, 2048/8192 16 us, 96 tokens 42, for 34 MB of
 // weights).  Its sums stay unrounded in 32 bits for the combine, which then is a launch of its own (4.7).  Layers, us, apart /
 // shared: one token, 1024/4096, 64 experts 26.9 / 23.8; 16 tokens, 2048/8192, 64 experts 174.2 / 169.6, two tokens, plain weights
 // 101.8 / 77.7; 40 tokens, 1024/4096, 128 experts 126 / 113; 96, top-2 of 32, skewed 196 / 169; 150 of 128 270 / 258.
+// On packed weights and more than 1024 columns, where the dense one alone fills half the chip and more, not
+//   - with fewer tokens than a 128th of the columns, unless all work-groups run at once: the dense ones make a round of their own, of the
+//     experts' columns per work-group (apart / shared: 2048/8192, 2 tokens, top-2 of 32 71.4 / 78.0, one token, top-2 51.2 / 53.5, but top-1
+//     44 / 41; 4096/16384, 2 of 16 142 / 154, 16 512 / 522, 32 the same; 1536/6144, one, top-2 of 32 1.08 times);
+//   - with so many that reading their rows again in every work-group of few columns is what the launch takes (2048/4096, 256
+//     tokens of 32, 16 columns 232 / 251, skewed 110 / 127; 2048/8192, 160 of 128, skewed 150 / 180, with 32 columns, 128 of 32 the same;
+//     4096/8192, 96 of 16, 32 columns 1.03, 64 0.98 times);
+//   - with a K below 4096 (2048/2048 1.00 to 1.12 times at 1 to 24 and 80 to 256 tokens).
+// With up to 1024 columns it gains everywhere (0.78 to 1.00 times, 512/2048, 1000/4000, 1024/4096 .. 16384) but beyond 208 tokens with K below
+// 8192 (1024/4096, 256 of 32 137.8 / 140.1).
 constexpr int kSharedTokens = 256;             // the few-weights kernel takes no second products of more rows
 bool dense2_shared(const moe_shape_t* s, const FfnPlan& p) {
-    return s->residual && s->T <= kSharedTokens && p.mfma && p.nf2 && p.ksplit2 == 1 && rows_pick_dense(s->T, s->d_model, s->flags & MOE_FLAG_PACKED_WEIGHTS);
+    const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
+    if (!s->residual || s->T > kSharedTokens || !p.mfma || !p.nf2 || p.ksplit2 != 1 || !rows_pick_dense(s->T, s->d_model, packed)) return false;
+    if (!packed) return true;
+    const long long T = s->T, N = s->d_model, K = s->d_ffn;
+    if (N <= 1024) return K >= 8192 || T * N <= 208 * 1024;
+    const long long kept = T * s->top_k, touched = s->E < kept ? s->E : kept;
+    const bool one_round = (touched + 1) * ((N + 16 * p.nf2 - 1) / (16 * p.nf2)) <= 256;
+    const bool few_rows = N <= 2048 ? T * K <= p.nf2 << 19 : T <= 32 * p.nf2;
+    return K >= 4096 && few_rows && (128 * T >= N || one_round);
 }
 
 // Where it does not: K split on the streaming kernel, whose sums the combine adds up (1: not that way).  For 33 to 192 tokens and a long K,

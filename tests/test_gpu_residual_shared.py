@@ -1,6 +1,6 @@
 """Residual layers whose dense branch shares the launch of the experts' second product in the few-weights kernel, its sums combined
 unrounded: tiles of 16, 32 and 64 rows on either side, one expert and all of them without rows for some, one and two choices, inner
-dimensions of whole and ragged 32-deep blocks, plain and packed weights -- through moe_layer_forward against the oracle."""
+dimensions of whole and ragged 32-deep blocks, plain and packed weights, and both sides of each bound of the rule -- through moe_layer_forward against the oracle."""
 import pytest
 
 from tests import gpu_util as U
@@ -12,7 +12,10 @@ pytestmark = pytest.mark.gpu
 # T, d, f, E, top_k, capacity, shared on plain, on packed weights
 CASES = [(1, 128, 256, 2, 1, 1, True, True), (2, 256, 512, 8, 2, 1, True, True), (16, 136, 264, 4, 1, 8, True, True), (17, 128, 1024, 4, 2, 17, False, True),
          (33, 256, 520, 16, 1, 3, True, True), (64, 512, 2048, 8, 1, 16, True, True), (65, 128, 512, 4, 2, 16, False, True), (100, 264, 1032, 32, 1, 1, False, True),
-         (256, 128, 1024, 16, 1, 16, False, True)]
+         (256, 128, 1024, 16, 1, 16, False, True),
+         (1, 1040, 4096, 8, 2, 1, True, True), (4, 1040, 4096, 8, 1, 1, False, False), (9, 1040, 4096, 8, 1, 2, False, True),
+         (16, 1040, 2048, 8, 1, 2, False, False), (120, 1040, 4096, 12, 1, 12, False, True), (129, 1040, 4096, 12, 1, 12, False, False),
+         (200, 1024, 4096, 16, 1, 16, False, True), (215, 1024, 4096, 16, 1, 16, False, False), (40, 2056, 8192, 4, 1, 10, False, True)]
 
 
 @pytest.mark.parametrize("T,d,f,E,k,C,plain,packed", CASES)
