@@ -180,15 +180,16 @@ bool gate_on_bf16(const moe_shape_t* s) { return s->dtype == MOE_BF16 && gate_bf
 //     tokens of 32, 16 columns 232 / 251, skewed 110 / 127; 2048/8192, 160 of 128, skewed 150 / 180, with 32 columns, 128 of 32 the same;
 //     4096/8192, 96 of 16, 32 columns 1.03, 64 0.98 times);
 //   - with a K below 4096 (2048/2048 1.00 to 1.12 times at 1 to 24 and 80 to 256 tokens).
-// With up to 1024 columns it gains everywhere (0.78 to 1.00 times, 512/2048, 1000/4000, 1024/4096 .. 16384) but beyond 208 tokens with K below
-// 8192 (1024/4096, 256 of 32 137.8 / 140.1).
+// With up to 1024 columns it gains (0.78 to 1.00 times, 512/2048, 1000/4000, 1024/4096 .. 16384), but with many tokens and a shorter K (1024/4096,
+// 256 of 32 137.8 / 140.1; 1024/256, 200 of 32 46.6 / 48.9).  Plain weights, which take that kernel for a few rows only: 0.68 to 1.00
+// times but with many columns and a short K (2048/1024, one token, top-2 of 32 31.6 / 32.7, 4096/1024 37.5 / 40.7, 4096/4096 66.1 / 64.6).
 constexpr int kSharedTokens = 256;             // the few-weights kernel takes no second products of more rows
 bool dense2_shared(const moe_shape_t* s, const FfnPlan& p) {
     const bool packed = s->flags & MOE_FLAG_PACKED_WEIGHTS;
     if (!s->residual || s->T > kSharedTokens || !p.mfma || !p.nf2 || p.ksplit2 != 1 || !rows_pick_dense(s->T, s->d_model, packed)) return false;
-    if (!packed) return true;
     const long long T = s->T, N = s->d_model, K = s->d_ffn;
-    if (N <= 1024) return K >= 8192 || T * N <= 208 * 1024;
+    if (!packed) return N <= 1536 || K >= N;
+    if (N <= 1024) return K >= 8192 || T * N <= (K < 2048 ? 128 : 208) * 1024;
     const long long kept = T * s->top_k, touched = s->E < kept ? s->E : kept;
     const bool one_round = (touched + 1) * ((N + 16 * p.nf2 - 1) / (16 * p.nf2)) <= 256;
     const bool few_rows = N <= 2048 ? T * K <= p.nf2 << 19 : T <= 32 * p.nf2;

@@ -15,7 +15,8 @@ CASES = [(1, 128, 256, 2, 1, 1, True, True), (2, 256, 512, 8, 2, 1, True, True),
          (256, 128, 1024, 16, 1, 16, False, True),
          (1, 1040, 4096, 8, 2, 1, True, True), (4, 1040, 4096, 8, 1, 1, False, False), (9, 1040, 4096, 8, 1, 2, False, True),
          (16, 1040, 2048, 8, 1, 2, False, False), (120, 1040, 4096, 12, 1, 12, False, True), (129, 1040, 4096, 12, 1, 12, False, False),
-         (200, 1024, 4096, 16, 1, 16, False, True), (215, 1024, 4096, 16, 1, 16, False, False), (40, 2056, 8192, 4, 1, 10, False, True)]
+         (200, 1024, 4096, 16, 1, 16, False, True), (215, 1024, 4096, 16, 1, 16, False, False), (40, 2056, 8192, 4, 1, 10, False, True),
+         (128, 1024, 1024, 16, 1, 16, False, True), (129, 1024, 1024, 16, 1, 16, False, False), (1, 2048, 2040, 2, 1, 1, False, False), (1, 2048, 2048, 2, 1, 1, True, False)]
 
 
 @pytest.mark.parametrize("T,d,f,E,k,C,plain,packed", CASES)
